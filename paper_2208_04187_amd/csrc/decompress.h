@@ -7,24 +7,23 @@ struct DecArgs {
     Regions rg;
     uint32_t P, H, W, HW, LH, LW, nb, WPP, B;
     uint32_t G;          // planes per workgroup
-    uint32_t q4;         // HW / 4
-    uint32_t w4;         // W / 4
+    uint32_t q4;         // HW / 4 (decompress_stream with whole8: HW / 8)
+    uint32_t w4;         // W / 4 (decompress_stream with whole8: W / 8)
     uint32_t Hs, LHs;    // 3-D maps: rows and block rows of one depth slice (H counts the rows of all slices)
-    uint32_t pair8;      // 2-byte elements, W a multiple of 8, output 16-byte aligned: a lane step writes 8 elements
+    uint32_t whole8;     // decompress_stream, 2-byte elements: rows and blocks are whole vectors of eight elements
     uint32_t out_off;    // decompress_words: byte offset of the staged output in LDS
     FastDiv d_q4, d_w4, d_B, d_W, d_HW, d_Hs, d_wpp;
 };
 
 // Index of the first block of the block row that holds row r; for a 3-D map (Appendix D,
 // UpSampling3D) r counts the rows of all depth slices.
-template <int ND, bool TESTED = false>
+template <int ND>
 __device__ __forceinline__ uint32_t lfc_row(const DecArgs& a, uint32_t r) {
-    auto div = [](uint32_t n, FastDiv f) { return TESTED ? fdiv_tested(n, f) : fdiv(n, f); };
     if constexpr (ND == 3) {
-        const uint32_t z = div(r, a.d_Hs);
-        return (div(z, a.d_B) * a.LHs + div(r - z * a.Hs, a.d_B)) * a.LW;
+        const uint32_t z = fdiv(r, a.d_Hs);
+        return (fdiv(z, a.d_B) * a.LHs + fdiv(r - z * a.Hs, a.d_B)) * a.LW;
     } else {
-        return div(r, a.d_B) * a.LW;
+        return fdiv(r, a.d_B) * a.LW;
     }
 }
 
@@ -47,8 +46,8 @@ __device__ __forceinline__ void store4(T* dst, size_t i, float a, float b, float
     } else {
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
         u32x2 o;
-        o.x = float_to_bf16_bits(a) | (float_to_bf16_bits(b) << 16);
-        o.y = float_to_bf16_bits(c) | (float_to_bf16_bits(d) << 16);
+        o.x = bf16_pack2(a, b);
+        o.y = bf16_pack2(c, d);
         __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(dst + i));
     }
 }
@@ -106,7 +105,8 @@ __device__ __forceinline__ void dec_lds(const DecArgs& a, uint32_t*& s_codes, fl
 }
 
 // W % 4 == 0 and B % 4 == 0: the four elements of a vector lie in one row and
-// share one LFC value.  A workgroup streams G whole planes.
+// share one LFC value.  A workgroup streams G whole planes.  Only what decompress_stream leaves comes here: planes
+// beyond its 32-bit index tricks and 2-byte maps that do not start on a 16-byte boundary.
 template <typename T, int BITS, int ND>
 __device__ __forceinline__ void decompress_rowvec_body(const DecArgs& a) {
     const DecPtrs pt = dec_ptrs(a.tab, a.rg);
@@ -119,47 +119,6 @@ __device__ __forceinline__ void decompress_rowvec_body(const DecArgs& a) {
     const uint32_t nvec = Gc * a.q4;
     constexpr uint32_t Lq = (1u << BITS) - 1u;
     T* out = static_cast<T*>(pt.xhat) + (size_t)p0 * a.HW;
-    if constexpr (sizeof(T) == 2) {
-        if (a.pair8) {
-            // two neighbouring vectors of one row per lane step: one 16-byte store
-            for (uint32_t vi = 2 * tid; vi < nvec; vi += 2 * kThreads) {
-                // (the divisions of this loop keep their test for the divisor 1: measured 1 % faster on the
-                // 256 x 256 x 56 x 56 bfloat16 map than without)
-                const uint32_t g = fdiv_tested(vi, a.d_q4);
-                const uint32_t fi = vi - g * a.q4;                     // even
-                const float2 dd = s_meta[g];
-                uint32_t lo, hi;                                       // codes of elements 0-3 and 4-7
-                if constexpr (BITS == 1) {
-                    lo = reinterpret_cast<const uint8_t*>(s_codes)[g * a.WPP * 4 + (fi >> 1)];
-                    hi = lo >> 4;
-                } else if constexpr (BITS == 2) {
-                    lo = reinterpret_cast<const uint16_t*>(s_codes)[(g * a.WPP * 4 + fi) >> 1];
-                    hi = lo >> 8;
-                } else if constexpr (BITS == 4) {
-                    lo = s_codes[(g * a.WPP * 2 + fi) >> 1];
-                    hi = lo >> 16;
-                } else {
-                    lo = s_codes[g * a.WPP + fi];
-                    hi = s_codes[g * a.WPP + fi + 1];
-                }
-                const uint32_t r = fdiv_tested(fi, a.d_w4);
-                const uint32_t c = (fi - r * a.w4) * 4;
-                const T* lrow = s_lfc + g * a.nb + lfc_row<ND, true>(a, r);
-                const float l0 = Elem<T>::load(lrow, fdiv_tested(c, a.d_B)), l1 = Elem<T>::load(lrow, fdiv_tested(c + 4, a.d_B));
-                uint32_t w[4];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    w[e] = float_to_bf16_bits(dequant((lo >> (2 * e * BITS)) & Lq, dd.y, dd.x, l0)) |
-                           (float_to_bf16_bits(dequant((lo >> ((2 * e + 1) * BITS)) & Lq, dd.y, dd.x, l0)) << 16);
-                    w[2 + e] = float_to_bf16_bits(dequant((hi >> (2 * e * BITS)) & Lq, dd.y, dd.x, l1)) |
-                               (float_to_bf16_bits(dequant((hi >> ((2 * e + 1) * BITS)) & Lq, dd.y, dd.x, l1)) << 16);
-                }
-                u32x4 o; o.x = w[0]; o.y = w[1]; o.z = w[2]; o.w = w[3];
-                __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(out + (size_t)vi * 4));
-            }
-            return;
-        }
-    }
     for (uint32_t vi = tid; vi < nvec; vi += kThreads) {
         const uint32_t g = fdiv(vi, a.d_q4);
         const uint32_t fi = vi - g * a.q4;        // vector index inside the plane
@@ -184,27 +143,33 @@ __global__ void __launch_bounds__(kThreads) decompress_rowvec(DecArgs a) { decom
 template <typename T, int BITS>
 __global__ void __launch_bounds__(kThreads) decompress_rowvec_3d(DecArgs a) { decompress_rowvec_body<T, BITS, 3>(a); }
 
-// The row-vector case again (W % 4 == 0, B % 4 == 0, 4-byte elements) without staging and without a
-// barrier: a workgroup is ONE wavefront that rebuilds kStreamK * 64 consecutive 16-byte vectors of the
-// map (4 KB for kStreamK = 4), wherever the plane boundaries fall.  Each lane finds the plane, row and
-// block of its vectors, loads their code byte / half-word / word, their plane's (delta, Delta) and their
-// block's H^L straight from the packed buffer (all of its lines are shared by many lanes and rounds, so
-// nearly all of these loads are cache hits), and stores.  All loads of the chunk are issued before the
-// first store.  Short-lived one-wavefront workgroups that write a few KB each are what the memory
-// system takes fastest (a write-only stream: 6.4 - 6.7 TB/s in 4 KB pieces, 5.5 in 32 KB ones), and with
-// no barrier the latency of the packed reads is hidden by the other wavefronts of the CU.
+// The row-vector case again (W % 4 == 0, B % 4 == 0) without staging and without a barrier: a workgroup is
+// ONE wavefront that rebuilds kStreamK * 64 consecutive 16-byte vectors of the map (4 KB for kStreamK = 4),
+// wherever the plane boundaries fall.  Each lane finds the plane, row and block of its vectors, loads their
+// code bytes, their plane's (delta, Delta) and their block's H^L straight from the packed buffer (all of its
+// lines are shared by many lanes and rounds, so nearly all of these loads are cache hits), and stores.  All
+// loads of the chunk are issued before the first store.  Short-lived one-wavefront workgroups that write a
+// few KB each are what the memory system takes fastest (a write-only stream: 6.4 - 6.7 TB/s in 4 KB pieces,
+// 5.5 in 32 KB ones), and with no barrier the latency of the packed reads is hidden by the other wavefronts
+// of the CU.
+// A lane step looks up a piece of PE elements of one row and one block: four of a 4-byte type (the vector),
+// eight of a 2-byte type where rows and blocks are whole vectors of eight (W8), else the vector's two halves
+// one by one (widths such as 28, block sizes such as 12, planes that end in the middle of a vector).
 constexpr int kStreamK = DIVISION_STREAM_K;
-template <typename T, int BITS, int ND>
+template <typename T, int BITS, int ND, bool W8>
 __device__ __forceinline__ void decompress_stream_body(const DecArgs& a) {
-    static_assert(sizeof(T) == 4, "4-byte elements");
+    constexpr int EPV = 16 / sizeof(T);                                 // elements per vector
+    constexpr int PE = W8 ? 8 : 4;                                      // elements per piece
+    constexpr int NP = EPV / PE;                                        // pieces per vector
+    static_assert(NP >= 1, "W8 is for 2-byte elements");
     constexpr int K = kStreamK;
     constexpr uint32_t Lq = (1u << BITS) - 1u;
-    constexpr uint32_t CBY = BITS / 2;                                  // code bytes per vector
+    constexpr uint32_t PB = PE * BITS / 8;                              // code bytes per piece (1-bit codes of four elements: half a byte)
     const DecPtrs pt = dec_ptrs(a.tab, a.rg);
     const uint32_t lane = threadIdx.x;
-    // first vector of the chunk, counted over the whole map: its plane g0 and its place r0 inside the
+    // first piece of the chunk, counted over the whole map: its plane g0 and its place r0 inside the
     // plane (uniform; the quotient by a binary64 reciprocal, then put right)
-    const uint64_t v0 = (uint64_t)blockIdx.x * (64u * K);
+    const uint64_t v0 = (uint64_t)blockIdx.x * (64u * K * NP);
     const uint64_t nvec = (uint64_t)a.P * a.q4;
     uint32_t g0 = (uint32_t)((double)v0 * (1.0 / (double)a.q4));
     int64_t r0 = (int64_t)(v0 - (uint64_t)g0 * a.q4);
@@ -213,45 +178,67 @@ __device__ __forceinline__ void decompress_stream_body(const DecArgs& a) {
     g0 = __builtin_amdgcn_readfirstlane(g0);
     const uint32_t t0 = __builtin_amdgcn_readfirstlane((uint32_t)r0);
 
-    uint32_t code[K];
-    float2 dd[K];
-    float lfc[K];
+    typedef typename std::conditional<PB == 8, uint64_t, uint32_t>::type code_t;
+    code_t code[K * NP];
+    float2 dd[K * NP];
+    float lfc[K * NP];
     const uint8_t* cbase = reinterpret_cast<const uint8_t*>(pt.codes);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const uint32_t t = t0 + 64u * k + lane;                           // < q4 + 64 K
+    for (int k = 0; k < K * NP; ++k) {
+        const uint32_t t = t0 + (uint32_t)NP * (64u * (k / NP) + lane) + (uint32_t)(k % NP);     // < q4 + 64 K NP
         const uint32_t dg = fdiv(t, a.d_q4);
-        const uint32_t fi = t - dg * a.q4;                                // vector inside its plane
-        const uint32_t g = min(g0 + dg, a.P - 1u);                         // vectors past the map re-read its last plane
+        const uint32_t fi = t - dg * a.q4;                                // piece inside its plane
+        const uint32_t g = min(g0 + dg, a.P - 1u);                         // pieces past the map re-read its last plane
         const uint32_t r = fdiv(fi, a.d_w4);
-        const uint32_t c = (fi - r * a.w4) * 4u;
+        const uint32_t c = (fi - r * a.w4) * (uint32_t)PE;
         const uint32_t blk = lfc_row<ND>(a, r) + fdiv(c, a.d_B);
-        const uint8_t* cp = cbase + (size_t)g * a.WPP * 4u + (BITS == 1 ? (size_t)(fi >> 1) : (size_t)fi * CBY);
-        if constexpr (BITS == 1) code[k] = (uint32_t)*cp >> ((fi & 1u) * 4u);     // four 1-bit codes: half a byte
-        else if constexpr (BITS == 2) code[k] = *cp;
-        else if constexpr (BITS == 4) code[k] = *reinterpret_cast<const uint16_t*>(cp);
-        else code[k] = *reinterpret_cast<const uint32_t*>(cp);
+        const uint8_t* cp = cbase + (size_t)g * a.WPP * 4u + (PB == 0 ? (size_t)(fi >> 1) : (size_t)fi * PB);
+        if constexpr (PB == 0) code[k] = (uint32_t)*cp >> ((fi & 1u) * 4u);       // four 1-bit codes: half a byte
+        else if constexpr (PB == 1) code[k] = *cp;
+        else if constexpr (PB == 2) code[k] = *reinterpret_cast<const uint16_t*>(cp);
+        else if constexpr (PB == 4) code[k] = *reinterpret_cast<const uint32_t*>(cp);
+        else code[k] = (uint64_t)reinterpret_cast<const uint32_t*>(cp)[0] | ((uint64_t)reinterpret_cast<const uint32_t*>(cp)[1] << 32);
         dd[k] = meta_load(pt.meta, g, kC16<T>);
         lfc[k] = lfc_load<T>(pt.lfc, (size_t)g * a.nb + blk, kC16<T>);
     }
-    T* out = static_cast<T*>(pt.xhat) + v0 * 4u;
-    const uint64_t left = nvec - v0;                                      // vectors from the chunk's start to the map's end
+    T* out = static_cast<T*>(pt.xhat) + v0 * PE;
+    const uint64_t left = nvec - v0;                                      // pieces from the chunk's start to the map's end
+    constexpr uint32_t PBY = PE * sizeof(T);                              // bytes of a piece
     const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
-        out, 0, (int)(left < 64u * K ? (uint32_t)left * 16u : 64u * K * 16u), 0x00020000);
+        out, 0, (int)(left < 64u * K * NP ? (uint32_t)left * PBY : 64u * K * 16u), 0x00020000);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        float v[EPV];
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            const int n = k * NP + e / PE;
+            v[e] = dequant((uint32_t)(code[n] >> ((e % PE) * BITS)) & Lq, dd[n].y, dd[n].x, lfc[n]);
+        }
         u32x4 o;
-        o.x = __float_as_uint(dequant(code[k] & Lq, dd[k].y, dd[k].x, lfc[k]));
-        o.y = __float_as_uint(dequant((code[k] >> BITS) & Lq, dd[k].y, dd[k].x, lfc[k]));
-        o.z = __float_as_uint(dequant((code[k] >> (2 * BITS)) & Lq, dd[k].y, dd[k].x, lfc[k]));
-        o.w = __float_as_uint(dequant((code[k] >> (3 * BITS)) & Lq, dd[k].y, dd[k].x, lfc[k]));
-        store_b128_checked(o, ors, lane * 16u + (uint32_t)(k * 1024), DIVISION_STREAM_STORE_AUX);   // past the map: dropped
+        if constexpr (sizeof(T) == 4) o = u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+        else o = u32x4{bf16_pack2(v[0], v[1]), bf16_pack2(v[2], v[3]), bf16_pack2(v[EPV - 4], v[EPV - 3]), bf16_pack2(v[EPV - 2], v[EPV - 1])};
+        store_b128_checked(o, ors, lane * 16u + (uint32_t)(k * 1024), DIVISION_STREAM_STORE_AUX);   // past the map: dropped, dword by dword
     }
 }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_body<T, BITS, 2>(a); }
+__global__ void __launch_bounds__(64) decompress_stream(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_body<T, BITS, 2, false>(a); }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_body<T, BITS, 3>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_body<T, BITS, 3, false>(a); }
+// The same for 2-byte elements: decompress_rowvec, one wavefront per chunk.  The staged kernel of that name keeps what
+// does not start on a 16-byte boundary.  256 x 256 x 56 x 56 (b = 2): staged 77 us (5.3 TB/s), this one 68.5 us
+// (6.0 TB/s); 32 x 512 x 1 x 3072 (b = 4): 27 us and 20.8 us.
+struct DecStreamArgs : DecArgs {};
+template <typename T, int BITS, int ND>
+__device__ __forceinline__ void decompress_rowvec_stream(const DecArgs& a) {
+    if constexpr (sizeof(T) == 2) {
+        if (a.whole8) decompress_stream_body<T, BITS, ND, true>(a);
+        else decompress_stream_body<T, BITS, ND, false>(a);
+    }
+}
+template <typename T, int BITS>
+__global__ void __launch_bounds__(64) decompress_rowvec(DecStreamArgs a) { decompress_rowvec_stream<T, BITS, 2>(a); }
+template <typename T, int BITS>
+__global__ void __launch_bounds__(64) decompress_rowvec_3d(DecStreamArgs a) { decompress_rowvec_stream<T, BITS, 3>(a); }
 
 // The stream kernel for maps whose rows, blocks or planes are not whole vectors (odd widths, any B; 4-byte
 // elements): a workgroup is again ONE wavefront that rebuilds kStreamK * 64 consecutive, aligned 16-byte

@@ -12,12 +12,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
 
-// fp32 -> bf16, round to nearest even (NaN kept quiet)
-__device__ __forceinline__ uint32_t float_to_bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+// Two fp32 -> bf16 in one word (a in the low half), round to nearest even, a NaN kept quiet: one gfx950 conversion
+// instruction.  It gives the bits of the integer rule (u + 0x7fff + bit 16) >> 16 (NaN: u >> 16 | 0x40) for every one of
+// the 2^32 inputs (compared exhaustively on the device); the integer rule is seven instructions and a branch per value.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pack2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2_t));
 }
+__device__ __forceinline__ uint32_t float_to_bf16_bits(float f) { return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)f); }
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {
@@ -60,10 +63,9 @@ __device__ __forceinline__ uint32_t pair_word(uint32_t xw, uint32_t k2) {
 // with fastdiv_ok).  The divisor 1 has no 32-bit multiplier: its m is 0 and `one` is all ones, so that the quotient
 // needs no test (a test on m, uniform as it is, became a scalar branch per division: 13 in decompress_stream, 228
 // in compress_units, each ending a basic block in the middle of the loads; without them decompress_stream runs
-// 1.5-2.5 % faster).  fdiv_tested is the form with the test, kept for the one loop that measured faster with it.
+// 1.5-2.5 % faster).
 struct FastDiv { uint32_t one, m; };
 __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv f) { return __umulhi(n, f.m) | (n & f.one); }
-__device__ __forceinline__ uint32_t fdiv_tested(uint32_t n, FastDiv f) { return f.m ? __umulhi(n, f.m) : n; }
 static FastDiv make_fastdiv(uint32_t d) {
     FastDiv f; f.one = d <= 1 ? 0xffffffffu : 0u; f.m = d <= 1 ? 0u : (uint32_t)((1ull << 32) / d) + 1u; return f;
 }

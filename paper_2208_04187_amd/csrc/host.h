@@ -753,7 +753,7 @@ uint64_t dec_planes(const Layout& L, size_t es, uint64_t mult) {
     return G;
 }
 
-// Fills the decompress launch plan; returns 7 (row vectors of 4-byte elements, a wavefront per chunk), 0 (row vectors), 3 (block table),
+// Fills the decompress launch plan; returns 7 (row vectors, a wavefront per chunk), 0 (row vectors), 3 (block table),
 // 8 (4-byte elements of any width, a wavefront per chunk), 6 (four consecutive elements
 // per lane step, any width), 5 (word by word through LDS), 1 (flat), 4 (lane per plane) or 2 (scalar).
 // Hs = rows of one depth slice, D = depth slices (1 for a 2-D map; the table kernel takes 2-D maps only).
@@ -792,25 +792,31 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
     }
     // fast path: rows are whole vectors that sit inside one block
     if (W % 4 == 0 && B % 4 == 0 && small_idx && out_vec_aligned) {
+        // one wavefront per 64 * kStreamK vectors, no staging; the lookups go by pieces of four elements, or of eight
+        // 2-byte elements where rows and blocks are whole vectors
+        if (es == 4 || ((uintptr_t)xhat % 16) == 0) {
+            const uint64_t pe = es == 2 && W % 8 == 0 && B % 8 == 0 ? 8 : 4;
+            const uint64_t chunk = 64ull * kStreamK * (16 / es / pe);      // pieces
+            const uint64_t q = L.HW / pe, npiece = L.P * q;
+            if (fastdiv_ok(q + chunk, q) && fastdiv_ok(q, (uint64_t)W / pe) && (npiece + chunk - 1) / chunk < (1ull << 31) &&
+                npiece < (1ull << 40)) {
+                a->whole8 = pe == 8;
+                a->q4 = (uint32_t)q;
+                a->w4 = (uint32_t)((uint64_t)W / pe);
+                a->d_q4 = make_fastdiv(a->q4);
+                a->d_w4 = make_fastdiv(a->w4);
+                *grid = (uint32_t)((npiece + chunk - 1) / chunk);
+                return 7;
+            }
+        }
         a->q4 = (uint32_t)(L.HW / 4);
         a->w4 = (uint32_t)(W / 4);
-        // 4-byte elements: one wavefront per 64 * kStreamK vectors, no staging
-        const uint64_t chunk = 64ull * kStreamK;
-        const uint64_t nvec = L.P * (L.HW / 4);
-        if (es == 4 && fastdiv_ok(a->q4 + chunk, a->q4) && fastdiv_ok(a->q4, a->w4) && (nvec + chunk - 1) / chunk < (1ull << 31) &&
-            nvec < (1ull << 40)) {
-            a->d_q4 = make_fastdiv(a->q4);
-            a->d_w4 = make_fastdiv(a->w4);
-            *grid = (uint32_t)((nvec + chunk - 1) / chunk);
-            return 7;
-        }
         uint64_t G = dec_planes(L, es, 1);
         while (G > 1 && !fastdiv_ok(G * a->q4 + kThreads, a->q4)) --G;
         if (fastdiv_ok(G * a->q4 + kThreads, a->q4) && fastdiv_ok(a->q4, a->w4) && dec_lds_bytes(L, es, G) <= kDecLdsMax) {
             a->G = (uint32_t)G;
             a->d_q4 = make_fastdiv(a->q4);
             a->d_w4 = make_fastdiv(a->w4);
-            a->pair8 = es == 2 && W % 8 == 0 && ((uintptr_t)xhat % 16) == 0;
             *grid = (uint32_t)((L.P + G - 1) / G);
             return 0;
         }
@@ -996,6 +1002,14 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
         constexpr int BITS = decltype(bits)::value;
         const int kind = c.kind;
         void (*kern)(DecArgs);
+        if (kind == 7 && sizeof(T) == 2) {
+            DecStreamArgs sa;
+            static_cast<DecArgs&>(sa) = c.a;
+            void (*rv)(DecStreamArgs);
+            if (c.flat) rv = decompress_rowvec<T, BITS>; else rv = decompress_rowvec_3d<T, BITS>;
+            hipLaunchKernelGGL(rv, dim3(c.gx, c.gy), dim3(64), 0, c.st, sa);
+            return hipGetLastError();
+        }
         if (kind == 7 || kind == 8 || kind == 9) {
             if (kind == 7) kern = c.flat ? decompress_stream<T, BITS> : decompress_stream_3d<T, BITS>;
             else if (kind == 9) kern = decompress_stream_one<T, BITS>;
@@ -1010,12 +1024,13 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
             hipLaunchKernelGGL(kern, dim3(c.gx, c.gy), dim3(64 * c.nw), c.lds, c.st, c.a);
             return hipGetLastError();
         }
-        if (c.flat)
-            kern = kind == 0 ? decompress_rowvec<T, BITS> : kind == 3 ? decompress_table<T, BITS>
+        if (kind == 0) { if (c.flat) kern = decompress_rowvec<T, BITS>; else kern = decompress_rowvec_3d<T, BITS>; }
+        else if (c.flat)
+            kern = kind == 3 ? decompress_table<T, BITS>
                  : kind == 5 ? decompress_words<T, BITS> : kind == 1 ? decompress_flat<T, BITS>
                  : kind == 4 ? decompress_lane<T, BITS> : decompress_scalar<T, BITS>;
         else
-            kern = kind == 0 ? decompress_rowvec_3d<T, BITS> : kind == 5 ? decompress_words_3d<T, BITS>
+            kern = kind == 5 ? decompress_words_3d<T, BITS>
                  : kind == 1 ? decompress_flat_3d<T, BITS>
                  : kind == 4 ? decompress_lane<T, BITS> : decompress_scalar_3d<T, BITS>;
         const hipError_t e = allow_large_lds(kern, c.lds);
@@ -1254,7 +1269,7 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
         if (kind == 6)
             n = snprintf(out, cap, "decompress_units<%s, %d, %d>", tn, b, (int)a.G);
         else if (kind == 7)
-            n = snprintf(out, cap, "decompress_stream%s<%s, %d>", sfx, tn, b);
+            n = snprintf(out, cap, "%s%s<%s, %d>", es == 2 ? "decompress_rowvec" : "decompress_stream", sfx, tn, b);
         else if (kind == 8)
             n = snprintf(out, cap, "decompress_stream_any%s<%s, %d>", sfx, tn, b);
         else if (kind == 9)

@@ -1,0 +1,64 @@
+"""Small maps at the edges of the kernels' tiles (remainders, halves of vectors, first and last planes), bit for bit
+against the CPU oracle: packed buffers and rebuilt maps are whole numbers and single IEEE operations, so equal."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2208_04187_amd as pkg
+
+pytestmark = pytest.mark.gpu
+
+FORMATS = {"f32": (torch.float32, False, oracle.F32), "bf16": (torch.bfloat16, False, oracle.BF16),
+           "c16": (torch.float32, True, oracle.F32_C16)}
+
+
+def _host(t):
+    """numpy form of a tensor: float32 as it is, bfloat16 as its 16-bit patterns"""
+    return t.view(torch.int16).numpy().view(np.uint16) if t.dtype == torch.bfloat16 else t.numpy()
+
+
+def _round_trip(shape, B, b, mode, seed=7, offset=0, relu=False):
+    """Compress and rebuild a map whose rebuilt copy starts `offset` elements into its buffer."""
+    dtype, c16, dt = FORMATS[mode]
+    three = len(shape) == 5
+    gen = torch.Generator().manual_seed(seed * 1000 + B * 10 + b)
+    x = torch.randn(shape, generator=gen)
+    x = (x.relu() if relu else x).to(dtype)
+    xh = _host(x)
+    comp = pkg.division_compress_3d if three else pkg.division_compress
+    dec = pkg.division_decompress_3d if three else pkg.division_decompress
+    nbytes = (pkg.division_packed_bytes_3d if three else pkg.division_packed_bytes)(*shape, B, b, dtype, c16)
+    packed = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda:0")
+    comp(x.to("cuda:0"), B, b, seed, packed=packed, c16=c16)
+    ref = oracle.compress(xh, B, b, seed, dt)
+    torch.cuda.synchronize()
+    assert np.array_equal(packed.cpu().numpy(), ref), "packed buffer"
+    guard = 16
+    buf = torch.full((offset + x.numel() + guard,), -1.0, dtype=dtype, device="cuda:0")
+    dec(packed, shape, B, b, dtype, out=buf[offset:offset + x.numel()].view(shape), c16=c16)
+    torch.cuda.synchronize()
+    want = oracle.decompress(ref, shape, B, b, dt)
+    got = _host(buf[offset:offset + x.numel()].cpu()).reshape(shape)
+    assert np.array_equal(np.asarray(got).view(np.uint8), np.asarray(want).reshape(shape).view(np.uint8)), "rebuilt map"
+    assert bool((buf[:offset] == -1).all()) and bool((buf[offset + x.numel():] == -1).all()), "written outside the map"
+
+
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+@pytest.mark.parametrize("shape,B,offset", [
+    ((3, 5, 1, 8), 8, 0),                # a plane is one vector
+    ((1, 1, 1, 4), 4, 0),                # half a vector in all
+    ((3, 7, 5, 28), 8, 0),               # rows of 3.5 vectors: a vector spans two rows and two planes
+    ((3, 7, 5, 12), 4, 0),
+    ((5, 3, 6, 24), 12, 0),              # whole rows, blocks of a vector and a half
+    ((2, 3, 16, 40), 8, 0),
+    ((2, 3, 16, 40), 8, 4),              # the rebuilt map starts in the middle of a vector
+    ((1, 1, 7, 1024), 64, 0),
+    ((9, 57, 1, 264), 8, 0),             # chunk ends inside a plane
+    ((2, 3, 3, 9, 16), 8, 0),
+    ((2, 3, 3, 5, 20), 4, 0),
+])
+def test_two_byte_rows_of_whole_pieces(shape, B, b, offset):
+    _round_trip(shape, B, b, "bf16", offset=offset)
