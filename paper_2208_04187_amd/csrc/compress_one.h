@@ -158,33 +158,64 @@ __global__ void __launch_bounds__(64) compress_one(OneArgs a) {
 
 // 1-D maps (Appendix D, AveragePooling1D: Minibatch x Channel x N, the maps of linear and
 // transformer layers) whose block is a power-of-two number of 16-byte vectors (B = 4, 8, 16, 32, 64
-// for fp32): laid out like compress_one, the `upb` vectors of a block sit in neighbouring lanes of
-// one round, so a block's sum is a DPP reduction over those lanes and its LFC stays in a register.
-// No LDS.  The planes of a wavefront are contiguous: their vectors are read through one bounds-checked
-// buffer (a lane whose vector lies past its plane reads its neighbour's data or zero and is masked in
-// the arithmetic), codes and H^L leave through bounds-checked buffer stores with the offset pushed out
-// of range where nothing is to be written: no branch depends on a lane or on the round, loads and
-// rounds are straight-line code that the compiler is free to interleave.  K as in compress_one.
+// for fp32): laid out like compress_one, vector u of a plane in lane u mod S of round u / S.  The planes of
+// a wavefront are contiguous: their vectors are read through one bounds-checked buffer, codes and H^L leave
+// through bounds-checked buffer stores (planes past the map are past the buffers), so no branch depends on a
+// lane or on the round: loads and rounds are straight-line code that the compiler is free to interleave.
+// K as in compress_one.
+//
+// What bounds it is the vector ALUs, so what a block costs beyond its elements is kept small:
+// - LU >= 0: a block is 1 << LU = 1, 2 or 4 vectors; its sum is LU DPP steps over neighbouring lanes.
+// - LU < 0: longer blocks (8 vectors and more).  A 64-bit DPP step is two moves and an addition, and every lane
+//   would repeat the block's mean; instead the lanes park their partial sums in LDS, ONE lane per block of the
+//   whole wavefront adds them in the same tree order, takes the mean, stores H^L and hands it out through LDS.
+//   LU = -1: a block lies in one round.  LU = -2: S is half a block, so that a plane of a few hundred bytes
+//   (96 tokens) leaves no lane empty, and a lane first adds its two rounds of the block.
+// - Only rounds that can hold vectors past the plane (k >= first_masked) are masked; in the others every block is
+//   whole, its count a power of two and the mean an exact scaling.
+// Before and after (every lane repeating the 64-bit reduction and the mean, rounds tested at run time): 64 x 3136 planes
+// of 384 floats cached as bfloat16, B = 64, b = 2: 72 -> 56 us (5.5 TB/s of x); of 96 floats: 32 -> 21.5 us;
+// 32 x 512 planes of 3072 bfloat16, B = 8, b = 4: 36 -> 28.8 us.
 constexpr int kLineUnits = 13;
+template <int LU> struct LineArgs : OneArgs {};
 // NG > 1: planes of at most R = K / NG rounds (a few hundred bytes each): a wavefront takes NG groups of
 // 64 / S planes one after the other, all their loads issued first, so that it has K vectors per lane in
 // flight like the instances for larger planes (two or three would not cover the memory latency).
-template <typename T, int BITS, int K, int NG = 1>
-__global__ void __launch_bounds__(64) compress_line(OneArgs a) {
+// The fourth argument counts what the twelve rounds of such an instance are cut into: plane groups, or for LU = -2,
+// where two rounds make a block (three rounds a plane, four groups), the K / 2 rounds of whole blocks.
+constexpr int line_groups(int K, int N, int LU) { return K == 12 && LU == -2 ? 4 : N; }
+template <typename T, int BITS, int K, int N, int LU>
+__device__ __forceinline__ void compress_line_body(const OneArgs& a) {
+    constexpr int NG = line_groups(K, N, LU);
     constexpr int R = K / NG;
     static_assert(R * NG == K, "whole groups");
+    constexpr bool LDS = LU < 0;
+    constexpr int UR = LU == -2 ? 2 : 1;                  // rounds per block
+    constexpr int RB = (R + UR - 1) / UR;                 // rounds of blocks
+    // the host gives an instance planes of at least this many rounds, so the earlier ones are whole
+    constexpr int first_masked = NG > 1 ? R - 1 : K == 13 ? 6 : K == 6 ? 4 : K == 4 ? 3 : 0;
     constexpr uint32_t EPV = 16 / sizeof(T);
     constexpr uint32_t CBV = EPV * BITS / 8;
     constexpr bool HALF = EPV * BITS == 4;                // 1-bit codes of a 4-element vector: half a byte
+    constexpr bool KEEP = sizeof(T) == 4 || R <= 6;       // residuals stay in registers between the extremes and the codes
     constexpr float Lf = float((1 << BITS) - 1);
     constexpr uint32_t kDrop = 0x80000000u;              // an offset past every buffer here (and no wrap when a round's offset is added): the access is dropped
+    constexpr uint32_t LB = (sizeof(T) == 2 || kC16<T>) ? 2u : 4u;          // bytes of a cached H^L value
     const uint32_t tid = threadIdx.x;
     const CompPtrs pt = comp_ptrs(a.tab, a.rg, tid);
-    const uint32_t sub = tid & (a.S - 1u);
+    const uint32_t S = a.S, sub = tid & (S - 1u), lp = tid >> a.S_log2;
     const uint32_t ppw = a.ppw * NG;                     // planes of the wavefront
     const uint32_t p0 = xcd_run_index(blockIdx.x, gridDim.x) * ppw;
     const uint32_t Gc = min(ppw, a.P - p0);
 
+    // Offset of round r's piece (`bytes` per vector) given that of round 0: in a whole round the step goes into the scalar
+    // operand, otherwise a lane without a vector there is sent past the buffer.
+    struct Place { uint32_t v, s; };
+    auto place = [&](int r, uint32_t off, uint32_t bytes) -> Place {
+        const uint32_t step = (uint32_t)r * S * bytes;
+        if (r < first_masked) return Place{off, step};
+        return Place{sub + (uint32_t)r * S < a.qv && off != kDrop ? off + step : kDrop, 0u};
+    };
     u32x4 q[K];
     {
         const T* src = static_cast<const T*>(pt.x) + (size_t)p0 * a.HW;
@@ -192,58 +223,127 @@ __global__ void __launch_bounds__(64) compress_line(OneArgs a) {
             __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, (int)(Gc * a.HW * sizeof(T)), 0x00020000);
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            const uint32_t pl = (uint32_t)g * a.ppw + (tid >> a.S_log2);
-            const uint32_t off0 = pl < Gc ? (pl * a.qv + sub) * 16u : kDrop;
+            const uint32_t off0 = ((g * a.ppw + lp) * a.qv + sub) * 16u;          // a plane past the map is past the buffer
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                // no round is tested (see compress_one); a vector past the plane's end is not fetched
-                const uint32_t u = sub + (uint32_t)r * a.S;
-                q[g * R + r] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, u < a.qv ? off0 + (uint32_t)r * a.S * 16u : kDrop, 0, kLoadAux);
+                // a vector past the plane's end is not fetched
+                const Place at = place(r, off0, 16u);
+                q[g * R + r] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at.v, (int)at.s, kLoadAux);
             }
         }
     }
-    // every block but the plane's last has upb vectors: their reciprocals are taken once, not per round
     const uint32_t cnt_full = a.upb * EPV, cnt_last = (a.qv - (a.nb - 1u) * a.upb) * EPV;
-    const double rcp_full = 1.0 / (double)cnt_full, rcp_last = 1.0 / (double)cnt_last;
+    const double rcp_last = LU == 0 ? 0.0 : 1.0 / (double)cnt_last;
+    const double rcp_full = __longlong_as_double((long long)(1023u - (31u - (uint32_t)__builtin_clz(cnt_full))) << 52);     // a power of two
     uint8_t* cwave = reinterpret_cast<uint8_t*>(pt.codes) + (size_t)p0 * a.WPP * 4;
     const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(cwave, 0, (int)(Gc * a.WPP * 4u), 0x00020000);
-    constexpr uint32_t LB = (sizeof(T) == 2 || kC16<T>) ? 2u : 4u;          // bytes of a cached H^L value
     const __amdgpu_buffer_rsrc_t lrs = __builtin_amdgcn_make_buffer_rsrc(
         static_cast<uint8_t*>(pt.lfc) + (size_t)p0 * a.nb * LB, 0, (int)(Gc * a.nb * LB), 0x00020000);
+    auto put_lfc = [&](float v, Place at) {
+        if constexpr (LB == 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(__float_as_uint(v) >> 16), lrs, at.v, (int)at.s, 0);     // v is a bfloat16
+        else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), lrs, at.v, (int)at.s, 0);
+    };
     const uint32_t rscale = 1u << (16 - BITS);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-    const uint32_t pl = (uint32_t)g * a.ppw + (tid >> a.S_log2);
-    const uint32_t p = p0 + pl;
-    const bool live = pl < Gc;
-    // ---- AveragePooling1D: block sums over the lanes of a block, residual extremes of the plane
-    float lfcv[R];
-    float mn = __builtin_inff(), mx = -__builtin_inff();
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const uint32_t u = sub + (uint32_t)k * a.S;
-        const bool valid = u < a.qv;
+    auto vector_sum = [&](const u32x4& v) -> double {              // (a vector past the plane was read as zero)
         float f[EPV];
-        unpack_vec<T>(q[g * R + k], f);
+        unpack_vec<T>(v, f);
         double s4 = ((double)f[0] + (double)f[1]) + ((double)f[2] + (double)f[3]);
         if constexpr (EPV == 8) s4 += ((double)f[4] + (double)f[5]) + ((double)f[6] + (double)f[7]);
-        s4 = valid ? s4 + 0.0 : 0.0;                  // a block of negative zeros sums to +0, as a sum from 0 does
-        const double Sb = group_sum_any(a.upb, s4);
-        const uint32_t ustart = u & ~(a.upb - 1u);
-        const bool last = ustart + a.upb >= a.qv;                              // the last block may be short
-        const float lfc = lfc_round<T>(mean_with_rcp(Sb, last ? cnt_last : cnt_full, last ? rcp_last : rcp_full), kC16<T>);
-        lfcv[k] = lfc;
-        float hmn = __builtin_inff(), hmx = -__builtin_inff();
+        return s4;
+    };
+
+    // ---- AveragePooling1D, blocks of 8 vectors and more: the sums of all groups through LDS
+    extern __shared__ float4 smem4[];
+    const uint32_t logM = min(a.upb_log2, a.S_log2), bpr_log = 6u - logM;        // lanes that share a block, blocks per round
+    const uint32_t prow = 64u + (1u << bpr_log);                                  // doubles per round of blocks, one of padding per block
+    double* part = reinterpret_cast<double*>(smem4);                              // [NG * RB][prow]
+    float* lfcs = reinterpret_cast<float*>(part + NG * RB * prow);                // [NG * RB << bpr_log]
+    if constexpr (LDS) {
+        const uint32_t slot = tid + (tid >> logM);
 #pragma unroll
-        for (uint32_t e = 0; e < EPV; ++e) {
-            const float h = f[e] - lfc;
-            hmn = fminf(hmn, h);
-            hmx = fmaxf(hmx, h);
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                double s = vector_sum(q[g * R + rb * UR]);
+                if constexpr (UR == 2) { if (rb * UR + 1 < R) s += vector_sum(q[g * R + (rb * UR + 1 < R ? rb * UR + 1 : 0)]); }
+                part[(g * RB + rb) * prow + slot] = s;
+            }
+        wave_sync();
+        for (uint32_t t0 = 0; t0 < ((uint32_t)(NG * RB) << bpr_log); t0 += 64u) {
+            const uint32_t t = min(t0 + tid, ((uint32_t)(NG * RB) << bpr_log) - 1u);
+            const uint32_t row = t >> bpr_log, gl = t & ((1u << bpr_log) - 1u);
+            const double* ps = part + row * prow + gl * ((1u << logM) + 1u);
+            auto tree8 = [&](int i) -> double { return ((ps[i] + ps[i + 1]) + (ps[i + 2] + ps[i + 3])) + ((ps[i + 4] + ps[i + 5]) + (ps[i + 6] + ps[i + 7])); };
+            double Sb = tree8(0);
+            if (logM >= 4) Sb += tree8(8);
+            if (logM >= 5) Sb += tree8(16) + tree8(24);
+            if (logM >= 6) Sb += (tree8(32) + tree8(40)) + (tree8(48) + tree8(56));
+            const uint32_t g = row / (uint32_t)RB, rb = row - g * (uint32_t)RB;
+            const uint32_t l0 = gl << logM;                                       // the block's first lane
+            const uint32_t pl = g * a.ppw + (l0 >> a.S_log2);
+            const uint32_t blk = (rb << (a.S_log2 - logM)) + ((l0 & (S - 1u)) >> logM);
+            const bool last = blk + 1u == a.nb;                                   // the last block may be short
+            const float m = lfc_round<T>(mean_with_rcp(Sb + 0.0, last ? cnt_last : cnt_full, last ? rcp_last : rcp_full), kC16<T>);
+            lfcs[t] = m;
+            put_lfc(m, Place{blk < a.nb ? (pl * a.nb + blk) * LB : kDrop, 0u});
         }
-        mn = fminf(mn, valid ? hmn : __builtin_inff());
-        mx = fmaxf(mx, valid ? hmx : -__builtin_inff());
+        wave_sync();
     }
-    group_minmax(a.S, mn, mx);
+
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+    const uint32_t pl = (uint32_t)g * a.ppw + lp;
+    const uint32_t p = p0 + pl;
+    const bool live = pl < Gc;
+    // ---- shorter blocks: sums over the lanes of a block; residual extremes of the plane
+    float lfcv[R];
+    float h[KEEP ? R : 1][EPV];
+    float mn = __builtin_inff(), mx = -__builtin_inff();
+    auto place_block = [&](int k, uint32_t off) -> Place {
+        const uint32_t step = (((uint32_t)k * S) >> a.upb_log2) * LB;
+        if (k < first_masked) return Place{off, step};
+        return Place{sub + (uint32_t)k * S < a.qv && off != kDrop ? off + step : kDrop, 0u};
+    };
+    const uint32_t lo0 = (sub & (a.upb - 1u)) == 0 ? (pl * a.nb + (sub >> a.upb_log2)) * LB : kDrop;     // H^L of the block whose first vector this is
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const bool masked = k >= first_masked;
+        const bool valid = !masked || sub + (uint32_t)k * S < a.qv;
+        float lfc;
+        if constexpr (LDS) {
+            lfc = lfcs[((uint32_t)(g * RB + k / UR) << bpr_log) + (tid >> logM)];
+        } else {
+            const double Sb = group_sum<(LU < 0 ? 1 : 1 << LU)>(vector_sum(q[g * R + k]));
+            float m;
+            if (LU == 0 || !masked) m = (float)(Sb * rcp_full);                    // exact scaling by a power of two
+            else {
+                const uint32_t u = sub + (uint32_t)k * S;
+                const bool last = (u & ~(a.upb - 1u)) + a.upb >= a.qv;             // the last block may be short
+                m = mean_with_rcp(Sb, last ? cnt_last : cnt_full, last ? rcp_last : rcp_full);
+            }
+            lfc = lfc_round<T>(m + 0.0f, kC16<T>);       // a block of negative zeros has mean +0, as a sum from 0 does
+            // (S is a multiple of the block's 1 << LU vectors)
+            put_lfc(lfc, place_block(k, lo0));
+        }
+        lfcv[k] = lfc;
+        float f[EPV];
+        unpack_vec<T>(q[g * R + k], f);
+        float vmn = mn, vmx = mx;
+#pragma unroll
+        for (uint32_t e = 0; e < EPV; ++e) f[e] = f[e] - lfc;
+#pragma unroll
+        for (uint32_t e = 0; e < EPV; e += 2) {
+            vmn = fminf(vmn, fminf(f[e], f[e + 1]));
+            vmx = fmaxf(vmx, fmaxf(f[e], f[e + 1]));
+        }
+        mn = valid ? vmn : mn;
+        mx = valid ? vmx : mx;
+        if constexpr (KEEP) {
+#pragma unroll
+            for (uint32_t e = 0; e < EPV; ++e) h[k][e] = f[e];
+        }
+    }
+    group_minmax(S, mn, mx);
     float delta, Delta, inv;
     plane_scale_any(mn, mx, Lf, kC16<T>, delta, Delta, inv);
     const float invs = inv * (float)(1u << (32 - BITS));
@@ -257,43 +357,49 @@ __global__ void __launch_bounds__(64) compress_line(OneArgs a) {
         for (uint32_t t = 0; t < padb; ++t) cbase[cbytes + t] = 0;
     }
     // ---- residual, Quant, packing
+    const uint32_t co0 = HALF ? ((sub & 1u) == 0 ? pl * a.WPP * 4u + (sub >> 1) : kDrop) : pl * a.WPP * 4u + sub * CBV;
+    const uint32_t xs0 = k1 + sub * (EPV / 2) * kWeyl;
 #pragma unroll
     for (int k = 0; k < R; ++k) {
-        const uint32_t u = sub + (uint32_t)k * a.S;
-        const bool wr = live && u < a.qv;
-        {
-            // H^L of the block whose first vector this is
-            const uint32_t lo = wr && (u & (a.upb - 1u)) == 0 ? (pl * a.nb + (u >> a.upb_log2)) * LB : kDrop;
-            if constexpr (LB == 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)float_to_bf16_bits(lfcv[k]), lrs, lo, 0, 0);
-            else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(lfcv[k]), lrs, lo, 0, 0);
-        }
-        float h[EPV];
-        unpack_vec<T>(q[g * R + k], h);
+        const uint32_t u = sub + (uint32_t)k * S;
+        const bool valid = k < first_masked || u < a.qv;
+        float f[EPV];
+        if constexpr (KEEP) {
 #pragma unroll
-        for (uint32_t e = 0; e < EPV; ++e) h[e] = h[e] - lfcv[k];
-        const uint32_t xw0 = k1 + (u * (EPV / 2)) * kWeyl;
-        const uint32_t co = wr ? pl * a.WPP * 4u + u * CBV : kDrop;
+            for (uint32_t e = 0; e < EPV; ++e) f[e] = h[k][e];
+        } else {
+            unpack_vec<T>(q[g * R + k], f);
+#pragma unroll
+            for (uint32_t e = 0; e < EPV; ++e) f[e] = f[e] - lfcv[k];
+        }
+        const uint32_t xw0 = xs0 + ((uint32_t)k * S * (EPV / 2)) * kWeyl;
         if constexpr (CBV <= 4) {
             uint32_t c = 0;
 #pragma unroll
             for (int j = EPV / 2 - 1; j >= 0; --j)
-                c = push_pair<BITS>(c, h[2 * j], h[2 * j + 1], delta, invs, xw0 + (uint32_t)j * kWeyl, k2, rscale);
+                c = push_pair<BITS>(c, f[2 * j], f[2 * j + 1], delta, invs, xw0 + (uint32_t)j * kWeyl, k2, rscale);
             if constexpr (HALF) {
-                c = wr ? c : 0u;
+                // the even lane of a pair stores the byte of both vectors (a vector past the plane gives zeros)
+                c = valid ? c : 0u;
                 c |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xB1, 0xf, 0xf, true) << 4;     // quad_perm [1,0,3,2]
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, wr && (sub & 1u) == 0 ? pl * a.WPP * 4u + (u >> 1) : kDrop, 0, 0);
-            } else if constexpr (CBV == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, co, 0, 0);
-            else if constexpr (CBV == 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c, crs, co, 0, 0);
-            else __builtin_amdgcn_raw_buffer_store_b32(c, crs, co, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, valid && co0 != kDrop ? co0 + (uint32_t)k * S / 2u : kDrop, 0, 0);
+            } else {
+                const Place at = place(k, co0, CBV);
+                if constexpr (CBV == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, at.v, (int)at.s, 0);
+                else if constexpr (CBV == 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c, crs, at.v, (int)at.s, 0);
+                else __builtin_amdgcn_raw_buffer_store_b32(c, crs, at.v, (int)at.s, 0);
+            }
         } else {
             uint32_t lo = 0, hi = 0;
-            hi = push_pair<BITS>(hi, h[6], h[7], delta, invs, xw0 + 3u * kWeyl, k2, rscale);
-            hi = push_pair<BITS>(hi, h[4], h[5], delta, invs, xw0 + 2u * kWeyl, k2, rscale);
-            lo = push_pair<BITS>(lo, h[2], h[3], delta, invs, xw0 + kWeyl, k2, rscale);
-            lo = push_pair<BITS>(lo, h[0], h[1], delta, invs, xw0, k2, rscale);
+            hi = push_pair<BITS>(hi, f[6], f[7], delta, invs, xw0 + 3u * kWeyl, k2, rscale);
+            hi = push_pair<BITS>(hi, f[4], f[5], delta, invs, xw0 + 2u * kWeyl, k2, rscale);
+            lo = push_pair<BITS>(lo, f[2], f[3], delta, invs, xw0 + kWeyl, k2, rscale);
+            lo = push_pair<BITS>(lo, f[0], f[1], delta, invs, xw0, k2, rscale);
             typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{lo, hi}, crs, co, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{lo, hi}, crs, valid ? co0 + (uint32_t)k * S * CBV : kDrop, 0, 0);
         }
     }
     }
 }
+template <typename T, int BITS, int K, int N, int LU>
+__global__ void __launch_bounds__(64) compress_line(LineArgs<LU> a) { compress_line_body<T, BITS, K, N, LU>(a); }

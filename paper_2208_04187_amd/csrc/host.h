@@ -559,19 +559,24 @@ bool one_shape(const Layout& L, size_t es, const void* x) {
     return plan_one(L, es, x, &tmp, &g);
 }
 
+// Instance of compress_line: log2 of a block's vectors up to 2, beyond that block sums through LDS (-1), or with two
+// rounds per block (-2).
+int line_lu(const OneArgs& a) { return a.upb_log2 <= 2 ? (int)a.upb_log2 : a.upb > a.S ? -2 : -1; }
+
 // Fills the plan of compress_line: a 1-D map (one row) of whole 16-byte vectors, several blocks per
 // plane, a block a power-of-two number of vectors, at most kOneUnits vectors per lane.
-bool plan_line(const Layout& L, int64_t D, int64_t H, int B, size_t es, const void* x, OneArgs* a, uint32_t* grid) {
+bool plan_line(const Layout& L, int64_t D, int64_t H, int B, size_t es, const void* x, OneArgs* a, uint32_t* grid, size_t* lds) {
     const uint64_t epv = 16 / es;
     if (D != 1 || H != 1 || L.nb < 2 || ((uintptr_t)x % 16) != 0 || L.HW % epv != 0 || (uint64_t)B % epv != 0) return false;
     const uint64_t qv = L.HW / epv, upb = (uint64_t)B / epv;
     if ((upb & (upb - 1)) != 0 || upb > 64 || qv > (uint64_t)kLineUnits * 64) return false;
     uint32_t upb_log = 0;
     while ((1ull << upb_log) < upb) ++upb_log;
-    // lanes per plane: a power of two that holds a block, at least 8 (a plane's lanes then read 128
-    // contiguous bytes per round)
-    uint32_t best_S = 0, best_log = 0, K = 0;
-    if (!pick_lanes_and_rounds(qv, upb_log > 3 ? upb_log : 3, &best_S, &best_log, &K)) return false;
+    // lanes per plane: a power of two that holds a block, or half of one that goes through LDS, at least 8 (a
+    // plane's lanes then read 128 contiguous bytes per round)
+    uint32_t best_S = 0, best_log = 0, K = 0, min_log = upb_log > 3 ? upb_log - 1 : 3;
+    if (min_log < 3) min_log = 3;
+    if (!pick_lanes_and_rounds(qv, min_log, &best_S, &best_log, &K)) return false;
     // planes of at most three rounds: twelve rounds of several plane groups per wavefront
     const uint32_t R = (uint32_t)((qv + best_S - 1) / best_S);
     a->NG = K == 3 ? 12u / R : 1u;
@@ -583,6 +588,14 @@ bool plan_line(const Layout& L, int64_t D, int64_t H, int B, size_t es, const vo
     a->upb = (uint32_t)upb; a->upb_log2 = upb_log;
     a->nb = (uint32_t)L.nb;
     *grid = (uint32_t)((L.P + (uint64_t)a->ppw * a->NG - 1) / ((uint64_t)a->ppw * a->NG));
+    *lds = 0;
+    const int lu = line_lu(*a);
+    if (lu < 0) {
+        // one binary64 partial sum per lane and round of blocks (a pad per block), one H^L per block
+        const uint64_t Ri = a->K / a->NG, rows = a->NG * (lu == -2 ? (Ri + 1) / 2 : Ri);
+        const uint64_t bpr = 64u >> (a->upb_log2 < a->S_log2 ? a->upb_log2 : a->S_log2);       // blocks per round
+        *lds = (size_t)(rows * (64 + bpr) * 8 + rows * bpr * 4);
+    }
     return true;
 }
 
@@ -926,12 +939,27 @@ hipError_t launch_one(const OneArgs& a, dim3 gd, hipStream_t st) {
     hipLaunchKernelGGL(kern, gd, dim3(64), 0, st, a);
     return hipGetLastError();
 }
-template <typename T, int BITS>
-hipError_t launch_line(const OneArgs& a, dim3 gd, hipStream_t st) {
-    void (*kern)(OneArgs) = a.K == 12 ? (a.NG == 12 ? compress_line<T, BITS, 12, 12> : a.NG == 6 ? compress_line<T, BITS, 12, 6> : compress_line<T, BITS, 12, 4>)
-                          : a.K == 4 ? compress_line<T, BITS, 4> : a.K == 6 ? compress_line<T, BITS, 6> : compress_line<T, BITS, 13>;
-    hipLaunchKernelGGL(kern, gd, dim3(64), 0, st, a);
+template <typename T, int BITS, int LU>
+hipError_t launch_line_lu(const OneArgs& a, dim3 gd, size_t lds, hipStream_t st) {
+    LineArgs<LU> la;
+    static_cast<OneArgs&>(la) = a;
+    void (*kern)(LineArgs<LU>);
+    if (a.K == 12) {
+        if constexpr (LU == -2) kern = compress_line<T, BITS, 12, 6, LU>;              // three rounds per plane (see line_groups)
+        else kern = a.NG == 12 ? compress_line<T, BITS, 12, 12, LU> : a.NG == 6 ? compress_line<T, BITS, 12, 6, LU> : compress_line<T, BITS, 12, 4, LU>;
+    } else kern = a.K == 4 ? compress_line<T, BITS, 4, 1, LU> : a.K == 6 ? compress_line<T, BITS, 6, 1, LU> : compress_line<T, BITS, 13, 1, LU>;
+    hipLaunchKernelGGL(kern, gd, dim3(64), lds, st, la);
     return hipGetLastError();
+}
+template <typename T, int BITS>
+hipError_t launch_line(const OneArgs& a, dim3 gd, size_t lds, hipStream_t st) {
+    switch (line_lu(a)) {
+        case 0: return launch_line_lu<T, BITS, 0>(a, gd, lds, st);
+        case 1: return launch_line_lu<T, BITS, 1>(a, gd, lds, st);
+        case 2: return launch_line_lu<T, BITS, 2>(a, gd, lds, st);
+        case -1: return launch_line_lu<T, BITS, -1>(a, gd, lds, st);
+        default: return launch_line_lu<T, BITS, -2>(a, gd, lds, st);
+    }
 }
 
 template <typename T>
@@ -950,7 +978,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case ITEMS: return launch_items<T, 1>(c.B, c.vec, c.ia, gd, lds, st);
             case UNITS: return launch_units<T, 1>(c.nw, c.ua, gd, lds, st);
             case ONE: return launch_one<T, 1>(c.oa, gd, st);
-            case LINE: return launch_line<T, 1>(c.oa, gd, st);
+            case LINE: return launch_line<T, 1>(c.oa, gd, lds, st);
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
             default: {
                 void (*kern)(AnyArgs) = flat ? compress_any<T, 1> : compress_any_3d<T, 1>;
@@ -971,7 +999,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case TILE: return launch_tile<T, BITS>(c.B, c.vec, c.a, gd, lds, st);
             case LANE: hipLaunchKernelGGL((compress_lane<T, BITS>), gd, dim3(64), lds, st, c.la); return hipGetLastError();
             case ONE: return launch_one<T, BITS>(c.oa, gd, st);
-            case LINE: return launch_line<T, BITS>(c.oa, gd, st);
+            case LINE: return launch_line<T, BITS>(c.oa, gd, lds, st);
             case ROWS: {
                 void (*kern)(RowsArgs) = flat ? compress_rows<T, BITS> : compress_rows_3d<T, BITS>;
                 const hipError_t e = allow_large_lds(kern, lds);
@@ -1153,10 +1181,10 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         // 1-bit codes (Q = 1) have no instance of the wave, rows and plane kernels, nor of the units kernel with
         // sixteen wavefronts: the wave kernel's shapes go to the tile kernel, the others to the general kernel
         const bool wide = b != 1;
-        if (line_first(L, es) && plan_line(L, D, H, B, es, xa, &oa, &grid)) { kind = LINE; oa.tab = tab; oa.rg = rg; lds = 0; }
+        if (line_first(L, es) && plan_line(L, D, H, B, es, xa, &oa, &grid, &lds)) { kind = LINE; oa.tab = tab; oa.rg = rg; }
         else if (plan_regs(L, D, H, W, B, es, xa, &ra, &grid, &lds, &nw)) { kind = REGS; ra.tab = tab; ra.rg = rg; }
         else if (plan_lane(L, es, xa, &la, &grid, &lds)) { kind = LANE; la.tab = tab; la.rg = rg; }
-        else if (plan_line(L, D, H, B, es, xa, &oa, &grid)) { kind = LINE; oa.tab = tab; oa.rg = rg; lds = 0; }
+        else if (plan_line(L, D, H, B, es, xa, &oa, &grid, &lds)) { kind = LINE; oa.tab = tab; oa.rg = rg; }
         else if (flat && plan_strip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = STRIP; sa.tab = tab; sa.rg = rg; }
         else if (flat && plan_rowstrip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = ROWSTRIP; sa.tab = tab; sa.rg = rg; }
         else if (flat && plan_items(L, H, W, B, es, xa, &ia, &grid, &lds, &vec)) { kind = ITEMS; ia.tab = tab; ia.rg = rg; }
@@ -1235,14 +1263,14 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
     if (direction == 0) {
         const bool wide = b != 1;        // as in compress_impl
         TileArgs a{}; WaveArgs wa{}; RegsArgs ra{}; ItemsArgs ia{}; LaneArgs la{}; RowsArgs wa2{}; PlaneArgs pa{}; OneArgs oa{}; UnitsArgs ua{}; StripArgs sa{}; size_t lds = 0; uint32_t grid = 0; int vec = 1, nt = 64, nw = 1;
-        if (line_first(L, es) && plan_line(L, D, H, B, es, data, &oa, &grid))
-            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u>", tn, b, oa.K, oa.NG);
+        if (line_first(L, es) && plan_line(L, D, H, B, es, data, &oa, &grid, &lds))
+            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u>", tn, b, oa.K, line_lu(oa) == -2 && oa.K == 12 ? 6u : oa.NG);
         else if (plan_regs(L, D, H, W, B, es, data, &ra, &grid, &lds, &nw))
             n = snprintf(out, cap, "compress_regs%s<%s, %d, %d, %d>", sfx, tn, b, (B == 4 || B == 8) ? B : 0, nw);
         else if (plan_lane(L, es, data, &la, &grid, &lds))
             n = snprintf(out, cap, "compress_lane<%s, %d>", tn, b);
-        else if (plan_line(L, D, H, B, es, data, &oa, &grid))
-            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u>", tn, b, oa.K, oa.NG);
+        else if (plan_line(L, D, H, B, es, data, &oa, &grid, &lds))
+            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u>", tn, b, oa.K, line_lu(oa) == -2 && oa.K == 12 ? 6u : oa.NG);
         else if (flat && plan_strip(L, H, W, B, es, data, &sa, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_strip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
         else if (flat && plan_rowstrip(L, H, W, B, es, data, &sa, &grid, &lds, &vec))

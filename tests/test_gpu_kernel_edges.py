@@ -62,3 +62,18 @@ def _round_trip(shape, B, b, mode, seed=7, offset=0, relu=False):
 ])
 def test_two_byte_rows_of_whole_pieces(shape, B, b, offset):
     _round_trip(shape, B, b, "bf16", offset=offset)
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+@pytest.mark.parametrize("shape,B", [
+    ((3, 5, 1, 96), 64),                 # a block of two rounds, the last one short; rounds past the plane
+    ((1, 1, 1, 96), 64),                 # a single plane: the other groups lie past the map
+    ((7, 11, 1, 160), 128),
+    ((5, 9, 1, 192), 64), ((3, 67, 1, 232), 64), ((2, 3, 1, 776), 64), ((2, 3, 1, 1536), 128),
+    ((1, 3, 1, 1544), 256),              # a block is a whole wavefront of vectors, the last one two vectors
+    ((3, 5, 1, 104), 32), ((2, 9, 1, 1000), 32),
+    ((5, 7, 1, 72), 8), ((2, 3, 1, 2056), 8), ((2, 3, 1, 1032), 16),
+])
+def test_rows_of_power_of_two_blocks(shape, B, b, mode):
+    _round_trip(shape, B, b, mode)
