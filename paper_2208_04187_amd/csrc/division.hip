@@ -33,7 +33,9 @@
 //   compress_units   planes (2-D or 3-D maps) of 256 to about 27K elements whose rows or blocks are not whole
 //                    16-byte vectors (odd widths: 27x27, 55x55, 147x147; B = 18): four consecutive elements per lane step
 //                    whatever the width, the block of each element looked up in a table made once per
-//                    workgroup, the plane parked in LDS for the block sums, next plane's loads in flight
+//                    workgroup, the plane parked in LDS for the block sums, next plane's loads in flight; for
+//                    4-byte elements under B = 4 and 8 the instances of compress_seg.h: sixteen elements of a block per
+//                    item, loaded straight from global memory and kept in registers
 //   compress_wave    other planes up to 17 KB, B = 4, 8: one wavefront per chunk of planes staged in LDS
 //   compress_tile    other planes up to 156 KB, B = 4, 8: four wavefronts per chunk staged in LDS
 //   compress_one     planes that are a single block (B = 64 on 56x56 and below): flat vectors in registers
@@ -130,6 +132,7 @@ constexpr int kLoadReuse = 0;
 #include "compress_lane.h"
 #include "compress_regs.h"
 #include "compress_units.h"
+#include "compress_seg.h"
 #include "compress_one.h"
 #include "compress_rows.h"
 #include "compress_plane.h"

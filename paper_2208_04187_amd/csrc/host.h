@@ -253,6 +253,67 @@ hipError_t launch_units(int nw, const UnitsArgs& a, dim3 grid, size_t lds, hipSt
     return hipGetLastError();
 }
 
+// Fills the plan of compress_seg_body (4-byte elements, B = 4 or 8), for the planes of compress_units; false when the
+// shape is not covered (an odd number of elements per slice in a 3-D map: rows would start anywhere in an element
+// pair) or would leave too many lanes idle.  One or two items per lane, whichever takes fewer instructions per plane: about
+// 216 for an item and 250 for a wavefront's share of everything else (five and seven items per lane were slower, 173 us
+// against 102 on 64 x 64 x 147 x 147: 156 to 208 registers).
+bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, SegArgs* a, uint32_t* grid, size_t* lds,
+              uint32_t* nt_out, int* K_out) {
+    if (es != 4 || (B != 4 && B != 8) || (D > 1 && (H * W) % 2 != 0)) return false;
+    const uint64_t CW = ((uint64_t)W + 3) / 4, irows = ((uint64_t)H + 3) / 4, rows = irows * (uint64_t)D;
+    if (CW > kSegThreads) return false;
+    uint64_t best_nt = 0, best = ~0ull;
+    int best_K = 0;
+    for (const int K : {1, 2}) {
+        const uint64_t RS = (rows + K - 1) / K;                       // item rows per round
+        const uint64_t nt = (RS * CW + 63) / 64 * 64;
+        if (nt > kSegThreads) continue;
+        const uint64_t cost = nt / 64 * (216 * (uint64_t)K + 250);
+        if (cost < best) { best = cost; best_nt = nt; best_K = K; }
+    }
+    if (best_K == 0) return false;
+    // at least 60 % of the lanes' slots hold elements of the plane
+    if (L.HW * 10 < 6ull * 16 * best_K * best_nt) return false;
+    const size_t need = 8 * rows * CW + 64 + 8 * (best_nt / 64) + 4 * L.nb + 4 * L.WPP;
+    const uint64_t top = rows + (uint64_t)best_K * best_nt;
+    if (need > (48u << 10) || !fastdiv_ok(top, irows) || !fastdiv_ok(kSegThreads, CW) || !fastdiv_ok(L.nb + best_nt, L.LW) || !fastdiv_ok(L.nb + best_nt, L.LH * L.LW)) return false;
+    a->P = (uint32_t)L.P; a->D = (uint32_t)D; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
+    a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
+    a->CW = (uint32_t)CW; a->RS = (uint32_t)(best_nt / CW); a->irows = (uint32_t)irows; a->rows = (uint32_t)rows;
+    a->cz0 = (uint32_t)(D < B ? D : B);
+    a->cz1 = (uint32_t)(D - (int64_t)(L.LD - 1) * B);
+    a->d_irows = make_fastdiv((uint32_t)irows); a->d_slice = make_fastdiv((uint32_t)(L.LH * L.LW)); a->d_LW = make_fastdiv((uint32_t)L.LW);
+    a->d_CW = make_fastdiv((uint32_t)CW);
+    *grid = (uint32_t)L.P;
+    *nt_out = (uint32_t)best_nt;
+    *K_out = best_K;
+    *lds = need;
+    return true;
+}
+
+template <typename T, int BITS, int K, int B, bool ODD>
+hipError_t launch_seg_as(const SegArgs& s, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
+    if constexpr (sizeof(T) == 4) {
+        SegUnits<B, ODD, K> a;
+        static_cast<SegArgs&>(a) = s;
+        void (*kern)(SegUnits<B, ODD, K>) = compress_units<T, BITS, B, ODD, K>;
+        hipLaunchKernelGGL(kern, grid, dim3(nt), lds, st, a);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+}
+template <typename T, int BITS, int K>
+hipError_t launch_seg_K(int B, const SegArgs& a, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
+    const bool odd = a.W % 2 != 0;
+    if (B == 8) return odd ? launch_seg_as<T, BITS, K, 8, true>(a, nt, grid, lds, st) : launch_seg_as<T, BITS, K, 8, false>(a, nt, grid, lds, st);
+    return odd ? launch_seg_as<T, BITS, K, 4, true>(a, nt, grid, lds, st) : launch_seg_as<T, BITS, K, 4, false>(a, nt, grid, lds, st);
+}
+template <typename T, int BITS>
+hipError_t launch_seg(int K, int B, const SegArgs& a, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
+    return K == 1 ? launch_seg_K<T, BITS, 1>(B, a, nt, grid, lds, st) : launch_seg_K<T, BITS, 2>(B, a, nt, grid, lds, st);
+}
+
 // one-block planes with an odd element count: the shapes the lane-per-plane kernels take
 bool lane_shape(const Layout& L) { return L.nb == 1 && (L.HW & 1) == 1 && L.HW <= 64; }
 
@@ -924,6 +985,7 @@ struct CompLaunch {
     size_t lds;
     hipStream_t st;
     TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa;
+    SegArgs sg; uint32_t seg_nt; int seg_K;      // kind UNITS with seg_nt != 0: the kernel of compress_seg.h with that many threads
 };
 struct DecLaunch {
     int kind, flat, nw;
@@ -976,7 +1038,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case ROWSTRIP: return launch_rowstrip<T, 1>(c.vec, c.sa, gd, lds, st);
             case LANE: hipLaunchKernelGGL((compress_lane<T, 1>), gd, dim3(64), lds, st, c.la); return hipGetLastError();
             case ITEMS: return launch_items<T, 1>(c.B, c.vec, c.ia, gd, lds, st);
-            case UNITS: return launch_units<T, 1>(c.nw, c.ua, gd, lds, st);
+            case UNITS: if (c.seg_nt) return launch_seg<T, 1>(c.seg_K, c.B, c.sg, c.seg_nt, gd, lds, st); return launch_units<T, 1>(c.nw, c.ua, gd, lds, st);
             case ONE: return launch_one<T, 1>(c.oa, gd, st);
             case LINE: return launch_line<T, 1>(c.oa, gd, lds, st);
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
@@ -994,7 +1056,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case STRIP: return launch_strip<T, BITS>(c.vec, c.sa, gd, lds, st);
             case ROWSTRIP: return launch_rowstrip<T, BITS>(c.vec, c.sa, gd, lds, st);
             case ITEMS: return launch_items<T, BITS>(c.B, c.vec, c.ia, gd, lds, st);
-            case UNITS: return launch_units<T, BITS>(c.nw, c.ua, gd, lds, st);
+            case UNITS: if (c.seg_nt) return launch_seg<T, BITS>(c.seg_K, c.B, c.sg, c.seg_nt, gd, lds, st); return launch_units<T, BITS>(c.nw, c.ua, gd, lds, st);
             case WAVE: return launch_wave<T, BITS>(c.B, c.vec, c.wa, gd, lds, st);
             case TILE: return launch_tile<T, BITS>(c.B, c.vec, c.a, gd, lds, st);
             case LANE: hipLaunchKernelGGL((compress_lane<T, BITS>), gd, dim3(64), lds, st, c.la); return hipGetLastError();
@@ -1197,6 +1259,10 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         else if (wide && plan_plane(L, D, H, W, B, es, xa, &pa, &grid, &lds)) { kind = PLANE; pa.tab = tab; pa.rg = rg; }
         else use_any();
         CompLaunch c{};
+        if (kind == UNITS && plan_seg(L, D, H, W, B, es, &c.sg, &grid, &lds, &c.seg_nt, &c.seg_K)) {
+            c.sg.tab = tab;
+            c.sg.rg = rg;
+        }
         c.kind = kind; c.B = B; c.vec = vec; c.nt = nt; c.nw = nw; c.flat = flat;
         c.gx = grid; c.gy = (uint32_t)cnt; c.lds = lds; c.st = st;
         c.sa = sa; c.a = a; c.wa = wa; c.ra = ra; c.ia = ia; c.la = la; c.wa2 = wa2; c.pa = pa; c.oa = oa; c.g = g; c.ua = ua;

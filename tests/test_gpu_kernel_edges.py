@@ -77,3 +77,18 @@ def test_two_byte_rows_of_whole_pieces(shape, B, b, offset):
 ])
 def test_rows_of_power_of_two_blocks(shape, B, b, mode):
     _round_trip(shape, B, b, mode)
+
+
+@pytest.mark.parametrize("mode", ["f32", "c16"])
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+@pytest.mark.parametrize("shape,B", [
+    ((1, 1, 17, 17), 8), ((41, 101, 17, 17), 8),          # one plane; several planes per workgroup, the last one short
+    ((3, 7, 13, 13), 4), ((5, 5, 9, 13), 8), ((2, 3, 35, 35), 8), ((29, 67, 35, 35), 4), ((1, 3, 64, 55), 8), ((2, 2, 2, 17), 4),
+    ((2, 3, 19, 19), 8), ((3, 2, 21, 23), 4), ((3, 3, 40, 33), 8),                 # whole block rows; a last column of one element
+    ((1, 2, 73, 73), 8), ((2, 3, 57, 41), 4), ((1, 2, 101, 97), 8), ((1, 1, 128, 111), 4), ((1, 2, 147, 147), 8), ((1, 1, 163, 163), 8),
+    ((2, 2, 300, 5), 8), ((1, 2, 200, 3), 4), ((2, 1, 3, 1001), 8), ((2, 2, 9, 250), 4),           # narrower than a block; few rows
+    ((2, 3, 4, 14, 14), 8), ((3, 5, 9, 14, 14), 8), ((1, 2, 5, 16, 9), 4), ((2, 2, 3, 22, 30), 8), ((1, 3, 2, 30, 35), 4),
+    ((2, 2, 3, 15, 21), 8),                               # an odd number of elements per slice
+])
+def test_items_of_sixteen_elements(shape, B, b, mode):
+    _round_trip(shape, B, b, mode, relu=b == 2)
