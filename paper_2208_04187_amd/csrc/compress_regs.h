@@ -271,10 +271,11 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
         // ---- scale of Eq. (quantization), keys, meta
         float delta, Delta, inv;
         plane_scale_any(mn, mx, Lf, kC16<T>, delta, Delta, inv);
-        const float invs = inv * (float)(1u << (32 - BITS));
+        float invs = inv * (float)(1u << (32 - BITS));
         const uint32_t k1 = mix32(p ^ pt.seed_a);
-        const uint32_t k2 = mix32(k1 + pt.seed_c);
+        uint32_t k2 = mix32(k1 + pt.seed_c);
         if (tid == 0) meta_store(pt.meta, p, delta, Delta, kC16<T>);
+        keep_in_vgpr(delta, invs, k2);
 
         // ---- Quant + packing: a unit is two element pairs = 4 codes (one byte for b = 2, a word for b = 8)
         {

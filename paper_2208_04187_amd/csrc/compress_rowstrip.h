@@ -98,11 +98,13 @@ __global__ void __launch_bounds__(64) compress_rowstrip(StripArgs a) {
 #pragma unroll
     for (int e = 0; e < W; ++e) Sm[e / B] += (double)x[e];
     float lfc[NSEG];
+    const double rcp_rows = count_rcp(max(rows, 1u));
 #pragma unroll
     for (int s = 0; s < NSEG; ++s) {
         const double Sb = group_sum<B>(valid ? Sm[s] : 0.0);
         const uint32_t cols = (uint32_t)(W - B * s < B ? W - B * s : B);     // a constant once the loop is unrolled
-        lfc[s] = lfc_round<T>(mean_of(Sb, max(rows, 1u) * cols), kC16<T>);
+        // the reciprocal of the count as a product: at most 4 ulp off, exact for powers of two
+        lfc[s] = lfc_round<T>(mean_with_rcp(Sb, max(rows, 1u) * cols, rcp_rows * (1.0 / (double)cols)), kC16<T>);
     }
     if (valid && sl % B == 0) {
 #pragma unroll

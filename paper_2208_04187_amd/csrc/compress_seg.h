@@ -37,7 +37,7 @@ __device__ __forceinline__ uint32_t push_half(uint32_t acc, float h, bool odd, f
     // one element of a pair: push_pair without the other
     uint32_t x = xw;
     x ^= x >> 16; x *= 0x7feb352du;
-    x = x ^ (x >> 15) ^ k2; x *= 0x846ca68bu;
+    x = xor3(x, x >> 15, k2); x *= 0x846ca68bu;
     uint32_t T = (uint32_t)((h - delta) * invs), s;
     if constexpr (BITS == 8) T = min(T, 255u << 24);
     if (odd) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(s) : "v"(x), "s"(rscale), "v"(T));

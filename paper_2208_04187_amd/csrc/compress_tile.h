@@ -13,7 +13,7 @@ __device__ __forceinline__ uint32_t push_pair(uint32_t acc, float h0, float h1, 
                                               uint32_t xw, uint32_t k2, uint32_t rscale) {
     uint32_t x = xw;
     x ^= x >> 16; x *= 0x7feb352du;
-    x = x ^ (x >> 15) ^ k2; x *= 0x846ca68bu;
+    x = xor3(x, x >> 15, k2); x *= 0x846ca68bu;
     // final x ^= x >> 16: the high half is unchanged, the low half becomes lo ^ hi
     const uint32_t xl = x ^ (x >> 16);
     uint32_t T1 = (uint32_t)((h1 - delta) * invs);

@@ -49,11 +49,15 @@ __host__ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
     return x;
 }
 
+// a ^ b ^ c in one instruction (gfx950; the compiler does not form it): 4.5 cycles per wavefront where two xors take 5.2, or 7
+// when one operand sits in a scalar register
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
 // random word of element pair j of a plane with keys (k1, k2); xw = k1 + j*kWeyl
 __device__ __forceinline__ uint32_t pair_word(uint32_t xw, uint32_t k2) {
     uint32_t x = xw;
     x ^= x >> 16; x *= 0x7feb352du;
-    x = x ^ (x >> 15) ^ k2; x *= 0x846ca68bu;
+    x = xor3(x, x >> 15, k2); x *= 0x846ca68bu;
     x ^= x >> 16;
     return x;
 }
