@@ -24,6 +24,8 @@ struct WaveArgs {
 // those boundaries are the binary64 numbers whose low 29 bits read 1000...0 (and, for d itself to
 // land on the other side, nothing closer than that): if the low 29 bits of q are at least 16 ulp
 // from that pattern, no boundary is within 16 ulp of q, d is within 3, so both round alike.
+// (The kernels' reciprocals may be up to 4 ulp off 1/cnt, see count_rcp: that is at most 8 ulp of q, so q and d are then
+// within 10 ulp, still inside the 16.)
 // A nonzero q below 2^-126 rounds to a subnormal binary32, which drops more than 29 bits, so the
 // pattern test does not see its boundaries: it takes the division.  (q >= 2^-126 > d cannot
 // disagree: d is then within 3 ulp below 2^-126, q's low bits are near zero, both round to 2^-126.)
