@@ -114,10 +114,12 @@ __device__ __forceinline__ void compress_seg_body(const SegArgs& a) {
         }
         // the plane's last item row: rows past the map count for nothing in the sum and are NaN after it.  With one item
         // per lane they are made zeros here and NaN later (62 registers, eight wavefronts per SIMD: 64 x 512 x 29 x 29 in
-        // 35 us against 38); with two items a second copy of the sum is the faster form (64 x 64 x 147 x 147: 102 us against 133).
+        // 35 us against 38); with two items a second copy of the sum is the faster form, off the
+        // main path as the hint says: 76 registers, two workgroups of eleven wavefronts per CU; without the hint 102
+        // registers and one workgroup (64 x 64 x 147 x 147: 102 us against 133).
         double s = 0.0;
         partial[k] = __any(nr[k] != R && nr[k] != 0);
-        if (K > 1 && partial[k]) {
+        if (K > 1 && __builtin_expect(partial[k], 0)) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
