@@ -313,7 +313,9 @@ __device__ __forceinline__ void compress_line_body(const OneArgs& a) {
         if constexpr (LDS) {
             lfc = lfcs[((uint32_t)(g * RB + k / UR) << bpr_log) + (tid >> logM)];
         } else {
-            const double Sb = group_sum<(LU < 0 ? 1 : 1 << LU)>(vector_sum(q[g * R + k]));
+            // a block of negative zeros sums to +0, as a sum from 0 does; added before the rounding to binary32, where a tiny
+            // negative sum may become -0, which is then the mean
+            const double Sb = group_sum<(LU < 0 ? 1 : 1 << LU)>(vector_sum(q[g * R + k])) + 0.0;
             float m;
             if (LU == 0 || !masked) m = (float)(Sb * rcp_full);                    // exact scaling by a power of two
             else {
@@ -321,7 +323,7 @@ __device__ __forceinline__ void compress_line_body(const OneArgs& a) {
                 const bool last = (u & ~(a.upb - 1u)) + a.upb >= a.qv;             // the last block may be short
                 m = mean_with_rcp(Sb, last ? cnt_last : cnt_full, last ? rcp_last : rcp_full);
             }
-            lfc = lfc_round<T>(m + 0.0f, kC16<T>);       // a block of negative zeros has mean +0, as a sum from 0 does
+            lfc = lfc_round<T>(m, kC16<T>);
             // (S is a multiple of the block's 1 << LU vectors)
             put_lfc(lfc, place_block(k, lo0));
         }

@@ -20,12 +20,13 @@ def _host(t):
     return t.view(torch.int16).numpy().view(np.uint16) if t.dtype == torch.bfloat16 else t.numpy()
 
 
-def _round_trip(shape, B, b, mode, seed=7, offset=0, relu=False):
-    """Compress and rebuild a map whose rebuilt copy starts `offset` elements into its buffer."""
+def _round_trip(shape, B, b, mode, seed=7, offset=0, relu=False, x=None):
+    """Compress and rebuild a map (x, or normal values) whose rebuilt copy starts `offset` elements into its buffer."""
     dtype, c16, dt = FORMATS[mode]
     three = len(shape) == 5
     gen = torch.Generator().manual_seed(seed * 1000 + B * 10 + b)
-    x = torch.randn(shape, generator=gen)
+    if x is None:
+        x = torch.randn(shape, generator=gen)
     x = (x.relu() if relu else x).to(dtype)
     xh = _host(x)
     comp = pkg.division_compress_3d if three else pkg.division_compress
@@ -77,6 +78,23 @@ def test_two_byte_rows_of_whole_pieces(shape, B, b, offset):
 ])
 def test_rows_of_power_of_two_blocks(shape, B, b, mode):
     _round_trip(shape, B, b, mode)
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+@pytest.mark.parametrize("shape,B", [
+    ((1, 3, 1, 768), 8), ((1, 3, 1, 768), 4), ((1, 3, 1, 768), 16),         # every round whole
+    ((2, 3, 1, 200), 8), ((2, 3, 1, 72), 8), ((2, 3, 1, 24), 4), ((1, 2, 1, 1032), 16),      # the last round partly past the plane
+    ((1, 3, 1, 96), 64), ((1, 2, 1, 160), 128),                             # block sums through LDS
+    ((1, 2, 29, 29), 8), ((1, 2, 17, 17), 8), ((1, 2, 56, 56), 8),
+])
+def test_tiny_negative_sum_has_mean_minus_zero(shape, B, mode):
+    """A sum of one smallest negative number: its mean underflows to -0, which is kept; only a block of -0 has mean +0."""
+    tiny = -(2.0 ** -133 if mode == "bf16" else 2.0 ** -149)
+    x = torch.zeros(shape)
+    x.view(-1)[::B] = tiny                        # at most one in the blocks of a one-row map
+    x[0, 1] = -x[0, 1].abs()                      # the same beside -0,
+    x[0, 1, :B, :B] = -0.0                        # and a block of -0 alone
+    _round_trip(shape, B, 2, mode, x=x)
 
 
 @pytest.mark.parametrize("mode", ["f32", "c16"])
