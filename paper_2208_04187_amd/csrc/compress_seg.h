@@ -27,8 +27,8 @@ struct SegArgs {
 // elements per slice, or one slice), so which rows start in the middle of an element pair is known at compile
 // time (ODD): such a row hashes one pair more and needs no selects.
 // The last column is narrower: what its items read past their row (the next row's first elements, zero past
-// the plane) gets the weight 0 in the sum (a fused multiply-add where the others' weight is 1: exact, and as fast
-// as the addition) and NaN for H^L, which minimum and maximum skip and the quantiser turns into code 0.
+// the plane) gets the weight 0 in the sum (a fused multiply-add where the others' weight is 1: exact for finite
+// values, see below for the others, and as fast as the addition) and NaN for H^L, which minimum and maximum skip and the quantiser turns into code 0.
 // What bounds it: vector instructions, then the latency between its barriers.  Against the kernel that parks the plane in
 // LDS (compress_units of compress_units.h): 64 x 64 x 147 x 147 under B = 8 136 -> 102 us (3.5 TB/s of x), 73 x 73 47 -> 35, 127 x 127
 // 110 -> 62, 64 x 512 x 29 x 29 49 -> 35, the volumes 32 x 256 x 4 x 14 x 14 20 -> 12.5.
@@ -139,6 +139,15 @@ __device__ __forceinline__ void compress_seg_body(const SegArgs& a) {
 #pragma unroll
                 for (int e = 0; e < C; ++e) s = __builtin_fma((double)x[k][r][e], wt[e], s);
         }
+        // 0 * x is NaN for an infinity or a NaN, which must not reach a block it is not in: a sum that is not finite is
+        // taken again over the elements of the item alone (never on ordinary inputs: sums of binary32 values are finite)
+        if (__builtin_expect(__any(!(__builtin_fabs(s) < __builtin_inf())), 0)) {
+            s = 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int e = 0; e < C; ++e) s += r < nr[k] && j * C + (uint32_t)e < W ? (double)x[k][r][e] : 0.0;
+        }
         const uint32_t row = row0 + a.RS * (uint32_t)k;
         if (row0 < a.RS && row < a.rows) part[row * a.CW + j] = s;        // a row past the map was read as zeros
     }
@@ -190,7 +199,7 @@ __device__ __forceinline__ void compress_seg_body(const SegArgs& a) {
         }
         float le[C];
 #pragma unroll
-        for (int e = 0; e < C; ++e) le[e] = m + nn[e];    // (a mean is never -0)
+        for (int e = 0; e < C; ++e) le[e] = m + nn[e];    // (a mean of -0 becomes +0: such a block holds a negative element, no extreme and no code depends on it)
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll

@@ -110,3 +110,47 @@ def test_tiny_negative_sum_has_mean_minus_zero(shape, B, mode):
 ])
 def test_items_of_sixteen_elements(shape, B, b, mode):
     _round_trip(shape, B, b, mode, relu=b == 2)
+
+
+@pytest.mark.parametrize("mode", ["f32", "c16"])
+@pytest.mark.parametrize("shape,B", [
+    ((4, 6, 29, 29), 8), ((4, 6, 29, 29), 4), ((4, 6, 37, 37), 8), ((4, 6, 40, 33), 8), ((4, 6, 73, 73), 8),       # an item per lane
+    ((4, 6, 147, 147), 8), ((4, 6, 147, 147), 4), ((4, 6, 127, 127), 8), ((4, 6, 101, 97), 8),                     # two items
+    ((4, 6, 4, 14, 14), 8), ((4, 6, 9, 14, 14), 8), ((4, 6, 8, 18, 26), 8), ((4, 6, 5, 16, 9), 4), ((4, 6, 5, 22, 22), 4),
+    ((4, 6, 56, 56), 8), ((4, 6, 28, 28), 8), ((4, 6, 17, 17), 8), ((4, 6, 57, 57), 18), ((4, 6, 1, 768), 8), ((4, 6, 1, 96), 64),
+])
+def test_a_value_that_is_not_finite_stays_in_its_block(shape, B, mode):
+    """One NaN or infinity per plane, in the first and last columns and rows among other places: the codes of such a
+    plane are unspecified, the means of its other blocks are not."""
+    dtype, c16, dt = FORMATS[mode]
+    three = len(shape) == 5
+    dims = (1,) * (5 - len(shape)) + shape[2:]
+    planes, rng = shape[0] * shape[1], np.random.default_rng(sum(shape) + B)
+    x = torch.randn(shape, generator=torch.Generator().manual_seed(B))
+    flat = x.view((planes,) + dims)
+    hit, low = [], [-(-d // B) for d in dims]
+    for p in range(planes):
+        at = [int(rng.choice([0, d - 1, rng.integers(0, d), min(d - 1, 4 * int(rng.integers(0, d // 4 + 1)))])) for d in dims]
+        at[2] = 0 if p % 2 == 0 else at[2]                       # what the last column's loads run into
+        flat[(p, *at)] = (float("nan"), float("inf"), -float("inf"))[p % 3]
+        hit.append(((at[0] // B) * low[1] + at[1] // B) * low[2] + at[2] // B)
+    comp, dec = (pkg.division_compress_3d, pkg.division_decompress_3d) if three else (pkg.division_compress, pkg.division_decompress)
+    packed = comp(x.to("cuda:0"), B, 2, 3, c16=c16)
+    back = dec(packed, shape, B, 2, dtype, c16=c16)
+    torch.cuda.synchronize()
+    lay = (pkg.division_packed_layout_3d if three else pkg.division_packed_layout)(*shape, B, 2, dtype, c16)
+    view = np.uint16 if c16 else np.uint32
+
+    def means(buf):
+        return np.ascontiguousarray(buf[lay["lfc_off"]:lay["lfc_off"] + lay["lfc_bytes"]]).view(view).reshape(planes, -1)
+
+    got, want = means(packed.cpu().numpy()), means(oracle.compress(x.numpy(), B, 2, 3, dt))
+    exponent = 0x7F80 if c16 else 0x7F800000
+    finite_got, finite_want = (got & exponent) != exponent, (want & exponent) != exponent
+    assert np.array_equal(np.nonzero(~finite_want)[1], np.array(hit))                      # one mean per plane
+    assert np.array_equal(finite_got, finite_want), np.argwhere(finite_got != finite_want)[:8]
+    assert np.array_equal(got[finite_want], want[finite_want])
+    nan = back.cpu().view((planes,) + dims)[0::3].isnan()                                 # planes that hold a NaN
+    for i, m in enumerate(nan):
+        b0 = [v // B * B for v in np.argwhere(m.numpy())[0]]
+        assert not bool(m.sum() > m[b0[0]:b0[0] + B, b0[1]:b0[1] + B, b0[2]:b0[2] + B].sum()), "the block's neighbours came back as NaN"
