@@ -237,8 +237,7 @@ int division_maxpool_backward(const void *mask, size_t mask_bytes, const void *g
  * (direction 1, data = xhat) would launch for these arguments, as it appears
  * in a kernel trace, e.g. "compress_tile<float, 2, 8, 4>".  The choice depends
  * on the shape, the block size and the 16-byte alignment of `data` (which may
- * be null: treated as aligned).  out is a host buffer of cap bytes.  The last argument of
- * compress_units is its size class; a trace shows some of its instances with further arguments.
+ * be null: treated as aligned).  out is a host buffer of cap bytes.
  * Returns DIVISION_OK, or DIVISION_ESIZE when cap is too small.
  */
 int division_kernel_name(int direction, const void *data,

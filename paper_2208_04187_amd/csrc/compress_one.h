@@ -177,16 +177,11 @@ __global__ void __launch_bounds__(64) compress_one(OneArgs a) {
 // of 384 floats cached as bfloat16, B = 64, b = 2: 72 -> 56 us (5.5 TB/s of x); of 96 floats: 32 -> 21.5 us;
 // 32 x 512 planes of 3072 bfloat16, B = 8, b = 4: 36 -> 28.8 us.
 constexpr int kLineUnits = 13;
-template <int LU> struct LineArgs : OneArgs {};
 // NG > 1: planes of at most R = K / NG rounds (a few hundred bytes each): a wavefront takes NG groups of
 // 64 / S planes one after the other, all their loads issued first, so that it has K vectors per lane in
 // flight like the instances for larger planes (two or three would not cover the memory latency).
-// The fourth argument counts what the twelve rounds of such an instance are cut into: plane groups, or for LU = -2,
-// where two rounds make a block (three rounds a plane, four groups), the K / 2 rounds of whole blocks.
-constexpr int line_groups(int K, int N, int LU) { return K == 12 && LU == -2 ? 4 : N; }
-template <typename T, int BITS, int K, int N, int LU>
-__device__ __forceinline__ void compress_line_body(const OneArgs& a) {
-    constexpr int NG = line_groups(K, N, LU);
+template <typename T, int BITS, int K, int NG, int LU>
+__global__ void __launch_bounds__(64) compress_line(OneArgs a) {
     constexpr int R = K / NG;
     static_assert(R * NG == K, "whole groups");
     constexpr bool LDS = LU < 0;
@@ -403,5 +398,3 @@ __device__ __forceinline__ void compress_line_body(const OneArgs& a) {
     }
     }
 }
-template <typename T, int BITS, int K, int N, int LU>
-__global__ void __launch_bounds__(64) compress_line(LineArgs<LU> a) { compress_line_body<T, BITS, K, N, LU>(a); }

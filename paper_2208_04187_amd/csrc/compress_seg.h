@@ -1,5 +1,5 @@
-// Part of division.hip (included inside its unnamed namespace, after compress_units.h): the instances of compress_units that hold
-// sixteen elements of a block per item (4-byte elements, B = 4 and 8).
+// Part of division.hip (included inside its unnamed namespace): compress_seg, items of sixteen elements of a block in
+// registers (4-byte elements, B = 4 and 8).
 
 // ------------------------------------------------------------------ compress, sixteen elements of a block per item
 
@@ -45,8 +45,9 @@ __device__ __forceinline__ uint32_t push_half(uint32_t acc, float h, bool odd, f
     return __builtin_amdgcn_alignbit(acc, s, 32 - BITS);
 }
 
-template <typename T, int BITS, int B, int K, bool ODD>
-__device__ __forceinline__ void compress_seg_body(const SegArgs& a) {
+constexpr uint32_t kSegThreads = 768;
+template <typename T, int BITS, int B, bool ODD, int K>
+__global__ void __launch_bounds__(kSegThreads) compress_seg(SegArgs a) {
     static_assert(sizeof(T) == 4 && (B == 4 || B == 8), "4-byte elements");
     constexpr int R = 4, C = 4;                           // rows and columns of an item
     constexpr uint32_t IPB = B / 4;                       // item rows, and items per row, of a block
@@ -257,11 +258,4 @@ __device__ __forceinline__ void compress_seg_body(const SegArgs& a) {
     sync();
     uint32_t* dst = pt.codes + (size_t)p * a.WPP;
     for (uint32_t w = tid; w < a.WPP; w += NT) dst[w] = cw[w];
-}
-
-template <int B, bool ODD, int K> struct SegUnits : SegArgs {};
-constexpr uint32_t kSegThreads = 768;
-template <typename T, int BITS, int B, bool ODD, int K>
-__global__ void __launch_bounds__(kSegThreads) compress_units(SegUnits<B, ODD, K> a) {
-    if constexpr (sizeof(T) == 4) compress_seg_body<T, BITS, B, K, ODD>(a);
 }

@@ -220,25 +220,17 @@ __device__ __forceinline__ void decompress_stream_body(const DecArgs& a) {
         store_b128_checked(o, ors, lane * 16u + (uint32_t)(k * 1024), DIVISION_STREAM_STORE_AUX);   // past the map: dropped, dword by dword
     }
 }
-template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_body<T, BITS, 2, false>(a); }
-template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_body<T, BITS, 3, false>(a); }
-// The same for 2-byte elements: decompress_rowvec, one wavefront per chunk.  The staged kernel of that name keeps what
-// does not start on a 16-byte boundary.  256 x 256 x 56 x 56 (b = 2): staged 77 us (5.3 TB/s), this one 68.5 us
-// (6.0 TB/s); 32 x 512 x 1 x 3072 (b = 4): 27 us and 20.8 us.
-struct DecStreamArgs : DecArgs {};
 template <typename T, int BITS, int ND>
-__device__ __forceinline__ void decompress_rowvec_stream(const DecArgs& a) {
-    if constexpr (sizeof(T) == 2) {
-        if (a.whole8) decompress_stream_body<T, BITS, ND, true>(a);
-        else decompress_stream_body<T, BITS, ND, false>(a);
-    }
+__device__ __forceinline__ void decompress_stream_pieces(const DecArgs& a) {
+    if constexpr (sizeof(T) == 2) { if (a.whole8) { decompress_stream_body<T, BITS, ND, true>(a); return; } }
+    decompress_stream_body<T, BITS, ND, false>(a);
 }
+// 2-byte elements, against staging in LDS (decompress_rowvec, which keeps what does not start on a 16-byte boundary):
+// 256 x 256 x 56 x 56 (b = 2) 77 us (5.3 TB/s) staged, 68.5 us (6.0 TB/s) here; 32 x 512 x 1 x 3072 (b = 4) 27 us and 20.8 us.
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_rowvec(DecStreamArgs a) { decompress_rowvec_stream<T, BITS, 2>(a); }
+__global__ void __launch_bounds__(64) decompress_stream(DecArgs a) { decompress_stream_pieces<T, BITS, 2>(a); }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_rowvec_3d(DecStreamArgs a) { decompress_rowvec_stream<T, BITS, 3>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { decompress_stream_pieces<T, BITS, 3>(a); }
 
 // The stream kernel for maps whose rows, blocks or planes are not whole vectors (odd widths, any B; 4-byte
 // elements): a workgroup is again ONE wavefront that rebuilds kStreamK * 64 consecutive, aligned 16-byte

@@ -33,9 +33,9 @@
 //   compress_units   planes (2-D or 3-D maps) of 256 to about 27K elements whose rows or blocks are not whole
 //                    16-byte vectors (odd widths: 27x27, 55x55, 147x147; B = 18): four consecutive elements per lane step
 //                    whatever the width, the block of each element looked up in a table made once per
-//                    workgroup, the plane parked in LDS for the block sums, next plane's loads in flight; for
-//                    4-byte elements under B = 4 and 8 the instances of compress_seg.h: sixteen elements of a block per
-//                    item, loaded straight from global memory and kept in registers
+//                    workgroup, the plane parked in LDS for the block sums, next plane's loads in flight
+//   compress_seg     those of 4-byte elements under B = 4 and 8: sixteen elements of a block per item, loaded straight
+//                    from global memory and kept in registers
 //   compress_wave    other planes up to 17 KB, B = 4, 8: one wavefront per chunk of planes staged in LDS
 //   compress_tile    other planes up to 156 KB, B = 4, 8: four wavefronts per chunk staged in LDS
 //   compress_one     planes that are a single block (B = 64 on 56x56 and below): flat vectors in registers
@@ -43,8 +43,8 @@
 //   compress_plane   planes beyond LDS with vector rows and blocks (video volumes, image-sized maps):
 //                    a workgroup per plane, two vector passes over x
 //   compress_any     everything else (giant planes with odd extents): scalar, slow
-//   decompress_stream / decompress_stream_any / decompress_stream_one: 4-byte elements, one wavefront per 4 KB chunk of aligned vectors, no LDS:
-//                    rows of whole vectors inside one block (_stream), or any width where a vector may span two rows
+//   decompress_stream / decompress_stream_any / decompress_stream_one: one wavefront per 4 KB chunk of aligned vectors, no LDS:
+//                    rows of whole vectors inside one block (_stream, also 2-byte maps), or 4-byte elements of any width where a vector may span two rows
 //                    and two planes (_stream_any: each element finds its plane and block, six loads per vector;
 //                    _stream_one: planes that are one block)
 //   decompress_rowvec / _table / _words / _flat / _lane / _scalar: streaming, the packed slice of a
@@ -54,7 +54,7 @@
 //                    consecutive elements per lane step, block table made once per workgroup, the next
 //                    plane's codes and LFC in flight
 // Code widths: 2, 4 and 8 bits in every kernel; 1 bit (four codes of a unit = half a byte) in compress_regs,
-// compress_strip, compress_rowstrip, compress_lane, compress_items, compress_units (up to 8 wavefronts), compress_one,
+// compress_strip, compress_rowstrip, compress_lane, compress_items, compress_units (up to 8 wavefronts), compress_seg, compress_one,
 // compress_line, compress_tile, compress_any and in
 // every decompress kernel.
 // The kernels with a _3d twin take N x C x D x H x W maps with B x B x B blocks (Appendix D).

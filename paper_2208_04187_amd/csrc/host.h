@@ -253,7 +253,7 @@ hipError_t launch_units(int nw, const UnitsArgs& a, dim3 grid, size_t lds, hipSt
     return hipGetLastError();
 }
 
-// Fills the plan of compress_seg_body (4-byte elements, B = 4 or 8), for the planes of compress_units; false when the
+// Fills the plan of compress_seg (4-byte elements, B = 4 or 8), for the planes of compress_units; false when the
 // shape is not covered (an odd number of elements per slice in a 3-D map: rows would start anywhere in an element
 // pair) or would leave too many lanes idle.  One or two items per lane, whichever takes fewer instructions per plane: about
 // 216 for an item and 250 for a wavefront's share of everything else (five and seven items per lane were slower, 173 us
@@ -292,22 +292,16 @@ bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es
     return true;
 }
 
-template <typename T, int BITS, int K, int B, bool ODD>
-hipError_t launch_seg_as(const SegArgs& s, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
+template <typename T, int BITS, int K>
+hipError_t launch_seg_K(int B, const SegArgs& a, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
-        SegUnits<B, ODD, K> a;
-        static_cast<SegArgs&>(a) = s;
-        void (*kern)(SegUnits<B, ODD, K>) = compress_units<T, BITS, B, ODD, K>;
+        const bool odd = a.W % 2 != 0;
+        void (*kern)(SegArgs) = B == 8 ? (odd ? compress_seg<T, BITS, 8, true, K> : compress_seg<T, BITS, 8, false, K>)
+                                       : (odd ? compress_seg<T, BITS, 4, true, K> : compress_seg<T, BITS, 4, false, K>);
         hipLaunchKernelGGL(kern, grid, dim3(nt), lds, st, a);
         return hipGetLastError();
     }
     return hipErrorInvalidValue;
-}
-template <typename T, int BITS, int K>
-hipError_t launch_seg_K(int B, const SegArgs& a, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
-    const bool odd = a.W % 2 != 0;
-    if (B == 8) return odd ? launch_seg_as<T, BITS, K, 8, true>(a, nt, grid, lds, st) : launch_seg_as<T, BITS, K, 8, false>(a, nt, grid, lds, st);
-    return odd ? launch_seg_as<T, BITS, K, 4, true>(a, nt, grid, lds, st) : launch_seg_as<T, BITS, K, 4, false>(a, nt, grid, lds, st);
 }
 template <typename T, int BITS>
 hipError_t launch_seg(int K, int B, const SegArgs& a, uint32_t nt, dim3 grid, size_t lds, hipStream_t st) {
@@ -976,7 +970,7 @@ hipError_t with_bits(int b, F&& f) {
                                                                   : f(std::integral_constant<int, 8>{});
 }
 
-enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, WAVE, TILE, ONE, ROWS, PLANE, ANY };
+enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, SEG, WAVE, TILE, ONE, ROWS, PLANE, ANY };
 
 // everything a compress launch needs once the plan is made (the arguments of the kernel that was picked)
 struct CompLaunch {
@@ -985,7 +979,7 @@ struct CompLaunch {
     size_t lds;
     hipStream_t st;
     TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa;
-    SegArgs sg; uint32_t seg_nt; int seg_K;      // kind UNITS with seg_nt != 0: the kernel of compress_seg.h with that many threads
+    SegArgs sg; uint32_t seg_nt; int seg_K;      // kind SEG: threads, items per lane
 };
 struct DecLaunch {
     int kind, flat, nw;
@@ -1003,14 +997,12 @@ hipError_t launch_one(const OneArgs& a, dim3 gd, hipStream_t st) {
 }
 template <typename T, int BITS, int LU>
 hipError_t launch_line_lu(const OneArgs& a, dim3 gd, size_t lds, hipStream_t st) {
-    LineArgs<LU> la;
-    static_cast<OneArgs&>(la) = a;
-    void (*kern)(LineArgs<LU>);
+    void (*kern)(OneArgs);
     if (a.K == 12) {
-        if constexpr (LU == -2) kern = compress_line<T, BITS, 12, 6, LU>;              // three rounds per plane (see line_groups)
+        if constexpr (LU == -2) kern = compress_line<T, BITS, 12, 4, LU>;              // (blocks of two rounds, several per plane: three rounds)
         else kern = a.NG == 12 ? compress_line<T, BITS, 12, 12, LU> : a.NG == 6 ? compress_line<T, BITS, 12, 6, LU> : compress_line<T, BITS, 12, 4, LU>;
     } else kern = a.K == 4 ? compress_line<T, BITS, 4, 1, LU> : a.K == 6 ? compress_line<T, BITS, 6, 1, LU> : compress_line<T, BITS, 13, 1, LU>;
-    hipLaunchKernelGGL(kern, gd, dim3(64), lds, st, la);
+    hipLaunchKernelGGL(kern, gd, dim3(64), lds, st, a);
     return hipGetLastError();
 }
 template <typename T, int BITS>
@@ -1038,7 +1030,8 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case ROWSTRIP: return launch_rowstrip<T, 1>(c.vec, c.sa, gd, lds, st);
             case LANE: hipLaunchKernelGGL((compress_lane<T, 1>), gd, dim3(64), lds, st, c.la); return hipGetLastError();
             case ITEMS: return launch_items<T, 1>(c.B, c.vec, c.ia, gd, lds, st);
-            case UNITS: if (c.seg_nt) return launch_seg<T, 1>(c.seg_K, c.B, c.sg, c.seg_nt, gd, lds, st); return launch_units<T, 1>(c.nw, c.ua, gd, lds, st);
+            case UNITS: return launch_units<T, 1>(c.nw, c.ua, gd, lds, st);
+            case SEG: return launch_seg<T, 1>(c.seg_K, c.B, c.sg, c.seg_nt, gd, lds, st);
             case ONE: return launch_one<T, 1>(c.oa, gd, st);
             case LINE: return launch_line<T, 1>(c.oa, gd, lds, st);
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
@@ -1056,7 +1049,8 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case STRIP: return launch_strip<T, BITS>(c.vec, c.sa, gd, lds, st);
             case ROWSTRIP: return launch_rowstrip<T, BITS>(c.vec, c.sa, gd, lds, st);
             case ITEMS: return launch_items<T, BITS>(c.B, c.vec, c.ia, gd, lds, st);
-            case UNITS: if (c.seg_nt) return launch_seg<T, BITS>(c.seg_K, c.B, c.sg, c.seg_nt, gd, lds, st); return launch_units<T, BITS>(c.nw, c.ua, gd, lds, st);
+            case UNITS: return launch_units<T, BITS>(c.nw, c.ua, gd, lds, st);
+            case SEG: return launch_seg<T, BITS>(c.seg_K, c.B, c.sg, c.seg_nt, gd, lds, st);
             case WAVE: return launch_wave<T, BITS>(c.B, c.vec, c.wa, gd, lds, st);
             case TILE: return launch_tile<T, BITS>(c.B, c.vec, c.a, gd, lds, st);
             case LANE: hipLaunchKernelGGL((compress_lane<T, BITS>), gd, dim3(64), lds, st, c.la); return hipGetLastError();
@@ -1092,14 +1086,6 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
         constexpr int BITS = decltype(bits)::value;
         const int kind = c.kind;
         void (*kern)(DecArgs);
-        if (kind == 7 && sizeof(T) == 2) {
-            DecStreamArgs sa;
-            static_cast<DecArgs&>(sa) = c.a;
-            void (*rv)(DecStreamArgs);
-            if (c.flat) rv = decompress_rowvec<T, BITS>; else rv = decompress_rowvec_3d<T, BITS>;
-            hipLaunchKernelGGL(rv, dim3(c.gx, c.gy), dim3(64), 0, c.st, sa);
-            return hipGetLastError();
-        }
         if (kind == 7 || kind == 8 || kind == 9) {
             if (kind == 7) kern = c.flat ? decompress_stream<T, BITS> : decompress_stream_3d<T, BITS>;
             else if (kind == 9) kern = decompress_stream_one<T, BITS>;
@@ -1114,13 +1100,12 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
             hipLaunchKernelGGL(kern, dim3(c.gx, c.gy), dim3(64 * c.nw), c.lds, c.st, c.a);
             return hipGetLastError();
         }
-        if (kind == 0) { if (c.flat) kern = decompress_rowvec<T, BITS>; else kern = decompress_rowvec_3d<T, BITS>; }
-        else if (c.flat)
-            kern = kind == 3 ? decompress_table<T, BITS>
+        if (c.flat)
+            kern = kind == 0 ? decompress_rowvec<T, BITS> : kind == 3 ? decompress_table<T, BITS>
                  : kind == 5 ? decompress_words<T, BITS> : kind == 1 ? decompress_flat<T, BITS>
                  : kind == 4 ? decompress_lane<T, BITS> : decompress_scalar<T, BITS>;
         else
-            kern = kind == 5 ? decompress_words_3d<T, BITS>
+            kern = kind == 0 ? decompress_rowvec_3d<T, BITS> : kind == 5 ? decompress_words_3d<T, BITS>
                  : kind == 1 ? decompress_flat_3d<T, BITS>
                  : kind == 4 ? decompress_lane<T, BITS> : decompress_scalar_3d<T, BITS>;
         const hipError_t e = allow_large_lds(kern, c.lds);
@@ -1259,10 +1244,7 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         else if (wide && plan_plane(L, D, H, W, B, es, xa, &pa, &grid, &lds)) { kind = PLANE; pa.tab = tab; pa.rg = rg; }
         else use_any();
         CompLaunch c{};
-        if (kind == UNITS && plan_seg(L, D, H, W, B, es, &c.sg, &grid, &lds, &c.seg_nt, &c.seg_K)) {
-            c.sg.tab = tab;
-            c.sg.rg = rg;
-        }
+        if (kind == UNITS && plan_seg(L, D, H, W, B, es, &c.sg, &grid, &lds, &c.seg_nt, &c.seg_K)) { kind = SEG; c.sg.tab = tab; c.sg.rg = rg; }
         c.kind = kind; c.B = B; c.vec = vec; c.nt = nt; c.nw = nw; c.flat = flat;
         c.gx = grid; c.gy = (uint32_t)cnt; c.lds = lds; c.st = st;
         c.sa = sa; c.a = a; c.wa = wa; c.ra = ra; c.ia = ia; c.la = la; c.wa2 = wa2; c.pa = pa; c.oa = oa; c.g = g; c.ua = ua;
@@ -1330,21 +1312,26 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
         const bool wide = b != 1;        // as in compress_impl
         TileArgs a{}; WaveArgs wa{}; RegsArgs ra{}; ItemsArgs ia{}; LaneArgs la{}; RowsArgs wa2{}; PlaneArgs pa{}; OneArgs oa{}; UnitsArgs ua{}; StripArgs sa{}; size_t lds = 0; uint32_t grid = 0; int vec = 1, nt = 64, nw = 1;
         if (line_first(L, es) && plan_line(L, D, H, B, es, data, &oa, &grid, &lds))
-            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u>", tn, b, oa.K, line_lu(oa) == -2 && oa.K == 12 ? 6u : oa.NG);
+            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u, %d>", tn, b, oa.K, oa.NG, line_lu(oa));
         else if (plan_regs(L, D, H, W, B, es, data, &ra, &grid, &lds, &nw))
             n = snprintf(out, cap, "compress_regs%s<%s, %d, %d, %d>", sfx, tn, b, (B == 4 || B == 8) ? B : 0, nw);
         else if (plan_lane(L, es, data, &la, &grid, &lds))
             n = snprintf(out, cap, "compress_lane<%s, %d>", tn, b);
         else if (plan_line(L, D, H, B, es, data, &oa, &grid, &lds))
-            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u>", tn, b, oa.K, line_lu(oa) == -2 && oa.K == 12 ? 6u : oa.NG);
+            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u, %d>", tn, b, oa.K, oa.NG, line_lu(oa));
         else if (flat && plan_strip(L, H, W, B, es, data, &sa, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_strip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
         else if (flat && plan_rowstrip(L, H, W, B, es, data, &sa, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_rowstrip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
         else if (flat && plan_items(L, H, W, B, es, data, &ia, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_items<%s, %d, %d, %d, %d>", tn, b, B, vec, H == 1 ? 1 : B);
-        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, es, data, &ua, &grid, &lds, &nw) && (wide || nw != 16))
-            n = snprintf(out, cap, "compress_units<%s, %d, %d>", tn, b, nw);
+        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, es, data, &ua, &grid, &lds, &nw) && (wide || nw != 16)) {
+            SegArgs sg{}; uint32_t seg_nt = 0; int seg_K = 0;
+            if (plan_seg(L, D, H, W, B, es, &sg, &grid, &lds, &seg_nt, &seg_K))
+                n = snprintf(out, cap, "compress_seg<%s, %d, %d, %s, %d>", tn, b, B, W % 2 != 0 ? "true" : "false", seg_K);
+            else
+                n = snprintf(out, cap, "compress_units<%s, %d, %d>", tn, b, nw);
+        }
         else if (wide && flat && plan_wave(L, H, W, B, b, es, data, &wa, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_wave<%s, %d, %d, %d>", tn, b, B, vec);
         else if (flat && plan_tile(L, H, W, B, b, es, data, &a, &grid, &lds, &vec, &nt))
@@ -1363,7 +1350,7 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
         if (kind == 6)
             n = snprintf(out, cap, "decompress_units<%s, %d, %d>", tn, b, (int)a.G);
         else if (kind == 7)
-            n = snprintf(out, cap, "%s%s<%s, %d>", es == 2 ? "decompress_rowvec" : "decompress_stream", sfx, tn, b);
+            n = snprintf(out, cap, "decompress_stream%s<%s, %d>", sfx, tn, b);
         else if (kind == 8)
             n = snprintf(out, cap, "decompress_stream_any%s<%s, %d>", sfx, tn, b);
         else if (kind == 9)

@@ -79,13 +79,15 @@ def test_volume_kernels_cover_what_the_cases_claim():
     assert kn(0, (1, 2, 16, 56, 56), 8, 2) == "compress_regs_3d<float, 2, 8, 16>"
     assert kn(0, (1, 2, 16, 56, 56), 8, 2, torch.bfloat16) == "compress_regs_3d<bf16_t, 2, 8, 16>"
     assert kn(0, (2, 3, 5, 9, 13), 4, 2) == "compress_units<float, 2, 1>"
+    assert kn(0, (2, 3, 4, 14, 14), 8, 2) == "compress_seg<float, 2, 8, false, 1>"
+    assert kn(0, (2, 3, 8, 18, 26), 8, 2) == "compress_seg<float, 2, 8, false, 2>"
     assert kn(0, (2, 2, 8, 27, 27), 8, 2) == "compress_units<float, 2, 4>"
     assert kn(0, (5, 3, 4, 9, 9), 8, 2) == "compress_units<float, 2, 0>"
     assert kn(0, (3, 2, 5, 7, 7), 4, 2) == "compress_rows_3d<float, 2>"
     assert kn(0, (1, 2, 24, 40, 64), 16, 2) == "compress_plane_3d<float, 2>"
     assert kn(0, (1, 2, 33, 35, 37), 16, 2) == "compress_any_3d<float, 2>"
     assert kn(1, (3, 5, 16, 16, 16), 8, 2) == "decompress_stream_3d<float, 2>"
-    assert kn(1, (3, 5, 16, 16, 16), 8, 2, torch.bfloat16) == "decompress_rowvec_3d<bf16_t, 2>"
+    assert kn(1, (3, 5, 16, 16, 16), 8, 2, torch.bfloat16) == "decompress_stream_3d<bf16_t, 2>"
     assert kn(1, (2, 3, 5, 9, 13), 4, 2) == "decompress_stream_any_3d<float, 2>"
     assert kn(1, (2, 3, 5, 9, 13), 4, 2, torch.bfloat16) == "decompress_units<bf16_t, 2, 1>"
     assert kn(1, (2, 2, 3, 35, 35), 4, 4, torch.bfloat16) == "decompress_units<bf16_t, 4, 2>"

@@ -20,6 +20,13 @@ def _host(t):
     return t.view(torch.int16).numpy().view(np.uint16) if t.dtype == torch.bfloat16 else t.numpy()
 
 
+def _names(shape, B, b, mode, out_ptr=0):
+    """Kernel instances that compress and rebuild the map"""
+    dtype, c16, _ = FORMATS[mode]
+    kn = pkg.division_kernel_name_3d if len(shape) == 5 else pkg.division_kernel_name
+    return kn(0, shape, B, b, dtype, c16=c16), kn(1, shape, B, b, dtype, data_ptr=out_ptr, c16=c16)
+
+
 def _round_trip(shape, B, b, mode, seed=7, offset=0, relu=False, x=None):
     """Compress and rebuild a map (x, or normal values) whose rebuilt copy starts `offset` elements into its buffer."""
     dtype, c16, dt = FORMATS[mode]
@@ -62,21 +69,26 @@ def _round_trip(shape, B, b, mode, seed=7, offset=0, relu=False, x=None):
     ((2, 3, 3, 5, 20), 4, 0),
 ])
 def test_two_byte_rows_of_whole_pieces(shape, B, b, offset):
+    assert _names(shape, B, b, "bf16", 256 + 2 * offset)[1].startswith("decompress_rowvec<" if offset else "decompress_stream")
     _round_trip(shape, B, b, "bf16", offset=offset)
 
 
 @pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
 @pytest.mark.parametrize("b", [1, 2, 4, 8])
-@pytest.mark.parametrize("shape,B", [
-    ((3, 5, 1, 96), 64),                 # a block of two rounds, the last one short; rounds past the plane
-    ((1, 1, 1, 96), 64),                 # a single plane: the other groups lie past the map
-    ((7, 11, 1, 160), 128),
-    ((5, 9, 1, 192), 64), ((3, 67, 1, 232), 64), ((2, 3, 1, 776), 64), ((2, 3, 1, 1536), 128),
-    ((1, 3, 1, 1544), 256),              # a block is a whole wavefront of vectors, the last one two vectors
-    ((3, 5, 1, 104), 32), ((2, 9, 1, 1000), 32),
-    ((5, 7, 1, 72), 8), ((2, 3, 1, 2056), 8), ((2, 3, 1, 1032), 16),
+@pytest.mark.parametrize("shape,B,lu4,lu2", [
+    # shape, B, how a block is summed in 4-byte and 2-byte maps: log2 of its vectors (DPP), through LDS (-1), two rounds of it (-2)
+    ((3, 5, 1, 96), 64, -2, -1),         # a block of two rounds, the last one short; rounds past the plane
+    ((1, 1, 1, 96), 64, -2, -1),         # a single plane: the other groups lie past the map
+    ((7, 11, 1, 160), 128, -2, -2),
+    ((5, 9, 1, 192), 64, -2, -1), ((3, 67, 1, 232), 64, -1, -1), ((2, 3, 1, 776), 64, -1, -1), ((2, 3, 1, 1536), 128, -1, -1),
+    ((1, 3, 1, 1544), 256, -2, -2),      # a block is a whole wavefront of vectors, the last one two vectors
+    ((3, 5, 1, 104), 32, -1, 2), ((2, 9, 1, 1000), 32, -1, 2),
+    ((5, 7, 1, 72), 8, 1, 0), ((2, 3, 1, 2056), 8, None, 0), ((2, 3, 1, 1032), 16, 2, 1),      # (4-byte planes of 514 vectors: compress_regs)
+    ((5, 7, 1, 72), 4, 0, None), ((3, 5, 1, 2040), 4, 0, None), ((3, 5, 1, 2040), 16, 2, 1),
 ])
-def test_rows_of_power_of_two_blocks(shape, B, b, mode):
+def test_rows_of_power_of_two_blocks(shape, B, lu4, lu2, b, mode):
+    name, lu = _names(shape, B, b, mode)[0], lu2 if mode == "bf16" else lu4
+    assert name.startswith("compress_line<") and name.endswith(", %d>" % lu) if lu is not None else not name.startswith("compress_line<"), name
     _round_trip(shape, B, b, mode)
 
 
@@ -99,24 +111,32 @@ def test_tiny_negative_sum_has_mean_minus_zero(shape, B, mode):
 
 @pytest.mark.parametrize("mode", ["f32", "c16"])
 @pytest.mark.parametrize("b", [1, 2, 4, 8])
-@pytest.mark.parametrize("shape,B", [
-    ((1, 1, 17, 17), 8), ((41, 101, 17, 17), 8),          # one plane; several planes per workgroup, the last one short
-    ((3, 7, 13, 13), 4), ((5, 5, 9, 13), 8), ((2, 3, 35, 35), 8), ((29, 67, 35, 35), 4), ((1, 3, 64, 55), 8), ((2, 2, 2, 17), 4),
-    ((2, 3, 19, 19), 8), ((3, 2, 21, 23), 4), ((3, 3, 40, 33), 8),                 # whole block rows; a last column of one element
-    ((1, 2, 73, 73), 8), ((2, 3, 57, 41), 4), ((1, 2, 101, 97), 8), ((1, 1, 128, 111), 4), ((1, 2, 147, 147), 8), ((1, 1, 163, 163), 8),
-    ((2, 2, 300, 5), 8), ((1, 2, 200, 3), 4), ((2, 1, 3, 1001), 8), ((2, 2, 9, 250), 4),           # narrower than a block; few rows
-    ((2, 3, 4, 14, 14), 8), ((3, 5, 9, 14, 14), 8), ((1, 2, 5, 16, 9), 4), ((2, 2, 3, 22, 30), 8), ((1, 3, 2, 30, 35), 4),
-    ((2, 2, 3, 15, 21), 8),                               # an odd number of elements per slice
+@pytest.mark.parametrize("shape,B,items", [
+    # shape, B, items of sixteen elements per lane (0: another kernel takes the planes)
+    ((1, 1, 17, 17), 8, 0), ((41, 101, 17, 17), 8, 0),    # a row per lane: one plane; several planes per workgroup, the last one short
+    ((3, 7, 13, 13), 4, 0), ((5, 5, 9, 13), 8, 0), ((2, 3, 35, 35), 8, 0), ((29, 67, 35, 35), 4, 0), ((1, 3, 64, 55), 8, 0), ((2, 2, 2, 17), 4, 0),
+    ((2, 3, 19, 19), 8, 0), ((3, 2, 21, 23), 4, 0), ((2, 3, 57, 41), 4, 0), ((1, 1, 163, 163), 8, 0),         # too few slots filled, too many items
+    ((2, 2, 300, 5), 8, 0), ((1, 2, 200, 3), 4, 0), ((2, 2, 9, 250), 4, 0), ((3, 5, 9, 14, 14), 8, 0), ((2, 2, 3, 22, 30), 8, 0), ((1, 3, 2, 30, 35), 4, 0),
+    ((2, 2, 3, 15, 21), 8, 0),                            # an odd number of elements per slice
+    ((3, 5, 29, 29), 8, 1), ((3, 5, 29, 29), 4, 1), ((1, 1, 29, 29), 8, 1), ((2, 1, 3, 1001), 8, 1), ((2, 2, 100, 37), 8, 1),   # (29: 28 rows and one)
+    ((2, 3, 4, 14, 14), 8, 1), ((1, 2, 5, 16, 9), 4, 1), ((5, 41, 4, 14, 14), 4, 1),
+    ((3, 3, 40, 33), 8, 2), ((1, 2, 73, 73), 8, 2), ((1, 2, 101, 97), 8, 2), ((1, 1, 128, 111), 4, 2), ((1, 2, 147, 147), 8, 2),
+    ((1, 2, 127, 129), 8, 2), ((3, 5, 28, 45), 8, 2), ((1, 2, 1000, 5), 4, 2), ((2, 2, 8, 18, 26), 8, 2), ((1, 2, 4, 30, 34), 8, 2), ((1, 2, 6, 22, 35), 8, 2),
 ])
-def test_items_of_sixteen_elements(shape, B, b, mode):
+def test_items_of_sixteen_elements(shape, B, items, b, mode):
+    name = _names(shape, B, b, mode)[0]
+    if b == 1 and shape[2:] == (147, 147):
+        items = 0                                         # (no 1-bit instance of sixteen wavefronts in the kernel asked first)
+    assert name.startswith("compress_seg<") and name.endswith(", %d>" % items) if items else not name.startswith("compress_seg<"), name
     _round_trip(shape, B, b, mode, relu=b == 2)
 
 
 @pytest.mark.parametrize("mode", ["f32", "c16"])
 @pytest.mark.parametrize("shape,B", [
-    ((4, 6, 29, 29), 8), ((4, 6, 29, 29), 4), ((4, 6, 37, 37), 8), ((4, 6, 40, 33), 8), ((4, 6, 73, 73), 8),       # an item per lane
-    ((4, 6, 147, 147), 8), ((4, 6, 147, 147), 4), ((4, 6, 127, 127), 8), ((4, 6, 101, 97), 8),                     # two items
-    ((4, 6, 4, 14, 14), 8), ((4, 6, 9, 14, 14), 8), ((4, 6, 8, 18, 26), 8), ((4, 6, 5, 16, 9), 4), ((4, 6, 5, 22, 22), 4),
+    ((4, 6, 29, 29), 8), ((4, 6, 29, 29), 4), ((4, 6, 4, 14, 14), 8), ((4, 6, 5, 16, 9), 4),       # an item of sixteen elements per lane
+    ((4, 6, 37, 37), 8), ((4, 6, 40, 33), 8), ((4, 6, 73, 73), 8), ((4, 6, 147, 147), 8), ((4, 6, 147, 147), 4),   # two items
+    ((4, 6, 127, 127), 8), ((4, 6, 101, 97), 8), ((4, 6, 8, 18, 26), 8), ((4, 6, 4, 30, 34), 8), ((4, 6, 6, 22, 35), 8),
+    ((4, 6, 9, 14, 14), 8), ((4, 6, 5, 22, 22), 4),                                                                 # other kernels
     ((4, 6, 56, 56), 8), ((4, 6, 28, 28), 8), ((4, 6, 17, 17), 8), ((4, 6, 57, 57), 18), ((4, 6, 1, 768), 8), ((4, 6, 1, 96), 64),
 ])
 def test_a_value_that_is_not_finite_stays_in_its_block(shape, B, mode):

@@ -472,12 +472,12 @@ ONE_BIT_CASES = [
     ((3, 67, 7, 7), 8, "compress_lane<float, 1>", "decompress_lane"),
     ((2, 3, 5, 5), 8, "compress_lane<float, 1>", "decompress_lane"),
     ((1, 1, 1, 1), 8, "compress_lane<float, 1>", "decompress_lane"),
-    ((2, 9, 1, 96), 64, "compress_line<float, 1, 12, 6>", "decompress_stream"),
-    ((2, 9, 1, 768), 8, "compress_line<float, 1, 6, 1>", "decompress_stream"),
-    ((2, 9, 1, 768), 64, "compress_line<float, 1, 6, 1>", "decompress_stream"),
-    ((5, 9, 1, 196), 16, "compress_line<float, 1, 4, 1>", "decompress_stream"),      # 49 vectors: the last byte holds one
-    ((3, 7, 1, 100), 8, "compress_line<float, 1, 4, 1>", "decompress_stream"),       # 25 vectors
-    ((7, 9, 1, 24), 8, "compress_line<float, 1, 12, 12>", "decompress_stream"),
+    ((2, 9, 1, 96), 64, "compress_line<float, 1, 12, 4, -2>", "decompress_stream"),
+    ((2, 9, 1, 768), 8, "compress_line<float, 1, 6, 1, 1>", "decompress_stream"),
+    ((2, 9, 1, 768), 64, "compress_line<float, 1, 6, 1, -1>", "decompress_stream"),
+    ((5, 9, 1, 196), 16, "compress_line<float, 1, 4, 1, 2>", "decompress_stream"),      # 49 vectors: the last byte holds one
+    ((3, 7, 1, 100), 8, "compress_line<float, 1, 4, 1, 1>", "decompress_stream"),       # 25 vectors
+    ((7, 9, 1, 24), 8, "compress_line<float, 1, 12, 12, 1>", "decompress_stream"),
     ((2, 3, 1, 3072), 64, "compress_regs<float, 1, 0, 1>", "decompress_stream"),
     ((2, 3, 1, 3072), 4096, "compress_one<float, 1, 13>", "decompress_stream"),
     ((3, 5, 56, 56), 64, "compress_one<float, 1, 13>", "decompress_stream"),
@@ -495,15 +495,19 @@ ONE_BIT_CASES = [
     ((2, 3, 44, 46), 8, "compress_tile<float, 1, 8, 2, 256>", "decompress_"),
     ((1, 2, 300, 300), 8, "compress_any<float, 1>", "decompress_"),
     ((2, 3, 28, 28), 3, "compress_any<float, 1>", "decompress_table"),
-    ((2, 2, 100, 37), 8, "compress_units<float, 1, 2>", "decompress_table"),
-    ((2, 3, 53, 53), 4, "compress_units<float, 1, 2>", "decompress_stream_any"),
-    ((2, 3, 57, 57), 8, "compress_units<float, 1, 2>", "decompress_stream_any"),
+    ((2, 2, 100, 37), 8, "compress_seg<float, 1, 8, true, 1>", "decompress_table"),
+    ((2, 3, 53, 53), 4, "compress_seg<float, 1, 4, true, 2>", "decompress_stream_any"),
+    ((2, 3, 57, 57), 8, "compress_seg<float, 1, 8, true, 2>", "decompress_stream_any"),
     ((2, 3, 55, 55), 8, "compress_rowstrip<float, 1, 55, 8>", "decompress_stream_any"),
     ((3, 2, 33, 17), 12, "compress_units<float, 1, 1>", "decompress_stream_any"),
-    ((2, 3, 29, 29), 8, "compress_units<float, 1, 1>", "decompress_stream_any"),       # 841 elements: a lone unit in the last byte
-    ((2, 3, 37, 37), 8, "compress_units<float, 1, 1>", "decompress_stream_any"),
-    ((2, 3, 73, 73), 8, "compress_units<float, 1, 4>", "decompress_stream_any"),
-    ((1, 3, 125, 125), 8, "compress_units<float, 1, 8>", "decompress_stream_any"),
+    ((2, 3, 29, 29), 8, "compress_seg<float, 1, 8, true, 1>", "decompress_stream_any"),       # 841 elements: a lone unit in the last byte
+    ((2, 3, 37, 37), 8, "compress_seg<float, 1, 8, true, 2>", "decompress_stream_any"),
+    ((2, 3, 73, 73), 8, "compress_seg<float, 1, 8, true, 2>", "decompress_stream_any"),
+    ((2, 3, 73, 73), 18, "compress_units<float, 1, 4>", "decompress_stream_any"),
+    ((2, 3, 37, 37), 18, "compress_units<float, 1, 1>", "decompress_stream_any"),
+    ((2, 3, 57, 57), 18, "compress_units<float, 1, 2>", "decompress_stream_any"),
+    ((1, 3, 125, 125), 8, "compress_seg<float, 1, 8, true, 2>", "decompress_stream_any"),
+    ((1, 3, 125, 125), 18, "compress_units<float, 1, 8>", "decompress_stream_any"),
     ((1, 2, 147, 147), 8, "compress_tile<float, 1, 8, 1, 256>", "decompress_stream_any"),   # sixteen wavefronts per plane: no 1-bit instance of the units kernel
     ((1, 2, 147, 147), 18, "compress_any<float, 1>", "decompress_stream_any"),
     ((5, 7, 19, 19), 8, "compress_units<float, 1, 0>", "decompress_stream_any"),        # 16 lanes per plane
@@ -1004,12 +1008,19 @@ UNITS_CASES = [
     ((1, 2, 1000, 5), 4, 4),
 ]
 
+SEG_PLANES = {(57, 57), (53, 53), (29, 29), (147, 147), (149, 149), (73, 73), (38, 75), (127, 129), (3000, 3), (1000, 5)}
+# the same planes of 4-byte elements under block sizes that leave them to the units kernel
+UNITS_CASES += [((2, 3, 57, 57), 18, 2), ((3, 2, 53, 53), 12, 4), ((3, 5, 29, 29), 12, 2), ((2, 2, 147, 147), 18, 2), ((1, 3, 149, 149), 12, 4),
+                ((2, 2, 73, 73), 18, 4), ((2, 3, 38, 75), 12, 4), ((1, 3, 127, 129), 18, 2), ((2, 2, 3000, 3), 3, 2), ((1, 2, 1000, 5), 3, 4)]
+
 
 @pytest.mark.parametrize("shape,B,b", UNITS_CASES)
 @pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
 def test_register_kernel_any_width_matches_oracle(shape, B, b, mode):
     dtype = torch.bfloat16 if mode == "bf16" else torch.float32
-    assert pkg.division_kernel_name(0, shape, B, b, dtype, c16=mode == "c16").startswith("compress_units<")
+    # (4-byte elements: most of the planes under B = 4 and 8 are taken as items of sixteen elements)
+    seg = mode != "bf16" and shape[2:] in SEG_PLANES and B in (4, 8)
+    assert pkg.division_kernel_name(0, shape, B, b, dtype, c16=mode == "c16").startswith("compress_seg<" if seg else "compress_units<")
     if shape[3] % 2 == 1 and shape[2] * shape[3] >= 512:      # (smaller planes are rebuilt chunk-wise in LDS)
         # (4-byte elements: the wavefront-per-chunk kernel for any width where a plane has several blocks of 4 and more)
         assert pkg.division_kernel_name(1, shape, B, b, dtype, c16=mode == "c16").startswith(("decompress_units<", "decompress_stream_any<", "decompress_stream_one<"))
@@ -1018,10 +1029,14 @@ def test_register_kernel_any_width_matches_oracle(shape, B, b, mode):
 
 # more planes than workgroups: a workgroup takes every grid-th plane, the next one's loads in flight
 @pytest.mark.parametrize("shape,B,b", [((21, 100, 57, 57), 8, 2), ((3, 100, 147, 147), 8, 2), ((42, 100, 29, 29), 4, 4),
-                                        ((3, 1001, 37, 37), 8, 2), ((5, 4001, 19, 19), 8, 2)])
+                                        ((3, 1001, 37, 37), 8, 2), ((5, 4001, 19, 19), 8, 2),
+                                        ((21, 100, 57, 57), 18, 2), ((3, 100, 147, 147), 18, 2), ((42, 100, 29, 29), 12, 4),
+                                        ((5, 1001, 37, 37), 18, 2)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_register_kernel_any_width_many_planes(shape, B, b, dtype):
-    assert pkg.division_kernel_name(0, shape, B, b, dtype).startswith("compress_units<")
+    # (compress_seg: a workgroup per plane, here more than the XCD-aware order deals out in its runs)
+    seg = dtype == torch.float32 and B in (4, 8) and shape[2] != 19
+    assert pkg.division_kernel_name(0, shape, B, b, dtype).startswith("compress_seg<" if seg else "compress_units<")
     x = _relu_normal(shape, 4242 + shape[1], dtype)
     xh, _ = to_host_array(x)
     dt = oracle.BF16 if dtype == torch.bfloat16 else oracle.F32

@@ -176,7 +176,7 @@ def test_the_planner_names_a_kernel_for_every_shape_of_a_seeded_grid():
     import torch
     rng = np.random.default_rng(4187)
     comp = {"compress_regs", "compress_regs_3d", "compress_lane", "compress_line", "compress_strip", "compress_rowstrip",
-            "compress_items", "compress_units", "compress_wave", "compress_tile", "compress_one", "compress_rows",
+            "compress_items", "compress_units", "compress_seg", "compress_wave", "compress_tile", "compress_one", "compress_rows",
             "compress_rows_3d", "compress_plane", "compress_plane_3d", "compress_any", "compress_any_3d"}
     dec = {"decompress_stream", "decompress_stream_3d", "decompress_stream_any", "decompress_stream_any_3d",
            "decompress_stream_one", "decompress_rowvec", "decompress_rowvec_3d", "decompress_table", "decompress_units",
@@ -201,7 +201,7 @@ def test_the_planner_names_a_kernel_for_every_shape_of_a_seeded_grid():
             assert family in families, name
             assert args.split(", ")[1].rstrip(">") == str(b), name
             seen.add(family)
-    assert len(seen) >= 28, sorted(seen)
+    assert len(seen) >= 29 and "compress_seg" in seen, sorted(seen)
 
 
 # which kernel the host picks for a shape (a host-side decision: no GPU needed to ask)
@@ -220,7 +220,7 @@ DISPATCH = [
     ((64, 64, 147, 147), 8, 1, "compress_tile<float, 1, 8, 1, 256>", "decompress_stream_any<float, 1>"),
     ((64, 64, 147, 147), 18, 1, "compress_any<float, 1>", "decompress_stream_any<float, 1>"),
     ((64, 96, 64, 64), 8, 1, "compress_tile<float, 1, 8, 4, 256>", "decompress_stream<float, 1>"),
-    ((256, 128, 1, 768), 8, 1, "compress_line<float, 1, 6, 1>", "decompress_stream<float, 1>"),
+    ((256, 128, 1, 768), 8, 1, "compress_line<float, 1, 6, 1, 1>", "decompress_stream<float, 1>"),
     ((64, 256, 56, 56), 64, 1, "compress_one<float, 1, 13>", "decompress_stream<float, 1>"),
     ((64, 512, 28, 28), 3, 1, "compress_any<float, 1>", "decompress_table<float, 1>"),
     ((64, 64, 112, 112), 8, 2, "compress_regs<float, 2, 8, 4>", "decompress_stream<float, 2>"),
@@ -247,14 +247,24 @@ DISPATCH = [
     ((8, 8, 17, 17), 8, 2, "compress_rowstrip<float, 2, 17, 8>", "decompress_stream_any<float, 2>"),
     ((8, 8, 13, 13), 8, 2, "compress_rowstrip<float, 2, 13, 8>", "decompress_stream_any<float, 2>"),
     ((8, 8, 27, 27), 4, 2, "compress_rowstrip<float, 2, 27, 4>", "decompress_stream_any<float, 2>"),
-    ((8, 8, 29, 29), 4, 2, "compress_units<float, 2, 1>", "decompress_stream_any<float, 2>"),
+    ((8, 8, 29, 29), 4, 2, "compress_seg<float, 2, 4, true, 1>", "decompress_stream_any<float, 2>"),
     ((8, 8, 19, 19), 8, 2, "compress_units<float, 2, 0>", "decompress_stream_any<float, 2>"),
     ((8, 8, 11, 11), 8, 2, "compress_wave<float, 2, 8, 1>", "decompress_stream_any<float, 2>"),
     ((8, 8, 35, 35), 8, 2, "compress_rowstrip<float, 2, 35, 8>", "decompress_stream_any<float, 2>"),
-    ((8, 8, 73, 73), 8, 2, "compress_units<float, 2, 4>", "decompress_stream_any<float, 2>"),
-    ((4, 4, 147, 147), 8, 2, "compress_units<float, 2, 16>", "decompress_stream_any<float, 2>"),
+    ((8, 8, 73, 73), 8, 2, "compress_seg<float, 2, 8, true, 2>", "decompress_stream_any<float, 2>"),
+    ((4, 4, 147, 147), 8, 2, "compress_seg<float, 2, 8, true, 2>", "decompress_stream_any<float, 2>"),
+    ((4, 4, 147, 147), 18, 2, "compress_units<float, 2, 16>", "decompress_stream_any<float, 2>"),
+    # items of sixteen elements: at least 60 % of the lanes' slots filled (26 x 45: 57 %), at most 768 lanes
+    ((8, 8, 26, 45), 8, 2, "compress_units<float, 2, 1>", "decompress_stream_any<float, 2>"),
+    ((8, 8, 26, 47), 8, 2, "compress_units<float, 2, 1>", "decompress_stream_any<float, 2>"),
+    ((8, 8, 28, 45), 8, 2, "compress_seg<float, 2, 8, true, 2>", "decompress_table<float, 2>"),
+    ((8, 8, 163, 163), 8, 2, "compress_units<float, 2, 16>", "decompress_stream_any<float, 2>"),
+    # one-row maps: several plane groups per wavefront, blocks of two rounds, blocks through LDS
+    ((64, 98, 1, 96), 64, 2, "compress_line<float, 2, 12, 4, -2>", "decompress_stream<float, 2>"),
+    ((64, 98, 1, 96), 8, 2, "compress_line<float, 2, 12, 4, 1>", "decompress_stream<float, 2>"),
+    ((64, 98, 1, 384), 64, 2, "compress_line<float, 2, 6, 1, -1>", "decompress_stream<float, 2>"),
     ((4, 4, 30, 30), 4, 2, "compress_wave<float, 2, 4, 2>", "decompress_table<float, 2>"),
-    ((2, 2, 1, 768), 8, 4, "compress_line<float, 4, 6, 1>", "decompress_stream<float, 4>"),
+    ((2, 2, 1, 768), 8, 4, "compress_line<float, 4, 6, 1, 1>", "decompress_stream<float, 4>"),
     ((5, 33, 14, 14), 12, 4, "compress_strip<float, 4, 14, 12>", "decompress_table<float, 4>"),
     ((5, 33, 24, 24), 18, 4, "compress_rows<float, 4>", "decompress_table<float, 4>"),
     ((1, 1, 300, 300), 18, 2, "compress_any<float, 2>", "decompress_scalar<float, 2>"),
@@ -273,5 +283,14 @@ def test_kernel_choice_for_3d_maps_and_2_byte_elements():
     assert pkg.division_kernel_name_3d(1, (2, 4, 16, 56, 56), 8, 2) == "decompress_stream_3d<float, 2>"
     assert pkg.division_kernel_name(0, (8, 8, 55, 55), 8, 2, torch.bfloat16) == "compress_rowstrip<bf16_t, 2, 55, 8>"
     assert pkg.division_kernel_name(0, (8, 8, 55, 55), 18, 2, torch.bfloat16) == "compress_units<bf16_t, 2, 2>"
+    assert pkg.division_kernel_name(0, (8, 8, 73, 73), 8, 2, torch.bfloat16) == "compress_units<bf16_t, 2, 4>"
+    assert pkg.division_kernel_name(0, (8, 8, 73, 73), 8, 2, torch.float32, c16=True) == "compress_seg<f32c16_t, 2, 8, true, 2>"
+    assert pkg.division_kernel_name_3d(0, (2, 4, 4, 14, 14), 8, 2) == "compress_seg<float, 2, 8, false, 1>"
+    assert pkg.division_kernel_name_3d(0, (2, 4, 4, 15, 15), 8, 2) == "compress_units<float, 2, 1>"      # an odd number of elements per slice
+    # rows of whole pieces: staged in LDS only where the rebuilt map does not start on a 16-byte boundary
+    assert pkg.division_kernel_name(1, (8, 8, 56, 56), 8, 2, torch.bfloat16) == "decompress_stream<bf16_t, 2>"
+    assert pkg.division_kernel_name(1, (8, 8, 28, 28), 8, 2, torch.bfloat16, data_ptr=256) == "decompress_stream<bf16_t, 2>"
+    assert pkg.division_kernel_name(1, (8, 8, 56, 56), 8, 2, torch.bfloat16, data_ptr=264) == "decompress_rowvec<bf16_t, 2>"
+    assert pkg.division_kernel_name_3d(1, (2, 4, 4, 28, 28), 8, 2, torch.bfloat16) == "decompress_stream_3d<bf16_t, 2>"
     assert pkg.division_kernel_name(1, (8, 8, 55, 55), 8, 2, torch.bfloat16) == "decompress_units<bf16_t, 2, 2>"
     assert pkg.division_kernel_name(0, (8, 8, 56, 56), 8, 2, torch.float32, c16=True) == "compress_regs<f32c16_t, 2, 8, 1>"
