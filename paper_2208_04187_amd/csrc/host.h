@@ -40,6 +40,9 @@ int make_layout(int64_t N, int64_t C, int64_t D, int64_t H, int64_t W, int B, in
 
 uint64_t gcd_u64(uint64_t a, uint64_t b) { while (b) { uint64_t t = a % b; a = b; b = t; } return a; }
 
+// A launch may have at most 2^32 - 1 threads along x
+bool launch_ok(uint64_t workgroups, uint64_t threads) { return workgroups * threads < (1ull << 32); }
+
 // fdiv(n, d) is exact while n*d < 2^32
 bool fastdiv_ok(uint64_t n_max, uint64_t d) { return n_max * d < (1ull << 32); }
 
@@ -277,6 +280,8 @@ bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es
     if (L.HW * 10 < 6ull * 16 * best_K * best_nt) return false;
     const size_t need = 8 * rows * CW + 64 + 8 * (best_nt / 64) + 4 * L.nb + 4 * L.WPP;
     const uint64_t top = rows + (uint64_t)best_K * best_nt;
+    // a workgroup per plane: maps of about 165 GB and more stay with compress_units, whose workgroups walk over the planes
+    if (!launch_ok(L.P, best_nt)) return false;
     if (need > (48u << 10) || !fastdiv_ok(top, irows) || !fastdiv_ok(kSegThreads, CW) || !fastdiv_ok(L.nb + best_nt, L.LW) || !fastdiv_ok(L.nb + best_nt, L.LH * L.LW)) return false;
     a->P = (uint32_t)L.P; a->D = (uint32_t)D; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
@@ -629,20 +634,26 @@ bool plan_line(const Layout& L, int64_t D, int64_t H, int B, size_t es, const vo
     while ((1ull << upb_log) < upb) ++upb_log;
     // lanes per plane: a power of two that holds a block, or half of one that goes through LDS, at least 8 (a
     // plane's lanes then read 128 contiguous bytes per round)
-    uint32_t best_S = 0, best_log = 0, K = 0, min_log = upb_log > 3 ? upb_log - 1 : 3;
-    if (min_log < 3) min_log = 3;
-    if (!pick_lanes_and_rounds(qv, min_log, &best_S, &best_log, &K)) return false;
-    // planes of at most three rounds: twelve rounds of several plane groups per wavefront
-    const uint32_t R = (uint32_t)((qv + best_S - 1) / best_S);
-    a->NG = K == 3 ? 12u / R : 1u;
-    a->K = K == 3 ? 12u : K;
+    const uint32_t whole_log = upb_log > 3 ? upb_log : 3;
+    uint32_t min_log = upb_log > 3 ? upb_log - 1 : 3;
+    for (;; min_log = whole_log) {
+        uint32_t best_S = 0, best_log = 0, K = 0;
+        if (!pick_lanes_and_rounds(qv, min_log, &best_S, &best_log, &K)) return false;
+        // planes of at most three rounds: twelve rounds of several plane groups per wavefront
+        const uint32_t R = (uint32_t)((qv + best_S - 1) / best_S);
+        a->NG = K == 3 ? 12u / R : 1u;
+        a->K = K == 3 ? 12u : K;
+        a->S = best_S; a->S_log2 = best_log;
+        a->ppw = 64u / best_S;
+        const uint64_t g = (L.P + (uint64_t)a->ppw * a->NG - 1) / ((uint64_t)a->ppw * a->NG);
+        *grid = (uint32_t)g;
+        // lanes for half a block may mean more and smaller wavefronts, too many for one launch of a map beyond 200 GB
+        if (launch_ok(g, 64) || min_log == whole_log) break;
+    }
     a->P = (uint32_t)L.P; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP;
     a->qv = (uint32_t)qv;
-    a->S = best_S; a->S_log2 = best_log;
-    a->ppw = 64u / best_S;
     a->upb = (uint32_t)upb; a->upb_log2 = upb_log;
     a->nb = (uint32_t)L.nb;
-    *grid = (uint32_t)((L.P + (uint64_t)a->ppw * a->NG - 1) / ((uint64_t)a->ppw * a->NG));
     *lds = 0;
     const int lu = line_lu(*a);
     if (lu < 0) {
@@ -866,8 +877,9 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
             const uint64_t pe = es == 2 && W % 8 == 0 && B % 8 == 0 ? 8 : 4;
             const uint64_t chunk = 64ull * kStreamK * (16 / es / pe);      // pieces
             const uint64_t q = L.HW / pe, npiece = L.P * q;
+            // (2-byte maps of 256 GB and more: the staged kernel, whose workgroups rebuild 32 KB each)
             if (fastdiv_ok(q + chunk, q) && fastdiv_ok(q, (uint64_t)W / pe) && (npiece + chunk - 1) / chunk < (1ull << 31) &&
-                npiece < (1ull << 40)) {
+                npiece < (1ull << 40) && (es == 4 || launch_ok((npiece + chunk - 1) / chunk, 64))) {
                 a->whole8 = pe == 8;
                 a->q4 = (uint32_t)q;
                 a->w4 = (uint32_t)((uint64_t)W / pe);

@@ -294,3 +294,21 @@ def test_kernel_choice_for_3d_maps_and_2_byte_elements():
     assert pkg.division_kernel_name_3d(1, (2, 4, 4, 28, 28), 8, 2, torch.bfloat16) == "decompress_stream_3d<bf16_t, 2>"
     assert pkg.division_kernel_name(1, (8, 8, 55, 55), 8, 2, torch.bfloat16) == "decompress_units<bf16_t, 2, 2>"
     assert pkg.division_kernel_name(0, (8, 8, 56, 56), 8, 2, torch.float32, c16=True) == "compress_regs<f32c16_t, 2, 8, 1>"
+
+
+def test_maps_beyond_one_launch_keep_a_kernel_that_takes_them():
+    """A launch has fewer than 2^32 threads; maps of hundreds of GB fit the card.  Kernels of many small workgroups
+    leave them to those whose workgroups take more planes."""
+    import torch
+    kn = pkg.division_kernel_name
+    # a workgroup of 64 lanes per 29 x 29 plane: 2^26 planes are 2^32 threads (226 GB)
+    assert kn(0, (2 ** 13, 2 ** 13 - 1, 29, 29), 8, 2) == "compress_seg<float, 2, 8, true, 1>"
+    assert kn(0, (2 ** 13, 2 ** 13, 29, 29), 8, 2) == "compress_units<float, 2, 1>"
+    assert kn(0, (2 ** 12, 2 ** 13, 73, 73), 8, 2) == "compress_units<float, 2, 4>"
+    # eight planes of 100 floats per wavefront with lanes for half a block of 64: 2^29 planes (215 GB)
+    assert kn(0, (2 ** 14, 2 ** 15 - 1, 1, 100), 64, 2) == "compress_line<float, 2, 4, 1, -2>"
+    assert kn(0, (2 ** 14, 2 ** 15, 1, 100), 64, 2) == "compress_line<float, 2, 12, 6, -1>"
+    # 4 KB of a 2-byte map per wavefront: 2^37 elements (256 GB)
+    assert kn(1, (2 ** 13, 2 ** 12, 1, 4096), 64, 1, torch.bfloat16) == "decompress_rowvec<bf16_t, 1>"
+    assert kn(1, (2 ** 13, 2 ** 12 - 1, 1, 4096), 64, 1, torch.bfloat16) == "decompress_stream<bf16_t, 1>"
+    assert kn(1, (2 ** 13, 2 ** 12, 64, 64), 8, 2, torch.bfloat16) == "decompress_rowvec<bf16_t, 2>"
