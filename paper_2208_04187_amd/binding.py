@@ -113,7 +113,14 @@ def _stream(stream) -> int:
 # Size of a packed buffer: a function of whole numbers alone, asked for on every call of a training step with the same
 # few shapes (1.3 us through the C entry, 0.15 us from the table).
 @functools.lru_cache(maxsize=4096)
+def _packed_bytes_of_ints(N, C, D, H, W, B, b, dt):
+    return int(lib().division_packed_bytes_3d(N, C, D, H, W, B, b, dt))
+
+
 def _packed_bytes(N, C, D, H, W, B, b, dt):
+    # other objects that the C entry takes (0-d arrays and tensors) may change or have no hash, and 8.0 == 8 is refused there
+    if type(B) is int and type(b) is int:
+        return _packed_bytes_of_ints(N, C, D, H, W, B, b, dt)
     return int(lib().division_packed_bytes_3d(N, C, D, H, W, B, b, dt))
 
 

@@ -312,3 +312,22 @@ def test_maps_beyond_one_launch_keep_a_kernel_that_takes_them():
     assert kn(1, (2 ** 13, 2 ** 12, 1, 4096), 64, 1, torch.bfloat16) == "decompress_rowvec<bf16_t, 1>"
     assert kn(1, (2 ** 13, 2 ** 12 - 1, 1, 4096), 64, 1, torch.bfloat16) == "decompress_stream<bf16_t, 1>"
     assert kn(1, (2 ** 13, 2 ** 12, 64, 64), 8, 2, torch.bfloat16) == "decompress_rowvec<bf16_t, 2>"
+
+
+def test_packed_size_of_arguments_that_are_not_plain_ints():
+    """What compress asks for its packed buffer: the answer of the C entry for every kind of argument, also when the
+    table of sizes holds one for an equal key."""
+    import numpy as np
+    import torch
+    from paper_2208_04187_amd.binding import _packed_bytes
+    want = pkg.division_packed_bytes(2, 3, 16, 16, 8, 2)
+    assert _packed_bytes(2, 3, 1, 16, 16, 8, 2, 0) == want
+    for B in (np.int64(8), np.array(8), torch.tensor(8)):
+        assert _packed_bytes(2, 3, 1, 16, 16, B, 2, 0) == want
+    for B in (8.0, np.float32(8), "8"):
+        with pytest.raises(ctypes.ArgumentError):
+            _packed_bytes(2, 3, 1, 16, 16, B, 2, 0)
+    t = torch.tensor(8)
+    assert _packed_bytes(2, 3, 1, 16, 16, t, 2, 0) == want
+    t.fill_(4)
+    assert _packed_bytes(2, 3, 1, 16, 16, t, 2, 0) == pkg.division_packed_bytes(2, 3, 16, 16, 4, 2) != want
