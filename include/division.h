@@ -339,6 +339,14 @@ int division_kernel_name_3d(int direction, const void *data, int64_t N, int64_t 
  */
 float division_block_mean_rule(double block_sum, uint32_t count, int *divided);
 
+/*
+ * The same with the reciprocal the caller names (the kernels' are up to 4 ulp off 1 / count), and the
+ * kernels' two Newton steps towards 1 / count from an estimate of it (theirs is the hardware's).
+ * count == 0 returns 0.
+ */
+float division_block_mean_rule_rcp(double block_sum, uint32_t count, double reciprocal, int *divided);
+double division_count_reciprocal(uint32_t count, double estimate);
+
 /* Version of this ABI (host-only). */
 int division_abi_version(void);
 

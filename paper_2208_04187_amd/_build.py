@@ -18,6 +18,8 @@ DIVISION = PKG / "csrc" / "division.hip"
 MASKS = PKG / "csrc" / "masks.hip"
 SRCS = [DIVISION, MASKS]
 LIB = PKG / "libdivision.so"
+CHECKS = PKG.parent / "tests" / "device_checks.hip"          # device helpers on their own, for the tests
+CHECKS_LIB = CHECKS.with_name("libdevice_checks.so")
 # (object name, source, extra flags)
 UNITS = [
     ("division_f32.o", DIVISION, ["-DDIVISION_PART=0"]),
@@ -69,3 +71,15 @@ def build(verbose: bool = False, extra_flags=(), out: Path | None = None) -> Pat
     finally:
         shutil.rmtree(objdir, ignore_errors=True)
     return lib_path
+
+
+def build_checks() -> Path:
+    """The tests' library of device helpers (device_checks.hip)."""
+    tmp = CHECKS_LIB.with_name(CHECKS_LIB.name + ".tmp%d" % os.getpid())
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, "-shared", "-o", str(tmp), str(CHECKS)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        tmp.unlink(missing_ok=True)
+        raise RuntimeError("hipcc failed on %s:\n%s" % (CHECKS.name, res.stderr))
+    os.replace(tmp, CHECKS_LIB)
+    return CHECKS_LIB

@@ -161,8 +161,7 @@ __device__ __forceinline__ void compress_strip_body(const StripArgs& a) {
         for (int s = 0; s < NSEG; ++s) {
             const double Sb = group_sum<LBR>(valid ? Sm[s] : 0.0);
             const uint32_t cols = (uint32_t)(W - B * s < B ? W - B * s : B);     // a constant once the loop is unrolled
-            // the reciprocal of the count as a product: at most 4 ulp off, exact for powers of two
-            lfc[s] = lfc_round<T>(mean_with_rcp(Sb, max(rows, 1u) * cols, rcp_rows * (1.0 / (double)cols)), kC16<T>);
+            lfc[s] = lfc_round<T>(mean_with_rcp(Sb, max(rows, 1u) * cols, count_rcp_times(rcp_rows, cols)), kC16<T>);
         }
         if (valid && sl % LBR == 0) {
 #pragma unroll

@@ -124,6 +124,7 @@ constexpr int kLoadReuse = 0;
 #endif
 
 #include "helpers.h"
+#include "block_mean.h"
 #include "compress_tile.h"
 #include "compress_wave.h"
 #include "compress_items.h"
@@ -373,11 +374,17 @@ int division_kernel_name(int direction, const void* data, int64_t N, int64_t C, 
 }
 
 float division_block_mean_rule(double block_sum, uint32_t count, int* divided) {
+    return division_block_mean_rule_rcp(block_sum, count, 1.0 / (double)count, divided);
+}
+
+float division_block_mean_rule_rcp(double block_sum, uint32_t count, double reciprocal, int* divided) {
     int d = 0;
-    const float m = count ? mean_of_host(block_sum, count, &d) : 0.0f;
+    const float m = count ? mean_of_host(block_sum, count, reciprocal, &d) : 0.0f;
     if (divided) *divided = d;
     return m;
 }
+
+double division_count_reciprocal(uint32_t count, double estimate) { return count ? count_rcp_from(count, estimate) : 0.0; }
 
 int division_kernel_name_3d(int direction, const void* data, int64_t N, int64_t C, int64_t D, int64_t H, int64_t W,
                             division_dtype dt, int B, int b, char* out, size_t cap) {

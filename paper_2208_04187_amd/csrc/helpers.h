@@ -14,7 +14,7 @@ __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_
 
 // Two fp32 -> bf16 in one word (a in the low half), round to nearest even, a NaN kept quiet: one gfx950 conversion
 // instruction.  It gives the bits of the integer rule (u + 0x7fff + bit 16) >> 16 (NaN: u >> 16 | 0x40) for every one of
-// the 2^32 inputs (compared exhaustively on the device); the integer rule is seven instructions and a branch per value.
+// the 2^32 inputs (tests/test_gpu_device_helpers.py compares them all); the integer rule is seven instructions and a branch per value.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bf16_pack2(float a, float b) {
