@@ -105,8 +105,8 @@ __device__ __forceinline__ void dec_lds(const DecArgs& a, uint32_t*& s_codes, fl
 }
 
 // W % 4 == 0 and B % 4 == 0: the four elements of a vector lie in one row and
-// share one LFC value.  A workgroup streams G whole planes.  Only what decompress_stream leaves comes here: planes
-// beyond its 32-bit index tricks and 2-byte maps that do not start on a 16-byte boundary.
+// share one LFC value.  A workgroup streams G whole planes.  Only 2-byte maps that decompress_stream leaves come here:
+// those that do not start on a 16-byte boundary, and those of 256 GB and more.
 template <typename T, int BITS, int ND>
 __device__ __forceinline__ void decompress_rowvec_body(const DecArgs& a) {
     const DecPtrs pt = dec_ptrs(a.tab, a.rg);
@@ -383,12 +383,12 @@ __device__ __forceinline__ void decompress_stream_any_body(const DecArgs& a) {
     }
 }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_any(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_any_body<T, BITS, 2>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_any(DecArgs a) { decompress_stream_any_body<T, BITS, 2>(a); }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_any_3d(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_any_body<T, BITS, 3>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_any_3d(DecArgs a) { decompress_stream_any_body<T, BITS, 3>(a); }
 // planes that are one block (any number of map dimensions): no rows or columns, H^L is the plane's
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { if constexpr (sizeof(T) == 4) decompress_stream_any_body<T, BITS, 0>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { decompress_stream_any_body<T, BITS, 0>(a); }
 
 // H*W a multiple of 4 and at most 255 blocks per plane: the LFC index of every
 // element of a plane is looked up in a table (one byte per element, four per

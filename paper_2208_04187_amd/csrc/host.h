@@ -832,7 +832,7 @@ uint64_t dec_planes(const Layout& L, size_t es, uint64_t mult) {
     return G;
 }
 
-// Fills the decompress launch plan; returns 7 (row vectors, a wavefront per chunk), 0 (row vectors), 3 (block table),
+// Fills the decompress launch plan; returns 7 (row vectors, a wavefront per chunk), 0 (row vectors of 2-byte elements, staged), 3 (block table),
 // 8 (4-byte elements of any width, a wavefront per chunk), 6 (four consecutive elements
 // per lane step, any width), 5 (word by word through LDS), 1 (flat), 4 (lane per plane) or 2 (scalar).
 // Hs = rows of one depth slice, D = depth slices (1 for a 2-D map; the table kernel takes 2-D maps only).
@@ -889,16 +889,20 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
                 return 7;
             }
         }
-        a->q4 = (uint32_t)(L.HW / 4);
-        a->w4 = (uint32_t)(W / 4);
-        uint64_t G = dec_planes(L, es, 1);
-        while (G > 1 && !fastdiv_ok(G * a->q4 + kThreads, a->q4)) --G;
-        if (fastdiv_ok(G * a->q4 + kThreads, a->q4) && fastdiv_ok(a->q4, a->w4) && dec_lds_bytes(L, es, G) <= kDecLdsMax) {
-            a->G = (uint32_t)G;
-            a->d_q4 = make_fastdiv(a->q4);
-            a->d_w4 = make_fastdiv(a->w4);
-            *grid = (uint32_t)((L.P + G - 1) / G);
-            return 0;
+        // 2-byte maps that do not start on a 16-byte boundary, or are too large for one launch of the above (4-byte maps meet
+        // neither: what the staged kernel's index tricks allow, the above's do)
+        if (es == 2) {
+            a->q4 = (uint32_t)(L.HW / 4);
+            a->w4 = (uint32_t)(W / 4);
+            uint64_t G = dec_planes(L, es, 1);
+            while (G > 1 && !fastdiv_ok(G * a->q4 + kThreads, a->q4)) --G;
+            if (fastdiv_ok(G * a->q4 + kThreads, a->q4) && fastdiv_ok(a->q4, a->w4) && dec_lds_bytes(L, es, G) <= kDecLdsMax) {
+                a->G = (uint32_t)G;
+                a->d_q4 = make_fastdiv(a->q4);
+                a->d_w4 = make_fastdiv(a->w4);
+                *grid = (uint32_t)((L.P + G - 1) / G);
+                return 0;
+            }
         }
     }
     // planes of whole vectors with few blocks: LFC indices from a table in LDS
@@ -1099,9 +1103,11 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
         const int kind = c.kind;
         void (*kern)(DecArgs);
         if (kind == 7 || kind == 8 || kind == 9) {
-            if (kind == 7) kern = c.flat ? decompress_stream<T, BITS> : decompress_stream_3d<T, BITS>;
-            else if (kind == 9) kern = decompress_stream_one<T, BITS>;
-            else kern = c.flat ? decompress_stream_any<T, BITS> : decompress_stream_any_3d<T, BITS>;
+            kern = c.flat ? decompress_stream<T, BITS> : decompress_stream_3d<T, BITS>;
+            if constexpr (sizeof(T) == 4) {                  // (the planner gives 2-byte maps kind 7 only)
+                if (kind == 9) kern = decompress_stream_one<T, BITS>;
+                else if (kind == 8) kern = c.flat ? decompress_stream_any<T, BITS> : decompress_stream_any_3d<T, BITS>;
+            }
             hipLaunchKernelGGL(kern, dim3(c.gx, c.gy), dim3(64), 0, c.st, c.a);
             return hipGetLastError();
         }
@@ -1113,13 +1119,16 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
             return hipGetLastError();
         }
         if (c.flat)
-            kern = kind == 0 ? decompress_rowvec<T, BITS> : kind == 3 ? decompress_table<T, BITS>
+            kern = kind == 3 ? decompress_table<T, BITS>
                  : kind == 5 ? decompress_words<T, BITS> : kind == 1 ? decompress_flat<T, BITS>
                  : kind == 4 ? decompress_lane<T, BITS> : decompress_scalar<T, BITS>;
         else
-            kern = kind == 0 ? decompress_rowvec_3d<T, BITS> : kind == 5 ? decompress_words_3d<T, BITS>
+            kern = kind == 5 ? decompress_words_3d<T, BITS>
                  : kind == 1 ? decompress_flat_3d<T, BITS>
                  : kind == 4 ? decompress_lane<T, BITS> : decompress_scalar_3d<T, BITS>;
+        if constexpr (sizeof(T) == 2) {                      // (and kind 0 to no others)
+            if (kind == 0) kern = c.flat ? decompress_rowvec<T, BITS> : decompress_rowvec_3d<T, BITS>;
+        }
         const hipError_t e = allow_large_lds(kern, c.lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, dim3(c.gx, c.gy), dim3(kind == 4 ? 64 : kThreads), c.lds, c.st, c.a);
