@@ -116,7 +116,7 @@ __global__ void __launch_bounds__(kSegThreads) compress_seg(SegArgs a) {
         // the plane's last item row: rows past the map count for nothing in the sum and are NaN after it.  With one item
         // per lane they are made zeros here and NaN later (62 registers, eight wavefronts per SIMD: 64 x 512 x 29 x 29 in
         // 35 us against 38); with two items a second copy of the sum is the faster form, off the
-        // main path as the hint says: 76 registers, two workgroups of eleven wavefronts per CU; without the hint 102
+        // main path as the hint says: 72 to 74 registers, two workgroups of eleven wavefronts per CU; without the hint 102
         // registers and one workgroup (64 x 64 x 147 x 147: 102 us against 133).
         double s = 0.0;
         partial[k] = __any(nr[k] != R && nr[k] != 0);
