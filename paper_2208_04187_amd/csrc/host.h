@@ -40,12 +40,6 @@ int make_layout(int64_t N, int64_t C, int64_t D, int64_t H, int64_t W, int B, in
 
 uint64_t gcd_u64(uint64_t a, uint64_t b) { while (b) { uint64_t t = a % b; a = b; b = t; } return a; }
 
-// A launch may have at most 2^32 - 1 threads along x
-bool launch_ok(uint64_t workgroups, uint64_t threads) { return workgroups * threads < (1ull << 32); }
-
-// fdiv(n, d) is exact while n*d < 2^32
-bool fastdiv_ok(uint64_t n_max, uint64_t d) { return n_max * d < (1ull << 32); }
-
 Regions make_regions(const Layout& L) {
     Regions rg;
     rg.meta_off = L.meta_off;

@@ -15,6 +15,7 @@
 #include "../../include/division.h"
 
 namespace {
+#include "fastdiv.h"
 
 constexpr int kThreads = 256;
 constexpr int kVecPerThread = 4;                  // 16-byte vectors a thread handles, kThreads apart
@@ -238,9 +239,27 @@ struct PoolArgs {
     void* out;             // y or grad_in
     uint32_t* mask;
     uint32_t P, H, W, HW, OH, OW, k;
-    uint32_t band;         // output rows a workgroup handles
-    uint32_t bands;        // bands per plane
+    uint32_t band;         // maxpool2_forward_fast: output rows a workgroup handles
+    uint32_t chunk;        // maxpool_forward_kernel: elements a workgroup handles (a multiple of 32)
+    uint32_t quick;        // every quotient below is exact with the multiplier (fastdiv_ok)
+    uint64_t n;            // elements of the map
+    uint64_t rows;         // maxpool2_forward_fast: output rows of all planes
+    double r_HW, r_wv;     // 1 / HW, 1 / pieces of a row
+    FastDiv d_HW, d_W, d_OH, d_OW, d_k, d_wv;
 };
+
+// quotient by the multiplier where the host found it exact for all numerators of this launch, else by the division
+__device__ __forceinline__ uint32_t quot(uint32_t n, uint32_t d, FastDiv f, uint32_t quick) { return quick ? fdiv(n, f) : n / d; }
+
+// n / d for n below 2^41 (one per workgroup): the quotient by rcp = 1.0 / d is at most one off
+__device__ __forceinline__ uint64_t quot64(uint64_t n, uint32_t d, double rcp, uint32_t* rest) {
+    uint64_t q = (uint64_t)((double)n * rcp);
+    int64_t r = (int64_t)(n - q * d);
+    if (r < 0) { --q; r += d; }
+    if (r >= (int64_t)d) { ++q; r -= d; }
+    *rest = __builtin_amdgcn_readfirstlane((uint32_t)r);
+    return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(q >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)q);
+}
 
 __global__ void __launch_bounds__(kThreads) zero_words(uint32_t* p, uint64_t n) {
     for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kThreads) p[i] = 0u;
@@ -250,112 +269,128 @@ template <typename T> __device__ __forceinline__ float as_float(T v);
 template <> __device__ __forceinline__ float as_float<float>(float v) { return v; }
 template <> __device__ __forceinline__ float as_float<uint16_t>(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
-// Forward: a workgroup takes a band of output rows of one plane.  Every thread scans whole
-// windows (first maximum in row-major order wins), writes the maxima and sets the location bits
-// in an LDS image of the band's slice of the mask; the slice then leaves as whole words, the two
-// words it may share with neighbouring slices by atomic OR (the mask is cleared beforehand).
-template <typename T, bool K2>
+// Forward, any size: a workgroup takes `chunk` consecutive elements of the map wherever rows and planes end, i.e. whole
+// mask words, and works on every window that has elements among them: the location bits (first maximum in row-major
+// order wins) are set in an LDS image of those words, which then leave with plain stores, and the maxima of the windows
+// that begin in the chunk are written.  The windows on a chunk's border are worked on by both neighbours, a few per cent
+// of the work; in exchange no word is shared, the mask needs no clearing, and small planes fill a workgroup like large
+// ones.  A workgroup per band of one plane, a cleared mask and atomics on the shared words took 98 us on
+// 22 x 2914 x 14 x 14 (k = 3, bfloat16), 39 us on 74 x 292 x 33 x 33 (k = 2, bfloat16) and 30 us on 8 x 64 x 224 x 224 (k = 3), this 9,
+// 15 and 19.5 (5.9 TB/s).
+// What bounds it: the load instructions (one per window row for pairs, one per element otherwise).
+// K: the window's extent where it is known (2, 3), else 0.  PAIR: k = 2, rows of whole aligned element pairs.
+template <typename T, int K, bool PAIR>
 __global__ void __launch_bounds__(kThreads) maxpool_forward_kernel(PoolArgs a) {
     extern __shared__ uint32_t words[];
     const uint32_t tid = threadIdx.x;
-    const uint32_t p = blockIdx.x / a.bands;
-    const uint32_t oi0 = (blockIdx.x - p * a.bands) * a.band;
-    const uint32_t oi1 = min(a.OH, oi0 + a.band);
-    const uint64_t start = (uint64_t)p * a.HW + (uint64_t)oi0 * a.k * a.W;      // first bit of the slice
-    const uint64_t end = (uint64_t)p * a.HW + (uint64_t)oi1 * a.k * a.W;        // one past its last bit
-    const uint64_t w0 = start >> 5;
-    const uint32_t nwords = (uint32_t)(((end - 1) >> 5) - w0) + 1u;
+    const uint32_t k = K ? (uint32_t)K : a.k;
+    const uint64_t e0 = (uint64_t)blockIdx.x * a.chunk;                       // first element, at a word boundary
+    const uint32_t len = (uint32_t)min((uint64_t)a.chunk, a.n - e0);
+    const uint32_t nwords = (len + 31u) >> 5;
     for (uint32_t w = tid; w < nwords; w += kThreads) words[w] = 0u;
+    // window rows with elements in the chunk: from row oi0 of plane p0 (oi0 == OH: row 0 of the next plane) to row
+    // oi1 of plane p1 (rows past a plane's last window belong to none)
+    uint32_t at0, at1;
+    const uint64_t p0 = quot64(e0, a.HW, a.r_HW, &at0), p1 = quot64(e0 + len - 1u, a.HW, a.r_HW, &at1);
+    const uint32_t oi0 = min(at0 / a.W / k, a.OH), oi1 = min(at1 / a.W / k, a.OH - 1u);
+    const uint64_t wr0 = p0 * a.OH + oi0, wr1 = p1 * a.OH + oi1;
+    const uint32_t nwin = wr1 >= wr0 ? (uint32_t)(wr1 - wr0 + 1u) * a.OW : 0u;
+    // base: the first window row's first element; the chunk begins `skip` elements behind it (negative: before it)
+    const uint64_t base = p0 * a.HW + (oi0 < a.OH ? (uint64_t)oi0 * k * a.W : (uint64_t)a.HW);
+    const int32_t skip = (int32_t)((int64_t)e0 - (int64_t)base);
+    const T* xp = static_cast<const T*>(a.in) + base;
+    T* yp = static_cast<T*>(a.out) + wr0 * a.OW;
+    const uint32_t of0 = oi0 < a.OH ? oi0 : 0u;                              // row inside its plane of the first window row
+    const uint32_t kW = k * a.W, gap = a.HW - a.OH * kW;                     // elements of a plane below its last window
     __syncthreads();
-
-    const T* xp = static_cast<const T*>(a.in) + (size_t)p * a.HW;
-    T* yp = static_cast<T*>(a.out) + (size_t)p * a.OH * a.OW;
-    const uint32_t nout = (oi1 - oi0) * a.OW;
-    for (uint32_t o = tid; o < nout; o += kThreads) {
-        const uint32_t r = o / a.OW;
+    for (uint32_t o = tid; o < nwin; o += kThreads) {
+        const uint32_t r = quot(o, a.OW, a.d_OW, a.quick);
         const uint32_t oj = o - r * a.OW;
-        const uint32_t oi = oi0 + r;
-        const uint32_t base = oi * a.k * a.W + oj * a.k;
-        uint32_t best = base;
+        const uint32_t g = quot(of0 + r, a.OH, a.d_OH, a.quick);             // planes behind the first
+        const uint32_t first = r * kW + g * gap + oj * k;                    // the window's first element, from base on
+        const T* xw = xp + first;
+        uint32_t best = 0;                                                   // place of the maximum, from `first` on
         T bt;
-        if (K2) {
-            // 2 x 2 window, rows of two adjacent elements each in one load (W even, x aligned to two elements)
+        if constexpr (PAIR) {
+            // rows of two adjacent elements each in one load
             struct alignas(2 * sizeof(T)) Pair { T a, b; };
-            const Pair r0 = *reinterpret_cast<const Pair*>(xp + base);
-            const Pair r1 = *reinterpret_cast<const Pair*>(xp + base + a.W);
+            const Pair r0 = *reinterpret_cast<const Pair*>(xw);
+            const Pair r1 = *reinterpret_cast<const Pair*>(xw + a.W);
             bt = r0.a;
-            float bv = as_float<T>(bt);
-            if (as_float<T>(r0.b) > bv) { bv = as_float<T>(r0.b); bt = r0.b; best = base + 1; }
-            if (as_float<T>(r1.a) > bv) { bv = as_float<T>(r1.a); bt = r1.a; best = base + a.W; }
-            if (as_float<T>(r1.b) > bv) { bv = as_float<T>(r1.b); bt = r1.b; best = base + a.W + 1; }
+            if (as_float<T>(r0.b) > as_float<T>(bt)) { bt = r0.b; best = 1; }
+            if (as_float<T>(r1.a) > as_float<T>(bt)) { bt = r1.a; best = a.W; }
+            if (as_float<T>(r1.b) > as_float<T>(bt)) { bt = r1.b; best = a.W + 1; }
+        } else if constexpr (K > 0) {
+            T t[K * K];
+#pragma unroll
+            for (int i = 0; i < K * K; ++i) t[i] = xw[(uint32_t)(i / K) * a.W + (uint32_t)(i % K)];
+            bt = t[0];
+#pragma unroll
+            for (int i = 1; i < K * K; ++i)
+                if (as_float<T>(t[i]) > as_float<T>(bt)) { bt = t[i]; best = (uint32_t)(i / K) * a.W + (uint32_t)(i % K); }
         } else {
-            bt = xp[base];
-            float bv = as_float<T>(bt);
-            for (uint32_t wr = 0; wr < a.k; ++wr)
-                for (uint32_t wc = 0; wc < a.k; ++wc) {
-                    const uint32_t idx = base + wr * a.W + wc;
-                    const T t = xp[idx];
-                    const float v = as_float<T>(t);
-                    if (v > bv) { bv = v; bt = t; best = idx; }
+            bt = xw[0];
+            for (uint32_t wr = 0; wr < k; ++wr)
+                for (uint32_t wc = 0; wc < k; ++wc) {
+                    const T t = xw[wr * a.W + wc];
+                    if (as_float<T>(t) > as_float<T>(bt)) { bt = t; best = wr * a.W + wc; }
                 }
         }
-        yp[oi * a.OW + oj] = bt;
-        const uint32_t bit = (uint32_t)((uint64_t)p * a.HW + best - (w0 << 5));
-        atomicOr(&words[bit >> 5], 1u << (bit & 31u));
+        const uint32_t at = first - (uint32_t)skip;                          // from the chunk's start on; others wrap past len
+        if (at < len) yp[o] = bt;
+        const uint32_t bit = at + best;
+        if (bit < len) atomicOr(&words[bit >> 5], 1u << (bit & 31u));
     }
     __syncthreads();
-    for (uint32_t w = tid; w < nwords; w += kThreads) {
-        const uint32_t v = words[w];
-        if (w == 0 || w == nwords - 1) { if (v) atomicOr(&a.mask[w0 + w], v); }
-        else a.mask[w0 + w] = v;
-    }
+    uint32_t* mp = a.mask + (e0 >> 5);
+    for (uint32_t w = tid; w < nwords; w += kThreads) mp[w] = words[w];
 }
 
-// Forward, k = 2 on rows of whole 8-element pieces (W % 8 == 0, H * W a multiple of 32, 16-byte aligned
+// Forward, k = 2 on rows of whole 8-element pieces (W % 8 == 0, an even number of rows, 16-byte aligned
 // x): a thread takes four adjacent windows, i.e. eight consecutive elements of two rows (two 16-byte loads
 // per row for 4-byte elements, one for 2-byte ones), writes their four maxima with one store and the eight
 // location bits of each row as one byte of the LDS image of the band's mask slice: bytes have one owner, so
-// there is no atomic, and a band of an even number of output rows is whole mask words, so the slice leaves
-// with plain stores and the mask needs no clearing beforehand.  The last band of a plane also writes the
-// (zero) bits of an odd last row.
-template <typename T>
+// there is no atomic.  With an even number of rows per plane the output rows of all planes are one run, so a
+// band of them is whole mask words wherever planes end, and small planes share a workgroup (a band used to end
+// with its plane: 12 x 22855 x 8 x 8 163 -> 14 us); the slice leaves with plain stores and the mask needs no clearing.
+// NT: non-temporal loads, for rows of at least a cache line (a stem's sequence of operators 306 us against 338 without: x does
+// not displace what the neighbours write); shorter rows share lines between loads (8 x 8: 23 us with them, 14 without).
+template <typename T, bool NT>
 __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
     extern __shared__ uint32_t words[];
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    constexpr uint32_t EPV = 16 / sizeof(T);             // elements per 16-byte load
     const uint32_t tid = threadIdx.x;
-    const uint32_t p = blockIdx.x / a.bands;
-    const uint32_t bnd = blockIdx.x - p * a.bands;
-    const uint32_t oi0 = bnd * a.band;
-    const uint32_t oi1 = min(a.OH, oi0 + a.band);
-    const uint32_t r0 = 2u * oi0;
-    const uint32_t r1 = bnd + 1 == a.bands ? a.H : 2u * oi1;                 // input rows [r0, r1) belong to this band
-    const uint64_t w0 = ((uint64_t)p * a.HW + (uint64_t)r0 * a.W) >> 5;      // first word of the slice (whole words)
-    const uint32_t nwords = (r1 - r0) * a.W / 32u;
+    const uint64_t oi0 = (uint64_t)blockIdx.x * a.band;                      // output rows, counted over all planes
+    const uint32_t nrows = (uint32_t)min((uint64_t)a.band, a.rows - oi0);
+    const uint64_t start = 2u * oi0 * a.W;                                   // first element, at a word boundary
+    const uint32_t nwords = (2u * nrows * a.W + 31u) / 32u;
     for (uint32_t w = tid; w < nwords; w += kThreads) words[w] = 0u;
     __syncthreads();
     uint8_t* bytes = reinterpret_cast<uint8_t*>(words);
-    const T* xp = static_cast<const T*>(a.in) + (size_t)p * a.HW;
-    T* yp = static_cast<T*>(a.out) + (size_t)p * a.OH * a.OW;
+    auto load = [](const T* p) -> u32x4 {
+        if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+        else return *reinterpret_cast<const u32x4*>(p);
+    };
+    const T* xp = static_cast<const T*>(a.in) + start;
+    T* yp = static_cast<T*>(a.out) + oi0 * a.OW;
     const uint32_t ow4 = a.OW / 4u;
-    const uint32_t n4 = (oi1 - oi0) * ow4;
+    const uint32_t n4 = nrows * ow4;
     for (uint32_t o4 = tid; o4 < n4; o4 += kThreads) {
-        const uint32_t r = o4 / ow4;
+        const uint32_t r = quot(o4, ow4, a.d_wv, a.quick);
         const uint32_t oj4 = o4 - r * ow4;
-        const uint32_t oi = oi0 + r;
-        const uint32_t base = 2u * oi * a.W + oj4 * 8u;                    // first of the eight elements, upper row
+        const uint32_t base = 2u * r * a.W + oj4 * 8u;                     // first of the eight elements, upper row
         uint32_t e0[8], e1[8];                                              // the two rows as fp32 bit patterns
         if constexpr (sizeof(T) == 4) {
-            const u32x4 a0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xp + base));
-            const u32x4 a1 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xp + base + 4));
-            const u32x4 b0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xp + base + a.W));
-            const u32x4 b1 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xp + base + a.W + 4));
+            const u32x4 a0 = load(xp + base);
+            const u32x4 a1 = load(xp + base + 4);
+            const u32x4 b0 = load(xp + base + a.W);
+            const u32x4 b1 = load(xp + base + a.W + 4);
             e0[0] = a0.x; e0[1] = a0.y; e0[2] = a0.z; e0[3] = a0.w; e0[4] = a1.x; e0[5] = a1.y; e0[6] = a1.z; e0[7] = a1.w;
             e1[0] = b0.x; e1[1] = b0.y; e1[2] = b0.z; e1[3] = b0.w; e1[4] = b1.x; e1[5] = b1.y; e1[6] = b1.z; e1[7] = b1.w;
         } else {
-            const u32x4 a0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xp + base));
-            const u32x4 b0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(xp + base + a.W));
+            const u32x4 a0 = load(xp + base);
+            const u32x4 b0 = load(xp + base + a.W);
             const uint32_t wa[4] = {a0.x, a0.y, a0.z, a0.w}, wb[4] = {b0.x, b0.y, b0.z, b0.w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -363,7 +398,6 @@ __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
                 e1[2 * j] = wb[j] << 16; e1[2 * j + 1] = wb[j] & 0xffff0000u;
             }
         }
-        (void)EPV;
         uint32_t m[4], byte0 = 0, byte1 = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -377,87 +411,151 @@ __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
             byte1 |= (loc >= 2 ? 1u << (loc - 2) : 0u) << (2 * j);
         }
         if constexpr (sizeof(T) == 4) {
-            __builtin_nontemporal_store(u32x4{m[0], m[1], m[2], m[3]}, reinterpret_cast<u32x4*>(yp + oi * a.OW + oj4 * 4u));
+            __builtin_nontemporal_store(u32x4{m[0], m[1], m[2], m[3]}, reinterpret_cast<u32x4*>(yp + (size_t)o4 * 4u));
         } else {
             __builtin_nontemporal_store(u32x2{(m[0] >> 16) | (m[1] & 0xffff0000u), (m[2] >> 16) | (m[3] & 0xffff0000u)},
-                                        reinterpret_cast<u32x2*>(yp + oi * a.OW + oj4 * 4u));
+                                        reinterpret_cast<u32x2*>(yp + (size_t)o4 * 4u));
         }
-        const uint32_t b0i = (2u * r * a.W + oj4 * 8u) >> 3;               // byte of the slice that holds the upper row's eight bits
+        const uint32_t b0i = base >> 3;                                     // byte of the slice that holds the upper row's eight bits
         bytes[b0i] = (uint8_t)byte0;
         bytes[b0i + (a.W >> 3)] = (uint8_t)byte1;
     }
     __syncthreads();
-    for (uint32_t w = tid; w < nwords; w += kThreads) a.mask[w0 + w] = words[w];
+    uint32_t* mp = a.mask + (start >> 5);
+    for (uint32_t w = tid; w < nwords; w += kThreads) mp[w] = words[w];
 }
 
-// Backward: grad_in = V (.) (1_{k x k} (x) grad_out).  VEC = 4: a thread takes four consecutive
-// elements of one row per step (W % 4 == 0, grad_in 16-byte resp. 8-byte aligned): one 16-byte
-// store, one mask word read.  VEC = 1: element by element.
-template <typename T, int VEC>
-__global__ void __launch_bounds__(kThreads) maxpool_backward_kernel(PoolArgs a) {
+// Backward, element by element: grad_in = V (.) (1_{k x k} (x) grad_out).  For maps that do not start on a 16-byte boundary
+// and planes of 2^28 output gradients and more; the others take the two kernels below.
+template <typename T>
+__global__ void __launch_bounds__(kThreads) maxpool_backward_scalar(PoolArgs a) {
     const uint32_t p = blockIdx.y;
     const T* gp = static_cast<const T*>(a.in) + (size_t)p * a.OH * a.OW;
     T* op = static_cast<T*>(a.out) + (size_t)p * a.HW;
     const uint64_t bit0 = (uint64_t)p * a.HW;
-    const uint32_t nv = a.HW / VEC;
-    for (uint32_t vi = blockIdx.x * kThreads + threadIdx.x; vi < nv; vi += gridDim.x * kThreads) {
-        const uint32_t i = vi * VEC;
+    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < a.HW; i += gridDim.x * kThreads) {
         const uint64_t bit = bit0 + i;
-        // HW % 4 == 0 when VEC == 4, so the four bits never straddle a word
-        const uint32_t bits = (a.mask[bit >> 5] >> (uint32_t)(bit & 31u)) & ((1u << VEC) - 1u);
+        const uint32_t set = (a.mask[bit >> 5] >> (uint32_t)(bit & 31u)) & 1u;
         const uint32_t r = i / a.W;
         const uint32_t c = i - r * a.W;
-        const uint32_t oi = r / a.k;
-        const T* grow = gp + oi * a.OW;
-        T v[VEC];
+        const uint32_t oi = r / a.k, oj = c / a.k;
+        op[i] = set && oi < a.OH && oj < a.OW ? gp[oi * a.OW + oj] : (T)0;
+    }
+}
+
+// Backward, any size on a 16-byte boundary: a wavefront rebuilds 4 KB of grad_in, 256 consecutive 16-byte vectors wherever
+// rows and planes end (the write stream of decompress_stream).  A vector's mask bits lie in one word; an element's place is
+// found from its vector's by counting on; the gradients of the elements whose bit is set come through a bounds-checked
+// buffer, the others' loads are out of its range, read as +0 and fetch nothing.  A workgroup per 512 elements of one plane and a
+// branch per element took 60 us on 74 x 292 x 33 x 33
+// (bfloat16) and 30 us on 2 x 716 x 42 x 207, this 22 and 12.5.  What bounds it: vector instructions (the steps from element to element).
+constexpr int kPoolVecs = 4;
+template <typename T>
+__global__ void __launch_bounds__(64) maxpool_backward_kernel(PoolArgs a) {
+    constexpr int EPV = Tr<T>::EPV;
+    constexpr int K = kPoolVecs;
+    constexpr uint32_t kDrop = 0x80000000u;
+    const uint32_t lane = threadIdx.x;
+    const uint64_t e0 = (uint64_t)blockIdx.x * (64u * K * EPV);
+    uint32_t at0;
+    const uint64_t p0 = quot64(e0, a.HW, a.r_HW, &at0);
+    const uint32_t OHW = a.OH * a.OW;
+    const T* gp = static_cast<const T*>(a.in) + p0 * OHW;
+    // gradients of plane p0 and those behind it that the chunk can reach
+    const uint64_t gbytes = min(((uint64_t)a.P - p0) * OHW * sizeof(T), (uint64_t)0x7ffffff0u);
+    const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(gp), 0, (int)gbytes, 0x00020000);
+    const uint64_t left = a.n - e0;
+    const uint64_t nwords = (a.n + 31u) >> 5;
+    uint32_t v[K][EPV];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const uint32_t oj = (c + e) / a.k;
-            v[e] = 0;
-            if (((bits >> e) & 1u) && oi < a.OH && oj < a.OW) v[e] = grow[oj];
+    for (int u = 0; u < K; ++u) {
+        const uint32_t ev = EPV * (64u * u + lane);                          // the vector's first element, from e0 on
+        const uint64_t w = (e0 + ev) >> 5;
+        const uint32_t bits = (w < nwords ? a.mask[w] : 0u) >> ((uint32_t)(e0 + ev) & 31u);
+        const uint32_t t = at0 + ev;
+        // (planes of more elements than a chunk: the vector lies in the first or the second one)
+        uint32_t g = a.HW >= 64u * K * EPV ? (t >= a.HW ? 1u : 0u) : quot(t, a.HW, a.d_HW, a.quick);
+        const uint32_t i = t - g * a.HW;
+        uint32_t r = quot(i, a.W, a.d_W, a.quick);
+        uint32_t c = i - r * a.W;
+        uint32_t oi = quot(r, a.k, a.d_k, a.quick), oj = quot(c, a.k, a.d_k, a.quick);
+        uint32_t cr = c - oj * a.k, rr = r - oi * a.k;                       // place inside the window
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            const bool set = ((bits >> e) & 1u) && oi < a.OH && oj < a.OW;
+            const uint32_t off = set ? (g * OHW + oi * a.OW + oj) * (uint32_t)sizeof(T) : kDrop;
+            if constexpr (sizeof(T) == 4) v[u][e] = __builtin_amdgcn_raw_buffer_load_b32(grs, off, 0, 0);
+            else v[u][e] = __builtin_amdgcn_raw_buffer_load_b16(grs, off, 0, 0);
+            // the next element: one column, and where they end one row, one plane on
+            ++c; ++cr;
+            const bool nw = cr == a.k;
+            oj += nw ? 1u : 0u; cr = nw ? 0u : cr;
+            const bool nr = c == a.W;
+            c = nr ? 0u : c; oj = nr ? 0u : oj; cr = nr ? 0u : cr;
+            r += nr ? 1u : 0u; rr += nr ? 1u : 0u;
+            const bool nv = rr == a.k;
+            oi += nv ? 1u : 0u; rr = nv ? 0u : rr;
+            const bool np = r == a.H;
+            r = np ? 0u : r; oi = np ? 0u : oi; rr = np ? 0u : rr;
+            g += np ? 1u : 0u;
         }
-        if constexpr (VEC == 4) {
-            struct alignas(4 * sizeof(T)) Quad { T q[4]; };
-            Quad o; o.q[0] = v[0]; o.q[1] = v[1]; o.q[2] = v[2]; o.q[3] = v[3];
-            *reinterpret_cast<Quad*>(op + i) = o;
-        } else {
-            op[i] = v[0];
+    }
+    T* out = static_cast<T*>(a.out) + e0;
+    const uint32_t obytes = left < 64u * K * EPV ? ((uint32_t)left * (uint32_t)sizeof(T)) & ~3u : 64u * K * 16u;
+    const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)obytes, 0x00020000);
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        u32x4 o;
+        if constexpr (sizeof(T) == 4) o = u32x4{v[u][0], v[u][1], v[u][2], v[u][3]};
+        else o = u32x4{v[u][0] | (v[u][1] << 16), v[u][2] | (v[u][3] << 16), v[u][EPV - 4] | (v[u][EPV - 3] << 16), v[u][EPV - 2] | (v[u][EPV - 1] << 16)};
+        // stores past the map are dropped by the bound, dword by dword; the whole offset in the vector operand (the
+        // compiler counts the wait states behind a wide store only without a scalar offset register)
+        __builtin_amdgcn_raw_buffer_store_b128(o, ors, (64u * u + lane) * 16u, 0, 2);
+    }
+    // a map of an odd number of 2-byte elements ends in the middle of a dword, which lies behind the bound
+    if constexpr (sizeof(T) == 2) {
+        if ((left & 1u) && left < 64u * K * EPV) {
+#pragma unroll
+            for (int u = 0; u < K; ++u)
+#pragma unroll
+                for (int e = 0; e < EPV; e += 2)
+                    if (EPV * (64u * u + lane) + (uint32_t)e + 1u == (uint32_t)left) out[left - 1u] = (T)v[u][e];
         }
     }
 }
 
-// Backward, k = 2 on rows of whole 4-element pieces (W % 4 == 0, 16-byte aligned grad_in, 8-byte aligned
-// grad_out): a thread rebuilds four consecutive elements of one row, which lie under two adjacent windows:
-// one mask word, one load of the two output gradients, one non-temporal 16-byte store; a workgroup of
-// one... four wavefronts writes 4 KB and ends (what a write stream wants here).
+// Backward, k = 2 on rows of whole 16-byte vectors (grad_in 16-byte, grad_out 8-byte aligned, an even number of rows): a thread
+// rebuilds one vector, which lies under two (4-byte elements) or four (2-byte elements) adjacent windows: one
+// mask word, one 8-byte load of their gradients, one non-temporal 16-byte store; a workgroup of four wavefronts
+// writes 4 KB and ends (what a write stream wants here).  With an even number of rows the rows of all planes are one run,
+// so planes end anywhere in a workgroup (one that ended with its plane: 12 x 22855 x 8 x 8 130 -> 12 us).
 template <typename T>
 __global__ void __launch_bounds__(kThreads) maxpool2_backward_fast(PoolArgs a) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    const uint32_t p = blockIdx.y;
-    const T* gp = static_cast<const T*>(a.in) + (size_t)p * a.OH * a.OW;
-    T* op = static_cast<T*>(a.out) + (size_t)p * a.HW;
-    const uint32_t vi = blockIdx.x * kThreads + threadIdx.x;
-    if (vi >= a.HW / 4u) return;
-    const uint32_t w4 = a.W / 4u;
-    const uint32_t r = vi / w4;
-    const uint32_t c = (vi - r * w4) * 4u;
-    const uint64_t bit = (uint64_t)p * a.HW + (uint64_t)vi * 4u;
-    const uint32_t bits = (a.mask[bit >> 5] >> (uint32_t)(bit & 31u)) & 15u;
-    // a row past the last whole window has no bits set: any row's gradients will do for the address
-    const uint32_t oi = min(r >> 1, a.OH - 1u);
-    const T* g = gp + oi * a.OW + (c >> 1);
-    uint32_t g0, g1;                                   // the two gradients as raw element bits
+    constexpr uint32_t EPV = Tr<T>::EPV;
+    const uint32_t wv = a.W / EPV;                                          // vectors of a row
+    uint32_t at0;
+    const uint64_t row0 = quot64((uint64_t)blockIdx.x * kThreads, wv, a.r_wv, &at0); // row, counted over all planes, of the block's first vector
+    const uint64_t vi = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (vi * EPV >= a.n) return;
+    const uint32_t t = at0 + threadIdx.x;
+    const uint32_t dr = quot(t, wv, a.d_wv, a.quick);
+    const uint32_t c = (t - dr * wv) * (EPV / 2u);                          // first of the vector's windows
+    const uint64_t bit = vi * EPV;
+    const uint32_t bits = a.mask[bit >> 5] >> (uint32_t)(bit & 31u);
+    const T* g = static_cast<const T*>(a.in) + ((row0 + dr) >> 1) * a.OW + c;
+    const u32x2 q = *reinterpret_cast<const u32x2*>(g);
+    u32x4 o;
     if constexpr (sizeof(T) == 4) {
-        const u32x2 v = *reinterpret_cast<const u32x2*>(g);
-        g0 = v.x; g1 = v.y;
+        o = u32x4{bits & 1u ? q.x : 0u, bits & 2u ? q.x : 0u, bits & 4u ? q.y : 0u, bits & 8u ? q.y : 0u};
     } else {
-        const uint32_t v = *reinterpret_cast<const uint32_t*>(g);
-        g0 = v & 0xffffu; g1 = v >> 16;
+        const uint32_t w[4] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16};
+        uint32_t d[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[j] = (bits & (1u << (2 * j)) ? w[j] : 0u) | (bits & (2u << (2 * j)) ? w[j] << 16 : 0u);
+        o = u32x4{d[0], d[1], d[2], d[3]};
     }
-    const uint32_t o0 = bits & 1u ? g0 : 0u, o1 = bits & 2u ? g0 : 0u, o2 = bits & 4u ? g1 : 0u, o3 = bits & 8u ? g1 : 0u;
-    if constexpr (sizeof(T) == 4) __builtin_nontemporal_store(u32x4{o0, o1, o2, o3}, reinterpret_cast<u32x4*>(op + (size_t)vi * 4u));
-    else __builtin_nontemporal_store(u32x2{o0 | (o1 << 16), o2 | (o3 << 16)}, reinterpret_cast<u32x2*>(op + (size_t)vi * 4u));
+    __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(static_cast<T*>(a.out) + bit));
 }
 
 int pool_args(bool forward, const void* in, void* out, const void* mask, int64_t N, int64_t C, int64_t H, int64_t W,
@@ -476,6 +574,8 @@ int pool_args(bool forward, const void* in, void* out, const void* mask, int64_t
     a->in = in; a->out = out; a->mask = static_cast<uint32_t*>(const_cast<void*>(mask));
     a->P = (uint32_t)P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)HW;
     a->OH = (uint32_t)(H / k); a->OW = (uint32_t)(W / k); a->k = (uint32_t)k;
+    a->n = P * HW;
+    a->r_HW = 1.0 / (double)HW;
     return DIVISION_OK;
 }
 
@@ -506,53 +606,54 @@ int division_maxpool_forward(const void* x, int64_t N, int64_t C, int64_t H, int
     const int rc = pool_args(true, x, y, mask, N, C, H, W, dt, k, mask_capacity, &a);
     if (rc != DIVISION_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const size_t esz = dt == DIVISION_BF16 ? 2 : 4;
-    if (k == 2 && a.OH > 0 && a.W % 8 == 0 && a.HW % 32 == 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % (4 * esz)) == 0) {
-        // bands of an even number of output rows (whole mask words), at most 64 Ki bits, enough of them to fill the machine
-#ifndef DIVISION_POOL_WG_BYTES
-#define DIVISION_POOL_WG_BYTES 8192
-#endif
-        // about 8 KB of x per workgroup (short-lived workgroups, many of them), at most 64 Ki mask bits
-        uint32_t band = (uint32_t)(DIVISION_POOL_WG_BYTES / (2ull * a.W * esz)) & ~1u;
+    const size_t es = dt == DIVISION_BF16 ? 2 : 4;
+    // rows of whole 8-element pieces, an even number of them per plane: the output rows of all planes are one run
+    if (k == 2 && a.H % 2 == 0 && a.W % 8 == 0 && a.W <= 16384 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % (4 * es)) == 0) {
+        // about 8 KB of x per workgroup (short-lived workgroups, many of them), an even number of output rows (whole mask
+        // words), at most 64 Ki mask bits
+        uint32_t band = (uint32_t)(8192 / (2ull * a.W * es)) & ~1u;
         if (band < 2) band = 2;
-        if (2ull * band * a.W > 65536) band = (uint32_t)(65536 / (2ull * a.W)) & ~1u;
-        if (band < 2) band = 0;
-        if (band >= 2) {
-            a.band = band;
-            a.bands = (a.OH + band - 1) / band;
-            const uint64_t grid = (uint64_t)a.P * a.bands;
-            // the last band of a plane also holds an odd last row
-            const size_t lds = ((size_t)(band + 1) * 2 * a.W) / 8 + 16;
-            if (grid <= 0x7fffffffull) {
-                void (*kern)(PoolArgs) = dt == DIVISION_F32 ? maxpool2_forward_fast<float> : maxpool2_forward_fast<uint16_t>;
-                hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kThreads), lds, st, a);
-                return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
-            }
+        a.band = band;
+        a.rows = (uint64_t)a.P * a.OH;
+        const uint64_t grid = (a.rows + band - 1) / band;
+        a.d_wv = make_fastdiv(a.OW / 4);
+        a.quick = fastdiv_ok((uint64_t)band * (a.OW / 4), a.OW / 4);
+        if (launch_ok(grid, kThreads)) {
+            // rows shorter than a cache line: several loads touch each line, which then has to stay in the caches
+            const bool nt = a.W * es >= 128;
+            void (*kern)(PoolArgs) = dt == DIVISION_F32 ? (nt ? maxpool2_forward_fast<float, true> : maxpool2_forward_fast<float, false>)
+                                                        : (nt ? maxpool2_forward_fast<uint16_t, true> : maxpool2_forward_fast<uint16_t, false>);
+            hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kThreads), (size_t)band * 2 * a.W / 8 + 16, st, a);
+            return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
         }
     }
-    const uint64_t nwords = ((uint64_t)a.P * a.HW + 31) / 32;
-    const uint32_t zgrid = (uint32_t)((nwords + kThreads * 8ull - 1) / (kThreads * 8ull));
-    hipLaunchKernelGGL(zero_words, dim3(zgrid < 1 ? 1 : zgrid), dim3(kThreads), 0, st, a.mask, nwords);
-    if (hipGetLastError() != hipSuccess) return DIVISION_EHIP;
-    if (a.OH == 0 || a.OW == 0) return DIVISION_OK;          // no whole window: empty output, all-zero mask
-    // a band's slice of the mask lives in LDS: at most 64 Ki bits (+ the two edge words)
+    if (a.OH == 0 || a.OW == 0) {                            // no whole window: empty output, all-zero mask
+        const uint64_t nwords = (a.n + 31) / 32;
+        const uint32_t zgrid = (uint32_t)((nwords + kThreads * 8ull - 1) / (kThreads * 8ull));
+        hipLaunchKernelGGL(zero_words, dim3(zgrid < 1 ? 1 : zgrid), dim3(kThreads), 0, st, a.mask, nwords);
+        return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+    // A chunk has at least four window rows (at most a quarter of the windows are then worked on twice) and 1024
+    // elements (a workgroup's fixed work), at most 64 Ki window-row bits; beyond that the longer the better for the borders' sake, as
+    // long as there are eight workgroups per CU: 8192 elements (1 KB of mask words)
     const uint64_t row_bits = (uint64_t)a.k * a.W;
     if (row_bits > 65536) return DIVISION_ERANGE;
-    uint32_t band = (uint32_t)(65536 / row_bits);
-    if (band > a.OH) band = a.OH;
-    // small planes: fewer rows per band than fit, so that the launch still has enough workgroups
-    while (band > 1 && (uint64_t)a.P * ((a.OH + band - 1) / band) < 2048) band = (band + 1) / 2;
-    a.band = band;
-    a.bands = (a.OH + band - 1) / band;
-    const uint64_t grid = (uint64_t)a.P * a.bands;
-    if (grid > 0x7fffffffull) return DIVISION_ERANGE;
-    const size_t lds = 4 * ((size_t)band * row_bits / 32 + 2);
-    const size_t es = dt == DIVISION_BF16 ? 2 : 4;
-    const bool k2 = k == 2 && a.W % 2 == 0 && ((uintptr_t)x % (2 * es)) == 0;       // a.HW is even then
+    uint64_t chunk = 8192;
+    while (chunk > 1024 && a.n / chunk < 2048) chunk /= 2;
+    while (chunk < 4 * row_bits) chunk *= 2;
+    while (!launch_ok((a.n + chunk - 1) / chunk, kThreads)) chunk *= 2;       // maps of 2^37 elements and more: up to 2^40 in 2^24 workgroups
+    a.chunk = (uint32_t)chunk;
+    const uint64_t wrows = chunk / a.W + 2 + 2 * (chunk / a.HW + 2);          // at least the window rows of a chunk
+    a.d_OW = make_fastdiv(a.OW);
+    a.d_OH = make_fastdiv(a.OH);
+    a.quick = fastdiv_ok(wrows * a.OW + kThreads, a.OW) && fastdiv_ok(a.OH + wrows, a.OH);
+    const bool pair = k == 2 && a.W % 2 == 0 && ((uintptr_t)x % (2 * es)) == 0;
     void (*kern)(PoolArgs);
-    if (dt == DIVISION_F32) kern = k2 ? maxpool_forward_kernel<float, true> : maxpool_forward_kernel<float, false>;
-    else kern = k2 ? maxpool_forward_kernel<uint16_t, true> : maxpool_forward_kernel<uint16_t, false>;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kThreads), lds, st, a);
+    if (dt == DIVISION_F32) kern = pair ? maxpool_forward_kernel<float, 2, true> : k == 2 ? maxpool_forward_kernel<float, 2, false>
+                                 : k == 3 ? maxpool_forward_kernel<float, 3, false> : maxpool_forward_kernel<float, 0, false>;
+    else kern = pair ? maxpool_forward_kernel<uint16_t, 2, true> : k == 2 ? maxpool_forward_kernel<uint16_t, 2, false>
+              : k == 3 ? maxpool_forward_kernel<uint16_t, 3, false> : maxpool_forward_kernel<uint16_t, 0, false>;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)((a.n + chunk - 1) / chunk)), dim3(kThreads), (size_t)chunk / 8, st, a);
     return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
 }
 
@@ -562,25 +663,36 @@ int division_maxpool_backward(const void* mask, size_t mask_bytes, const void* g
     const int rc = pool_args(false, grad_out, grad_in, mask, N, C, H, W, dt, k, mask_bytes, &a);
     if (rc != DIVISION_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const size_t esz = dt == DIVISION_BF16 ? 2 : 4;
-    if (k == 2 && a.OH > 0 && a.OW > 0 && a.W % 4 == 0 && ((uintptr_t)grad_in % (4 * esz)) == 0 && ((uintptr_t)grad_out % (2 * esz)) == 0 &&
-        a.P <= 65535u) {
+    const size_t es = dt == DIVISION_BF16 ? 2 : 4;
+    const uint64_t epv = 16 / es;
+    const bool vec = ((uintptr_t)grad_in % 16) == 0;
+    const uint64_t nvec = (a.n + epv - 1) / epv;
+    if (k == 2 && a.H % 2 == 0 && a.W % epv == 0 && vec && ((uintptr_t)grad_out % 8) == 0 && launch_ok((nvec + kThreads - 1) / kThreads, kThreads)) {
+        a.d_wv = make_fastdiv((uint32_t)(a.W / epv));
+        a.r_wv = 1.0 / (double)(a.W / epv);
+        a.quick = fastdiv_ok(a.W / epv + kThreads, a.W / epv);
         void (*fast)(PoolArgs) = dt == DIVISION_F32 ? maxpool2_backward_fast<float> : maxpool2_backward_fast<uint16_t>;
-        hipLaunchKernelGGL(fast, dim3((a.HW / 4 + kThreads - 1) / kThreads, a.P), dim3(kThreads), 0, st, a);
+        hipLaunchKernelGGL(fast, dim3((uint32_t)((nvec + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, a);
         return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
     }
-    const bool vec4 = a.W % 4 == 0 && ((uintptr_t)grad_in % (4 * esz)) == 0;
-    void (*kern)(PoolArgs);
-    if (dt == DIVISION_F32) kern = vec4 ? maxpool_backward_kernel<float, 4> : maxpool_backward_kernel<float, 1>;
-    else kern = vec4 ? maxpool_backward_kernel<uint16_t, 4> : maxpool_backward_kernel<uint16_t, 1>;
-    const uint32_t per = vec4 ? 4u : 1u;
-    uint32_t gx = (a.HW / per + kThreads * 2u - 1) / (kThreads * 2u);
+    const uint64_t per_wave = 64ull * kPoolVecs, grid = (nvec + per_wave - 1) / per_wave, chunk = per_wave * epv;
+    const uint64_t reach = chunk / a.HW + 2;                                  // planes a chunk can reach
+    if (vec && launch_ok(grid, 64) && reach * a.OH * a.OW * es < (1ull << 31) && (uint64_t)a.HW + chunk < (1ull << 32)) {
+        a.d_HW = make_fastdiv(a.HW);
+        a.d_W = make_fastdiv(a.W);
+        a.d_k = make_fastdiv(a.k);
+        a.quick = (a.HW >= chunk || fastdiv_ok(a.HW + chunk, a.HW)) && fastdiv_ok(a.HW, a.W) && fastdiv_ok(a.H, a.k) && fastdiv_ok(a.W, a.k);
+        void (*kern)(PoolArgs) = dt == DIVISION_F32 ? maxpool_backward_kernel<float> : maxpool_backward_kernel<uint16_t>;
+        hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(64), 0, st, a);
+        return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+    void (*kern)(PoolArgs) = dt == DIVISION_F32 ? maxpool_backward_scalar<float> : maxpool_backward_scalar<uint16_t>;
+    uint32_t gx = (a.HW + kThreads * 2u - 1) / (kThreads * 2u);
     if (gx < 1) gx = 1;
     if (gx > 4096) gx = 4096;
     // grid.y takes a slice of planes per launch; a multiple of 32 planes, so that every slice's
     // first mask bit starts a word
     constexpr uint32_t kSlice = 65504;
-    const size_t es = dt == DIVISION_BF16 ? 2 : 4;
     for (uint32_t p0 = 0; p0 < a.P; p0 += kSlice) {
         PoolArgs b = a;
         const uint32_t np = a.P - p0 < kSlice ? a.P - p0 : kSlice;

@@ -213,3 +213,34 @@ def test_relu_fused_with_compression_on_values_at_the_edges_of_binary32(shape, B
     assert np.array_equal(y.cpu().view(bits[0]).numpy().view(bits[1]), y_ref.reshape(shape).view(bits[1]))
     assert np.array_equal(m.cpu().numpy().view(np.uint32), m_ref)
     assert np.array_equal(pk.cpu().numpy(), p_ref)
+
+
+# the chunked pooling kernels: chunk borders inside planes, rows and windows; planes far below and above a chunk; rows and
+# columns left over; maps that end in the middle of a vector, a word and (bfloat16) a dword; bands over several planes
+@pytest.mark.parametrize("shape,k", [((1, 1, 33, 65), 2), ((3, 5, 33, 33), 2), ((41, 7, 8, 8), 2), ((9, 31, 14, 14), 3), ((2, 3, 47, 101), 3),
+                                     ((700, 3, 2, 2), 2), ((900, 5, 3, 1), 1), ((3, 1, 4, 4100), 2), ((2, 2, 130, 67), 5), ((1, 3, 6, 24), 2),
+                                     ((5, 3, 10, 8), 2), ((1, 1, 1, 9000), 1), ((333, 1, 5, 5), 4), ((2, 1, 9, 4099), 4)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_maxpool_chunks_match_oracle(shape, k, dtype):
+    test_maxpool_matches_oracle(shape, k, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_maxpool_on_unaligned_buffers_matches_oracle(dtype):
+    for shape, k in (((3, 5, 12, 16), 2), ((2, 3, 9, 15), 3)):
+        N, C, H, W = shape
+        g = torch.Generator().manual_seed(7)
+        n, m = N * C * H * W, N * C * (H // k) * (W // k)
+        x, go = torch.randn(n, generator=g).to(dtype), torch.randn(m, generator=g).to(dtype)
+        y_ref, m_ref = oracle.maxpool_forward(_host(x)[0].reshape(shape), k, _host(x)[1])
+        g_ref = oracle.maxpool_backward(m_ref, _host(go)[0].reshape(y_ref.shape), shape, k, _host(go)[1])
+        xd, gd = torch.zeros(n + 1, dtype=dtype, device="cuda:0")[1:], torch.zeros(m + 1, dtype=dtype, device="cuda:0")[1:]
+        xd.copy_(x); gd.copy_(go)
+        y, mask = pkg.division_maxpool_forward(xd.view(shape), k)
+        out = torch.full((n + 2,), 7.0, dtype=dtype, device="cuda:0")
+        dt = 1 if dtype == torch.bfloat16 else 0
+        rc = pkg.lib().division_maxpool_backward(mask.data_ptr(), mask.numel() * 4, gd.data_ptr(), N, C, H, W, dt, k, out[1:].data_ptr(),
+                                                 torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0 and np.array_equal(mask.cpu().numpy().view(np.uint32), m_ref) and _same_bits(y, y_ref)
+        assert _same_bits(out[1:-1].view(shape), g_ref) and float(out[0]) == 7.0 and float(out[-1]) == 7.0
