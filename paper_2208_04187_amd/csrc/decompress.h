@@ -2,9 +2,7 @@
 
 // ------------------------------------------------------------------ decompress
 
-struct DecArgs {
-    DecTab tab;
-    Regions rg;
+struct DecShape {        // the maps of one shape
     uint32_t P, H, W, HW, LH, LW, nb, WPP, B;
     uint32_t G;          // planes per workgroup
     uint32_t q4;         // HW / 4 (decompress_stream with whole8: HW / 8)
@@ -13,12 +11,17 @@ struct DecArgs {
     uint32_t whole8;     // decompress_stream, 2-byte elements: rows and blocks are whole vectors of eight elements
     uint32_t out_off;    // decompress_words: byte offset of the staged output in LDS
     FastDiv d_q4, d_w4, d_B, d_W, d_HW, d_Hs, d_wpp;
+    double r_q4, r_HW;   // 1 / q4, 1 / HW: a division per wavefront is 30 binary64 instructions
+};
+struct DecArgs : DecShape {
+    DecTab tab;
+    Regions rg;
 };
 
 // Index of the first block of the block row that holds row r; for a 3-D map (Appendix D,
 // UpSampling3D) r counts the rows of all depth slices.
 template <int ND>
-__device__ __forceinline__ uint32_t lfc_row(const DecArgs& a, uint32_t r) {
+__device__ __forceinline__ uint32_t lfc_row(const DecShape& a, uint32_t r) {
     if constexpr (ND == 3) {
         const uint32_t z = fdiv(r, a.d_Hs);
         return (fdiv(z, a.d_B) * a.LHs + fdiv(r - z * a.Hs, a.d_B)) * a.LW;
@@ -157,7 +160,7 @@ __global__ void __launch_bounds__(kThreads) decompress_rowvec_3d(DecArgs a) { de
 // one by one (widths such as 28, block sizes such as 12, planes that end in the middle of a vector).
 constexpr int kStreamK = DIVISION_STREAM_K;
 template <typename T, int BITS, int ND, bool W8>
-__device__ __forceinline__ void decompress_stream_body(const DecArgs& a) {
+__device__ __forceinline__ void decompress_stream_body(const DecShape& a, const DecPtrs& pt, uint32_t chunk) {
     constexpr int EPV = 16 / sizeof(T);                                 // elements per vector
     constexpr int PE = W8 ? 8 : 4;                                      // elements per piece
     constexpr int NP = EPV / PE;                                        // pieces per vector
@@ -165,13 +168,12 @@ __device__ __forceinline__ void decompress_stream_body(const DecArgs& a) {
     constexpr int K = kStreamK;
     constexpr uint32_t Lq = (1u << BITS) - 1u;
     constexpr uint32_t PB = PE * BITS / 8;                              // code bytes per piece (1-bit codes of four elements: half a byte)
-    const DecPtrs pt = dec_ptrs(a.tab, a.rg);
     const uint32_t lane = threadIdx.x;
     // first piece of the chunk, counted over the whole map: its plane g0 and its place r0 inside the
     // plane (uniform; the quotient by a binary64 reciprocal, then put right)
-    const uint64_t v0 = (uint64_t)blockIdx.x * (64u * K * NP);
+    const uint64_t v0 = (uint64_t)chunk * (64u * K * NP);
     const uint64_t nvec = (uint64_t)a.P * a.q4;
-    uint32_t g0 = (uint32_t)((double)v0 * (1.0 / (double)a.q4));
+    uint32_t g0 = (uint32_t)((double)v0 * a.r_q4);
     int64_t r0 = (int64_t)(v0 - (uint64_t)g0 * a.q4);
     if (r0 < 0) { --g0; r0 += a.q4; }
     if (r0 >= (int64_t)a.q4) { ++g0; r0 -= a.q4; }
@@ -221,19 +223,18 @@ __device__ __forceinline__ void decompress_stream_body(const DecArgs& a) {
     }
 }
 template <typename T, int BITS, int ND>
-__device__ __forceinline__ void decompress_stream_pieces(const DecArgs& a) {
-    if constexpr (sizeof(T) == 2) { if (a.whole8) { decompress_stream_body<T, BITS, ND, true>(a); return; } }
-    decompress_stream_body<T, BITS, ND, false>(a);
+__device__ __forceinline__ void decompress_stream_pieces(const DecShape& a, const DecPtrs& pt, uint32_t chunk) {
+    if constexpr (sizeof(T) == 2) { if (a.whole8) { decompress_stream_body<T, BITS, ND, true>(a, pt, chunk); return; } }
+    decompress_stream_body<T, BITS, ND, false>(a, pt, chunk);
 }
 // 2-byte elements, against staging in LDS (decompress_rowvec, which keeps what does not start on a 16-byte boundary):
 // 256 x 256 x 56 x 56 (b = 2) 77 us (5.3 TB/s) staged, 68.5 us (6.0 TB/s) here; 32 x 512 x 1 x 3072 (b = 4) 27 us and 20.8 us.
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream(DecArgs a) { decompress_stream_pieces<T, BITS, 2>(a); }
+__global__ void __launch_bounds__(64) decompress_stream(DecArgs a) { decompress_stream_pieces<T, BITS, 2>(a, dec_ptrs(a.tab, a.rg), blockIdx.x); }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { decompress_stream_pieces<T, BITS, 3>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { decompress_stream_pieces<T, BITS, 3>(a, dec_ptrs(a.tab, a.rg), blockIdx.x); }
 
-// The stream kernel for maps whose rows, blocks or planes are not whole vectors (odd widths, any B; 4-byte
-// elements): a workgroup is again ONE wavefront that rebuilds kStreamK * 64 consecutive, aligned 16-byte
+// The stream kernel for maps whose rows, blocks or planes are not whole vectors (odd widths, any B): a workgroup is again ONE wavefront that rebuilds kStreamK * 64 consecutive, aligned 16-byte
 // vectors of the map wherever rows and planes end, without LDS or barrier.  A vector's four elements may
 // lie in two rows and in two planes (planes have at least 4 elements): each element finds its own plane,
 // row, column and block; the vector's codes are the 4 * BITS bits from its first element's place in its
@@ -247,7 +248,7 @@ __global__ void __launch_bounds__(64) decompress_stream_3d(DecArgs a) { decompre
 __device__ __forceinline__ uint32_t udiv2(uint32_t n, FastDiv f) { return __umulhi(n, f.m); }
 // offset of row r's first block among a plane's H^L values (r counts the rows of all depth slices)
 template <int ND>
-__device__ __forceinline__ uint32_t lfc_row2(const DecArgs& a, uint32_t r) {
+__device__ __forceinline__ uint32_t lfc_row2(const DecShape& a, uint32_t r) {
     if constexpr (ND == 3) {
         const uint32_t z = udiv2(r, a.d_Hs);
         return (udiv2(z, a.d_B) * a.LHs + udiv2(r - z * a.Hs, a.d_B)) * a.LW;
@@ -255,18 +256,24 @@ __device__ __forceinline__ uint32_t lfc_row2(const DecArgs& a, uint32_t r) {
         return udiv2(r, a.d_B) * a.LW;
     }
 }
+// Vectors a lane rebuilds and elements of a chunk: the lookups of 2-byte elements go by pieces of four as well, so half as
+// many vectors keep the same number of loads in flight per lane (and of registers: 64, eight wavefronts per SIMD).
+template <typename T> constexpr int kAnyVecs = sizeof(T) == 4 ? kStreamK : kStreamK / 2;
+template <typename T> constexpr uint32_t kAnyChunk = 64u * kAnyVecs<T> * (16 / sizeof(T));
 template <typename T, int BITS, int ND>
-__device__ __forceinline__ void decompress_stream_any_body(const DecArgs& a) {
-    static_assert(sizeof(T) == 4, "4-byte elements");
-    constexpr int K = kStreamK;
+__device__ __forceinline__ void decompress_stream_any_body(const DecShape& a, const DecPtrs& pt, uint32_t chunk) {
+    constexpr int NP = 4 / sizeof(T);                                      // pieces of four elements per vector
+    constexpr int VK = kAnyVecs<T>;                                        // vectors per lane
+    constexpr int K = VK * NP;                                             // pieces per lane
+    constexpr uint32_t CE = kAnyChunk<T>;                                  // elements per chunk
     constexpr uint32_t Lq = (1u << BITS) - 1u;
-    constexpr uint32_t LB = kC16<T> ? 2u : 4u, MB = kC16<T> ? 4u : 8u;     // bytes of one H^L value, of one (delta, Delta)
-    const DecPtrs pt = dec_ptrs(a.tab, a.rg);
+    constexpr bool L16 = sizeof(T) == 2 || kC16<T>;                        // H^L cached as bfloat16
+    constexpr uint32_t LB = L16 ? 2u : 4u, MB = kC16<T> ? 4u : 8u;         // bytes of one H^L value, of one (delta, Delta)
     const uint32_t lane = threadIdx.x;
     // first element of the chunk, counted over the whole map: its plane g0 and its place t0 inside the plane
-    const uint64_t e0 = (uint64_t)blockIdx.x * (256u * K);
+    const uint64_t e0 = (uint64_t)chunk * CE;
     const uint64_t ntot = (uint64_t)a.P * a.HW;
-    uint32_t g0 = (uint32_t)((double)e0 * (1.0 / (double)a.HW));
+    uint32_t g0 = (uint32_t)((double)e0 * a.r_HW);
     int64_t r0 = (int64_t)(e0 - (uint64_t)g0 * a.HW);
     if (r0 < 0) { --g0; r0 += a.HW; }
     if (r0 >= (int64_t)a.HW) { ++g0; r0 -= a.HW; }
@@ -285,7 +292,7 @@ __device__ __forceinline__ void decompress_stream_any_body(const DecArgs& a) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         // (products of two numbers below 2^24 use the full-rate 24-bit multiply; the host checks the sizes)
-        const uint32_t t = t0 + 4u * (64u * k + lane);                    // < HW + 256 K
+        const uint32_t t = t0 + 4u * ((uint32_t)NP * (64u * (k / NP) + lane) + (uint32_t)(k % NP));      // < HW + CE
         const uint32_t dg = udiv2(t, a.d_HW);
         const uint32_t i = t - __umul24(dg, a.HW);                        // the vector's first element inside its plane
         const uint32_t g = min(g0 + dg, a.P - 1u);                         // vectors past the map re-read its last plane
@@ -311,7 +318,7 @@ __device__ __forceinline__ void decompress_stream_any_body(const DecArgs& a) {
         }
         if constexpr (ND == 0) {
             // one block per plane: H^L of the plane and of the next one lie side by side, one load
-            if constexpr (kC16<T>) {
+            if constexpr (L16) {
                 lw[k][0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(lrs, g * 2u, 0, 0) << 16;     // (2-byte values: a 4-byte load
                 lw[k][1] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(lrs, g * 2u + 2u, 0, 0) << 16; // of both would not be aligned)
             } else {
@@ -348,14 +355,16 @@ __device__ __forceinline__ void decompress_stream_any_body(const DecArgs& a) {
             const bool wrap = c + j >= a.W;
             const uint32_t in_row = oa + (crem + j >= a.B ? LB : 0u);
             const uint32_t off = first ? (wrap ? ob : in_row) : oc;
-            if constexpr (kC16<T>) lw[k][j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(lrs, off, 0, 0) << 16;
+            if constexpr (L16) lw[k][j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(lrs, off, 0, 0) << 16;
             else lw[k][j] = __builtin_amdgcn_raw_buffer_load_b32(lrs, off, 0, 0);
         }
     }
     T* out = static_cast<T*>(pt.xhat) + e0;
     const uint64_t left = ntot - e0;                                      // elements from the chunk's start to the map's end
+    // (2-byte elements: whole dwords, see below)
     const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
-        out, 0, (int)(left < 256u * K ? (uint32_t)left * 4u : 256u * K * 4u), 0x00020000);
+        out, 0, (int)(left < CE ? ((uint32_t)left * (uint32_t)sizeof(T)) & ~3u : CE * (uint32_t)sizeof(T)), 0x00020000);
+    uint32_t ow[4];                                                       // the vector that leaves
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         uint32_t c = __builtin_amdgcn_alignbit(hi[k], lo[k], sh[k]);
@@ -378,17 +387,79 @@ __device__ __forceinline__ void decompress_stream_any_body(const DecArgs& a) {
             const uint32_t lfcw = ND == 0 ? (first ? lw[k][0] : lw[k][1]) : lw[k][j];
             ov[j] = __float_as_uint(dequant((c >> (j * BITS)) & Lq, first ? da.y : db.y, first ? da.x : db.x, __uint_as_float(lfcw)));
         }
-        u32x4 o; o.x = ov[0]; o.y = ov[1]; o.z = ov[2]; o.w = ov[3];
-        store_b128_checked(o, ors, lane * 16u + (uint32_t)(k * 1024), DIVISION_STREAM_STORE_AUX);   // past the map: dropped
+        if constexpr (NP == 1) {
+            ow[0] = ov[0]; ow[1] = ov[1]; ow[2] = ov[2]; ow[3] = ov[3];
+        } else {
+            ow[2 * (k % 2)] = bf16_pack2(__uint_as_float(ov[0]), __uint_as_float(ov[1]));
+            ow[2 * (k % 2) + 1] = bf16_pack2(__uint_as_float(ov[2]), __uint_as_float(ov[3]));
+        }
+        if (k % NP != NP - 1) continue;
+        const u32x4 o{ow[0], ow[1], ow[2], ow[3]};
+        store_b128_checked(o, ors, lane * 16u + (uint32_t)(k / NP * 1024), DIVISION_STREAM_STORE_AUX);   // past the map: dropped
+        if constexpr (NP == 2) {
+            // a map of an odd number of elements ends in the middle of a dword, which lies behind the bound
+            const uint32_t at = 8u * (64u * (uint32_t)(k / NP) + lane);
+            if ((left & 1u) && left < CE && (uint32_t)left - 1u - at < 8u)
+                out[left - 1u].v = (uint16_t)ow[((uint32_t)left - 1u - at) >> 1];
+        }
     }
 }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_any(DecArgs a) { decompress_stream_any_body<T, BITS, 2>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_any(DecArgs a) { decompress_stream_any_body<T, BITS, 2>(a, dec_ptrs(a.tab, a.rg), blockIdx.x); }
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_any_3d(DecArgs a) { decompress_stream_any_body<T, BITS, 3>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_any_3d(DecArgs a) { decompress_stream_any_body<T, BITS, 3>(a, dec_ptrs(a.tab, a.rg), blockIdx.x); }
 // planes that are one block (any number of map dimensions): no rows or columns, H^L is the plane's
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { decompress_stream_any_body<T, BITS, 0>(a); }
+__global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { decompress_stream_any_body<T, BITS, 0>(a, dec_ptrs(a.tab, a.rg), blockIdx.x); }
+
+// ---- maps of several shapes in one launch
+
+// The wavefront-per-chunk kernels over the maps of several shapes: a workgroup finds its shape and its map in tables of the
+// arguments (all uniform: scalar loads and compares) and runs the body that the shape would have a launch of its own for.
+// A launch of its own costs a shape the drain of the one before and its own filling, 2-4 us, and 2 us of the host.  The four
+// groups of a ResNet-18 / CIFAR step take 42 us in one launch, 48 in four; the seven odd-sized groups of an
+// AlexNet / Inception step 196 and 202; the eight groups of a Swin-T step 141 in eight, about 130 in one.  The look-up itself costs nothing
+// that shows (64 x 256 x 56 x 56 on its own 31.9 us, beside a tiny map 32.2).
+// What a workgroup must know before anything else (the shape's first workgroup, chunks per map, kind and first map) sits at fixed
+// places, so that everything else it reads depends on one wait for scalar loads and not on three.
+constexpr int kMixShapes = 16, kMixMaps = 32;
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));      // (vectors: three wide scalar loads; from arrays the compiler makes a load and a branch per shape)
+struct MixShape : DecShape { size_t meta_off, lfc_off; };
+struct MixArgs {
+    u32x16 first;                         // first workgroup of each shape (beyond the last shape: 2^32 - 1)
+    u32x16 chunks;                        // per map
+    u32x16 info;                          // kind (see plan_mix) | 16 for 2-D maps | its index << 5 | index of its first map << 16
+    MixShape shape[kMixShapes];
+    const void* pk[kMixMaps];
+    void* xhat[kMixMaps];
+};
+template <typename T, int BITS>
+__global__ void __launch_bounds__(64) decompress_mixed(MixArgs a) {
+    const u32x16 first = a.first, chunks = a.chunks, infos = a.info;
+    uint32_t c = 0, n = chunks[0], info = infos[0];
+#pragma unroll
+    for (int i = 1; i < kMixShapes; ++i) {
+        const bool past = blockIdx.x >= first[i];
+        c = past ? first[i] : c; n = past ? chunks[i] : n; info = past ? infos[i] : info;
+    }
+    c = blockIdx.x - c;
+    uint32_t m = info >> 16;
+    while (c >= n) { c -= n; ++m; }
+    const MixShape& h = a.shape[(info >> 5) & 31u];
+    const char* pk = static_cast<const char*>(a.pk[m]);
+    DecPtrs pt;
+    pt.codes = reinterpret_cast<const uint32_t*>(pk);
+    pt.meta = reinterpret_cast<const float*>(pk + h.meta_off);
+    pt.lfc = pk + h.lfc_off;
+    pt.xhat = a.xhat[m];
+    switch (info & 31u) {
+        case 7 | 16: decompress_stream_pieces<T, BITS, 2>(h, pt, c); break;
+        case 7: decompress_stream_pieces<T, BITS, 3>(h, pt, c); break;
+        case 8 | 16: decompress_stream_any_body<T, BITS, 2>(h, pt, c); break;
+        case 8: decompress_stream_any_body<T, BITS, 3>(h, pt, c); break;
+        default: decompress_stream_any_body<T, BITS, 0>(h, pt, c);
+    }
+}
 
 // H*W a multiple of 4 and at most 255 blocks per plane: the LFC index of every
 // element of a plane is looked up in a table (one byte per element, four per

@@ -43,8 +43,9 @@
 //   compress_plane   planes beyond LDS with vector rows and blocks (video volumes, image-sized maps):
 //                    a workgroup per plane, two vector passes over x
 //   compress_any     everything else (giant planes with odd extents): scalar, slow
+//   decompress_mixed the wavefront-per-chunk kernels below over the maps of several shapes in one launch (division_decompress_maps)
 //   decompress_stream / decompress_stream_any / decompress_stream_one: one wavefront per 4 KB chunk of aligned vectors, no LDS:
-//                    rows of whole vectors inside one block (_stream, also 2-byte maps), or 4-byte elements of any width where a vector may span two rows
+//                    rows of whole vectors inside one block (_stream), or any width where a vector may span two rows
 //                    and two planes (_stream_any: each element finds its plane and block, six loads per vector;
 //                    _stream_one: planes that are one block)
 //   decompress_rowvec / _table / _words / _flat / _lane / _scalar: streaming, the packed slice of a
@@ -92,8 +93,11 @@ DIVISION_BRIDGE hipError_t division_bridge_compress_f32(const void* launch, int 
 DIVISION_BRIDGE hipError_t division_bridge_compress_bf16(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_compress_c16(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_decompress_f32(const void* launch, int b);
+DIVISION_BRIDGE hipError_t division_bridge_decompress_mixed_f32(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_decompress_bf16(const void* launch, int b);
+DIVISION_BRIDGE hipError_t division_bridge_decompress_mixed_bf16(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_decompress_c16(const void* launch, int b);
+DIVISION_BRIDGE hipError_t division_bridge_decompress_mixed_c16(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_relu_f32(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_relu_bf16(const void* launch, int b);
 DIVISION_BRIDGE hipError_t division_bridge_relu_c16(const void* launch, int b);
@@ -148,16 +152,19 @@ constexpr int kLoadReuse = 0;
 #if DIVISION_HAS_F32
 hipError_t division_bridge_compress_f32(const void* c, int b) { return do_compress<float>(*static_cast<const CompLaunch*>(c), b); }
 hipError_t division_bridge_decompress_f32(const void* c, int b) { return do_decompress<float>(*static_cast<const DecLaunch*>(c), b); }
+hipError_t division_bridge_decompress_mixed_f32(const void* c, int b) { return do_decompress_mixed<float>(*static_cast<const MixLaunch*>(c), b); }
 hipError_t division_bridge_relu_f32(const void* c, int b) { return do_relu<float>(*static_cast<const CompLaunch*>(c), b); }
 #endif
 #if DIVISION_HAS_BF16
 hipError_t division_bridge_compress_bf16(const void* c, int b) { return do_compress<bf16_t>(*static_cast<const CompLaunch*>(c), b); }
 hipError_t division_bridge_decompress_bf16(const void* c, int b) { return do_decompress<bf16_t>(*static_cast<const DecLaunch*>(c), b); }
+hipError_t division_bridge_decompress_mixed_bf16(const void* c, int b) { return do_decompress_mixed<bf16_t>(*static_cast<const MixLaunch*>(c), b); }
 hipError_t division_bridge_relu_bf16(const void* c, int b) { return do_relu<bf16_t>(*static_cast<const CompLaunch*>(c), b); }
 #endif
 #if DIVISION_HAS_C16
 hipError_t division_bridge_compress_c16(const void* c, int b) { return do_compress<f32c16_t>(*static_cast<const CompLaunch*>(c), b); }
 hipError_t division_bridge_decompress_c16(const void* c, int b) { return do_decompress<f32c16_t>(*static_cast<const DecLaunch*>(c), b); }
+hipError_t division_bridge_decompress_mixed_c16(const void* c, int b) { return do_decompress_mixed<f32c16_t>(*static_cast<const MixLaunch*>(c), b); }
 hipError_t division_bridge_relu_c16(const void* c, int b) { return do_relu<f32c16_t>(*static_cast<const CompLaunch*>(c), b); }
 #endif
 
@@ -317,10 +324,24 @@ int division_relu_compress_fused(int64_t N, int64_t C, int64_t H, int64_t W, div
     return (Bc == 4 || Bc == 8) && plan_relu_items(L, H, W, Bc, es, aligned, &ia, &grid, &lds, &vec);
 }
 
+// Whether a map that one descriptor has written is read or written by another: such maps keep the order of the descriptors.
+static bool outputs_overlap(int count, const division_map* maps, const size_t* bytes) {
+    for (int i = 0; i < count; ++i) {
+        const uintptr_t o0 = (uintptr_t)maps[i].xhat, o1 = o0 + bytes[i];
+        for (int j = 0; j < count; ++j) {
+            const uintptr_t p0 = (uintptr_t)maps[j].packed, q0 = (uintptr_t)maps[j].xhat;
+            if ((o0 < p0 + maps[j].packed_bytes && p0 < o1) || (i != j && o0 < q0 + bytes[j] && q0 < o1)) return true;
+        }
+    }
+    return false;
+}
+
 // Both directions of the descriptor-array calls: validates every map, then serves the maps that
-// share a shape and parameters together, in order of first appearance.
+// share a shape and parameters together, in order of first appearance.  Decompression puts the maps of several shapes into one
+// launch where their kernel can take part in one (decompress_mixed) and no output overlaps another map.
 static int run_maps(int count, const division_map* maps, void* hip_stream, bool compress) {
     if (count < 0 || (count > 0 && !maps)) return DIVISION_EINVAL;
+    std::vector<size_t> bytes((size_t)count);
     for (int i = 0; i < count; ++i) {
         const division_map& m = maps[i];
         Layout L;
@@ -331,10 +352,17 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
         const size_t es = m.dt == DIVISION_BF16 ? 2 : 4;
         const void* data = compress ? m.x : m.xhat;
         if (((uintptr_t)data % es) != 0 || ((uintptr_t)m.packed % 16) != 0) return DIVISION_EALIGN;
+        bytes[(size_t)i] = L.P * L.HW * es;
     }
     auto same = [](const division_map& p, const division_map& q) {
         return p.N == q.N && p.C == q.C && p.D == q.D && p.H == q.H && p.W == q.W && p.dt == q.dt && p.B == q.B && p.b == q.b;
     };
+    // (a call of one shape, or of more maps than a few launches hold, has nothing to gain from mixing)
+    bool mix = false;
+    for (int i = 1; i < count && !compress && count <= 256; ++i) mix = mix || !same(maps[0], maps[i]);
+    mix = mix && !outputs_overlap(count, maps, bytes.data());
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    Mixer mixer;
     std::vector<char> done((size_t)count, 0);
     std::vector<const void*> in;
     std::vector<void*> out;
@@ -352,12 +380,33 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             if (maps[j].packed_bytes < cap) cap = maps[j].packed_bytes;
         }
         const division_map& m = maps[i];
+        if (mix && in.size() <= (size_t)kMixMaps) {
+            int64_t D = m.D, H = m.H, W = m.W;
+            squeeze_dims(D, H, W);
+            Layout L;
+            make_layout(m.N, m.C, D, H, W, m.B, m.b, (int)m.dt, &L);
+            const int B = covering_block(L, D, H, W, m.B);
+            uintptr_t all_out = 0;
+            for (void* o : out) all_out |= (uintptr_t)o;
+            DecShape sh{};
+            uint32_t chunks = 0;
+            const int kind = plan_mix(L, D, H, W, B, m.dt == DIVISION_BF16 ? 2 : 4, reinterpret_cast<const void*>(all_out), in.size(), &sh, &chunks);
+            const uint64_t workgroups = (uint64_t)chunks * in.size();
+            if (kind && launch_ok(workgroups, 64)) {
+                if (!mixer.fits(m.dt, m.b, in.size(), workgroups)) {
+                    const int rc = mixer.flush(st);
+                    if (rc != DIVISION_OK) return rc;
+                }
+                mixer.add(m.dt, m.b, L, D == 1, kind, sh, chunks, in.size(), in.data(), out.data());
+                continue;
+            }
+        }
         const int rc = compress
             ? compress_impl((int)in.size(), in.data(), out.data(), seeds.data(), m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, cap, hip_stream)
             : decompress_impl((int)in.size(), in.data(), out.data(), cap, m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, hip_stream);
         if (rc != DIVISION_OK) return rc;
     }
-    return DIVISION_OK;
+    return mixer.flush(st);
 }
 
 int division_compress_maps(int count, const division_map* maps, void* hip_stream) {

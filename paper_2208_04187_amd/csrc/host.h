@@ -826,22 +826,71 @@ uint64_t dec_planes(const Layout& L, size_t es, uint64_t mult) {
     return G;
 }
 
-// Fills the decompress launch plan; returns 7 (row vectors, a wavefront per chunk), 0 (row vectors of 2-byte elements, staged), 3 (block table),
-// 8 (4-byte elements of any width, a wavefront per chunk), 6 (four consecutive elements
-// per lane step, any width), 5 (word by word through LDS), 1 (flat), 4 (lane per plane) or 2 (scalar).
-// Hs = rows of one depth slice, D = depth slices (1 for a 2-D map; the table kernel takes 2-D maps only).
-int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat,
-                    DecArgs* a, uint32_t* grid) {
-    const int64_t H = D * Hs;
-    a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
+// What the decompress kernels read of a shape whatever the plan.  Hs = rows of one depth slice, D = depth slices (1 for a 2-D map).
+void dec_shape(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, DecShape* a) {
+    a->P = (uint32_t)L.P; a->H = (uint32_t)(D * Hs); a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)(L.LD * L.LH); a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
     a->Hs = (uint32_t)Hs; a->LHs = (uint32_t)L.LH;
     a->d_B = make_fastdiv((uint32_t)B);
     a->d_W = make_fastdiv((uint32_t)W);
     a->d_HW = make_fastdiv((uint32_t)L.HW);
     a->d_Hs = make_fastdiv((uint32_t)Hs);
-    const bool small_idx = fastdiv_ok((uint64_t)H, (uint64_t)B) && fastdiv_ok((uint64_t)W, (uint64_t)B) &&
-                           fastdiv_ok((uint64_t)H, (uint64_t)Hs);
+    a->r_HW = 1.0 / (double)L.HW;
+}
+bool dec_small_idx(int64_t D, int64_t Hs, int64_t W, int B) {
+    const uint64_t H = (uint64_t)(D * Hs);
+    return fastdiv_ok(H, (uint64_t)B) && fastdiv_ok((uint64_t)W, (uint64_t)B) && fastdiv_ok(H, (uint64_t)Hs);
+}
+
+// decompress_stream: rows and blocks of whole pieces, one wavefront per 64 * kStreamK vectors, no staging; the lookups go by pieces
+// of four elements, or of eight 2-byte elements where rows and blocks are whole vectors
+bool plan_stream(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat, DecShape* a, uint32_t* grid) {
+    if (W % 4 != 0 || B % 4 != 0 || !dec_small_idx(D, Hs, W, B) || ((uintptr_t)xhat % 16) != 0) return false;
+    const uint64_t pe = es == 2 && W % 8 == 0 && B % 8 == 0 ? 8 : 4;
+    const uint64_t chunk = 64ull * kStreamK * (16 / es / pe);      // pieces
+    const uint64_t q = L.HW / pe, npiece = L.P * q;
+    // (2-byte maps of 256 GB and more: the staged kernel, whose workgroups rebuild 32 KB each)
+    if (!fastdiv_ok(q + chunk, q) || !fastdiv_ok(q, (uint64_t)W / pe) || (npiece + chunk - 1) / chunk >= (1ull << 31) ||
+        npiece >= (1ull << 40) || (es == 2 && !launch_ok((npiece + chunk - 1) / chunk, 64)))
+        return false;
+    a->whole8 = pe == 8;
+    a->q4 = (uint32_t)q;
+    a->r_q4 = 1.0 / (double)q;
+    a->w4 = (uint32_t)((uint64_t)W / pe);
+    a->d_q4 = make_fastdiv(a->q4);
+    a->d_w4 = make_fastdiv(a->w4);
+    *grid = (uint32_t)((npiece + chunk - 1) / chunk);
+    return true;
+}
+
+// decompress_stream_any (several blocks per plane) and decompress_stream_one (one): rows, blocks or planes that are not whole
+// vectors, a wavefront per chunk of aligned vectors, every element finds its own plane and block.
+// (B >= 4 and W >= 4: a vector then leaves its row and its block column at most once, and no division is by 1; plane and plane
+// count below 2^24 for the 24-bit multiplies; the three regions of the packed buffer within 32-bit byte offsets)
+bool plan_any(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat, uint32_t* grid) {
+    if (L.HW < 4 || L.HW >= (1ull << 24) || L.P >= (1ull << 24) || ((uintptr_t)xhat % 16) != 0 || L.P * L.WPP * 4 >= (1ull << 31) ||
+        L.P * L.nb * 4 >= (1ull << 31) || L.P * 8 >= (1ull << 31))
+        return false;
+    if (L.nb > 1 && (W < 4 || B < 4 || (D > 1 && Hs < 2) || !dec_small_idx(D, Hs, W, B) || !fastdiv_ok(L.HW, (uint64_t)W) ||
+                     !fastdiv_ok((uint64_t)(D * Hs) + 1, (uint64_t)B)))
+        return false;
+    const uint64_t chunk = es == 2 ? kAnyChunk<bf16_t> : kAnyChunk<float>;     // elements
+    const uint64_t ntot = L.P * L.HW;
+    if (!fastdiv_ok(L.HW + chunk + 4, L.HW) || (ntot + chunk - 1) / chunk >= (1ull << 31) || ntot >= (1ull << 42)) return false;
+    *grid = (uint32_t)((ntot + chunk - 1) / chunk);
+    return true;
+}
+
+
+// Fills the decompress launch plan; returns 7 (row vectors, a wavefront per chunk), 0 (row vectors of 2-byte elements, staged), 3 (block table),
+// 8 (any width, a wavefront per chunk), 9 (the same for one-block planes), 6 (four consecutive elements
+// per lane step, any width), 5 (word by word through LDS), 1 (flat), 4 (lane per plane) or 2 (scalar).
+// Hs = rows of one depth slice, D = depth slices (1 for a 2-D map; the table kernel takes 2-D maps only).
+int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat,
+                    DecArgs* a, uint32_t* grid) {
+    const int64_t H = D * Hs;
+    dec_shape(L, D, Hs, W, B, a);
+    const bool small_idx = dec_small_idx(D, Hs, W, B);
     const bool out_vec_aligned = ((uintptr_t)xhat % (4 * es)) == 0;
     // one-block planes with an odd element count: a lane per plane, 64 planes per round
     if (lane_shape(L)) {
@@ -852,37 +901,12 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
         *grid = (nrounds + rpw - 1) / rpw;
         return 4;
     }
-    // 4-byte elements, one block per plane (not those of the lane kernel above, which measured the same on 7 x 7, nor those of the row-vector stream kernel below): a wavefront per
-    // chunk of aligned vectors, H^L is the plane's
-    if (es == 4 && L.nb == 1 && !(W % 4 == 0 && B % 4 == 0) && L.HW >= 4 && L.HW < (1ull << 24) && L.P < (1ull << 24) && out_vec_aligned &&
-        L.P * L.WPP * 4 < (1ull << 31) && L.P * 8 < (1ull << 31)) {
-        const uint64_t chunk = 256ull * kStreamK;                       // elements
-        const uint64_t ntot = L.P * L.HW;
-        if (fastdiv_ok(L.HW + chunk + 4, L.HW) && (ntot + chunk - 1) / chunk < (1ull << 31) && ntot < (1ull << 42)) {
-            *grid = (uint32_t)((ntot + chunk - 1) / chunk);
-            return 9;
-        }
-    }
+    // 4-byte elements, one block per plane (not those of the lane kernel above, which measured the same on 7 x 7, nor those of
+    // the row-vector stream kernel below): H^L is the plane's
+    if (es == 4 && L.nb == 1 && !(W % 4 == 0 && B % 4 == 0) && plan_any(L, D, Hs, W, B, es, xhat, grid)) return 9;
     // fast path: rows are whole vectors that sit inside one block
     if (W % 4 == 0 && B % 4 == 0 && small_idx && out_vec_aligned) {
-        // one wavefront per 64 * kStreamK vectors, no staging; the lookups go by pieces of four elements, or of eight
-        // 2-byte elements where rows and blocks are whole vectors
-        if (es == 4 || ((uintptr_t)xhat % 16) == 0) {
-            const uint64_t pe = es == 2 && W % 8 == 0 && B % 8 == 0 ? 8 : 4;
-            const uint64_t chunk = 64ull * kStreamK * (16 / es / pe);      // pieces
-            const uint64_t q = L.HW / pe, npiece = L.P * q;
-            // (2-byte maps of 256 GB and more: the staged kernel, whose workgroups rebuild 32 KB each)
-            if (fastdiv_ok(q + chunk, q) && fastdiv_ok(q, (uint64_t)W / pe) && (npiece + chunk - 1) / chunk < (1ull << 31) &&
-                npiece < (1ull << 40) && (es == 4 || launch_ok((npiece + chunk - 1) / chunk, 64))) {
-                a->whole8 = pe == 8;
-                a->q4 = (uint32_t)q;
-                a->w4 = (uint32_t)((uint64_t)W / pe);
-                a->d_q4 = make_fastdiv(a->q4);
-                a->d_w4 = make_fastdiv(a->w4);
-                *grid = (uint32_t)((npiece + chunk - 1) / chunk);
-                return 7;
-            }
-        }
+        if (plan_stream(L, D, Hs, W, B, es, xhat, a, grid)) return 7;
         // 2-byte maps that do not start on a 16-byte boundary, or are too large for one launch of the above (4-byte maps meet
         // neither: what the staged kernel's index tricks allow, the above's do)
         if (es == 2) {
@@ -911,20 +935,8 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
             return 3;
         }
     }
-    // 4-byte elements, rows, blocks or planes that are not whole vectors: a wavefront per chunk of aligned vectors,
-    // every element finds its own plane and block
-    // (several blocks per plane: one-block planes are the flat kernel's, measured faster there; B >= 4 and W >= 4: a
-    // vector then leaves its row and its block column at most once, and no division is by 1; plane and plane count
-    // below 2^24 for the 24-bit multiplies; the three regions of the packed buffer within 32-bit byte offsets)
-    if (es == 4 && L.nb > 1 && W >= 4 && B >= 4 && (D == 1 || Hs >= 2) && L.HW < (1ull << 24) && L.P < (1ull << 24) && small_idx && out_vec_aligned && fastdiv_ok(L.HW, (uint64_t)W) &&
-        fastdiv_ok((uint64_t)H + 1, (uint64_t)B) && L.P * L.WPP * 4 < (1ull << 31) && L.P * L.nb * 4 < (1ull << 31) && L.P * 8 < (1ull << 31)) {
-        const uint64_t chunk = 256ull * kStreamK;                       // elements
-        const uint64_t ntot = L.P * L.HW;
-        if (fastdiv_ok(L.HW + chunk + 4, L.HW) && (ntot + chunk - 1) / chunk < (1ull << 31) && ntot < (1ull << 42)) {
-            *grid = (uint32_t)((ntot + chunk - 1) / chunk);
-            return 8;
-        }
-    }
+    // 4-byte elements, rows, blocks or planes that are not whole vectors, several blocks per plane
+    if (es == 4 && L.nb > 1 && plan_any(L, D, Hs, W, B, es, xhat, grid)) return 8;
     // planes (2-D or 3-D) of 512 elements and more whose rows or blocks are not whole vectors: four consecutive
     // elements per lane step, planes starting on 4-byte boundaries
     if (Hs > 1 && small_idx && ((uintptr_t)xhat % 4) == 0 && L.nb <= 16383) {
@@ -944,6 +956,11 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
             return 6;
         }
     }
+    // 2-byte elements, planes below 512 elements or of one row: as 4-byte elements (64 x 768 x 17 x 17 14.0 us against 17.9 in
+    // decompress_words, 64 x 1024 x 14 x 14 under B = 64 9.4 against 13.8 in decompress_flat; from 512 elements on decompress_units, which looks
+    // nothing up per element, is level (35 x 35) or ahead (147 x 147: 46 us against 60); a map of one or two chunks is one or two
+    // wavefronts' work there and four here)
+    if (es == 2 && L.P * L.HW > 2 * kAnyChunk<bf16_t> && plan_any(L, D, Hs, W, B, es, xhat, grid)) return L.nb == 1 ? 9 : 8;
     // several blocks per plane, rows not whole vectors: rebuilt in LDS word by word
     if (L.nb > 1 && small_idx && out_vec_aligned && fastdiv_ok(L.HW, (uint64_t)W)) {
         const uint64_t unit = 4 / gcd_u64(4, L.HW);
@@ -980,6 +997,22 @@ hipError_t with_bits(int b, F&& f) {
                                                                   : f(std::integral_constant<int, 8>{});
 }
 
+// The kernel of a shape in a launch of several shapes: 7 (decompress_stream), 8 (_any), 9 (_one), or 0 where its maps have a launch
+// of their own.  `maps` of the shape that another kernel serves better keep it when they are large: at 8 M elements what it gains
+// (decompress_table 15 % on fp32 and 50-80 % on bfloat16 maps, decompress_units up to 30 %, decompress_lane 10 %) about equals what the
+// launch costs.
+int plan_mix(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat, uint64_t maps, DecShape* a, uint32_t* grid) {
+    DecArgs own{};
+    const int kind = plan_decompress(L, D, Hs, W, B, es, xhat, &own, grid);
+    if (kind != 7 && kind != 8 && kind != 9) {
+        if (kind == 0 || kind == 2 || maps * L.P * L.HW > (8u << 20) || !plan_any(L, D, Hs, W, B, es, xhat, grid)) return 0;
+        *a = own;
+        return L.nb == 1 ? 9 : 8;
+    }
+    *a = own;
+    return kind;
+}
+
 enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, SEG, WAVE, TILE, ONE, ROWS, PLANE, ANY };
 
 // everything a compress launch needs once the plan is made (the arguments of the kernel that was picked)
@@ -991,6 +1024,7 @@ struct CompLaunch {
     TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa;
     SegArgs sg; uint32_t seg_nt; int seg_K;      // kind SEG: threads, items per lane
 };
+struct MixLaunch { uint32_t grid; hipStream_t st; MixArgs a; };      // decompress_mixed
 struct DecLaunch {
     int kind, flat, nw;
     uint32_t gx, gy;
@@ -1098,10 +1132,8 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
         void (*kern)(DecArgs);
         if (kind == 7 || kind == 8 || kind == 9) {
             kern = c.flat ? decompress_stream<T, BITS> : decompress_stream_3d<T, BITS>;
-            if constexpr (sizeof(T) == 4) {                  // (the planner gives 2-byte maps kind 7 only)
-                if (kind == 9) kern = decompress_stream_one<T, BITS>;
-                else if (kind == 8) kern = c.flat ? decompress_stream_any<T, BITS> : decompress_stream_any_3d<T, BITS>;
-            }
+            if (kind == 9) kern = decompress_stream_one<T, BITS>;
+            else if (kind == 8) kern = c.flat ? decompress_stream_any<T, BITS> : decompress_stream_any_3d<T, BITS>;
             hipLaunchKernelGGL(kern, dim3(c.gx, c.gy), dim3(64), 0, c.st, c.a);
             return hipGetLastError();
         }
@@ -1131,6 +1163,15 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
     return b == 1 ? launch(std::integral_constant<int, 1>{}) : with_bits(b, launch);
 }
 
+template <typename T>
+hipError_t do_decompress_mixed(const MixLaunch& c, int b) {
+    auto launch = [&](auto bits) -> hipError_t {
+        hipLaunchKernelGGL((decompress_mixed<T, decltype(bits)::value>), dim3(c.grid), dim3(64), 0, c.st, c.a);
+        return hipGetLastError();
+    };
+    return b == 1 ? launch(std::integral_constant<int, 1>{}) : with_bits(b, launch);
+}
+
 // the Relu + compress kernels: the register kernel's planes (c.ra carries y and mask), c.kind == STRIP the
 // strip kernel's (c.sa) or, c.kind == ITEMS, the items kernel's (c.ia); one map per launch
 template <typename T>
@@ -1154,6 +1195,10 @@ hipError_t bridge_compress(division_dtype dt, const CompLaunch& c, int b) {
 hipError_t bridge_decompress(division_dtype dt, const DecLaunch& c, int b) {
     return dt == DIVISION_F32 ? division_bridge_decompress_f32(&c, b)
          : dt == DIVISION_BF16 ? division_bridge_decompress_bf16(&c, b) : division_bridge_decompress_c16(&c, b);
+}
+hipError_t bridge_decompress_mixed(division_dtype dt, const MixLaunch& c, int b) {
+    return dt == DIVISION_F32 ? division_bridge_decompress_mixed_f32(&c, b)
+         : dt == DIVISION_BF16 ? division_bridge_decompress_mixed_bf16(&c, b) : division_bridge_decompress_mixed_c16(&c, b);
 }
 hipError_t bridge_relu(division_dtype dt, const CompLaunch& c, int b) {
     return dt == DIVISION_F32 ? division_bridge_relu_f32(&c, b)
@@ -1309,6 +1354,39 @@ int decompress_impl(int count, const void* const* packed, void* const* xhat, siz
     }
     return DIVISION_OK;
 }
+
+// Launches that hold the maps of several shapes (one type and code width): shapes are added while they fit, then flushed.
+struct Mixer {
+    MixLaunch c{};
+    uint32_t nshape = 0, nmap = 0;
+    division_dtype dt = DIVISION_F32;
+    int b = 0;
+    bool fits(division_dtype d, int bits, size_t maps, uint64_t workgroups) const {
+        return nshape == 0 || (d == dt && bits == b && nshape < (uint32_t)kMixShapes && nmap + maps <= (size_t)kMixMaps && launch_ok(c.grid + workgroups, 64));
+    }
+    void add(division_dtype d, int bits, const Layout& L, bool flat, int kind, const DecShape& sh, uint32_t chunks, size_t maps,
+             const void* const* packed, void* const* xhat) {
+        if (nshape == 0) {
+            dt = d; b = bits;
+            c.grid = 0; nmap = 0;
+            for (int i = 0; i < kMixShapes; ++i) c.a.first[i] = 0xffffffffu;
+        }
+        MixShape& m = c.a.shape[nshape];
+        static_cast<DecShape&>(m) = sh;
+        m.meta_off = L.meta_off; m.lfc_off = L.lfc_off;
+        c.a.chunks[nshape] = chunks;
+        c.a.info[nshape] = (uint32_t)kind | (flat ? 16u : 0u) | nshape << 5 | nmap << 16;
+        c.a.first[nshape++] = c.grid;
+        for (size_t i = 0; i < maps; ++i) { c.a.pk[nmap] = packed[i]; c.a.xhat[nmap++] = xhat[i]; }
+        c.grid += chunks * (uint32_t)maps;
+    }
+    int flush(hipStream_t st) {
+        if (nshape == 0) return DIVISION_OK;
+        nshape = 0;
+        c.st = st;
+        return bridge_decompress_mixed(dt, c, b) == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+};
 
 int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int64_t D, int64_t H, int64_t W,
                      division_dtype dt, int B, int b, char* out, size_t cap) {

@@ -174,3 +174,52 @@ def test_a_value_that_is_not_finite_stays_in_its_block(shape, B, mode):
     for i, m in enumerate(nan):
         b0 = [v // B * B for v in np.argwhere(m.numpy())[0]]
         assert not bool(m.sum() > m[b0[0]:b0[0] + B, b0[1]:b0[1] + B, b0[2]:b0[2] + B].sum()), "the block's neighbours came back as NaN"
+
+
+# ---------------------------------------------------------------- maps of several shapes in one launch
+
+# rows of whole vectors (2-D, 3-D, 2-byte rows of half vectors), any width (2-D, 3-D; an odd number of elements; planes ending inside
+# vectors), one-block planes, and shapes that keep a launch of their own (rows or blocks below four)
+MIXED = [((2, 3, 28, 28), 8), ((3, 5, 14, 14), 8), ((5, 7, 7, 7), 8), ((1, 3, 55, 55), 8), ((2, 3, 12, 20), 12), ((1, 1, 13, 13), 8),
+         ((2, 3, 3, 9, 11), 4), ((2, 2, 4, 8, 8), 4), ((3, 3, 9, 3), 4), ((2, 2, 8, 8), 2), ((1, 5, 17, 9), 64), ((1, 7, 1, 197), 8),
+         ((2, 1, 1, 4100), 64), ((3, 1, 33, 65), 18), ((1, 2, 3, 35, 35), 8), ((4, 3, 5, 7), 4), ((2, 5, 9, 28), 4), ((2, 67, 2, 2), 8)]
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+def test_decompress_of_several_shapes_in_one_call(mode, b):
+    dtype, c16, dt = FORMATS[mode]
+    gen = torch.Generator().manual_seed(b)
+    specs = [s for k, s in enumerate(MIXED) for _ in range(1 + (k * 7 + b) % 4)]         # more maps and shapes than a launch holds
+    xs = [(torch.randn(s, generator=gen) * 1.5).to(dtype) for s, _ in specs]
+    Bs, bs = [B for _, B in specs], [b] * len(specs)
+    ref = [oracle.compress(_host(x), B, b, 50 + k, dt) for k, (x, B) in enumerate(zip(xs, Bs))]
+    packed = [torch.from_numpy(r).to("cuda:0") for r in ref]
+    bufs = [torch.full((x.numel() + 16,), -7.0, dtype=dtype, device="cuda:0") for x in xs]
+    out = [v[:x.numel()].view(x.shape) for v, x in zip(bufs, xs)]
+    pkg.division_decompress_maps(packed, [s for s, _ in specs], Bs, bs, dtype, out=out, c16=c16)
+    torch.cuda.synchronize()
+    for (shape, B), x, r, v in zip(specs, xs, ref, bufs):
+        want = np.asarray(oracle.decompress(r, shape, B, b, dt)).reshape(-1)
+        got = _host(v.cpu())
+        assert np.array_equal(got[:x.numel()].view(np.uint8), want.view(np.uint8)), (shape, B)
+        assert bool((v[x.numel():] == -7.0).all()), (shape, B)
+
+
+def test_decompress_of_maps_that_share_memory_keeps_their_order():
+    # the second map is rebuilt over the first one
+    gen = torch.Generator().manual_seed(1)
+    shapes = [((2, 3, 28, 28), 8), ((2, 3, 14, 14), 8), ((1, 2, 8, 8), 8)]
+    ref = [oracle.compress(torch.randn(s, generator=gen).numpy(), B, 2, 9, oracle.F32) for s, B in shapes]
+    area = torch.zeros(2 * 3 * 28 * 28, device="cuda:0")
+    last = torch.zeros(128, device="cuda:0")
+    pk = [torch.from_numpy(r).to("cuda:0") for r in ref]
+    outs = [area.view(2, 3, 28, 28), area[:1176].view(2, 3, 14, 14), last.view(1, 2, 8, 8)]
+    for _ in range(3):
+        area.zero_()
+        pkg.division_decompress_maps(pk, [s for s, _ in shapes], [B for _, B in shapes], 2, out=outs)
+        torch.cuda.synchronize()
+        want = np.asarray(oracle.decompress(ref[0], shapes[0][0], 8, 2, oracle.F32)).reshape(-1).copy()
+        want[:1176] = np.asarray(oracle.decompress(ref[1], shapes[1][0], 8, 2, oracle.F32)).reshape(-1)
+        assert np.array_equal(area.cpu().numpy(), want)
+        assert np.array_equal(last.cpu().numpy(), np.asarray(oracle.decompress(ref[2], shapes[2][0], 8, 2, oracle.F32)).reshape(-1))
