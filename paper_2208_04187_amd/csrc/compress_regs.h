@@ -8,7 +8,6 @@ struct RegsArgs {
     uint32_t P, H, W, HW, LH, LW, nb, WPP;
     uint32_t q4;         // units (4 consecutive elements) per plane = H*W/4
     uint32_t w4;         // units per row = W/4
-    uint32_t ppw;        // planes a workgroup handles one after the other
     uint32_t B;          // block size, read by the instance for any B (template argument 0) only
     FastDiv d_w4, d_LW, d_B, d_upb;      // d_upb divides by B / 4
     void* y;             // relu_compress_regs: the activation's output map and its 1-bit mask (one map per launch)
@@ -51,7 +50,9 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     float* red = lfcs + ((a.nb + 1 + 3) & ~3u);                        // [2*NW] cross-wave min / max
     double* zsum = reinterpret_cast<double*>(red + 2 * NW + 2);       // [nb*B] (3-D maps) one sum per block and depth slice
 
-    uint32_t blk[K];
+    constexpr bool PIPE = NW == 16;       // several planes per workgroup, see below
+    uint32_t blk[PIPE ? (K + 1) / 2 : K]; // each unit's block (PIPE: two to a register; nb is at most 13312)
+    auto block_of = [&](int k) -> uint32_t { return PIPE ? (k & 1 ? blk[k / 2] >> 16 : blk[k / 2] & 0xffffu) : blk[k]; };
     bool full_blocks = false;
     if constexpr (B != 0) full_blocks = (a.H % B) == 0 && (a.W % B) == 0 && (ND == 2 || (a.D % B) == 0);
     const uint32_t tid = threadIdx.x;
@@ -61,30 +62,38 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     auto round_live = [&](int k) -> bool { return FULL || (B != 0 && NW != 16 && ND == 2) || (uint32_t)(NT * k) < a.q4; };
 
     // One plane per workgroup (more workgroups, better balance than several planes each).  Which
-    // plane: see xcd_run_index.
-    const uint32_t p = xcd_run_index(blockIdx.x, a.P);
+    // plane: see xcd_run_index.  The sixteen-wavefront instances fill a CU alone, so nothing else there would read while
+    // they compute: a workgroup takes every grid-th plane, and as the codes of a unit leave, the next plane's unit is loaded
+    // into its registers: the volumes 32 x 64 x 16 x 56 x 56 119 -> 95 us (4.6 TB/s), 64 x 16 x 224 x 224 59 -> 48, in bfloat16 99 -> 74
+    // and 46 -> 36.  (The four-wavefront instances, several of which share a CU, lose by it: 64 x 128 x 8 x 28 x 28 45 -> 85.)
+    uint32_t p = PIPE ? blockIdx.x : xcd_run_index(blockIdx.x, a.P);
+    f32x4 x[K];                           // the units, from the load to the codes (2-byte elements: their two dwords in x and y at first)
+    auto plane_buffer = [&](uint32_t plane, bool there) {
+        const T* src = static_cast<const T*>(pt.x) + (size_t)plane * a.HW;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, there ? (int)(a.HW * sizeof(T)) : 0, 0x00020000);
+    };
+    auto load_unit = [&](const __amdgpu_buffer_rsrc_t& rsrc, int k) {
+        if constexpr (sizeof(T) == 4) {
+            x[k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, tid * 16u, k * NT * 16, kLoadAux));
+        } else {
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            const u32x2 h = __builtin_amdgcn_raw_buffer_load_b64(rsrc, tid * 8u, k * NT * 8, kLoadAux);
+            x[k].x = __uint_as_float(h.x); x[k].y = __uint_as_float(h.y);
+        }
+    };
+    // ---- load the plane first of all: coalesced, bounds-checked (units past the plane read as
+    // zero).  Everything the workgroup has to set up (the block of each unit, the sentinel)
+    // runs while the loads are in flight.
     {
-        // ---- load the plane first of all: coalesced, bounds-checked (units past the plane read as
-        // zero).  Everything the workgroup has to set up (the block of each unit, the sentinel)
-        // runs while the loads are in flight.
-        float x[K][4];
-        {
-            const T* src = static_cast<const T*>(pt.x) + (size_t)p * a.HW;
-            const __amdgpu_buffer_rsrc_t rsrc =
-                __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, (int)(a.HW * sizeof(T)), 0x00020000);
-            u32x4 q[K];
+        const __amdgpu_buffer_rsrc_t rsrc = plane_buffer(p, true);
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                q[k] = u32x4{0u, 0u, 0u, 0u};
-                if (!round_live(k)) continue;
-                if constexpr (sizeof(T) == 4) {
-                    q[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, tid * 16u, k * NT * 16, kLoadAux);
-                } else {
-                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                    const u32x2 h = __builtin_amdgcn_raw_buffer_load_b64(rsrc, tid * 8u, k * NT * 8, kLoadAux);
-                    q[k].x = h.x; q[k].y = h.y;
-                }
-            }
+        for (int k = 0; k < K; ++k) {
+            x[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (round_live(k)) load_unit(rsrc, k);
+        }
+    }
+    for (bool first = true;; first = false) {
+        if (first) {
             // which block each of the lane's units belongs to (nb = sentinel for units past the plane)
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -97,18 +106,17 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
                     bk = ((z / B) * a.LH + (row - z * a.H) / B) * a.LW + c4 / UPB;
                 } else if constexpr (B != 0) bk = (row / B) * a.LW + c4 / UPB;
                 else bk = fdiv(row, a.d_B) * a.LW + fdiv(c4, a.d_upb);
-                blk[k] = f < a.q4 ? bk : a.nb;
+                bk = f < a.q4 ? bk : a.nb;
+                if constexpr (!PIPE) blk[k] = bk;
+                else blk[k / 2] = k & 1 ? blk[k / 2] | bk << 16 : bk;
             }
             if (tid == 0) lfcs[a.nb] = __builtin_nanf("");
+        }
+        if constexpr (sizeof(T) == 2) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                if constexpr (sizeof(T) == 4) {
-                    x[k][0] = __uint_as_float(q[k].x); x[k][1] = __uint_as_float(q[k].y);
-                    x[k][2] = __uint_as_float(q[k].z); x[k][3] = __uint_as_float(q[k].w);
-                } else {
-                    x[k][0] = __uint_as_float(q[k].x << 16); x[k][1] = __uint_as_float(q[k].x & 0xffff0000u);
-                    x[k][2] = __uint_as_float(q[k].y << 16); x[k][3] = __uint_as_float(q[k].y & 0xffff0000u);
-                }
+                const uint32_t lo = __float_as_uint(x[k].x), hi = __float_as_uint(x[k].y);
+                x[k] = f32x4{__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u)};
             }
         }
         if constexpr (RELU) {
@@ -252,7 +260,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (!round_live(k)) continue;
-            const float lfc = lfcs[blk[k]];
+            const float lfc = lfcs[block_of(k)];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 x[k][e] = x[k][e] - lfc;
@@ -286,6 +294,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
             const __amdgpu_buffer_rsrc_t crs =
                 __builtin_amdgcn_make_buffer_rsrc(cbase, 0, (int)cbytes, 0x00020000);
             const uint32_t xw0 = k1 + (2u * tid) * kWeyl;
+            const __amdgpu_buffer_rsrc_t nrs = plane_buffer(p + gridDim.x, p + gridDim.x < a.P);      // (no next plane: nothing is fetched)
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (!round_live(k)) continue;
@@ -302,11 +311,15 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
                 } else if constexpr (CB == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, tid, k * NT, 0);
                 else if constexpr (CB == 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c, crs, tid * 2u, k * NT * 2, 0);
                 else __builtin_amdgcn_raw_buffer_store_b32(c, crs, tid * 4u, k * NT * 4, 0);
+                if constexpr (PIPE) load_unit(nrs, k);
             }
             // pad bytes of the plane's last word are zero
             const uint32_t padb = a.WPP * 4 - cbytes;
             if (tid < padb) cbase[cbytes + tid] = 0;
         }
+        if constexpr (!PIPE) break;
+        p += gridDim.x;
+        if (p >= a.P) break;
     }
 }
 

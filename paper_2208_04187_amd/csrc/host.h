@@ -141,14 +141,13 @@ bool plan_regs(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t e
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
     a->q4 = (uint32_t)q4; a->w4 = (uint32_t)w4;
-    a->ppw = 1;      // one plane per workgroup measured best (more workgroups, better balance)
     a->B = (uint32_t)B;
     a->d_w4 = make_fastdiv((uint32_t)w4);
     a->d_LW = make_fastdiv((uint32_t)L.LW);
     a->d_B = make_fastdiv((uint32_t)B);
     a->d_upb = make_fastdiv((uint32_t)B / 4);
     *lds = 8ull * kRegUnits * nt + 4ull * ((L.nb + 1 + 3) & ~3ull) + 8ull * nw + 16 + (D > 1 ? 8ull * L.nb * B + 16 : 0);
-    *grid = (uint32_t)((L.P + a->ppw - 1) / a->ppw);
+    *grid = (uint32_t)L.P;
     *nw_out = nw;
     return *lds <= (nw == 16 ? (size_t)kLdsMax : (size_t)(60u * 1024u));
 }
@@ -1305,6 +1304,11 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         else use_any();
         CompLaunch c{};
         if (kind == UNITS && plan_seg(L, D, H, W, B, es, &c.sg, &grid, &lds, &c.seg_nt, &c.seg_K)) { kind = SEG; c.sg.tab = tab; c.sg.rg = rg; }
+        // sixteen wavefronts per plane: a workgroup per CU, all maps together, each walking over its map's planes
+        if (kind == REGS && nw == 16) {
+            const uint32_t g = ((uint32_t)num_cus() + (uint32_t)cnt - 1) / (uint32_t)cnt;
+            grid = grid < g ? grid : g;
+        }
         c.kind = kind; c.B = B; c.vec = vec; c.nt = nt; c.nw = nw; c.flat = flat;
         c.gx = grid; c.gy = (uint32_t)cnt; c.lds = lds; c.st = st;
         c.sa = sa; c.a = a; c.wa = wa; c.ra = ra; c.ia = ia; c.la = la; c.wa2 = wa2; c.pa = pa; c.oa = oa; c.g = g; c.ua = ua;

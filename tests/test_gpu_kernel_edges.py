@@ -223,3 +223,20 @@ def test_decompress_of_maps_that_share_memory_keeps_their_order():
         want[:1176] = np.asarray(oracle.decompress(ref[1], shapes[1][0], 8, 2, oracle.F32)).reshape(-1)
         assert np.array_equal(area.cpu().numpy(), want)
         assert np.array_equal(last.cpu().numpy(), np.asarray(oracle.decompress(ref[2], shapes[2][0], 8, 2, oracle.F32)).reshape(-1))
+
+
+# planes of sixteen wavefronts: eight maps of 37 planes, more than there are workgroups, so that a workgroup takes several planes
+# (some one more than others) and loads the next one's units as the codes of the present one leave
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 8), ("bf16", 4), ("bf16", 1), ("c16", 2)])
+@pytest.mark.parametrize("shape,B", [((1, 37, 116, 116), 8), ((37, 1, 60, 240), 4), ((37, 1, 4, 60, 60), 8), ((1, 37, 8, 60, 100), 8)])
+def test_sixteen_wavefronts_over_several_planes(shape, B, mode, b):
+    dtype, c16, dt = FORMATS[mode]
+    name = _names(shape, B, b, mode)[0]
+    assert name.startswith("compress_regs") and name.endswith(", 16>"), name
+    gen = torch.Generator().manual_seed(b)
+    xs = [torch.randn(shape, generator=gen).to(dtype) for _ in range(8)]
+    seeds = [900 + k for k in range(8)]
+    packed = pkg.division_compress_maps([x.to("cuda:0") for x in xs], B, b, seeds, c16=c16)
+    torch.cuda.synchronize()
+    for x, s, p in zip(xs, seeds, packed):
+        assert np.array_equal(p.cpu().numpy(), oracle.compress(_host(x), B, b, s, dt, threads=16))
