@@ -19,6 +19,7 @@ MASKS = PKG / "csrc" / "masks.hip"
 SRCS = [DIVISION, MASKS]
 LIB = PKG / "libdivision.so"
 CHECKS = PKG.parent / "tests" / "device_checks.hip"          # device helpers on their own, for the tests
+FASTCALL = PKG / "_fastcall.so"                              # imported by binding.py
 CHECKS_LIB = CHECKS.with_name("libdevice_checks.so")
 # (object name, source, extra flags)
 UNITS = [
@@ -83,3 +84,22 @@ def build_checks() -> Path:
         raise RuntimeError("hipcc failed on %s:\n%s" % (CHECKS.name, res.stderr))
     os.replace(tmp, CHECKS_LIB)
     return CHECKS_LIB
+
+
+def build_fastcall() -> Path:
+    """The native side of binding.py (fastcall.cpp), against the headers and libraries of the torch that is installed."""
+    import sysconfig
+
+    import torch
+    root = Path(torch.__file__).resolve().parent
+    tmp = FASTCALL.with_name(FASTCALL.name + ".tmp%d" % os.getpid())
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I", str(root / "include"), "-I", str(root / "include" / "torch" / "csrc" / "api" / "include"),
+           "-I", sysconfig.get_paths()["include"], "-I", "/opt/rocm/include", "-o", str(tmp), str(PKG / "csrc" / "fastcall.cpp"),
+           "-L", str(root / "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        tmp.unlink(missing_ok=True)
+        raise RuntimeError("g++ failed on fastcall.cpp:\n" + res.stderr)
+    os.replace(tmp, FASTCALL)
+    return FASTCALL
