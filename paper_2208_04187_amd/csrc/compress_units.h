@@ -12,6 +12,7 @@ struct UnitsArgs {
     uint32_t nitem;      // nb * Bz * B row segments
     uint32_t S, S_log2;  // instance NW = 0: lanes per plane (8, 16 or 32), 64 / S planes per wavefront
     uint32_t reg_bytes;  // LDS bytes of one plane's region (a multiple of 16)
+    uint32_t J_log2;     // log2 of the lanes that add the rows of a block
     uint32_t nrounds;    // rounds of planes the grid walks over: P, or P / (64 / S) rounded up (NW = 0)
     FastDiv d_W, d_B, d_LW, d_H, d_BBz, d_slice;      // d_BBz divides by Bz * B, d_slice by LH * LW
 };
@@ -32,6 +33,11 @@ struct UnitsArgs {
 // NW = 1 .. 16: the NW wavefronts of the workgroup share one plane (S = 64 * NW).  NW = 0: small
 // planes (below 512 elements), S = 8, 16 or 32 lanes per plane and 64 / S planes per wavefront,
 // each with its own LDS region; reductions stay inside the S lanes.
+// What bounds it: vector instructions and, behind them, the chain of LDS round trips of a plane.  A workgroup takes one or
+// two planes of a map, so its tables weigh as much as the work: with the block looked up per element and for all eight rounds,
+// and one lane per block in the block sums, maps of 6 M elements took (us, before -> now) 27 x 27 under B = 64 17.6 -> 13.7, 35 x 35 under
+// B = 18 15.1 -> 12.1, 73 x 73 under B = 16 14.7 -> 12.8, 17 x 17 under B = 64 22.0 -> 18.5, 16 x 14 x 14 under B = 12 28.2 -> 17.4, 11 x 7 x 7 under
+// B = 8 22.7 -> 15.3; 55 x 55 in bfloat16 under B = 18 16.4 -> 13.1.
 constexpr int kUnitsK = 8;        // units, and row segments, per lane
 
 template <typename T, int BITS, int NW>
@@ -67,22 +73,49 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
     const uint32_t shift = sizeof(T) == 2 ? ((blockIdx.x * G + g) * a.HW) & 1u : 0u;
     const uint32_t shift0 = SUB ? 0u : shift;                             // of the round's first plane
 
-    // LDS byte offset of the LFC of each element's block (4 * nb = the sentinel for elements past the plane)
+    // LDS byte offset of the LFC of each element's block (4 * nb = the sentinel for elements past the plane).  Four
+    // consecutive elements enter another row, and another block of their row, at most once (W, B >= 3): the blocks of the
+    // first element and of the next row's start are looked up, the others follow.
     uint32_t lo[K][2];
+    const uint32_t allrows = a.D * a.H;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        if (!round_live(k)) continue;
+        const uint32_t e0 = 4u * (l + S * k);
         uint32_t off[4];
+        if (a.W >= 3 && a.B >= 3) {
+            const uint32_t ra = fdiv(e0, a.d_W), c = e0 - ra * a.W;      // row, counted over all depth slices
+            uint32_t r = ra, rn = ra + 1u, zb = 0, zbn = 0;
+            if (a.D > 1) {
+                const uint32_t z = fdiv(ra, a.d_H);
+                r = ra - z * a.H;
+                const bool wrap = r + 1u == a.H;
+                rn = wrap ? 0u : r + 1u;
+                zb = fdiv(z, a.d_B) * a.LH;
+                zbn = fdiv(wrap ? z + 1u : z, a.d_B) * a.LH;
+            }
+            const uint32_t bj = fdiv(c, a.d_B);
+            const bool past = ra >= allrows;
+            const uint32_t here = past ? a.nb : (zb + fdiv(r, a.d_B)) * a.LW + bj;
+            const uint32_t next = ra + 1u >= allrows ? a.nb : (zbn + fdiv(rn, a.d_B)) * a.LW;
+            const uint32_t left = past ? 4u : bj * a.B + a.B - c;         // elements to the block's right edge
+            const uint32_t rowleft = a.W - c;
+            off[0] = here;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t e = 4u * (l + S * k) + j;
-            const uint32_t ra = fdiv(e, a.d_W);                       // row, counted over all depth slices
-            const uint32_t c = e - ra * a.W;
-            const uint32_t z = fdiv(ra, a.d_H);
-            const uint32_t r = ra - z * a.H;
-            off[j] = 4u * (e < a.HW ? (fdiv(z, a.d_B) * a.LH + fdiv(r, a.d_B)) * a.LW + fdiv(c, a.d_B) : a.nb);
+            for (uint32_t j = 1; j < 4; ++j) off[j] = j < rowleft ? here + (j >= left ? 1u : 0u) : next;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t e = e0 + j;
+                const uint32_t ra = fdiv(e, a.d_W);
+                const uint32_t c = e - ra * a.W;
+                const uint32_t z = fdiv(ra, a.d_H);
+                const uint32_t r = ra - z * a.H;
+                off[j] = e < a.HW ? (fdiv(z, a.d_B) * a.LH + fdiv(r, a.d_B)) * a.LW + fdiv(c, a.d_B) : a.nb;
+            }
         }
-        lo[k][0] = off[0] | (off[1] << 16);
-        lo[k][1] = off[2] | (off[3] << 16);
+        lo[k][0] = (off[0] | (off[1] << 16)) << 2;
+        lo[k][1] = (off[2] | (off[3] << 16)) << 2;
     }
     // the row segments of the lane (item i = (block * Bz + slice of the block) * B + row of the block):
     // where the segment starts in the plane, and in the top bits how many elements it has (0: a row or
@@ -90,12 +123,18 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
     uint32_t it[K];
 #pragma unroll
     for (int m = 0; m < K; ++m) {
+        if (S * (uint32_t)m >= a.nitem) continue;
         const uint32_t i = l + S * m;
-        const uint32_t t = fdiv(i, a.d_BBz), rem = i - t * (a.Bz * a.B);
-        const uint32_t zz = fdiv(rem, a.d_B), rr = rem - zz * a.B;
-        const uint32_t bd = fdiv(t, a.d_slice), t2 = t - bd * (a.LH * a.LW);
+        const uint32_t t = fdiv(i, a.d_BBz);
+        uint32_t rr = i - t * (a.Bz * a.B), t2 = t, z = 0;
+        if (a.D > 1) {
+            const uint32_t zz = fdiv(rr, a.d_B), bd = fdiv(t, a.d_slice);
+            rr -= zz * a.B;
+            t2 -= bd * (a.LH * a.LW);
+            z = bd * a.B + zz;
+        }
         const uint32_t bi = fdiv(t2, a.d_LW), bj = t2 - bi * a.LW;
-        const uint32_t z = bd * a.B + zz, r = bi * a.B + rr;
+        const uint32_t r = bi * a.B + rr;
         const uint32_t bw = min(a.B, a.W - bj * a.B);
         it[m] = (i < a.nitem && z < a.D && r < a.H) ? ((z * a.H + r) * a.W + bj * a.B) | (bw << 20) : 0u;
     }
@@ -172,19 +211,35 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
         }
         sync();
 
-        // ---- step 2: a lane per block adds its rows, slice by slice from the top down
-        for (uint32_t t = l; t < a.nb; t += S) {
-            const uint32_t bd = fdiv(t, a.d_slice), t2 = t - bd * (a.LH * a.LW);
+        // ---- step 2: 2^J_log2 lanes per block (at most 16) add its rows, four reads in flight (rows and slices past the
+        // map hold 0); one lane per block, row by row, is a chain of up to B * Bz reads of LDS
+        const uint32_t J = 1u << a.J_log2, jl = l & (J - 1u);
+        for (uint32_t t = l >> a.J_log2; t < a.nb; t += S >> a.J_log2) {
+            uint32_t bd = 0, t2 = t;
+            if (a.D > 1) { bd = fdiv(t, a.d_slice); t2 = t - bd * (a.LH * a.LW); }
             const uint32_t bi = fdiv(t2, a.d_LW), bj = t2 - bi * a.LW;
             const uint32_t deps = min(a.Bz, a.D - bd * a.B);
             const uint32_t rows = min(a.B, a.H - bi * a.B);
             const uint32_t bw = min(a.B, a.W - bj * a.B);
+            const uint32_t n = (deps - 1u) * a.B + rows;
+            const double* rs = rsum + t * (a.Bz * a.B);
             double Sb = 0.0;
-            for (uint32_t zz = 0; zz < deps; ++zz)
-                for (uint32_t rr = 0; rr < rows; ++rr) Sb += rsum[(t * a.Bz + zz) * a.B + rr];
+            for (uint32_t u = jl; u < n; u += 4u * J) {
+                double v[4];
+#pragma unroll
+                for (uint32_t x = 0; x < 4; ++x) v[x] = rs[u + x * J < n ? u + x * J : u];
+#pragma unroll
+                for (uint32_t x = 0; x < 4; ++x) Sb += u + x * J < n ? v[x] : 0.0;
+            }
+            if (J > 1u) Sb += dpp_f64<kDppXor1>(Sb);
+            if (J > 2u) Sb += dpp_f64<kDppXor2>(Sb);
+            if (J > 4u) Sb += dpp_f64<kDppHalfMirror>(Sb);
+            if (J > 8u) Sb += dpp_f64<kDppMirror>(Sb);
             const float lfc = lfc_round<T>(mean_of(Sb, deps * rows * bw), kC16<T>);
-            lfcs[t] = lfc;
-            if (pv) lfc_store<T>(pt.lfc, (size_t)p * a.nb + t, lfc, kC16<T>);
+            if (jl == 0) {
+                lfcs[t] = lfc;
+                if (pv) lfc_store<T>(pt.lfc, (size_t)p * a.nb + t, lfc, kC16<T>);
+            }
         }
         sync();
 

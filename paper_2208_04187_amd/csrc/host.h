@@ -215,6 +215,10 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t 
     a->d_W = make_fastdiv((uint32_t)W);
     a->d_B = make_fastdiv((uint32_t)B);
     a->d_LW = make_fastdiv((uint32_t)L.LW);
+    // lanes per block in the block sums: as many as there are, at most 16, four rows and more for each
+    const uint64_t blockrows = (D > 1 ? (uint64_t)std::min<int64_t>(B, D) : 1) * (uint64_t)B;
+    a->J_log2 = 0;
+    while (a->J_log2 < 4 && (L.nb << (a->J_log2 + 1)) <= S && (8ull << a->J_log2) <= blockrows) ++a->J_log2;
     const uint64_t G = nw ? 1 : 64 / S;                       // planes per round
     const uint64_t reg = (16ull * q4p + 8ull * nitem + 4ull * ((L.nb + 1 + 3) & ~3ull) + 8ull * (nw ? nw : 1) + 16 + 15) & ~15ull;
     a->reg_bytes = (uint32_t)reg;

@@ -240,3 +240,15 @@ def test_sixteen_wavefronts_over_several_planes(shape, B, mode, b):
     torch.cuda.synchronize()
     for x, s, p in zip(xs, seeds, packed):
         assert np.array_equal(p.cpu().numpy(), oracle.compress(_host(x), B, b, s, dt, threads=16))
+
+
+# compress_units: the lookup of four elements at a time (rows that end anywhere inside them, widths and blocks of three, the last row,
+# the last slice) and of one (B = 2), one to sixteen lanes per block in the block sums, rounds of units and rows the plane does not have
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 4), ("bf16", 8), ("bf16", 1), ("c16", 2)])
+@pytest.mark.parametrize("shape,B", [((3, 5, 17, 17), 64), ((3, 5, 17, 17), 2), ((3, 3, 90, 3), 3), ((2, 3, 91, 3), 12), ((3, 3, 27, 27), 64), ((3, 3, 27, 27), 18),
+                                     ((2, 3, 13, 37), 5), ((2, 3, 65, 65), 64), ((2, 2, 73, 73), 3), ((3, 3, 11, 7, 7), 8), ((2, 3, 16, 14, 14), 12),
+                                     ((2, 2, 16, 28, 28), 16), ((2, 3, 9, 13, 3), 4), ((2, 3, 20, 21, 2), 4), ((2, 3, 2, 14, 14), 8), ((3, 3, 5, 9, 9), 2),
+                                     ((2, 2, 2, 28, 28), 12)])
+def test_units_block_lookup_and_block_sums(shape, B, mode, b):
+    assert _names(shape, B, b, mode)[0].startswith("compress_units<")
+    _round_trip(shape, B, b, mode)
