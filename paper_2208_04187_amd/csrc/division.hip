@@ -42,7 +42,7 @@
 //   compress_rows    any block size, small 3-D maps: chunk staged in LDS, vectors kept in registers for Quant
 //   compress_plane   planes beyond LDS with vector rows and blocks (video volumes, image-sized maps):
 //                    a workgroup per plane, two vector passes over x
-//   compress_any     everything else (giant planes with odd extents): scalar, slow
+//   compress_any     everything else (giant planes with odd extents, 1-bit codes of the shapes of compress_rows)
 //   decompress_mixed the wavefront-per-chunk kernels below over the maps of several shapes in one launch (division_decompress_maps)
 //   decompress_stream / decompress_stream_any / decompress_stream_one: one wavefront per 4 KB chunk of aligned vectors, no LDS:
 //                    rows of whole vectors inside one block (_stream), or any width where a vector may span two rows

@@ -1084,7 +1084,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
             default: {
                 void (*kern)(AnyArgs) = flat ? compress_any<T, 1> : compress_any_3d<T, 1>;
-                hipLaunchKernelGGL(kern, gd, dim3(kThreads), 0, st, c.g);
+                hipLaunchKernelGGL(kern, gd, dim3(c.nt), 0, st, c.g);
                 return hipGetLastError();
             }
         }
@@ -1119,7 +1119,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             }
             default: {
                 void (*kern)(AnyArgs) = flat ? compress_any<T, BITS> : compress_any_3d<T, BITS>;
-                hipLaunchKernelGGL(kern, gd, dim3(kThreads), 0, st, c.g);
+                hipLaunchKernelGGL(kern, gd, dim3(c.nt), 0, st, c.g);
                 return hipGetLastError();
             }
         }
@@ -1287,6 +1287,13 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
             g.P = (uint32_t)L.P; g.H = (uint32_t)H; g.W = (uint32_t)W; g.HW = (uint32_t)L.HW; g.D = (uint32_t)D;
             g.LH = (uint32_t)L.LH; g.LW = (uint32_t)L.LW; g.nb = (uint32_t)L.nb; g.WPP = (uint32_t)L.WPP; g.B = (uint32_t)B;
             grid = (uint32_t)L.P;
+            // a wavefront, four or sixteen per plane: one to sixteen rounds of four elements per lane; more lanes than 256 only
+            // where the launch still has fewer than 2^32
+            nt = L.HW <= 1024 ? 64 : L.HW <= 8192 || !launch_ok(L.P, 1024) ? kThreads : 1024;
+            // lanes per block: as many as there are, with a round of eight elements and more for each
+            const uint64_t elements = (uint64_t)std::min<int64_t>(B, W) * (uint64_t)std::min<int64_t>(B, H) * (uint64_t)std::min<int64_t>(B, D);
+            g.J_log2 = 0;
+            while (g.J_log2 < 6 && (L.nb << (g.J_log2 + 1)) <= (uint64_t)nt && (16ull << g.J_log2) <= elements) ++g.J_log2;
         };
         // 1-bit codes (Q = 1) have no instance of the wave, rows and plane kernels, nor of the units kernel with
         // sixteen wavefronts: the wave kernel's shapes go to the tile kernel, the others to the general kernel

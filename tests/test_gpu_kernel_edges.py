@@ -252,3 +252,16 @@ def test_sixteen_wavefronts_over_several_planes(shape, B, mode, b):
 def test_units_block_lookup_and_block_sums(shape, B, mode, b):
     assert _names(shape, B, b, mode)[0].startswith("compress_units<")
     _round_trip(shape, B, b, mode)
+
+
+# compress_any: workgroups of one, four and sixteen wavefronts, one to 64 lanes per block, lanes that share a word of codes (words that
+# end past the plane), rows and blocks of one and two elements, planes of an odd element count
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+@pytest.mark.parametrize("shape,B,b", [((3, 3, 6, 2), 3, 1), ((2, 3, 9, 1), 5, 1), ((2, 3, 28, 28), 3, 1), ((2, 3, 1, 768), 12, 1), ((2, 2, 1, 2475), 18, 1),
+                                       ((1, 2, 147, 147), 64, 1), ((2, 2, 147, 146), 18, 1), ((1, 2, 199, 199), 18, 2), ((1, 2, 203, 198), 64, 8),
+                                       ((1, 2, 201, 199), 2, 4), ((1, 1, 8200, 5), 64, 2), ((1, 1, 20000, 2), 64, 4), ((2, 3, 4, 7, 7), 4, 1),
+                                       ((1, 2, 8, 53, 53), 64, 1), ((1, 2, 33, 35, 37), 16, 2), ((1, 2, 33, 37, 33), 2, 4), ((1, 1, 150, 151, 2), 6, 8),
+                                       ((1, 2, 16, 57, 57), 4, 4)])
+def test_general_kernel_lanes_per_block(shape, B, b, mode):
+    assert _names(shape, B, b, mode)[0].startswith("compress_any")
+    _round_trip(shape, B, b, mode)
