@@ -38,7 +38,7 @@ constexpr int kRegUnits = 13;     // units per lane: planes of up to 13 * (threa
 // FULL: every one of the K rounds holds units of the plane, so no round is tested (a uniform test per
 // round puts each round into a basic block of its own that waits for every load; the instances that
 // must test because their planes may be short get a second copy of the body for planes that are not).
-template <typename T, int BITS, int B, int NW, bool RELU, int ND = 2, bool FULL = false>
+template <typename T, int BITS, int B, int NW, bool RELU, int ND = 2, bool FULL = false, bool PIPE = false>
 __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     constexpr int NT = 64 * NW;
     constexpr int K = kRegUnits;
@@ -50,7 +50,6 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     float* red = lfcs + ((a.nb + 1 + 3) & ~3u);                        // [2*NW] cross-wave min / max
     double* zsum = reinterpret_cast<double*>(red + 2 * NW + 2);       // [nb*B] (3-D maps) one sum per block and depth slice
 
-    constexpr bool PIPE = NW == 16;       // several planes per workgroup, see below
     uint32_t blk[PIPE ? (K + 1) / 2 : K]; // each unit's block (PIPE: two to a register; nb is at most 13312)
     auto block_of = [&](int k) -> uint32_t { return PIPE ? (k & 1 ? blk[k / 2] >> 16 : blk[k / 2] & 0xffffu) : blk[k]; };
     bool full_blocks = false;
@@ -65,7 +64,8 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     // plane: see xcd_run_index.  The sixteen-wavefront instances fill a CU alone, so nothing else there would read while
     // they compute: a workgroup takes every grid-th plane, and as the codes of a unit leave, the next plane's unit is loaded
     // into its registers: the volumes 32 x 64 x 16 x 56 x 56 119 -> 95 us (4.6 TB/s), 64 x 16 x 224 x 224 59 -> 48, in bfloat16 99 -> 74
-    // and 46 -> 36.  (The four-wavefront instances, several of which share a CU, lose by it: 64 x 128 x 8 x 28 x 28 45 -> 85.)
+    // and 46 -> 36.  A launch of no more planes than CUs takes the body without it (PIPE false: 255 volumes of 5 x 56 x 56 8.3 us, 10.9
+    // with it).  (The four-wavefront instances, several of which share a CU, lose by it: 64 x 128 x 8 x 28 x 28 45 -> 85.)
     uint32_t p = PIPE ? blockIdx.x : xcd_run_index(blockIdx.x, a.P);
     f32x4 x[K];                           // the units, from the load to the codes (2-byte elements: their two dwords in x and y at first)
     auto plane_buffer = [&](uint32_t plane, bool there) {
@@ -323,19 +323,25 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     }
 }
 
+template <typename T, int BITS, int B, int NW, int ND>
+__device__ __forceinline__ void compress_regs_rounds(const RegsArgs& a) {
+    const bool full = (uint32_t)(64 * NW * (kRegUnits - 1)) < a.q4;
+    if constexpr (NW == 16) {
+        if (gridDim.x < a.P) {
+            if (full) compress_regs_body<T, BITS, B, NW, false, ND, true, true>(a);
+            else compress_regs_body<T, BITS, B, NW, false, ND, false, true>(a);
+            return;
+        }
+    }
+    if (full) compress_regs_body<T, BITS, B, NW, false, ND, true>(a);
+    else compress_regs_body<T, BITS, B, NW, false, ND, false>(a);
+}
 template <typename T, int BITS, int B, int NW>
 __global__ void __launch_bounds__(64 * NW) compress_regs(RegsArgs a) {
-    if constexpr (B == 0 || NW == 16) {
-        if ((uint32_t)(64 * NW * (kRegUnits - 1)) < a.q4) compress_regs_body<T, BITS, B, NW, false, 2, true>(a);
-        else compress_regs_body<T, BITS, B, NW, false, 2, false>(a);
-    } else {
-        compress_regs_body<T, BITS, B, NW, false>(a);
-    }
+    if constexpr (B == 0 || NW == 16) compress_regs_rounds<T, BITS, B, NW, 2>(a);
+    else compress_regs_body<T, BITS, B, NW, false>(a);
 }
 template <typename T, int BITS, int B, int NW>
 __global__ void __launch_bounds__(64 * NW) relu_compress_regs(RegsArgs a) { compress_regs_body<T, BITS, B, NW, true>(a); }
 template <typename T, int BITS, int B, int NW>
-__global__ void __launch_bounds__(64 * NW) compress_regs_3d(RegsArgs a) {
-    if ((uint32_t)(64 * NW * (kRegUnits - 1)) < a.q4) compress_regs_body<T, BITS, B, NW, false, 3, true>(a);
-    else compress_regs_body<T, BITS, B, NW, false, 3, false>(a);
-}
+__global__ void __launch_bounds__(64 * NW) compress_regs_3d(RegsArgs a) { compress_regs_rounds<T, BITS, B, NW, 3>(a); }
