@@ -6,15 +6,15 @@ struct UnitsArgs {
     CompTab tab;
     Regions rg;
     uint32_t P, H, W, HW, LW, nb, WPP, B;      // H = rows of one depth slice
-    uint32_t D, LH, Bz;  // depth slices (1: a 2-D map), block rows per slice, depth of a block (B, or 1 for 2-D maps)
+    uint32_t D, LH, Br, Bz;      // depth slices (1: a 2-D map), block rows per slice, rows and depth of a block: B, or what the map has
     uint32_t q4;         // units (4 consecutive elements) per plane, the last one may be partly past it
     uint32_t q4p;        // q4 rounded up to whole rounds of the plane's lanes
-    uint32_t nitem;      // nb * Bz * B row segments
+    uint32_t nitem;      // nb * Bz * Br row segments
     uint32_t S, S_log2;  // instance NW = 0: lanes per plane (8, 16 or 32), 64 / S planes per wavefront
     uint32_t reg_bytes;  // LDS bytes of one plane's region (a multiple of 16)
     uint32_t J_log2;     // log2 of the lanes that add the rows of a block
     uint32_t nrounds;    // rounds of planes the grid walks over: P, or P / (64 / S) rounded up (NW = 0)
-    FastDiv d_W, d_B, d_LW, d_H, d_BBz, d_slice;      // d_BBz divides by Bz * B, d_slice by LH * LW
+    FastDiv d_W, d_B, d_Br, d_LW, d_H, d_BBz, d_slice;      // d_BBz divides by Bz * Br, d_slice by LH * LW
 };
 
 // Planes whose rows or blocks are not whole 16-byte vectors (odd widths: 55 x 55, 27 x 27,
@@ -31,17 +31,20 @@ struct UnitsArgs {
 // 3-D maps (Appendix D): planes of D x H x W elements with blocks of B x B x B; an element's block
 // and the row segments of a block are found with the depth as a third coordinate, the rest is the same.
 // NW = 1 .. 16: the NW wavefronts of the workgroup share one plane (S = 64 * NW).  NW = 0: small
-// planes (below 512 elements), S = 8, 16 or 32 lanes per plane and 64 / S planes per wavefront,
+// planes (32 to 511 elements), S = 8, 16 or 32 lanes per plane and 64 / S planes per wavefront,
 // each with its own LDS region; reductions stay inside the S lanes.
 // What bounds it: vector instructions and, behind them, the chain of LDS round trips of a plane.  A workgroup takes one or
 // two planes of a map, so its tables weigh as much as the work: with the block looked up per element and for all eight rounds,
 // and one lane per block in the block sums, maps of 6 M elements took (us, before -> now) 27 x 27 under B = 64 17.6 -> 13.7, 35 x 35 under
 // B = 18 15.1 -> 12.1, 73 x 73 under B = 16 14.7 -> 12.8, 17 x 17 under B = 64 22.0 -> 18.5, 16 x 14 x 14 under B = 12 28.2 -> 17.4, 11 x 7 x 7 under
 // B = 8 22.7 -> 15.3; 55 x 55 in bfloat16 under B = 18 16.4 -> 13.1.
+// Row segments only for the rows and slices a block has in the map (Br, Bz; before, B and B of them): maps of 4 M elements, 4 x 56 x 56 in
+// bfloat16 under B = 64 33.6 -> 14.5, 2 x 26 x 26 under B = 18 22.5 -> 12.5, 35 x 35 under B = 64 14.5 -> 10.6.
 constexpr int kUnitsK = 8;        // units, and row segments, per lane
 
+// (four wavefronts per SIMD: 128 registers, which is what the grid is sized for)
 template <typename T, int BITS, int NW>
-__global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a) {
+__global__ void __launch_bounds__(NW ? 64 * NW : 64, 4) compress_units(UnitsArgs a) {
     constexpr bool SUB = NW == 0;
     constexpr int NT = SUB ? 64 : 64 * NW;
     constexpr int K = kUnitsK;
@@ -117,7 +120,7 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
         lo[k][0] = (off[0] | (off[1] << 16)) << 2;
         lo[k][1] = (off[2] | (off[3] << 16)) << 2;
     }
-    // the row segments of the lane (item i = (block * Bz + slice of the block) * B + row of the block):
+    // the row segments of the lane (item i = (block * Bz + slice of the block) * Br + row of the block):
     // where the segment starts in the plane, and in the top bits how many elements it has (0: a row or
     // slice past the map, or no item)
     uint32_t it[K];
@@ -126,10 +129,10 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
         if (S * (uint32_t)m >= a.nitem) continue;
         const uint32_t i = l + S * m;
         const uint32_t t = fdiv(i, a.d_BBz);
-        uint32_t rr = i - t * (a.Bz * a.B), t2 = t, z = 0;
+        uint32_t rr = i - t * (a.Bz * a.Br), t2 = t, z = 0;
         if (a.D > 1) {
-            const uint32_t zz = fdiv(rr, a.d_B), bd = fdiv(t, a.d_slice);
-            rr -= zz * a.B;
+            const uint32_t zz = fdiv(rr, a.d_Br), bd = fdiv(t, a.d_slice);
+            rr -= zz * a.Br;
             t2 -= bd * (a.LH * a.LW);
             z = bd * a.B + zz;
         }
@@ -162,6 +165,10 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
     // a workgroup takes rounds blockIdx.x, blockIdx.x + gridDim.x, ...: the tables above are made once
     if (blockIdx.x < a.nrounds) issue_loads(blockIdx.x);
     for (uint32_t rd = blockIdx.x; rd < a.nrounds; rd += gridDim.x) {
+        // (NW = 0: what follows from the lane, S and the segments is not kept over the rounds: 166 registers, three wavefronts per SIMD
+        // where the grid counts on four)
+        uint32_t ln = l;
+        if constexpr (SUB) asm volatile("" : "+v"(ln));
         const uint32_t p = rd * G + g;
         const bool pv = p < a.P;                                          // (NW = 0) the last round may have fewer planes
         // ---- park the plane in LDS as fp32, then start the next round's loads: they fly while this one is worked on
@@ -176,11 +183,11 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
                                 __uint_as_float(q[k].y << 16), __uint_as_float(q[k].y & 0xffff0000u));
             }
             if (sizeof(T) == 2 && shift) {
-                float* d = xs + 4u * (l + S * k);
-                if (l + S * k != 0) d[-1] = v.x;
+                float* d = xs + 4u * (ln + S * k);
+                if (ln + S * k != 0) d[-1] = v.x;
                 d[0] = v.y; d[1] = v.z; d[2] = v.w;
             } else {
-                xs4[l + S * k] = v;
+                xs4[ln + S * k] = v;
             }
         }
         if (rd + gridDim.x < a.nrounds) issue_loads(rd + gridDim.x);
@@ -190,8 +197,10 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
 #pragma unroll
         for (int m = 0; m < K; ++m) {
             if (S * (uint32_t)m >= a.nitem) continue;
-            const uint32_t bw = it[m] >> 20;
-            const float* src = xs + (it[m] & 0xfffffu);
+            uint32_t seg = it[m];
+            if constexpr (SUB) asm volatile("" : "+v"(seg));
+            const uint32_t bw = seg >> 20;
+            const float* src = xs + (seg & 0xfffffu);
             double Sr = 0.0;
             uint32_t c = 0;
             for (; c + 8 <= bw; c += 8) {
@@ -207,22 +216,22 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
                 c += 4;
             }
             for (; c < bw; ++c) Sr += (double)src[c];
-            if (l + S * m < a.nitem) rsum[l + S * m] = Sr;
+            if (ln + S * m < a.nitem) rsum[ln + S * m] = Sr;
         }
         sync();
 
         // ---- step 2: 2^J_log2 lanes per block (at most 16) add its rows, four reads in flight (rows and slices past the
-        // map hold 0); one lane per block, row by row, is a chain of up to B * Bz reads of LDS
-        const uint32_t J = 1u << a.J_log2, jl = l & (J - 1u);
-        for (uint32_t t = l >> a.J_log2; t < a.nb; t += S >> a.J_log2) {
+        // map hold 0); one lane per block, row by row, is a chain of up to Br * Bz reads of LDS
+        const uint32_t J = 1u << a.J_log2, jl = ln & (J - 1u);
+        for (uint32_t t = ln >> a.J_log2; t < a.nb; t += S >> a.J_log2) {
             uint32_t bd = 0, t2 = t;
             if (a.D > 1) { bd = fdiv(t, a.d_slice); t2 = t - bd * (a.LH * a.LW); }
             const uint32_t bi = fdiv(t2, a.d_LW), bj = t2 - bi * a.LW;
             const uint32_t deps = min(a.Bz, a.D - bd * a.B);
             const uint32_t rows = min(a.B, a.H - bi * a.B);
             const uint32_t bw = min(a.B, a.W - bj * a.B);
-            const uint32_t n = (deps - 1u) * a.B + rows;
-            const double* rs = rsum + t * (a.Bz * a.B);
+            const uint32_t n = (deps - 1u) * a.Br + rows;
+            const double* rs = rsum + t * (a.Bz * a.Br);
             double Sb = 0.0;
             for (uint32_t u = jl; u < n; u += 4u * J) {
                 double v[4];
@@ -250,12 +259,12 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
         for (int k = 0; k < K; ++k) {
             if (!round_live(k)) continue;
             const char* lb = reinterpret_cast<const char*>(lfcs);
-            float4 v = xs4[l + S * k];
+            float4 v = xs4[ln + S * k];
             v.x -= *reinterpret_cast<const float*>(lb + (lo[k][0] & 0xffffu));
             v.y -= *reinterpret_cast<const float*>(lb + (lo[k][0] >> 16));
             v.z -= *reinterpret_cast<const float*>(lb + (lo[k][1] & 0xffffu));
             v.w -= *reinterpret_cast<const float*>(lb + (lo[k][1] >> 16));
-            xs4[l + S * k] = v;
+            xs4[ln + S * k] = v;
             mn = fminf(fminf(mn, v.x), fminf(v.y, fminf(v.z, v.w)));
             mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
         }
@@ -277,7 +286,7 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
         const float invs = inv * (float)(1u << (32 - BITS));
         const uint32_t k1 = mix32(p ^ pt.seed_a);
         const uint32_t k2 = mix32(k1 + pt.seed_c);
-        if (l == 0 && pv) meta_store(pt.meta, p, delta, Delta, kC16<T>);
+        if (ln == 0 && pv) meta_store(pt.meta, p, delta, Delta, kC16<T>);
 
         // ---- Quant + packing: a unit is two element pairs = 4 codes; a lane reads back the residuals it wrote
         {
@@ -290,37 +299,39 @@ __global__ void __launch_bounds__(NW ? 64 * NW : 64) compress_units(UnitsArgs a)
             uint8_t* cround = reinterpret_cast<uint8_t*>(pt.codes) + (size_t)pf * a.WPP * 4;
             const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
                 cround, 0, (int)(SUB ? min(G, a.P - pf) * a.WPP * 4u : cbytes), 0x00020000);
-            const uint32_t cvoff = g * a.WPP * 4u + l * CB;
-            const uint32_t cvoff1 = (l & 1u) ? 0x80000000u : g * a.WPP * 4u + (l >> 1);     // 1-bit codes: the odd lane stores nothing
+            const uint32_t cvoff = g * a.WPP * 4u + ln * CB;
+            const uint32_t cvoff1 = (ln & 1u) ? 0x80000000u : g * a.WPP * 4u + (ln >> 1);     // 1-bit codes: the odd lane stores nothing
             (void)cvoff1;
-            const uint32_t xw0 = k1 + (2u * l) * kWeyl;
+            const uint32_t xw0 = k1 + (2u * ln) * kWeyl;
             const uint32_t tailmask = tail ? (1u << (tail * BITS)) - 1u : 0xffffffffu;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (!round_live(k)) continue;
-                const float4 v = xs4[l + S * k];
+                const float4 v = xs4[ln + S * k];
                 const uint32_t xw = xw0 + (2u * S * (uint32_t)k) * kWeyl;
                 uint32_t c = push_pair<BITS>(0u, v.z, v.w, delta, invs, xw + kWeyl, k2, rscale);
                 c = push_pair<BITS>(c, v.x, v.y, delta, invs, xw, k2, rscale);
                 // the last unit's elements past the plane leave zero bits
-                if (l + S * k + 1 == a.q4) c &= tailmask;
+                if (ln + S * k + 1 == a.q4) c &= tailmask;
                 if constexpr (BITS == 1) {
                     // the four codes of a unit are half a byte: the even lane of a pair stores the byte of both
-                    // units (a unit past the plane contributes zeros, the odd lane's store is dropped)
-                    const bool in = l + S * k < a.q4;
+                    // units (a unit past the plane contributes zeros, the odd lane's store is dropped, and so is a byte behind
+                    // the plane's: by the buffer's end where it ends there)
+                    const bool in = ln + S * k < a.q4;
                     c = in ? c : 0u;
                     c |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xB1, 0xf, 0xf, true) << 4;   // quad_perm [1,0,3,2]
-                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, in ? cvoff1 + (uint32_t)(S * k / 2) : 0x80000000u, 0, 0);
+                    if constexpr (SUB) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, in ? cvoff1 + (uint32_t)(S * k / 2) : 0x80000000u, 0, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, cvoff1, (int)(S * k / 2), 0);
                     continue;
                 }
-                if (SUB && l + S * k >= a.q4) continue;
+                if (SUB && ln + S * k >= a.q4) continue;
                 if constexpr (CB == 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, crs, cvoff, (int)(S * k), 0);
                 else if constexpr (CB == 2) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)c, crs, cvoff, (int)(S * k * 2), 0);
                 else __builtin_amdgcn_raw_buffer_store_b32(c, crs, cvoff, (int)(S * k * 4), 0);
             }
             // pad bytes of the plane's last word are zero
             const uint32_t padb = a.WPP * 4 - cbytes;
-            if (l < padb && pv) cround[(size_t)g * a.WPP * 4 + cbytes + l] = 0;
+            if (ln < padb && pv) cround[(size_t)g * a.WPP * 4 + cbytes + ln] = 0;
         }
         sync();      // xs, rsum, lfcs and red are reused
     }

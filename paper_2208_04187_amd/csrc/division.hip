@@ -30,11 +30,11 @@
 //   compress_items   planes of at most 64 pooling items (28x28, 14x14, CIFAR shapes), B = 4, 8: a lane per
 //                    pooling item, loaded straight from global memory, DPP reductions (relu_compress_items:
 //                    the same with a Relu applied to the rows as they arrive)
-//   compress_units   planes (2-D or 3-D maps) of 256 to about 27K elements whose rows or blocks are not whole
+//   compress_units   planes (1-, 2- or 3-D maps) of 256 to about 27K elements (from 32 or 80 in maps of many planes) whose rows or blocks are not whole
 //                    16-byte vectors (odd widths: 27x27, 55x55, 147x147; B = 18): four consecutive elements per lane step
 //                    whatever the width, the block of each element looked up in a table made once per
 //                    workgroup, the plane parked in LDS for the block sums, next plane's loads in flight
-//   compress_seg     those of 4-byte elements under B = 4 and 8: sixteen elements of a block per item, loaded straight
+//   compress_seg     those of 4-byte elements under B = 4 and 8, even widths of maps of many planes among them: sixteen elements of a block per item, loaded straight
 //                    from global memory and kept in registers
 //   compress_wave    other planes up to 17 KB, B = 4, 8: one wavefront per chunk of planes staged in LDS
 //   compress_tile    other planes up to 156 KB, B = 4, 8: four wavefronts per chunk staged in LDS

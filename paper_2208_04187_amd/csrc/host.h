@@ -168,26 +168,35 @@ hipError_t launch_regs(int B, int nw, const RegsArgs& a, dim3 grid, size_t lds, 
 // Fills the plan of the register kernel for any width; false when the shape is not covered: 2-D maps
 // of at most 8 x 1024 units that fit LDS beside their row sums (up to about 163 x 163 elements).
 constexpr uint64_t kUnitsMin = 128;       // units per plane from which a plane gets a whole wavefront or more
-constexpr uint64_t kUnitsSubMin = 64;     // units per plane from which the instance with 16 or 32 lanes per plane is used
-                                          // (17 x 17: 1.7 -> 2.3 TB/s; 13 x 13 and 15 x 15 are no faster than in compress_wave)
-bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, const void* x,
+constexpr uint64_t kUnitsSubMin = 64;     // units per plane from which the instance with 8, 16 or 32 lanes per plane is used under B = 4
+                                          // and 8 in two dimensions (below, compress_wave is level or ahead: 14 x 5 under B = 8 11.5 us against 14.9)
+constexpr uint64_t kUnitsSubMinAny = 20;  // under other block sizes and in three dimensions, where compress_rows takes what is left: 13 x 13
+                                          // under B = 64 16.6 us there and 11.3 here, 2 x 7 x 7 under B = 12 17.8 and 15.1; level at 18 units (14 x 5)
+constexpr uint64_t kUnitsRowMin = 8;      // for maps of one row (maps of 4 M elements, against compress_wave: rows of 335 under B = 8 28.9 us
+                                          // and 11.9 here, 1521 under B = 4 30.9 and 14.1)
+constexpr uint64_t kUnitsManyPlanes = 256;      // planes (a CU each) from which maps of one row and small planes leave the chunk
+                                          // kernels (wave, rows): below, a launch is its latency in either
+bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x,
                 UnitsArgs* a, uint32_t* grid, size_t* lds, int* nw_out) {
-    if (H == 1 || ((uintptr_t)x % 4) != 0) return false;
+    if (((uintptr_t)x % 4) != 0 || (H == 1 && L.P < kUnitsManyPlanes)) return false;
     // small planes of even width under B = 4 and 8 are the wavefront kernel's (pairs of elements per
     // lane): measured faster there
-    if (D == 1 && (B == 4 || B == 8) && W % 2 == 0 && 4ull * L.HW + 16ull <= kWavePlaneMax) return false;
+    // (one row: only those a lane of the wavefront kernel, which takes B rows, would do little of)
+    if (D == 1 && H > 1 && (B == 4 || B == 8) && W % 2 == 0 && 4ull * L.HW + 16ull <= kWavePlaneMax) return false;
     const uint64_t q4 = (L.HW + 3) / 4;
     if (L.nb > 16383 || B > 4095) return false;              // LFC offsets are kept as 16-bit byte offsets
     // 2-D planes below 2048 elements with whole-vector rows: compress_rows keeps their vectors in registers
     // and is the faster one (28 x 28 under B = 12: 43 us against 49)
-    if (D == 1 && W % 4 == 0 && q4 < 512) return false;
-    const uint64_t Bz = D > 1 ? (uint64_t)B : 1;              // depth of a block
-    const uint64_t nitem = L.nb * Bz * (uint64_t)B;
+    // (not 1-bit codes of maps of one row, which the general kernel would get: rows of 96 under B = 12 45 us there, 15 here)
+    if (D == 1 && W % 4 == 0 && q4 < 512 && !(H == 1 && b == 1)) return false;
+    const uint64_t Bz = (uint64_t)std::min<int64_t>(B, D), Br = (uint64_t)std::min<int64_t>(B, H);      // depth and rows of a block
+    const uint64_t nitem = L.nb * Bz * Br;
     int nw = 1;
     uint64_t S = 64;                                          // lanes per plane
     if (q4 < kUnitsMin) {
         // small planes: 8, 16 or 32 lanes each, several planes per wavefront
-        if (q4 < kUnitsSubMin) return false;
+        const bool many = L.P >= kUnitsManyPlanes;
+        if (q4 < (!many ? kUnitsSubMin : H == 1 ? kUnitsRowMin : D == 1 && (B == 4 || B == 8) ? kUnitsSubMin : kUnitsSubMinAny)) return false;
         S = 8;
         while (S < 64 && (q4 > (uint64_t)kUnitsK * S || nitem > (uint64_t)kUnitsK * S)) S *= 2;
         nw = S < 64 ? 0 : 1;
@@ -199,14 +208,15 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t 
     if (q4 > (uint64_t)kUnitsK * S || nitem > (uint64_t)kUnitsK * S) return false;       // 8 units and 8 row segments per lane
     const uint64_t q4p = (q4 + S - 1) / S * S;
     if (!fastdiv_ok(4ull * kUnitsK * S + 4, (uint64_t)W) || !fastdiv_ok(4ull * kUnitsK * S + 4, (uint64_t)B) ||
-        !fastdiv_ok(nitem + S, (uint64_t)B * Bz) || !fastdiv_ok(L.nb + S, L.LH * L.LW) ||
+        !fastdiv_ok(nitem + S, Br * Bz) || !fastdiv_ok(L.nb + S, L.LH * L.LW) ||
         !fastdiv_ok(4ull * kUnitsK * S + 4, (uint64_t)H))
         return false;
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
-    a->D = (uint32_t)D; a->LH = (uint32_t)L.LH; a->Bz = (uint32_t)Bz;
+    a->D = (uint32_t)D; a->LH = (uint32_t)L.LH; a->Br = (uint32_t)Br; a->Bz = (uint32_t)Bz;
     a->d_H = make_fastdiv((uint32_t)H);
-    a->d_BBz = make_fastdiv((uint32_t)(Bz * (uint64_t)B));
+    a->d_Br = make_fastdiv((uint32_t)Br);
+    a->d_BBz = make_fastdiv((uint32_t)(Bz * Br));
     a->d_slice = make_fastdiv((uint32_t)(L.LH * L.LW));
     a->q4 = (uint32_t)q4; a->q4p = (uint32_t)q4p; a->nitem = (uint32_t)nitem;
     a->S = (uint32_t)S;
@@ -216,9 +226,8 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t 
     a->d_B = make_fastdiv((uint32_t)B);
     a->d_LW = make_fastdiv((uint32_t)L.LW);
     // lanes per block in the block sums: as many as there are, at most 16, four rows and more for each
-    const uint64_t blockrows = (D > 1 ? (uint64_t)std::min<int64_t>(B, D) : 1) * (uint64_t)B;
     a->J_log2 = 0;
-    while (a->J_log2 < 4 && (L.nb << (a->J_log2 + 1)) <= S && (8ull << a->J_log2) <= blockrows) ++a->J_log2;
+    while (a->J_log2 < 4 && (L.nb << (a->J_log2 + 1)) <= S && (8ull << a->J_log2) <= Bz * Br) ++a->J_log2;
     const uint64_t G = nw ? 1 : 64 / S;                       // planes per round
     const uint64_t reg = (16ull * q4p + 8ull * nitem + 4ull * ((L.nb + 1 + 3) & ~3ull) + 8ull * (nw ? nw : 1) + 16 + 15) & ~15ull;
     a->reg_bytes = (uint32_t)reg;
@@ -1305,7 +1314,7 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         else if (flat && plan_strip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = STRIP; sa.tab = tab; sa.rg = rg; }
         else if (flat && plan_rowstrip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = ROWSTRIP; sa.tab = tab; sa.rg = rg; }
         else if (flat && plan_items(L, H, W, B, es, xa, &ia, &grid, &lds, &vec)) { kind = ITEMS; ia.tab = tab; ia.rg = rg; }
-        else if (!one_shape(L, es, xa) && plan_units(L, D, H, W, B, es, xa, &ua, &grid, &lds, &nw) && (wide || nw != 16)) { kind = UNITS; ua.tab = tab; ua.rg = rg; }
+        else if (!one_shape(L, es, xa) && plan_units(L, D, H, W, B, b, es, xa, &ua, &grid, &lds, &nw) && (wide || nw != 16)) { kind = UNITS; ua.tab = tab; ua.rg = rg; }
         else if (wide && flat && plan_wave(L, H, W, B, b, es, xa, &wa, &grid, &lds, &vec)) {
             kind = WAVE; wa.tab = tab; wa.rg = rg;
         } else if (flat && plan_tile(L, H, W, B, b, es, xa, &a, &grid, &lds, &vec, &nt)) { kind = TILE; a.tab = tab; a.rg = rg; }
@@ -1433,7 +1442,7 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
             n = snprintf(out, cap, "compress_rowstrip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
         else if (flat && plan_items(L, H, W, B, es, data, &ia, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_items<%s, %d, %d, %d, %d>", tn, b, B, vec, H == 1 ? 1 : B);
-        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, es, data, &ua, &grid, &lds, &nw) && (wide || nw != 16)) {
+        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, b, es, data, &ua, &grid, &lds, &nw) && (wide || nw != 16)) {
             SegArgs sg{}; uint32_t seg_nt = 0; int seg_K = 0;
             if (plan_seg(L, D, H, W, B, es, &sg, &grid, &lds, &seg_nt, &seg_K))
                 n = snprintf(out, cap, "compress_seg<%s, %d, %d, %s, %d>", tn, b, B, W % 2 != 0 ? "true" : "false", seg_K);

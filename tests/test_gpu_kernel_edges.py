@@ -248,7 +248,9 @@ def test_sixteen_wavefronts_over_several_planes(shape, B, mode, b):
 @pytest.mark.parametrize("shape,B", [((3, 5, 17, 17), 64), ((3, 5, 17, 17), 2), ((3, 3, 90, 3), 3), ((2, 3, 91, 3), 12), ((3, 3, 27, 27), 64), ((3, 3, 27, 27), 18),
                                      ((2, 3, 13, 37), 5), ((2, 3, 65, 65), 64), ((2, 2, 73, 73), 3), ((3, 3, 11, 7, 7), 8), ((2, 3, 16, 14, 14), 12),
                                      ((2, 2, 16, 28, 28), 16), ((2, 3, 9, 13, 3), 4), ((2, 3, 20, 21, 2), 4), ((2, 3, 2, 14, 14), 8), ((3, 3, 5, 9, 9), 2),
-                                     ((2, 2, 2, 28, 28), 12)])
+                                     ((2, 2, 2, 28, 28), 12), ((3, 87, 1, 33), 8), ((3, 87, 1, 69), 4), ((2, 131, 1, 131), 18), ((1, 257, 1, 1521), 4),
+                                     ((1, 256, 1, 2049), 8), ((3, 87, 13, 13), 64), ((5, 53, 9, 9), 12), ((3, 87, 2, 7, 7), 12), ((3, 87, 3, 5, 7), 4),
+                                     ((2, 2, 4, 56, 56), 64)])
 def test_units_block_lookup_and_block_sums(shape, B, mode, b):
     assert _names(shape, B, b, mode)[0].startswith("compress_units<")
     _round_trip(shape, B, b, mode)
@@ -257,9 +259,8 @@ def test_units_block_lookup_and_block_sums(shape, B, mode, b):
 # compress_any: workgroups of one, four and sixteen wavefronts, one to 64 lanes per block, lanes that share a word of codes (words that
 # end past the plane), rows and blocks of one and two elements, planes of an odd element count
 @pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
-@pytest.mark.parametrize("shape,B,b", [((3, 3, 6, 2), 3, 1), ((2, 3, 9, 1), 5, 1), ((2, 3, 28, 28), 3, 1), ((2, 3, 1, 768), 12, 1), ((2, 2, 1, 2475), 18, 1),
-                                       ((1, 2, 147, 147), 64, 1), ((2, 2, 147, 146), 18, 1), ((1, 2, 199, 199), 18, 2), ((1, 2, 203, 198), 64, 8),
-                                       ((1, 2, 201, 199), 2, 4), ((1, 1, 8200, 5), 64, 2), ((1, 1, 20000, 2), 64, 4), ((2, 3, 4, 7, 7), 4, 1),
+@pytest.mark.parametrize("shape,B,b", [((3, 3, 6, 2), 3, 1), ((2, 3, 9, 1), 5, 1), ((2, 3, 28, 28), 3, 1), ((2, 3, 2, 768), 12, 1), ((1, 2, 147, 147), 64, 1), ((2, 2, 147, 146), 18, 1), ((1, 2, 199, 199), 18, 2), ((1, 2, 203, 198), 64, 8),
+                                       ((1, 2, 201, 199), 2, 4), ((1, 1, 8200, 5), 64, 2), ((1, 1, 20000, 2), 64, 4), ((2, 3, 3, 3, 5), 2, 1),
                                        ((1, 2, 8, 53, 53), 64, 1), ((1, 2, 33, 35, 37), 16, 2), ((1, 2, 33, 37, 33), 2, 4), ((1, 1, 150, 151, 2), 6, 8),
                                        ((1, 2, 16, 57, 57), 4, 4)])
 def test_general_kernel_lanes_per_block(shape, B, b, mode):
