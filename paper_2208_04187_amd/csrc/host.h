@@ -174,21 +174,33 @@ constexpr uint64_t kUnitsSubMinAny = 20;  // under other block sizes and in thre
                                           // under B = 64 16.6 us there and 11.3 here, 2 x 7 x 7 under B = 12 17.8 and 15.1; level at 18 units (14 x 5)
 constexpr uint64_t kUnitsRowMin = 8;      // for maps of one row (maps of 4 M elements, against compress_wave: rows of 335 under B = 8 28.9 us
                                           // and 11.9 here, 1521 under B = 4 30.9 and 14.1)
-constexpr uint64_t kUnitsManyPlanes = 256;      // planes (a CU each) from which maps of one row and small planes leave the chunk
+constexpr uint64_t kUnitsManyPlanes = 256;      // planes (a CU each) from which maps of one row, small planes and even widths leave the chunk
                                           // kernels (wave, rows): below, a launch is its latency in either
+bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, SegArgs* a, uint32_t* grid, size_t* lds,
+              uint32_t* nt_out, int* K_out);
 bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x,
                 UnitsArgs* a, uint32_t* grid, size_t* lds, int* nw_out) {
     if (((uintptr_t)x % 4) != 0 || (H == 1 && L.P < kUnitsManyPlanes)) return false;
     // small planes of even width under B = 4 and 8 are the wavefront kernel's (pairs of elements per
     // lane): measured faster there
     // (one row: only those a lane of the wavefront kernel, which takes B rows, would do little of)
-    if (D == 1 && H > 1 && (B == 4 || B == 8) && W % 2 == 0 && 4ull * L.HW + 16ull <= kWavePlaneMax) return false;
+    bool seg = false;
+    if (D == 1 && H > 1 && (B == 4 || B == 8) && W % 2 == 0 && 4ull * L.HW + 16ull <= kWavePlaneMax) {
+        // (4-byte elements, a plane for every CU: compress_seg where it takes them; 4 M elements of 57 x 70 under B = 4 36.2 -> 9.3 us,
+        // 19 x 46 under B = 8 14.3 -> 7.9, 42 x 18 11.1 -> 8.5, 63 x 32 9.8 -> 8.4, 116 x 12 level)
+        SegArgs t{};
+        uint32_t g = 0, nt = 0;
+        size_t l = 0;
+        int K = 0;
+        seg = b != 1 && L.P >= kUnitsManyPlanes && plan_seg(L, D, H, W, B, es, &t, &g, &l, &nt, &K);
+        if (!seg) return false;
+    }
     const uint64_t q4 = (L.HW + 3) / 4;
     if (L.nb > 16383 || B > 4095) return false;              // LFC offsets are kept as 16-bit byte offsets
     // 2-D planes below 2048 elements with whole-vector rows: compress_rows keeps their vectors in registers
     // and is the faster one (28 x 28 under B = 12: 43 us against 49)
     // (not 1-bit codes of maps of one row, which the general kernel would get: rows of 96 under B = 12 45 us there, 15 here)
-    if (D == 1 && W % 4 == 0 && q4 < 512 && !(H == 1 && b == 1)) return false;
+    if (D == 1 && W % 4 == 0 && q4 < 512 && !(H == 1 && b == 1) && !seg) return false;
     const uint64_t Bz = (uint64_t)std::min<int64_t>(B, D), Br = (uint64_t)std::min<int64_t>(B, H);      // depth and rows of a block
     const uint64_t nitem = L.nb * Bz * Br;
     int nw = 1;

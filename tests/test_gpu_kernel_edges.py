@@ -266,3 +266,11 @@ def test_units_block_lookup_and_block_sums(shape, B, mode, b):
 def test_general_kernel_lanes_per_block(shape, B, b, mode):
     assert _names(shape, B, b, mode)[0].startswith("compress_any")
     _round_trip(shape, B, b, mode)
+
+
+# compress_seg on planes of even widths (multiples of 4 and not, ragged block rows and columns), of 256 planes and more
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 8), ("c16", 4)])
+@pytest.mark.parametrize("shape,B", [((2, 130, 42, 18), 8), ((1, 257, 26, 70), 4), ((1, 256, 19, 46), 8), ((1, 256, 57, 70), 4)])
+def test_items_of_even_widths(shape, B, mode, b):
+    assert _names(shape, B, b, mode)[0].startswith("compress_seg<")
+    _round_trip(shape, B, b, mode)
