@@ -674,6 +674,8 @@ __global__ void __launch_bounds__(kThreads) decompress_words_3d(DecArgs a) { dec
 // every plane: a table of LDS offsets made once per workgroup, which then takes planes blockIdx.x,
 // blockIdx.x + gridDim.x, ...  A plane's LFC goes through LDS (two buffers, one barrier per plane);
 // the next plane's codes, LFC and meta are loaded while the current one is rebuilt.
+// What bounds it on maps of a few planes per workgroup: the table.  Looked up per element and for all eight rounds, maps of 4 M bfloat16 elements
+// took (us, the call's 7 us of host included) 35 x 35 9.9, 55 x 55 10.2, 147 x 147 9.8; per unit and for the rounds there are 7.7, 7.9, 8.0.
 constexpr int kUnitsLfc = 4;      // LFC values a lane stages per plane: planes of up to 4 * threads blocks
 template <typename T, int BITS, int NW>
 __global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) {
@@ -697,22 +699,47 @@ __global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) {
     // same for all planes of the workgroup: the grid is a multiple of 4, or every workgroup has one plane.
     const uint32_t shift = (blockIdx.x * a.HW) & 3u;
 
-    // LDS byte offset of the LFC of each element's block (elements outside the plane: block 0, never stored)
+    // LDS byte offset of the LFC of each element's block (elements outside the plane: any block, never stored).  As in
+    // compress_units: the blocks of the unit's first element and of the next row's start are looked up, the others follow.
     uint32_t lo[K][2];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
+        if (!round_live(k)) continue;
         uint32_t off[4];
+        if (a.W >= 3 && a.B >= 3) {
+            const uint32_t f = tid + NT * k, before = f ? 0u : shift;     // elements of the unit before the plane
+            const uint32_t e0 = f ? 4u * f - shift : 0u;
+            const uint32_t ra = fdiv(e0, a.d_W), c = e0 - ra * a.W;      // row, counted over all depth slices
+            uint32_t r = ra, rn = ra + 1u, zb = 0, zbn = 0;
+            if (a.Hs != a.H) {
+                const uint32_t z = fdiv(ra, a.d_Hs);
+                r = ra - z * a.Hs;
+                const bool wrap = r + 1u == a.Hs;
+                rn = wrap ? 0u : r + 1u;
+                zb = fdiv(z, a.d_B) * a.LHs;
+                zbn = fdiv(wrap ? z + 1u : z, a.d_B) * a.LHs;
+            }
+            const uint32_t bj = fdiv(c, a.d_B);
+            const uint32_t here = ra >= a.H ? 0u : (zb + fdiv(r, a.d_B)) * a.LW + bj;
+            const uint32_t next = ra + 1u >= a.H ? 0u : (zbn + fdiv(rn, a.d_B)) * a.LW;
+            const uint32_t left = ra >= a.H ? 8u : bj * a.B + a.B - c + before;      // elements of the unit to the block's right edge
+            const uint32_t rowleft = a.W - c + before;
+            off[0] = here;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t e = 4u * (tid + NT * k) + j - shift;       // wraps for the element before the plane
-            const uint32_t ra = fdiv(e, a.d_W);                       // row, counted over all depth slices
-            const uint32_t c = e - ra * a.W;
-            const uint32_t z = fdiv(ra, a.d_Hs);
-            const uint32_t r = ra - z * a.Hs;
-            off[j] = e < a.HW ? 4u * ((fdiv(z, a.d_B) * a.LHs + fdiv(r, a.d_B)) * a.LW + fdiv(c, a.d_B)) : 0u;
+            for (uint32_t j = 1; j < 4; ++j) off[j] = j < rowleft ? here + (j >= left ? 1u : 0u) : next;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t e = 4u * (tid + NT * k) + j - shift;       // wraps for the element before the plane
+                const uint32_t ra = fdiv(e, a.d_W);
+                const uint32_t c = e - ra * a.W;
+                const uint32_t z = fdiv(ra, a.d_Hs);
+                const uint32_t r = ra - z * a.Hs;
+                off[j] = e < a.HW ? (fdiv(z, a.d_B) * a.LHs + fdiv(r, a.d_B)) * a.LW + fdiv(c, a.d_B) : 0u;
+            }
         }
-        lo[k][0] = off[0] | (off[1] << 16);
-        lo[k][1] = off[2] | (off[3] << 16);
+        lo[k][0] = (off[0] | (off[1] << 16)) << 2;
+        lo[k][1] = (off[2] | (off[3] << 16)) << 2;
     }
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     u32x2 wide[K];      // .x: the unit's codes as loaded; shifted units: the two code words the unit's codes lie in
