@@ -21,6 +21,8 @@ LIB = PKG / "libdivision.so"
 CHECKS = PKG.parent / "tests" / "device_checks.hip"          # device helpers on their own, for the tests
 FASTCALL = PKG / "_fastcall.so"                              # imported by binding.py
 CHECKS_LIB = CHECKS.with_name("libdevice_checks.so")
+HOST_CHECKS = CHECKS.with_name("host_checks.hip")            # the launches that the library plans, for the tests
+HOST_CHECKS_LIB = HOST_CHECKS.with_name("libhost_checks.so")
 # (object name, source, extra flags)
 UNITS = [
     ("division_f32.o", DIVISION, ["-DDIVISION_PART=0"]),
@@ -75,14 +77,15 @@ def build(verbose: bool = False, extra_flags=(), out: Path | None = None) -> Pat
 
 
 def build_checks() -> Path:
-    """The tests' library of device helpers (device_checks.hip)."""
-    tmp = CHECKS_LIB.with_name(CHECKS_LIB.name + ".tmp%d" % os.getpid())
-    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, "-shared", "-o", str(tmp), str(CHECKS)]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        tmp.unlink(missing_ok=True)
-        raise RuntimeError("hipcc failed on %s:\n%s" % (CHECKS.name, res.stderr))
-    os.replace(tmp, CHECKS_LIB)
+    """The tests' libraries: device helpers on their own (device_checks.hip), planned launches (host_checks.hip)."""
+    for src, lib in ((CHECKS, CHECKS_LIB), (HOST_CHECKS, HOST_CHECKS_LIB)):
+        tmp = lib.with_name(lib.name + ".tmp%d" % os.getpid())
+        cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, "-shared", "-Wl,-Bsymbolic", "-o", str(tmp), str(src)]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            tmp.unlink(missing_ok=True)
+            raise RuntimeError("hipcc failed on %s:\n%s" % (src.name, res.stderr))
+        os.replace(tmp, lib)
     return CHECKS_LIB
 
 

@@ -9,6 +9,7 @@ struct RegsArgs {
     uint32_t q4;         // units (4 consecutive elements) per plane = H*W/4
     uint32_t w4;         // units per row = W/4
     uint32_t B;          // block size, read by the instance for any B (template argument 0) only
+    uint32_t maps;       // sixteen wavefronts: maps whose planes the workgroups walk over together, or 0 (a workgroup per plane)
     FastDiv d_w4, d_LW, d_B, d_upb;      // d_upb divides by B / 4
     void* y;             // relu_compress_regs: the activation's output map and its 1-bit mask (one map per launch)
     uint32_t* mask;
@@ -37,7 +38,8 @@ constexpr int kRegUnits = 13;     // units per lane: planes of up to 13 * (threa
 // units of a block are found with the depth as a third coordinate, everything else is the same.
 // FULL: every one of the K rounds holds units of the plane, so no round is tested (a uniform test per
 // round puts each round into a basic block of its own that waits for every load; the instances that
-// must test because their planes may be short get a second copy of the body for planes that are not).
+// must test because their planes may be short get a second copy of the body for planes that are not; the walk over
+// several planes has no tested copy: rounds past the plane load zeros and store nothing).
 template <typename T, int BITS, int B, int NW, bool RELU, int ND = 2, bool FULL = false, bool PIPE = false>
 __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     constexpr int NT = 64 * NW;
@@ -55,21 +57,25 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     bool full_blocks = false;
     if constexpr (B != 0) full_blocks = (a.H % B) == 0 && (a.W % B) == 0 && (ND == 2 || (a.D % B) == 0);
     const uint32_t tid = threadIdx.x;
-    const CompPtrs pt = comp_ptrs(a.tab, a.rg, tid);
+    // PIPE: planes blockIdx.x, blockIdx.x + gridDim.x, ... of all maps one after the other; map ti, its plane p
+    uint32_t ti = PIPE ? 0u : blockIdx.y, p = blockIdx.x;
+    auto to_map = [&](uint32_t& map, uint32_t& plane) { while (plane >= a.P) { plane -= a.P; ++map; } };
+    if constexpr (PIPE) to_map(ti, p);
+    else p = xcd_run_index(p, a.P);
+    if constexpr (!PIPE) { if (blockIdx.x == 0) zero_pads(a.tab, a.rg, ti, tid); }
     // rounds of units a plane has (uniform); the one- and four-wavefront instances for B = 4 and 8
     // always run all K (their planes fill at least eight of them)
     auto round_live = [&](int k) -> bool { return FULL || (B != 0 && NW != 16 && ND == 2) || (uint32_t)(NT * k) < a.q4; };
 
     // One plane per workgroup (more workgroups, better balance than several planes each).  Which
     // plane: see xcd_run_index.  The sixteen-wavefront instances fill a CU alone, so nothing else there would read while
-    // they compute: a workgroup takes every grid-th plane, and as the codes of a unit leave, the next plane's unit is loaded
-    // into its registers: the volumes 32 x 64 x 16 x 56 x 56 119 -> 95 us (4.6 TB/s), 64 x 16 x 224 x 224 59 -> 48, in bfloat16 99 -> 74
-    // and 46 -> 36.  A launch of no more planes than CUs takes the body without it (PIPE false: 255 volumes of 5 x 56 x 56 8.3 us, 10.9
-    // with it).  (The four-wavefront instances, several of which share a CU, lose by it: 64 x 128 x 8 x 28 x 28 45 -> 85.)
-    uint32_t p = PIPE ? blockIdx.x : xcd_run_index(blockIdx.x, a.P);
+    // they compute: where the launch has more planes than CUs (regs_walk) a workgroup takes every grid-th plane of all maps, and as the
+    // codes of a unit leave, the next plane's unit is loaded
+    // into its registers: the volumes 32 x 64 x 16 x 56 x 56 119 -> 95 us (4.6 TB/s), 64 x 16 x 224 x 224 59 -> 48, in bfloat16 99 -> 73
+    // and 46 -> 36.  (The four-wavefront instances, several of which share a CU, lose by it: 64 x 128 x 8 x 28 x 28 45 -> 85.)
     f32x4 x[K];                           // the units, from the load to the codes (2-byte elements: their two dwords in x and y at first)
-    auto plane_buffer = [&](uint32_t plane, bool there) {
-        const T* src = static_cast<const T*>(pt.x) + (size_t)plane * a.HW;
+    auto plane_buffer = [&](const void* map, uint32_t plane, bool there) {
+        const T* src = static_cast<const T*>(map) + (size_t)plane * a.HW;
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, there ? (int)(a.HW * sizeof(T)) : 0, 0x00020000);
     };
     auto load_unit = [&](const __amdgpu_buffer_rsrc_t& rsrc, int k) {
@@ -85,7 +91,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     // zero).  Everything the workgroup has to set up (the block of each unit, the sentinel)
     // runs while the loads are in flight.
     {
-        const __amdgpu_buffer_rsrc_t rsrc = plane_buffer(p, true);
+        const __amdgpu_buffer_rsrc_t rsrc = plane_buffer(a.tab.x[ti], p, true);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             x[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -93,6 +99,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
         }
     }
     for (bool first = true;; first = false) {
+        const CompPtrs pt = comp_ptrs_of(a.tab, a.rg, ti);
         if (first) {
             // which block each of the lane's units belongs to (nb = sentinel for units past the plane)
 #pragma unroll
@@ -285,6 +292,9 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
         if (tid == 0) meta_store(pt.meta, p, delta, Delta, kC16<T>);
         keep_in_vgpr(delta, invs, k2);
 
+        uint32_t nti = ti, np = p + gridDim.x;                       // PIPE: the next plane
+        if constexpr (PIPE) to_map(nti, np);
+        const bool there = PIPE && nti < a.maps;
         // ---- Quant + packing: a unit is two element pairs = 4 codes (one byte for b = 2, a word for b = 8)
         {
             const uint32_t rscale = 1u << (16 - BITS);
@@ -294,7 +304,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
             const __amdgpu_buffer_rsrc_t crs =
                 __builtin_amdgcn_make_buffer_rsrc(cbase, 0, (int)cbytes, 0x00020000);
             const uint32_t xw0 = k1 + (2u * tid) * kWeyl;
-            const __amdgpu_buffer_rsrc_t nrs = plane_buffer(p + gridDim.x, p + gridDim.x < a.P);      // (no next plane: nothing is fetched)
+            const __amdgpu_buffer_rsrc_t nrs = plane_buffer(a.tab.x[there ? nti : 0u], there ? np : 0u, there);      // (no next plane: nothing is fetched)
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (!round_live(k)) continue;
@@ -317,9 +327,10 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
             const uint32_t padb = a.WPP * 4 - cbytes;
             if (tid < padb) cbase[cbytes + tid] = 0;
         }
-        if constexpr (!PIPE) break;
-        p += gridDim.x;
-        if (p >= a.P) break;
+        if constexpr (PIPE) { if (p == 0) zero_pads(a.tab, a.rg, ti, tid); }
+        if (!there) break;
+        ti = nti;
+        p = np;
     }
 }
 
@@ -327,11 +338,7 @@ template <typename T, int BITS, int B, int NW, int ND>
 __device__ __forceinline__ void compress_regs_rounds(const RegsArgs& a) {
     const bool full = (uint32_t)(64 * NW * (kRegUnits - 1)) < a.q4;
     if constexpr (NW == 16) {
-        if (gridDim.x < a.P) {
-            if (full) compress_regs_body<T, BITS, B, NW, false, ND, true, true>(a);
-            else compress_regs_body<T, BITS, B, NW, false, ND, false, true>(a);
-            return;
-        }
+        if (a.maps) { compress_regs_body<T, BITS, B, NW, false, ND, true, true>(a); return; }
     }
     if (full) compress_regs_body<T, BITS, B, NW, false, ND, true>(a);
     else compress_regs_body<T, BITS, B, NW, false, ND, false>(a);

@@ -73,7 +73,8 @@
 
 // The kernels are instantiated per element / cache type (float, bf16_t, f32c16_t).  To build the
 // library in parallel this file can be compiled three times with -DDIVISION_PART=0, 1, 2: each part
-// instantiates the kernels of one type behind three bridge functions, part 0 also holds the C ABI.
+// instantiates the kernels of one type behind four bridge functions, part 0 also holds the C ABI; part 3
+// is the C ABI alone, for a test that stands in for the bridges and reads the planned launches.
 // Without the macro one translation unit holds everything.
 #if !defined(DIVISION_PART)
 #define DIVISION_HOST 1
@@ -81,7 +82,7 @@
 #define DIVISION_HAS_BF16 1
 #define DIVISION_HAS_C16 1
 #else
-#define DIVISION_HOST (DIVISION_PART == 0)
+#define DIVISION_HOST (DIVISION_PART == 0 || DIVISION_PART == 3)
 #define DIVISION_HAS_F32 (DIVISION_PART == 0)
 #define DIVISION_HAS_BF16 (DIVISION_PART == 1)
 #define DIVISION_HAS_C16 (DIVISION_PART == 2)

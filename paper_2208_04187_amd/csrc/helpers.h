@@ -180,15 +180,10 @@ struct DecTab { const void* pk[kMaxBatch]; void* xhat[kMaxBatch]; };
 // after them that must read as zero (each shorter than 16 bytes).
 struct Regions { size_t meta_off, lfc_off; size_t pad_off[3]; uint32_t pad_len[3]; };
 
-// this workgroup's tensor
+// the parts of map ti of the table
 struct CompPtrs { const void* x; uint32_t* codes; float* meta; void* lfc; uint32_t seed_a, seed_c; };
-__device__ __forceinline__ CompPtrs comp_ptrs(const CompTab& tab, const Regions& rg, uint32_t tid) {
-    const uint32_t ti = blockIdx.y;
+__device__ __forceinline__ CompPtrs comp_ptrs_of(const CompTab& tab, const Regions& rg, uint32_t ti) {
     char* pk = static_cast<char*>(tab.pk[ti]);
-    if (blockIdx.x == 0 && tid < 48) {
-        const uint32_t k = tid >> 4, j = tid & 15u;
-        if (j < rg.pad_len[k]) pk[rg.pad_off[k] + j] = 0;
-    }
     CompPtrs pt;
     pt.x = tab.x[ti];
     pt.codes = reinterpret_cast<uint32_t*>(pk);
@@ -197,6 +192,19 @@ __device__ __forceinline__ CompPtrs comp_ptrs(const CompTab& tab, const Regions&
     pt.seed_a = tab.seed_a[ti];
     pt.seed_c = tab.seed_c[ti];
     return pt;
+}
+// the bytes between and behind the regions of map ti read as zero
+__device__ __forceinline__ void zero_pads(const CompTab& tab, const Regions& rg, uint32_t ti, uint32_t tid) {
+    if (tid < 48) {
+        const uint32_t k = tid >> 4, j = tid & 15u;
+        if (j < rg.pad_len[k]) static_cast<char*>(tab.pk[ti])[rg.pad_off[k] + j] = 0;
+    }
+}
+// this workgroup's tensor
+__device__ __forceinline__ CompPtrs comp_ptrs(const CompTab& tab, const Regions& rg, uint32_t tid) {
+    const uint32_t ti = blockIdx.y;
+    if (blockIdx.x == 0) zero_pads(tab, rg, ti, tid);
+    return comp_ptrs_of(tab, rg, ti);
 }
 struct DecPtrs { const uint32_t* codes; const float* meta; const void* lfc; void* xhat; };
 __device__ __forceinline__ DecPtrs dec_ptrs(const DecTab& tab, const Regions& rg) {

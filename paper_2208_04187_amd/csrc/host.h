@@ -152,6 +152,19 @@ bool plan_regs(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t e
     return *lds <= (nw == 16 ? (size_t)kLdsMax : (size_t)(60u * 1024u));
 }
 
+// Whether a workgroup per CU walks over the planes of all maps of a launch of sixteen-wavefront instances, loading the next
+// plane as the codes of the present one leave, or each plane has a workgroup of its own.  A workgroup fills its CU, so one more
+// than there are CUs would wait until others have walked to their end: the walk is over all maps together (a grid per map,
+// rounded up, made 3, 5, 6 and 7 maps 1.25-1.5 times slower: 3 maps of 64 x 16 x 224 x 224 55.4 us each with a workgroup per
+// plane, 69.2 so, 43.5 together).  The walk runs all thirteen rounds of units untested, so planes of fewer rounds want fewer of
+// them wasted or more planes to overlap (fp32 / bfloat16, a workgroup per plane -> walk): 257 planes of 12.2 rounds 23.9 -> 21.6 / 20.9 -> 18.7,
+// of 10.6 rounds 20.5 -> 19.4 / 18.5 -> 18.3, of 8.3 rounds 17.7 -> 18.0 / 16.7 -> 18.0; 1024 planes of 8.3 rounds 42.9 -> 39.5 / 34.3 -> 33.8,
+// of 6.2 rounds 34.8 -> 33.2 / 28.9 -> 32.3.
+bool regs_walk(uint64_t planes, uint64_t q4) {
+    const uint64_t cus = (uint64_t)num_cus(), round = 1024;
+    return q4 > 10 * round ? planes > cus : q4 > 8 * round && planes >= 4 * cus;
+}
+
 template <typename T, int BITS>
 hipError_t launch_regs(int B, int nw, const RegsArgs& a, dim3 grid, size_t lds, hipStream_t st) {
     void (*kern)(RegsArgs);
@@ -1336,13 +1349,10 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         else use_any();
         CompLaunch c{};
         if (kind == UNITS && plan_seg(L, D, H, W, B, es, &c.sg, &grid, &lds, &c.seg_nt, &c.seg_K)) { kind = SEG; c.sg.tab = tab; c.sg.rg = rg; }
-        // sixteen wavefronts per plane: a workgroup per CU, all maps together, each walking over its map's planes
-        if (kind == REGS && nw == 16) {
-            const uint32_t g = ((uint32_t)num_cus() + (uint32_t)cnt - 1) / (uint32_t)cnt;
-            grid = grid < g ? grid : g;
-        }
+        uint32_t rows = (uint32_t)cnt;                            // of the grid: the maps, or one where the workgroups walk over all of them
+        if (kind == REGS && nw == 16 && regs_walk(L.P * (uint64_t)cnt, L.HW / 4)) { ra.maps = rows; rows = 1; grid = (uint32_t)num_cus(); }
         c.kind = kind; c.B = B; c.vec = vec; c.nt = nt; c.nw = nw; c.flat = flat;
-        c.gx = grid; c.gy = (uint32_t)cnt; c.lds = lds; c.st = st;
+        c.gx = grid; c.gy = rows; c.lds = lds; c.st = st;
         c.sa = sa; c.a = a; c.wa = wa; c.ra = ra; c.ia = ia; c.la = la; c.wa2 = wa2; c.pa = pa; c.oa = oa; c.g = g; c.ua = ua;
         const hipError_t err = bridge_compress(dt, c, b);
         if (err != hipSuccess) return DIVISION_EHIP;

@@ -242,6 +242,23 @@ def test_sixteen_wavefronts_over_several_planes(shape, B, mode, b):
         assert np.array_equal(p.cpu().numpy(), oracle.compress(_host(x), B, b, s, dt, threads=16))
 
 
+# the walk over the planes of several maps: maps that begin in the middle of a workgroup's stride, more than one map between two planes
+# of a workgroup, planes that do not fill the last rounds of units, pad bytes of every map
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 1), ("bf16", 2), ("bf16", 1), ("bf16", 8), ("c16", 4)])
+@pytest.mark.parametrize("shape,B,maps", [((1, 87, 224, 224), 8, 3), ((1, 51, 204, 204), 4, 7), ((1, 53, 16, 56, 56), 8, 5), ((1, 150, 9, 68, 68), 8, 2), ((1, 300, 224, 224), 4, 1)])
+def test_sixteen_wavefronts_walk_over_several_maps(shape, B, maps, mode, b):
+    dtype, c16, dt = FORMATS[mode]
+    gen = torch.Generator().manual_seed(b)
+    xs = [torch.randn(shape, generator=gen).to(dtype) for _ in range(maps)]
+    seeds = [77 + 3 * k for k in range(maps)]
+    ref = [oracle.compress(_host(x), B, b, s, dt, threads=16) for x, s in zip(xs, seeds)]
+    packed = [torch.full((r.size,), 0xA5, dtype=torch.uint8, device="cuda:0") for r in ref]
+    pkg.division_compress_maps([x.to("cuda:0") for x in xs], B, b, seeds, packed=packed, c16=c16)
+    torch.cuda.synchronize()
+    for r, p in zip(ref, packed):
+        assert np.array_equal(p.cpu().numpy(), r)
+
+
 # compress_units: the lookup of four elements at a time (rows that end anywhere inside them, widths and blocks of three, the last row,
 # the last slice) and of one (B = 2), one to sixteen lanes per block in the block sums, rounds of units and rows the plane does not have
 @pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 4), ("bf16", 8), ("bf16", 1), ("c16", 2)])
