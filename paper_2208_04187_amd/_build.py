@@ -23,6 +23,8 @@ FASTCALL = PKG / "_fastcall.so"                              # imported by bindi
 CHECKS_LIB = CHECKS.with_name("libdevice_checks.so")
 HOST_CHECKS = CHECKS.with_name("host_checks.hip")            # the launches that the library plans, for the tests
 HOST_CHECKS_LIB = HOST_CHECKS.with_name("libhost_checks.so")
+MASK_CHECKS = CHECKS.with_name("mask_checks.hip")
+MASK_CHECKS_LIB = MASK_CHECKS.with_name("libmask_checks.so")
 # (object name, source, extra flags)
 UNITS = [
     ("division_f32.o", DIVISION, ["-DDIVISION_PART=0"]),
@@ -77,8 +79,8 @@ def build(verbose: bool = False, extra_flags=(), out: Path | None = None) -> Pat
 
 
 def build_checks() -> Path:
-    """The tests' libraries: device helpers on their own (device_checks.hip), planned launches (host_checks.hip)."""
-    for src, lib in ((CHECKS, CHECKS_LIB), (HOST_CHECKS, HOST_CHECKS_LIB)):
+    """The tests' libraries: device helpers on their own (device_checks.hip), planned launches (host_checks.hip, mask_checks.hip)."""
+    for src, lib in ((CHECKS, CHECKS_LIB), (HOST_CHECKS, HOST_CHECKS_LIB), (MASK_CHECKS, MASK_CHECKS_LIB)):
         tmp = lib.with_name(lib.name + ".tmp%d" % os.getpid())
         cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *HIPCC_FLAGS, "-shared", "-Wl,-Bsymbolic", "-o", str(tmp), str(src)]
         res = subprocess.run(cmd, capture_output=True, text=True)

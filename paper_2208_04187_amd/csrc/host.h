@@ -156,7 +156,7 @@ bool plan_regs(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t e
 // plane as the codes of the present one leave, or each plane has a workgroup of its own.  A workgroup fills its CU, so one more
 // than there are CUs would wait until others have walked to their end: the walk is over all maps together (a grid per map,
 // rounded up, made 3, 5, 6 and 7 maps 1.25-1.5 times slower: 3 maps of 64 x 16 x 224 x 224 55.4 us each with a workgroup per
-// plane, 69.2 so, 43.5 together).  The walk runs all thirteen rounds of units untested, so planes of fewer rounds want fewer of
+// plane, 69.2 so, 45.3 together).  The walk runs all thirteen rounds of units untested, so planes of fewer rounds want fewer of
 // them wasted or more planes to overlap (fp32 / bfloat16, a workgroup per plane -> walk): 257 planes of 12.2 rounds 23.9 -> 21.6 / 20.9 -> 18.7,
 // of 10.6 rounds 20.5 -> 19.4 / 18.5 -> 18.3, of 8.3 rounds 17.7 -> 18.0 / 16.7 -> 18.0; 1024 planes of 8.3 rounds 42.9 -> 39.5 / 34.3 -> 33.8,
 // of 6.2 rounds 34.8 -> 33.2 / 28.9 -> 32.3.

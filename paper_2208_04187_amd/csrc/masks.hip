@@ -242,10 +242,12 @@ struct PoolArgs {
     uint32_t band;         // maxpool2_forward_fast: output rows a workgroup handles
     uint32_t chunk;        // maxpool_forward_kernel: elements a workgroup handles (a multiple of 32)
     uint32_t quick;        // every quotient below is exact with the multiplier (fastdiv_ok)
+    uint32_t quick0;       // so are those of the place in the whole map
+    uint32_t lines;        // maxpool_backward_kernel: grad_in starts on a cache line
     uint64_t n;            // elements of the map
     uint64_t rows;         // maxpool2_forward_fast: output rows of all planes
-    double r_HW, r_wv;     // 1 / HW, 1 / pieces of a row
-    FastDiv d_HW, d_W, d_OH, d_OW, d_k, d_wv;
+    double r_HW, r_wv, r_hv;      // 1 / HW, 1 / pieces of a row, 1 / pieces of a plane
+    FastDiv d_HW, d_W, d_OH, d_OW, d_k, d_wv, d_hv;
 };
 
 // quotient by the multiplier where the host found it exact for all numerators of this launch, else by the division
@@ -259,6 +261,14 @@ __device__ __forceinline__ uint64_t quot64(uint64_t n, uint32_t d, double rcp, u
     if (r >= (int64_t)d) { ++q; r -= d; }
     *rest = __builtin_amdgcn_readfirstlane((uint32_t)r);
     return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(q >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)q);
+}
+
+// the same for a launch all of whose numerators n the multiplier takes (quick): scalar instructions; small launches are the latency of this
+__device__ __forceinline__ uint64_t quot64(uint64_t n, uint32_t d, FastDiv f, uint32_t quick, double rcp, uint32_t* rest) {
+    if (!quick) return quot64(n, d, rcp, rest);
+    const uint32_t q = fdiv((uint32_t)n, f);
+    *rest = (uint32_t)n - q * d;
+    return q;
 }
 
 __global__ void __launch_bounds__(kThreads) zero_words(uint32_t* p, uint64_t n) {
@@ -425,8 +435,8 @@ __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
     for (uint32_t w = tid; w < nwords; w += kThreads) mp[w] = words[w];
 }
 
-// Backward, element by element: grad_in = V (.) (1_{k x k} (x) grad_out).  For maps that do not start on a 16-byte boundary
-// and planes of 2^28 output gradients and more; the others take the two kernels below.
+// Backward, element by element: grad_in = V (.) (1_{k x k} (x) grad_out).  For 2-byte maps that start in the middle of a dword
+// or are small, and planes of 2^28 output gradients and more; the others take the two kernels below.
 template <typename T>
 __global__ void __launch_bounds__(kThreads) maxpool_backward_scalar(PoolArgs a) {
     const uint32_t p = blockIdx.y;
@@ -443,22 +453,20 @@ __global__ void __launch_bounds__(kThreads) maxpool_backward_scalar(PoolArgs a) 
     }
 }
 
-// Backward, any size on a 16-byte boundary: a wavefront rebuilds 4 KB of grad_in, 256 consecutive 16-byte vectors wherever
+// Backward, any size on a dword boundary: a wavefront rebuilds 64 K consecutive 16-byte vectors of grad_in (4 KB at K = 4) wherever
 // rows and planes end (the write stream of decompress_stream).  A vector's mask bits lie in one word; an element's place is
 // found from its vector's by counting on; the gradients of the elements whose bit is set come through a bounds-checked
 // buffer, the others' loads are out of its range, read as +0 and fetch nothing.  A workgroup per 512 elements of one plane and a
 // branch per element took 60 us on 74 x 292 x 33 x 33
 // (bfloat16) and 30 us on 2 x 716 x 42 x 207, this 22 and 12.5.  What bounds it: vector instructions (the steps from element to element).
-constexpr int kPoolVecs = 4;
-template <typename T>
+template <typename T, int K>
 __global__ void __launch_bounds__(64) maxpool_backward_kernel(PoolArgs a) {
     constexpr int EPV = Tr<T>::EPV;
-    constexpr int K = kPoolVecs;
     constexpr uint32_t kDrop = 0x80000000u;
     const uint32_t lane = threadIdx.x;
     const uint64_t e0 = (uint64_t)blockIdx.x * (64u * K * EPV);
     uint32_t at0;
-    const uint64_t p0 = quot64(e0, a.HW, a.r_HW, &at0);
+    const uint64_t p0 = quot64(e0, a.HW, a.d_HW, a.quick0, a.r_HW, &at0);
     const uint32_t OHW = a.OH * a.OW;
     const T* gp = static_cast<const T*>(a.in) + p0 * OHW;
     // gradients of plane p0 and those behind it that the chunk can reach
@@ -510,7 +518,10 @@ __global__ void __launch_bounds__(64) maxpool_backward_kernel(PoolArgs a) {
         else o = u32x4{v[u][0] | (v[u][1] << 16), v[u][2] | (v[u][3] << 16), v[u][EPV - 4] | (v[u][EPV - 3] << 16), v[u][EPV - 2] | (v[u][EPV - 1] << 16)};
         // stores past the map are dropped by the bound, dword by dword; the whole offset in the vector operand (the
         // compiler counts the wait states behind a wide store only without a scalar offset register)
-        __builtin_amdgcn_raw_buffer_store_b128(o, ors, (64u * u + lane) * 16u, 0, 2);
+        // (not non-temporal where they cut cache lines, whose halves would then leave one by one: fp32 maps of 0.5 M elements 8 bytes past
+        // a line 3.4 against 3.1 us)
+        if (a.lines) __builtin_amdgcn_raw_buffer_store_b128(o, ors, (64u * u + lane) * 16u, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b128(o, ors, (64u * u + lane) * 16u, 0, 0);
     }
     // a map of an odd number of 2-byte elements ends in the middle of a dword, which lies behind the bound
     if constexpr (sizeof(T) == 2) {
@@ -524,38 +535,63 @@ __global__ void __launch_bounds__(64) maxpool_backward_kernel(PoolArgs a) {
     }
 }
 
-// Backward, k = 2 on rows of whole 16-byte vectors (grad_in 16-byte, grad_out 8-byte aligned, an even number of rows): a thread
-// rebuilds one vector, which lies under two (4-byte elements) or four (2-byte elements) adjacent windows: one
-// mask word, one 8-byte load of their gradients, one non-temporal 16-byte store; a workgroup of four wavefronts
-// writes 4 KB and ends (what a write stream wants here).  With an even number of rows the rows of all planes are one run,
-// so planes end anywhere in a workgroup (one that ended with its plane: 12 x 22855 x 8 x 8 130 -> 12 us).
-template <typename T>
+// Backward, k = 2 on rows of whole pieces of PE elements (grad_in aligned to a piece, grad_out to its PE / 2 gradients): a thread
+// rebuilds one piece, which lies under PE / 2 adjacent windows: one mask word, one load of their gradients, one non-temporal
+// store; a workgroup of four wavefronts writes 4 KB (2 KB) and ends (what a write stream wants here).  The rows of all planes are
+// one run, so planes end anywhere in a workgroup (one that ended with its plane: 12 x 22855 x 8 x 8 130 -> 12 us); the last row of a
+// plane of odd height (ODD) has no bits set, so any window row's gradients will do for its address.
+// PE: whole 16-byte vectors where the rows allow it; four 2-byte elements (widths such as 28 or 100, half the bytes per store)
+// otherwise.  Maps of 12 M elements, the general kernel above -> this: bfloat16 28 x 28 13.0 -> 6.6 us, 100 x 100 12.5 -> 6.6, 111 x 100
+// 12.6 -> 7.0, 223 x 224 13.2 -> 6.5; fp32 111 x 112 12.8 -> 11.1.
+template <typename T, int PE> constexpr int kPieces = PE * sizeof(T) == 8 ? 2 : 1;      // a thread's, kThreads apart: 4 KB per workgroup
+template <typename T, int PE, bool ODD>
 __global__ void __launch_bounds__(kThreads) maxpool2_backward_fast(PoolArgs a) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    constexpr uint32_t EPV = Tr<T>::EPV;
-    const uint32_t wv = a.W / EPV;                                          // vectors of a row
-    uint32_t at0;
-    const uint64_t row0 = quot64((uint64_t)blockIdx.x * kThreads, wv, a.r_wv, &at0); // row, counted over all planes, of the block's first vector
-    const uint64_t vi = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (vi * EPV >= a.n) return;
-    const uint32_t t = at0 + threadIdx.x;
-    const uint32_t dr = quot(t, wv, a.d_wv, a.quick);
-    const uint32_t c = (t - dr * wv) * (EPV / 2u);                          // first of the vector's windows
-    const uint64_t bit = vi * EPV;
-    const uint32_t bits = a.mask[bit >> 5] >> (uint32_t)(bit & 31u);
-    const T* g = static_cast<const T*>(a.in) + ((row0 + dr) >> 1) * a.OW + c;
-    const u32x2 q = *reinterpret_cast<const u32x2*>(g);
-    u32x4 o;
-    if constexpr (sizeof(T) == 4) {
-        o = u32x4{bits & 1u ? q.x : 0u, bits & 2u ? q.x : 0u, bits & 4u ? q.y : 0u, bits & 8u ? q.y : 0u};
-    } else {
-        const uint32_t w[4] = {q.x & 0xffffu, q.x >> 16, q.y & 0xffffu, q.y >> 16};
-        uint32_t d[4];
+    constexpr int U = kPieces<T, PE>;
+    const uint32_t wv = a.W / (uint32_t)PE, hv = a.HW / (uint32_t)PE;       // pieces of a row, of a plane
+    const uint64_t v0 = (uint64_t)blockIdx.x * (kThreads * U);
+    uint32_t at0;                                                           // place of the block's first piece in its plane (ODD) or row
+    const uint64_t first = ODD ? quot64(v0, hv, a.d_hv, a.quick0, a.r_hv, &at0) : quot64(v0, wv, a.d_wv, a.quick0, a.r_wv, &at0);
+    uint32_t bits[U];
+    u32x2 q[U];                                                             // the gradients (of a piece of 8 bytes: in x)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) d[j] = (bits & (1u << (2 * j)) ? w[j] : 0u) | (bits & (2u << (2 * j)) ? w[j] << 16 : 0u);
-        o = u32x4{d[0], d[1], d[2], d[3]};
+    for (int u = 0; u < U; ++u) {
+        const uint64_t bit = (v0 + kThreads * u + threadIdx.x) * PE;
+        if (bit >= a.n) break;
+        const uint32_t t = at0 + kThreads * u + threadIdx.x;
+        uint32_t c;
+        uint64_t wr;                                                        // window row, counted over all planes
+        if constexpr (ODD) {
+            // planes behind the block's first
+            const uint32_t g = hv >= (uint32_t)(kThreads * U) ? (t >= hv ? 1u : 0u) : fdiv(t, a.d_hv);
+            const uint32_t i = t - g * hv, r = quot(i, wv, a.d_wv, a.quick);
+            c = i - r * wv;
+            wr = (first + g) * a.OH + min(r >> 1, a.OH - 1u);
+        } else {
+            const uint32_t dr = quot(t, wv, a.d_wv, a.quick);
+            c = t - dr * wv;
+            wr = (first + dr) >> 1;
+        }
+        bits[u] = a.mask[bit >> 5] >> (uint32_t)(bit & 31u);
+        const T* g = static_cast<const T*>(a.in) + wr * a.OW + c * (PE / 2u);
+        if constexpr (U == 2) q[u].x = *reinterpret_cast<const uint32_t*>(g);
+        else q[u] = *reinterpret_cast<const u32x2*>(g);
     }
-    __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(static_cast<T*>(a.out) + bit));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t bit = (v0 + kThreads * u + threadIdx.x) * PE;
+        if (bit >= a.n) break;
+        T* out = static_cast<T*>(a.out) + bit;
+        const uint32_t m = bits[u], x = q[u].x, y = q[u].y;
+        // two 2-byte elements under window j of the piece
+        auto pair = [&](uint32_t w, int j) -> uint32_t { return (m & (1u << (2 * j)) ? w : 0u) | (m & (2u << (2 * j)) ? w << 16 : 0u); };
+        if constexpr (sizeof(T) == 4)
+            __builtin_nontemporal_store(u32x4{m & 1u ? x : 0u, m & 2u ? x : 0u, m & 4u ? y : 0u, m & 8u ? y : 0u}, reinterpret_cast<u32x4*>(out));
+        else if constexpr (PE == 8)
+            __builtin_nontemporal_store(u32x4{pair(x & 0xffffu, 0), pair(x >> 16, 1), pair(y & 0xffffu, 2), pair(y >> 16, 3)}, reinterpret_cast<u32x4*>(out));
+        else
+            __builtin_nontemporal_store(u32x2{pair(x & 0xffffu, 0), pair(x >> 16, 1)}, reinterpret_cast<u32x2*>(out));
+    }
 }
 
 int pool_args(bool forward, const void* in, void* out, const void* mask, int64_t N, int64_t C, int64_t H, int64_t W,
@@ -665,24 +701,43 @@ int division_maxpool_backward(const void* mask, size_t mask_bytes, const void* g
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const size_t es = dt == DIVISION_BF16 ? 2 : 4;
     const uint64_t epv = 16 / es;
-    const bool vec = ((uintptr_t)grad_in % 16) == 0;
-    const uint64_t nvec = (a.n + epv - 1) / epv;
-    if (k == 2 && a.H % 2 == 0 && a.W % epv == 0 && vec && ((uintptr_t)grad_out % 8) == 0 && launch_ok((nvec + kThreads - 1) / kThreads, kThreads)) {
-        a.d_wv = make_fastdiv((uint32_t)(a.W / epv));
-        a.r_wv = 1.0 / (double)(a.W / epv);
-        a.quick = fastdiv_ok(a.W / epv + kThreads, a.W / epv);
-        void (*fast)(PoolArgs) = dt == DIVISION_F32 ? maxpool2_backward_fast<float> : maxpool2_backward_fast<uint16_t>;
-        hipLaunchKernelGGL(fast, dim3((uint32_t)((nvec + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, a);
+    // rows of whole pieces: 16 bytes, or four 2-byte elements
+    const uint64_t pe = a.W % epv == 0 && ((uintptr_t)grad_in % 16) == 0 ? epv : 4;
+    const uint64_t per_block = kThreads * (pe * es == 8 ? 2 : 1), nblock = (a.n / pe + per_block - 1) / per_block;      // as kPieces
+    if (k == 2 && a.OH > 0 && a.W % pe == 0 && ((uintptr_t)grad_in % (pe * es)) == 0 && ((uintptr_t)grad_out % (pe / 2 * es)) == 0 &&
+        launch_ok(nblock, kThreads)) {
+        const uint64_t wv = a.W / pe;
+        const bool odd = a.H % 2 != 0;
+        a.d_wv = make_fastdiv((uint32_t)wv);
+        a.r_wv = 1.0 / (double)wv;
+        a.d_hv = make_fastdiv((uint32_t)(a.HW / pe));
+        a.r_hv = 1.0 / (double)(a.HW / pe);
+        a.quick = odd ? fastdiv_ok(a.HW / pe, wv) : fastdiv_ok(wv + per_block, wv);
+        a.quick0 = fastdiv_ok(a.n / pe + per_block, odd ? a.HW / pe : wv);
+        void (*fast)(PoolArgs) = dt == DIVISION_F32 ? (odd ? maxpool2_backward_fast<float, 4, true> : maxpool2_backward_fast<float, 4, false>)
+                               : pe == 8 ? (odd ? maxpool2_backward_fast<uint16_t, 8, true> : maxpool2_backward_fast<uint16_t, 8, false>)
+                                         : (odd ? maxpool2_backward_fast<uint16_t, 4, true> : maxpool2_backward_fast<uint16_t, 4, false>);
+        hipLaunchKernelGGL(fast, dim3((uint32_t)nblock), dim3(kThreads), 0, st, a);
         return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
     }
-    const uint64_t per_wave = 64ull * kPoolVecs, grid = (nvec + per_wave - 1) / per_wave, chunk = per_wave * epv;
+    const uint64_t nvec = (a.n + epv - 1) / epv;
+    // Vectors a lane: one where the launch is short, whose time is the chain of a wavefront's elements (maps of 1 M elements fp32 4.4 -> 3.9 us,
+    // bfloat16 5.6 -> 3.6), four beyond (16 M: fp32 18.0 -> 14.0; bfloat16 level at 20 M).  2-byte maps of a few planes and chunks have
+    // half the chain again with an element a lane (32 K: 2.8 -> 2.5; level at 256 K).
+    const bool f32 = dt == DIVISION_F32;
+    const uint64_t vecs = a.n <= ((f32 ? 4u : 12u) << 20) ? 1 : 4;
+    const bool few = !f32 && a.n <= (1u << 17) && a.P <= 1024;
+    const uint64_t per_wave = 64 * vecs, grid = (nvec + per_wave - 1) / per_wave, chunk = per_wave * epv;
     const uint64_t reach = chunk / a.HW + 2;                                  // planes a chunk can reach
-    if (vec && launch_ok(grid, 64) && reach * a.OH * a.OW * es < (1ull << 31) && (uint64_t)a.HW + chunk < (1ull << 32)) {
+    if (!few && ((uintptr_t)grad_in % 4) == 0 && launch_ok(grid, 64) && reach * a.OH * a.OW * es < (1ull << 31) && (uint64_t)a.HW + chunk < (1ull << 32)) {
+        a.quick0 = fastdiv_ok(a.n, a.HW);
+        a.lines = ((uintptr_t)grad_in % 128) == 0;
         a.d_HW = make_fastdiv(a.HW);
         a.d_W = make_fastdiv(a.W);
         a.d_k = make_fastdiv(a.k);
         a.quick = (a.HW >= chunk || fastdiv_ok(a.HW + chunk, a.HW)) && fastdiv_ok(a.HW, a.W) && fastdiv_ok(a.H, a.k) && fastdiv_ok(a.W, a.k);
-        void (*kern)(PoolArgs) = dt == DIVISION_F32 ? maxpool_backward_kernel<float> : maxpool_backward_kernel<uint16_t>;
+        void (*kern)(PoolArgs) = f32 ? (vecs == 4 ? maxpool_backward_kernel<float, 4> : maxpool_backward_kernel<float, 1>)
+                                     : (vecs == 4 ? maxpool_backward_kernel<uint16_t, 4> : maxpool_backward_kernel<uint16_t, 1>);
         hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(64), 0, st, a);
         return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
     }

@@ -244,3 +244,27 @@ def test_maxpool_on_unaligned_buffers_matches_oracle(dtype):
         torch.cuda.synchronize()
         assert rc == 0 and np.array_equal(mask.cpu().numpy().view(np.uint32), m_ref) and _same_bits(y, y_ref)
         assert _same_bits(out[1:-1].view(shape), g_ref) and float(out[0]) == 7.0 and float(out[-1]) == 7.0
+
+
+# backward: odd heights (planes of less and more pieces than a workgroup takes, the last row without windows), rows of four-element pieces,
+# maps that end in the middle of a workgroup's second piece, outputs and gradients on 4- and 8-byte boundaries
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("gi_at,go_at", [(0, 0), (2, 0), (4, 0), (6, 2), (0, 2), (0, 1), (1, 1)])
+@pytest.mark.parametrize("shape,k", [((3, 7, 27, 28), 2), ((2, 9, 3, 4), 2), ((1, 5, 101, 100), 2), ((1, 3, 67, 64), 2), ((5, 41, 5, 12), 2), ((2, 3, 28, 44), 2),
+                                     ((1, 1, 3, 2052), 2), ((300, 7, 9, 16), 2), ((2, 3, 13, 11), 3), ((1, 5, 30, 28), 3), ((700, 3, 10, 15), 4)])
+def test_maxpool_backward_on_any_boundary_matches_oracle(shape, k, gi_at, go_at, dtype):
+    N, C, H, W = shape
+    n, m = N * C * H * W, N * C * (H // k) * (W // k)
+    gen = torch.Generator().manual_seed(H * W)
+    x, go = torch.randn(n, generator=gen).to(dtype), torch.randn(m, generator=gen).to(dtype)
+    _, m_ref = oracle.maxpool_forward(_host(x)[0].reshape(shape), k, _host(x)[1])
+    g_ref = oracle.maxpool_backward(m_ref, _host(go)[0].reshape((N, C, H // k, W // k)), shape, k, _host(go)[1])
+    mask = torch.from_numpy(m_ref.view(np.int32)).to("cuda:0")
+    gd = torch.zeros(m + go_at, dtype=dtype, device="cuda:0")[go_at:]
+    gd.copy_(go)
+    out = torch.full((gi_at + n + 8,), 7.0, dtype=dtype, device="cuda:0")
+    rc = pkg.lib().division_maxpool_backward(mask.data_ptr(), mask.numel() * 4, gd.data_ptr(), N, C, H, W, 1 if dtype == torch.bfloat16 else 0, k,
+                                             out[gi_at:].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and _same_bits(out[gi_at:gi_at + n].view(shape), g_ref)
+    assert (out[:gi_at].float() == 7.0).all() and (out[gi_at + n:].float() == 7.0).all()

@@ -65,3 +65,47 @@ def test_sixteen_wavefronts_take_no_more_workgroups_than_cus_where_they_walk(hos
             assert launch.walked == maps and launch.gy == 1 and launch.gx <= min(cus, maps * planes)
         else:
             assert (launch.gx, launch.gy) == (planes, maps)
+
+
+@pytest.fixture(scope="module")
+def pool():
+    if not _build.MASK_CHECKS_LIB.exists():
+        _build.build_checks()
+    lib = ctypes.CDLL(str(_build.MASK_CHECKS_LIB))
+    i64, ci, vp, sz = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t
+    lib.division_maxpool_forward.argtypes = [vp, i64, i64, i64, i64, ci, ci, vp, vp, sz, vp]
+    lib.division_maxpool_backward.argtypes = [vp, sz, vp, i64, i64, i64, i64, ci, ci, vp, vp]
+    lib.check_pool_kernel.restype = ctypes.c_char_p
+    lib.check_pool_kernel.argtypes = [ctypes.POINTER(ctypes.c_uint32)]
+    return lib
+
+
+def _pool_backward(lib, shape, dt, k, offset=0):
+    es = 2 if dt == BF16 else 4
+    rc = lib.division_maxpool_backward(1 << 40, 1 << 40, 1 << 41, *shape, dt, k, (1 << 42) + offset * es, None)
+    groups = ctypes.c_uint32()
+    return rc, lib.check_pool_kernel(ctypes.byref(groups)).decode().strip("()"), groups.value
+
+
+@pytest.mark.parametrize("dt", [F32, BF16])
+@pytest.mark.parametrize("offset", [0, 4])
+@pytest.mark.parametrize("H", [2, 27, 28, 100, 223])
+@pytest.mark.parametrize("W", [4, 12, 28, 32, 44, 100, 224])
+def test_pooling_backward_of_whole_pieces_streams(pool, dt, offset, H, W):
+    """k = 2 on rows of whole four-element pieces at such a boundary: no widths, heights or offsets that miss the streaming kernel."""
+    P = max(1, 12_000_000 // (H * W))
+    rc, name, groups = _pool_backward(pool, (1, P, H, W), dt, 2, offset)
+    assert rc == 0 and name.startswith("maxpool2_backward_fast<"), name
+    pieces = P * H * W // int(name.split(",")[1])
+    assert groups * 256 * (2 if name.startswith("maxpool2_backward_fast<uint16_t, 4") else 1) >= pieces
+    assert name.endswith("true>" if H % 2 else "false>")
+
+
+def test_pooling_backward_of_other_maps(pool):
+    for shape, dt, k, offset, want in (((64, 100, 27, 27), BF16, 2, 0, "maxpool_backward_kernel<uint16_t, 1>"), ((64, 600, 27, 27), BF16, 2, 0, "maxpool_backward_kernel<uint16_t, 4>"),
+                                       ((64, 100, 56, 56), BF16, 3, 2, "maxpool_backward_kernel<uint16_t, 4>"), ((64, 100, 56, 56), BF16, 3, 1, "maxpool_backward_scalar<uint16_t>"),
+                                       ((4, 32, 14, 14), BF16, 3, 0, "maxpool_backward_scalar<uint16_t>"), ((4, 512, 7, 7), BF16, 3, 0, "maxpool_backward_kernel<uint16_t, 1>"),
+                                       ((4, 32, 14, 14), F32, 3, 0, "maxpool_backward_kernel<float, 1>"), ((64, 100, 56, 56), F32, 3, 1, "maxpool_backward_kernel<float, 4>"),
+                                       ((64, 600, 27, 28), BF16, 2, 2, "maxpool_backward_kernel<uint16_t, 4>")):
+        rc, name, _ = _pool_backward(pool, shape, dt, k, offset)
+        assert rc == 0 and name == want, (shape, dt, k, offset, name)
