@@ -246,7 +246,7 @@ struct PoolArgs {
     uint32_t lines;        // maxpool_backward_kernel: grad_in starts on a cache line
     uint64_t n;            // elements of the map
     uint64_t rows;         // maxpool2_forward_fast: output rows of all planes
-    double r_HW, r_wv, r_hv;      // 1 / HW, 1 / pieces of a row, 1 / pieces of a plane
+    double r_HW, r_wv, r_hv, r_OH;      // 1 / HW, 1 / pieces of a row, 1 / pieces of a plane, 1 / OH
     FastDiv d_HW, d_W, d_OH, d_OW, d_k, d_wv, d_hv;
 };
 
@@ -363,9 +363,12 @@ __global__ void __launch_bounds__(kThreads) maxpool_forward_kernel(PoolArgs a) {
 // there is no atomic.  With an even number of rows per plane the output rows of all planes are one run, so a
 // band of them is whole mask words wherever planes end, and small planes share a workgroup (a band used to end
 // with its plane: 12 x 22855 x 8 x 8 163 -> 14 us); the slice leaves with plain stores and the mask needs no clearing.
+// 12 M elements of odd height, the general kernel above -> this: bfloat16 33 x 64 9.8 -> 7.1 us, 223 x 224 12.1 -> 7.4, fp32 223 x 224 14.7 -> 12.7.
 // NT: non-temporal loads, for rows of at least a cache line (a stem's sequence of operators 306 us against 338 without: x does
 // not displace what the neighbours write); shorter rows share lines between loads (8 x 8: 23 us with them, 14 without).
-template <typename T, bool NT>
+// ODD: an odd number of rows of whole mask words (W % 32 == 0): the slices of a band's rows follow each other except for the last row of
+// each plane, whose zero words leave with the slice of the band that holds the row before it.
+template <typename T, bool NT, bool ODD>
 __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
     extern __shared__ uint32_t words[];
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -373,8 +376,15 @@ __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
     const uint32_t tid = threadIdx.x;
     const uint64_t oi0 = (uint64_t)blockIdx.x * a.band;                      // output rows, counted over all planes
     const uint32_t nrows = (uint32_t)min((uint64_t)a.band, a.rows - oi0);
-    const uint64_t start = 2u * oi0 * a.W;                                   // first element, at a word boundary
-    const uint32_t nwords = (2u * nrows * a.W + 31u) / 32u;
+    // ODD: place of the first row in its plane, planes that end with a row of the band
+    uint32_t of0 = 0, ends = 0;
+    uint64_t start = 2u * oi0 * a.W;                                         // first element, at a word boundary
+    if constexpr (ODD) {
+        const uint64_t p0 = quot64(oi0, a.OH, a.d_OH, a.quick0, a.r_OH, &of0);
+        start += p0 * a.W;
+        ends = quot(of0 + nrows, a.OH, a.d_OH, a.quick);
+    }
+    const uint32_t nwords = (2u * nrows * a.W + ends * a.W + 31u) / 32u;
     for (uint32_t w = tid; w < nwords; w += kThreads) words[w] = 0u;
     __syncthreads();
     uint8_t* bytes = reinterpret_cast<uint8_t*>(words);
@@ -389,7 +399,8 @@ __global__ void __launch_bounds__(kThreads) maxpool2_forward_fast(PoolArgs a) {
     for (uint32_t o4 = tid; o4 < n4; o4 += kThreads) {
         const uint32_t r = quot(o4, ow4, a.d_wv, a.quick);
         const uint32_t oj4 = o4 - r * ow4;
-        const uint32_t base = 2u * r * a.W + oj4 * 8u;                     // first of the eight elements, upper row
+        uint32_t base = 2u * r * a.W + oj4 * 8u;                           // first of the eight elements, upper row
+        if constexpr (ODD) base += quot(of0 + r, a.OH, a.d_OH, a.quick) * a.W;
         uint32_t e0[8], e1[8];                                              // the two rows as fp32 bit patterns
         if constexpr (sizeof(T) == 4) {
             const u32x4 a0 = load(xp + base);
@@ -643,8 +654,9 @@ int division_maxpool_forward(const void* x, int64_t N, int64_t C, int64_t H, int
     if (rc != DIVISION_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const size_t es = dt == DIVISION_BF16 ? 2 : 4;
-    // rows of whole 8-element pieces, an even number of them per plane: the output rows of all planes are one run
-    if (k == 2 && a.H % 2 == 0 && a.W % 8 == 0 && a.W <= 16384 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % (4 * es)) == 0) {
+    // rows of whole 8-element pieces, an even number of them per plane or each of whole mask words: the output rows of all planes are one run
+    const bool odd = a.H % 2 != 0;
+    if (k == 2 && a.OH > 0 && a.W % (odd ? 32 : 8) == 0 && a.W <= 16384 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % (4 * es)) == 0) {
         // about 8 KB of x per workgroup (short-lived workgroups, many of them), an even number of output rows (whole mask
         // words), at most 64 Ki mask bits
         uint32_t band = (uint32_t)(8192 / (2ull * a.W * es)) & ~1u;
@@ -653,13 +665,21 @@ int division_maxpool_forward(const void* x, int64_t N, int64_t C, int64_t H, int
         a.rows = (uint64_t)a.P * a.OH;
         const uint64_t grid = (a.rows + band - 1) / band;
         a.d_wv = make_fastdiv(a.OW / 4);
-        a.quick = fastdiv_ok((uint64_t)band * (a.OW / 4), a.OW / 4);
+        a.d_OH = make_fastdiv(a.OH);
+        a.r_OH = 1.0 / (double)a.OH;
+        a.quick = fastdiv_ok((uint64_t)band * (a.OW / 4), a.OW / 4) && (!odd || fastdiv_ok((uint64_t)a.OH + band, a.OH));
+        a.quick0 = fastdiv_ok(a.rows, a.OH);
         if (launch_ok(grid, kThreads)) {
             // rows shorter than a cache line: several loads touch each line, which then has to stay in the caches
             const bool nt = a.W * es >= 128;
-            void (*kern)(PoolArgs) = dt == DIVISION_F32 ? (nt ? maxpool2_forward_fast<float, true> : maxpool2_forward_fast<float, false>)
-                                                        : (nt ? maxpool2_forward_fast<uint16_t, true> : maxpool2_forward_fast<uint16_t, false>);
-            hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kThreads), (size_t)band * 2 * a.W / 8 + 16, st, a);
+            void (*kern)(PoolArgs);
+            if (dt == DIVISION_F32) kern = odd ? (nt ? maxpool2_forward_fast<float, true, true> : maxpool2_forward_fast<float, false, true>)
+                                               : (nt ? maxpool2_forward_fast<float, true, false> : maxpool2_forward_fast<float, false, false>);
+            else kern = odd ? (nt ? maxpool2_forward_fast<uint16_t, true, true> : maxpool2_forward_fast<uint16_t, false, true>)
+                            : (nt ? maxpool2_forward_fast<uint16_t, true, false> : maxpool2_forward_fast<uint16_t, false, false>);
+            // the band's rows and, of an odd height, the last rows of the planes that end in it
+            const size_t bits = (size_t)band * 2 * a.W + (odd ? ((size_t)band / a.OH + 1) * a.W : 0);
+            hipLaunchKernelGGL(kern, dim3((uint32_t)grid), dim3(kThreads), bits / 8 + 16, st, a);
             return hipGetLastError() == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
         }
     }

@@ -23,10 +23,17 @@ static const char* pool_kernel() {
     NAMED((maxpool2_backward_fast<uint16_t, 4, true>));
     NAMED((maxpool2_backward_fast<uint16_t, 8, false>));
     NAMED((maxpool2_backward_fast<uint16_t, 8, true>));
+    NAMED((maxpool2_forward_fast<float, false, false>));
+    NAMED((maxpool2_forward_fast<float, true, false>));
+    NAMED((maxpool2_forward_fast<float, true, true>));
+    NAMED((maxpool2_forward_fast<uint16_t, false, false>));
+    NAMED((maxpool2_forward_fast<uint16_t, true, false>));
+    NAMED((maxpool2_forward_fast<uint16_t, false, true>));
+    NAMED((maxpool2_forward_fast<uint16_t, true, true>));
     return "";
 }
 
 extern "C" {
-// the kernel that division_maxpool_backward last launched, and its workgroups
+// the pooling kernel last launched (empty: another one), and its workgroups
 const char* check_pool_kernel(uint32_t* workgroups) { *workgroups = last_grid.x * last_grid.y; return pool_kernel(); }
 }

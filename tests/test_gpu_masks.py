@@ -268,3 +268,18 @@ def test_maxpool_backward_on_any_boundary_matches_oracle(shape, k, gi_at, go_at,
     torch.cuda.synchronize()
     assert rc == 0 and _same_bits(out[gi_at:gi_at + n].view(shape), g_ref)
     assert (out[:gi_at].float() == 7.0).all() and (out[gi_at + n:].float() == 7.0).all()
+
+
+# forward: odd heights of whole mask words (bands over several planes, planes of more and less than a band, bands that end with a plane),
+# windows of four and more (rows of a window in whole and in part pieces of four elements), values that tie across the pieces
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape,k", [((7, 9, 3, 32), 2), ((5, 41, 5, 64), 2), ((3, 5, 15, 32), 2), ((2, 3, 101, 96), 2), ((1, 3, 223, 224), 2), ((1, 2, 9, 4096), 2),
+                                     ((1, 1, 3, 16384), 2), ((3, 7, 28, 28), 4), ((2, 5, 21, 33), 5), ((2, 3, 40, 47), 6), ((31, 7, 7, 7), 7), ((2, 2, 64, 72), 8), ((1, 2, 50, 61), 13)])
+def test_maxpool_odd_heights_and_wide_windows_match_oracle(shape, k, dtype):
+    test_maxpool_matches_oracle(shape, k, dtype)
+    gen = torch.Generator().manual_seed(5)
+    x = torch.randint(-2, 3, shape, generator=gen).to(dtype)
+    y_ref, m_ref = oracle.maxpool_forward(_host(x)[0].reshape(shape), k, _host(x)[1])
+    y, mask = pkg.division_maxpool_forward(x.to("cuda:0"), k)
+    torch.cuda.synchronize()
+    assert np.array_equal(mask.cpu().numpy().view(np.uint32), m_ref) and _same_bits(y, y_ref)

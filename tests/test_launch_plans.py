@@ -109,3 +109,12 @@ def test_pooling_backward_of_other_maps(pool):
                                        ((64, 600, 27, 28), BF16, 2, 2, "maxpool_backward_kernel<uint16_t, 4>")):
         rc, name, _ = _pool_backward(pool, shape, dt, k, offset)
         assert rc == 0 and name == want, (shape, dt, k, offset, name)
+
+
+@pytest.mark.parametrize("dt", [F32, BF16])
+@pytest.mark.parametrize("H,W", [(33, 64), (223, 224), (101, 96), (15, 32), (28, 28), (27, 40)])
+def test_pooling_forward_of_odd_heights_streams(pool, dt, H, W):
+    """k = 2: even heights of whole eight-element pieces, and odd ones of whole mask words."""
+    assert pool.division_maxpool_forward(1 << 40, 4, 64, H, W, dt, 2, 1 << 41, 1 << 42, 1 << 40, None) == 0
+    name = pool.check_pool_kernel(ctypes.byref(ctypes.c_uint32())).decode()
+    assert name.startswith("(maxpool2_forward_fast<") == (W % (32 if H % 2 else 8) == 0)
