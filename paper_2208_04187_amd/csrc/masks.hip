@@ -665,8 +665,10 @@ int division_maxpool_forward(const void* x, int64_t N, int64_t C, int64_t H, int
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const size_t es = dt == DIVISION_BF16 ? 2 : 4;
     // rows of whole 8-element pieces, an even number of them per plane or each of whole mask words: the output rows of all planes are one run
-    const bool odd = a.H % 2 != 0;
-    if (k == 2 && a.OH > 0 && a.W % (odd ? 32 : 8) == 0 && a.W <= 16384 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % (4 * es)) == 0) {
+    // (not large fp32 maps of odd height and rows of up to 512 bytes, of which the general kernel has 12 M elements of 33 x 64 in 11.5 us, this
+    // one in 12.2; 33 x 160 12.4 and 12.2; 1 M elements of 33 x 64 3.8 and 3.3)
+    const bool odd = a.H % 2 != 0, pairs = odd && dt == DIVISION_F32 && a.W <= 128 && a.n > (4u << 20);
+    if (k == 2 && a.OH > 0 && !pairs && a.W % (odd ? 32 : 8) == 0 && a.W <= 16384 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % (4 * es)) == 0) {
         // about 8 KB of x per workgroup (short-lived workgroups, many of them), an even number of output rows (whole mask
         // words), at most 64 Ki mask bits
         uint32_t band = (uint32_t)(8192 / (2ull * a.W * es)) & ~1u;

@@ -118,3 +118,6 @@ def test_pooling_forward_of_odd_heights_streams(pool, dt, H, W):
     assert pool.division_maxpool_forward(1 << 40, 4, 64, H, W, dt, 2, 1 << 41, 1 << 42, 1 << 40, None) == 0
     name = pool.check_pool_kernel(ctypes.byref(ctypes.c_uint32())).decode()
     assert name.startswith("(maxpool2_forward_fast<") == (W % (32 if H % 2 else 8) == 0)
+    assert pool.division_maxpool_forward(1 << 40, 64, 160, H, W, dt, 2, 1 << 41, 1 << 42, 1 << 40, None) == 0
+    name = pool.check_pool_kernel(ctypes.byref(ctypes.c_uint32())).decode()
+    assert name.startswith("(maxpool2_forward_fast<") == (W % (32 if H % 2 else 8) == 0 and not (dt == F32 and H % 2 and W <= 128))
