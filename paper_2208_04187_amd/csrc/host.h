@@ -214,21 +214,40 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, 
     // and is the faster one (28 x 28 under B = 12: 43 us against 49)
     // (not 1-bit codes of maps of one row, which the general kernel would get: rows of 96 under B = 12 45 us there, 15 here)
     if (D == 1 && W % 4 == 0 && q4 < 512 && !(H == 1 && b == 1) && !seg) return false;
+    // calls that another kernel serves as well or better (maps of 0.01 to 8 M elements, that kernel -> this): one row of whole vectors under
+    // B = 4 (compress_tile 10.2 -> 12.7 us on 1746 rows of 2032, ahead by 1 % over all; by 8 and more elsewhere); 2-byte rows of an odd
+    // width of 256 to 1023 elements under larger blocks (compress_rows 12.1 -> 15.1 on 5340 rows of 663 under B = 64, 11 % ahead over
+    // all); small planes of one column (compress_rows 7.1 -> 8.9 on 3760 of 131 rows), and of 2-byte elements under B = 2 and 3
+    // (6.2 -> 7.2 on 2516 of 37 x 5)
+    if (H == 1 && B == 4 && W % 4 == 0) return false;
+    if (H == 1 && b != 1 && es == 2 && W % 2 != 0 && B > 8 && q4 >= 64 && q4 < 256) return false;
+    if (H > 1 && b != 1 && q4 < kUnitsSubMin && (W == 1 || (es == 2 && B < 4))) return false;
     const uint64_t Bz = (uint64_t)std::min<int64_t>(B, D), Br = (uint64_t)std::min<int64_t>(B, H);      // depth and rows of a block
     const uint64_t nitem = L.nb * Bz * Br;
+    const bool many = L.P >= kUnitsManyPlanes;
+    // Lanes per plane.  Few planes: the launch is the latency of one, for which lanes are given to all B rows (slices) of a block, also of
+    // those that the map does not have (153 volumes of 2 x 7 x 33 under B = 8 7.1 us so, 8.5 with lanes for its own).
+    uint64_t lanes_for = L.nb * (D > 1 ? (uint64_t)B : 1) * (uint64_t)B;
+    if (many || lanes_for > (uint64_t)kUnitsK * 1024) lanes_for = nitem;
     int nw = 1;
     uint64_t S = 64;                                          // lanes per plane
     if (q4 < kUnitsMin) {
         // small planes: 8, 16 or 32 lanes each, several planes per wavefront
-        const bool many = L.P >= kUnitsManyPlanes;
         if (q4 < (!many ? kUnitsSubMin : H == 1 ? kUnitsRowMin : D == 1 && (B == 4 || B == 8) ? kUnitsSubMin : kUnitsSubMinAny)) return false;
         S = 8;
-        while (S < 64 && (q4 > (uint64_t)kUnitsK * S || nitem > (uint64_t)kUnitsK * S)) S *= 2;
+        while (S < 64 && (q4 > (uint64_t)kUnitsK * S || lanes_for > (uint64_t)kUnitsK * S)) S *= 2;
         nw = S < 64 ? 0 : 1;
     }
     if (nw) {
-        while (nw < 16 && (q4 > (uint64_t)kUnitsK * 64 * nw || nitem > (uint64_t)kUnitsK * 64 * nw)) nw *= 2;
+        while (nw < 16 && (q4 > (uint64_t)kUnitsK * 64 * nw || lanes_for > (uint64_t)kUnitsK * 64 * nw)) nw *= 2;
         S = 64ull * nw;
+    }
+    // Many planes that still leave the machine idle: more lanes for each, up to a unit per lane, until there are eight wavefronts per CU (four
+    // and sixteen are slower: 8 lanes with eight units one after the other on 306 rows of 114 in bfloat16 under B = 2 10.0 us, 5.6 with 32; 2000
+    // maps of all sizes together 1.50 times as fast as the kernels that had them before with four, 1.53 with eight, 1.50 with sixteen)
+    if (many) {
+        while (S < (b == 1 ? 512u : 1024u) && L.P * S < 8 * 64 * (uint64_t)num_cus() && q4 > S) S *= 2;
+        nw = S < 64 ? 0 : (int)(S / 64);
     }
     if (q4 > (uint64_t)kUnitsK * S || nitem > (uint64_t)kUnitsK * S) return false;       // 8 units and 8 row segments per lane
     const uint64_t q4p = (q4 + S - 1) / S * S;

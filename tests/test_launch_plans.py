@@ -121,3 +121,27 @@ def test_pooling_forward_of_odd_heights_streams(pool, dt, H, W):
     assert pool.division_maxpool_forward(1 << 40, 64, 160, H, W, dt, 2, 1 << 41, 1 << 42, 1 << 40, None) == 0
     name = pool.check_pool_kernel(ctypes.byref(ctypes.c_uint32())).decode()
     assert name.startswith("(maxpool2_forward_fast<") == (W % (32 if H % 2 else 8) == 0 and not (dt == F32 and H % 2 and W <= 128))
+
+
+@pytest.mark.parametrize("shape,dt,B", [((306, 1, 1, 114), BF16, 2), ((832, 1, 1, 154), F32, 4), ((1940, 1, 1, 238), BF16, 8), ((297, 1, 104, 3), F32, 12), ((800, 2, 3, 37, 2), C16, 3),
+                                        ((260, 1, 1, 4099), F32, 18), ((512, 1, 19, 19), F32, 12)])
+def test_units_of_many_planes_have_lanes_for_a_machine_of_wavefronts(host, shape, dt, B):
+    """Eight wavefronts per CU, or a lane for every unit of four elements."""
+    planes, units = shape[0] * shape[1], (shape[-1] * shape[-2] * (shape[2] if len(shape) == 5 else 1) + 3) // 4
+    (launch,) = _maps(host, [(shape, dt, B, 2)])
+    name = (ctypes.c_char * 128)()
+    host.division_kernel_name_3d.argtypes = [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int64] * 5 + [ctypes.c_int] * 3 + [ctypes.c_char_p, ctypes.c_size_t]
+    assert host.division_kernel_name_3d(0, None, *_dims(shape), dt, B, 2, name, 128) == 0 and name.value.startswith(b"compress_units<")
+    assert launch.gx * max(launch.waves, 1) >= min(8 * host.check_cus(), planes * units // 64), (launch.gx, launch.waves)
+
+
+def test_calls_that_the_units_kernel_does_not_gain_keep_their_own(host):
+    pk = (ctypes.c_char * 128)()
+    host.division_kernel_name_3d.argtypes = [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int64] * 5 + [ctypes.c_int] * 3 + [ctypes.c_char_p, ctypes.c_size_t]
+    for shape, dt, B, b, want in (((1746, 1, 1, 2032), BF16, 4, 1, "compress_tile<"), ((1048, 1, 1, 7196), F32, 4, 8, "compress_tile<"), ((5340, 1, 1, 663), BF16, 64, 2, "compress_rows<"),
+                                  ((5340, 1, 1, 663), BF16, 64, 1, "compress_units<"), ((5340, 1, 1, 663), F32, 64, 2, "compress_units<"), ((3760, 1, 131, 1), F32, 2, 4, "compress_rows<"),
+                                  ((3760, 1, 131, 1), F32, 2, 1, "compress_units<"), ((2516, 1, 37, 5), BF16, 2, 4, "compress_rows<"), ((2516, 1, 37, 5), BF16, 12, 4, "compress_units<")):
+        assert host.division_kernel_name_3d(0, None, *_dims(shape), dt, B, b, pk, 128) == 0
+        assert pk.value.decode().startswith(want), (shape, dt, B, b, pk.value)
+    # few planes: lanes for all B slices of a block
+    assert _maps(host, [((153, 1, 2, 7, 33), BF16, 8, 2)])[0].waves == 1
