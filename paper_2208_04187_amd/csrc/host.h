@@ -191,7 +191,8 @@ constexpr uint64_t kUnitsManyPlanes = 256;      // planes (a CU each) from which
                                           // kernels (wave, rows): below, a launch is its latency in either
 bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, SegArgs* a, uint32_t* grid, size_t* lds,
               uint32_t* nt_out, int* K_out);
-bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x,
+// maps: of the launch.
+bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x, int maps,
                 UnitsArgs* a, uint32_t* grid, size_t* lds, int* nw_out) {
     if (((uintptr_t)x % 4) != 0 || (H == 1 && L.P < kUnitsManyPlanes)) return false;
     // small planes of even width under B = 4 and 8 are the wavefront kernel's (pairs of elements per
@@ -242,11 +243,11 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, 
         while (nw < 16 && (q4 > (uint64_t)kUnitsK * 64 * nw || lanes_for > (uint64_t)kUnitsK * 64 * nw)) nw *= 2;
         S = 64ull * nw;
     }
-    // Many planes that still leave the machine idle: more lanes for each, up to a unit per lane, until there are eight wavefronts per CU (four
+    // Many planes that still leave the machine idle (those of all maps of the launch): more lanes for each, up to a unit per lane, until there are eight wavefronts per CU (four
     // and sixteen are slower: 8 lanes with eight units one after the other on 306 rows of 114 in bfloat16 under B = 2 10.0 us, 5.6 with 32; 2000
     // maps of all sizes together 1.50 times as fast as the kernels that had them before with four, 1.53 with eight, 1.50 with sixteen)
     if (many) {
-        while (S < (b == 1 ? 512u : 1024u) && L.P * S < 8 * 64 * (uint64_t)num_cus() && q4 > S) S *= 2;
+        while (S < (b == 1 ? 512u : 1024u) && L.P * (uint64_t)maps * S < 8 * 64 * (uint64_t)num_cus() && q4 > S) S *= 2;
         nw = S < 64 ? 0 : (int)(S / 64);
     }
     if (q4 > (uint64_t)kUnitsK * S || nitem > (uint64_t)kUnitsK * S) return false;       // 8 units and 8 row segments per lane
@@ -1358,7 +1359,7 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         else if (flat && plan_strip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = STRIP; sa.tab = tab; sa.rg = rg; }
         else if (flat && plan_rowstrip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = ROWSTRIP; sa.tab = tab; sa.rg = rg; }
         else if (flat && plan_items(L, H, W, B, es, xa, &ia, &grid, &lds, &vec)) { kind = ITEMS; ia.tab = tab; ia.rg = rg; }
-        else if (!one_shape(L, es, xa) && plan_units(L, D, H, W, B, b, es, xa, &ua, &grid, &lds, &nw) && (wide || nw != 16)) { kind = UNITS; ua.tab = tab; ua.rg = rg; }
+        else if (!one_shape(L, es, xa) && plan_units(L, D, H, W, B, b, es, xa, cnt, &ua, &grid, &lds, &nw) && (wide || nw != 16)) { kind = UNITS; ua.tab = tab; ua.rg = rg; }
         else if (wide && flat && plan_wave(L, H, W, B, b, es, xa, &wa, &grid, &lds, &vec)) {
             kind = WAVE; wa.tab = tab; wa.rg = rg;
         } else if (flat && plan_tile(L, H, W, B, b, es, xa, &a, &grid, &lds, &vec, &nt)) { kind = TILE; a.tab = tab; a.rg = rg; }
@@ -1483,7 +1484,7 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
             n = snprintf(out, cap, "compress_rowstrip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
         else if (flat && plan_items(L, H, W, B, es, data, &ia, &grid, &lds, &vec))
             n = snprintf(out, cap, "compress_items<%s, %d, %d, %d, %d>", tn, b, B, vec, H == 1 ? 1 : B);
-        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, b, es, data, &ua, &grid, &lds, &nw) && (wide || nw != 16)) {
+        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, b, es, data, 1, &ua, &grid, &lds, &nw) && (wide || nw != 16)) {
             SegArgs sg{}; uint32_t seg_nt = 0; int seg_K = 0;
             if (plan_seg(L, D, H, W, B, es, &sg, &grid, &lds, &seg_nt, &seg_K))
                 n = snprintf(out, cap, "compress_seg<%s, %d, %d, %s, %d>", tn, b, B, W % 2 != 0 ? "true" : "false", seg_K);

@@ -133,6 +133,11 @@ def test_units_of_many_planes_have_lanes_for_a_machine_of_wavefronts(host, shape
     host.division_kernel_name_3d.argtypes = [ctypes.c_int, ctypes.c_void_p] + [ctypes.c_int64] * 5 + [ctypes.c_int] * 3 + [ctypes.c_char_p, ctypes.c_size_t]
     assert host.division_kernel_name_3d(0, None, *_dims(shape), dt, B, 2, name, 128) == 0 and name.value.startswith(b"compress_units<")
     assert launch.gx * max(launch.waves, 1) >= min(8 * host.check_cus(), planes * units // 64), (launch.gx, launch.waves)
+    # eight maps share the machine: no more lanes per plane than that takes, of the planes of all of them
+    (eight,) = _maps(host, [(shape, dt, B, 2)] * 8)
+    assert eight.gy == 8 and eight.waves <= launch.waves and eight.gx * max(eight.waves, 1) <= launch.gx * max(launch.waves, 1)
+    lone = _maps(host, [((8 * shape[0],) + shape[1:], dt, B, 2)])[0]
+    assert eight.waves == lone.waves
 
 
 def test_calls_that_the_units_kernel_does_not_gain_keep_their_own(host):
