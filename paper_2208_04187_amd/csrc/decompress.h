@@ -13,10 +13,8 @@ struct DecShape {        // the maps of one shape
     FastDiv d_q4, d_w4, d_B, d_W, d_HW, d_Hs, d_wpp;
     double r_q4, r_HW;   // 1 / q4, 1 / HW: a division per wavefront is 30 binary64 instructions
 };
-struct DecArgs : DecShape {
-    DecTab tab;
-    Regions rg;
-};
+struct DecHead { DecTab tab; Regions rg; };
+struct DecArgs : DecHead, DecShape {};
 
 // Index of the first block of the block row that holds row r; for a 3-D map (Appendix D,
 // UpSampling3D) r counts the rows of all depth slices.
