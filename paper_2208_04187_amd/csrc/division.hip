@@ -394,11 +394,11 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             const int kind = plan_mix(L, D, H, W, B, m.dt == DIVISION_BF16 ? 2 : 4, reinterpret_cast<const void*>(all_out), in.size(), &sh, &chunks);
             const uint64_t workgroups = (uint64_t)chunks * in.size();
             if (kind && launch_ok(workgroups, 64)) {
-                if (!mixer.fits(m.dt, m.b, in.size(), workgroups)) {
+                if (!mixer.fits(m, in.size(), workgroups)) {
                     const int rc = mixer.flush(st);
                     if (rc != DIVISION_OK) return rc;
                 }
-                mixer.add(m.dt, m.b, L, D == 1, kind, sh, chunks, in.size(), in.data(), out.data());
+                mixer.add(m, L, D == 1, kind, sh, chunks, in.size(), cap, in.data(), out.data());
                 continue;
             }
         }

@@ -41,12 +41,13 @@ def _launches(lib):
 
 
 def _maps(lib, entries, compress=True):
-    """entries: (shape, dt, B, b[, xhat]) per map, buffers 2^38 bytes apart where no address is named (never touched)"""
+    """entries: (shape, dt, B, b[, xhat[, packed[, packed_bytes]]]) per map, buffers 2^38 bytes apart where no address is named (never touched)"""
     descs = []
-    for i, (shape, dt, B, b, *out) in enumerate(entries):
+    for i, (shape, dt, B, b, *at) in enumerate(entries):
         need = lib.division_packed_bytes_3d(*_dims(shape), B, b, dt)
         base = (2 * i + 1) << 38
-        descs.append(_MapDesc(base, base + (1 << 37), out[0] if out else base, need, *_dims(shape), dt, B, b, 0))
+        out, packed, size = (list(at) + [None] * 3)[:3]
+        descs.append(_MapDesc(base, packed or base + (1 << 37), out or base, size or need, *_dims(shape), dt, B, b, 0))
     descs = (_MapDesc * len(descs))(*descs)
     call = lib.division_compress_maps if compress else lib.division_decompress_maps
     assert call(len(descs), descs, None) == 0
@@ -150,3 +151,22 @@ def test_calls_that_the_units_kernel_does_not_gain_keep_their_own(host):
         assert pk.value.decode().startswith(want), (shape, dt, B, b, pk.value)
     # few planes: lanes for all B slices of a block
     assert _maps(host, [((153, 1, 2, 7, 33), BF16, 8, 2)])[0].waves == 1
+
+
+A, B_, C_ = (2, 16, 28, 28), (3, 8, 33, 17), (5, 7, 14, 14)
+
+
+def test_maps_of_several_shapes_are_one_launch(host):
+    (launch,) = _maps(host, [(A, F32, 8, 2), (B_, F32, 8, 2), (A, F32, 8, 2), (C_, F32, 64, 2), (C_, F32, 4, 2)], compress=False)
+    assert (launch.what, launch.shapes, launch.maps) == (2, 4, 5)
+
+
+def test_a_shape_alone_in_its_launch_has_its_own_kernel(host):
+    """One shape of a type, or what is left when a launch is full: the kernel of the single-map call."""
+    found = _maps(host, [(A, F32, 8, 2), (B_, BF16, 8, 2), (B_, BF16, 8, 2), (C_, C16, 8, 2)], compress=False)
+    assert [(q.what, q.dt, q.gy) for q in found] == [(1, F32, 1), (1, BF16, 2), (1, C16, 1)]
+    alone = _maps(host, [(B_, BF16, 8, 2)] * 2, compress=False)
+    assert alone[0].kind == found[1].kind
+    found = _maps(host, [((1, k + 1, 28, 28), F32, 8, 2) for k in range(17)], compress=False)
+    assert [(q.what, q.shapes) for q in found] == [(2, 16), (1, 1)]
+
