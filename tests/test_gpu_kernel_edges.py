@@ -225,6 +225,22 @@ def test_decompress_of_maps_that_share_memory_keeps_their_order():
         assert np.array_equal(last.cpu().numpy(), np.asarray(oracle.decompress(ref[2], shapes[2][0], 8, 2, oracle.F32)).reshape(-1))
 
 
+# a map whose kernel has a launch of its own (B = 2) after one that waits for a launch of several shapes, over the same memory
+def test_decompress_of_a_map_with_a_launch_of_its_own_over_another_keeps_their_order():
+    shapes = [((2, 3, 28, 28), 8), ((2, 3, 15, 11), 2), ((1, 5, 14, 14), 8)]
+    gen = torch.Generator().manual_seed(9)
+    xs = [torch.randn(s, generator=gen) for s, _ in shapes]
+    ref = [oracle.compress(x.numpy(), B, 2, 5, oracle.F32) for x, (_, B) in zip(xs, shapes)]
+    back = [np.asarray(oracle.decompress(r, s, B, 2, oracle.F32)).reshape(-1) for r, (s, B) in zip(ref, shapes)]
+    packed = [torch.from_numpy(r).to("cuda:0") for r in ref]
+    area, last = torch.zeros(4704, device="cuda:0"), torch.zeros(980, device="cuda:0")
+    pkg.division_decompress_maps(packed, [s for s, _ in shapes], [B for _, B in shapes], 2, out=[area.view(shapes[0][0]), area[1000:1990].view(shapes[1][0]), last.view(shapes[2][0])])
+    torch.cuda.synchronize()
+    want = back[0].copy()
+    want[1000:1990] = back[1]
+    assert np.array_equal(area.cpu().numpy(), want) and np.array_equal(last.cpu().numpy(), back[2])
+
+
 # planes of sixteen wavefronts: eight maps of 37 planes, more than there are workgroups, so that a workgroup takes several planes
 # (some one more than others) and loads the next one's units as the codes of the present one leave
 @pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 8), ("bf16", 4), ("bf16", 1), ("c16", 2)])

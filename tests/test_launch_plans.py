@@ -170,3 +170,51 @@ def test_a_shape_alone_in_its_launch_has_its_own_kernel(host):
     found = _maps(host, [((1, k + 1, 28, 28), F32, 8, 2) for k in range(17)], compress=False)
     assert [(q.what, q.shapes) for q in found] == [(2, 16), (1, 1)]
 
+
+def _order(host, entries):
+    return [q.out for q in _maps(host, entries, compress=False)]
+
+
+def test_maps_that_share_memory_keep_the_order_of_their_descriptors(host):
+    x, y = 1 << 46, 1 << 47
+    size = 4 * 2 * 16 * 28 * 28
+    # B = 2 has a launch of its own and would go first: the overlapping map A before it has to be written before
+    own = (B_, F32, 2, 2)
+    for at in (x, x + size - 4, x - 16):
+        assert _order(host, [(A, F32, 8, 2, x), (*own, at), (C_, F32, 8, 2, y)]) == [x, at, y]
+    assert len(_maps(host, [(A, F32, 8, 2, x), (*own, x + size), (C_, F32, 8, 2, y)], compress=False)) == 2        # side by side: mixed
+    # a map rebuilt from a buffer that another map's output covers
+    assert _order(host, [(A, F32, 8, 2, x), (C_, F32, 8, 2, y, x + 256), (B_, F32, 8, 2)]) == [x, y, 5 << 38]
+    # two maps read one buffer: nothing is written there
+    assert len(_maps(host, [(A, F32, 8, 2, x, 1 << 48), (C_, F32, 8, 2, y, 1 << 48)], compress=False)) == 1
+
+
+def test_the_size_named_for_a_packed_buffer_does_not_decide_what_overlaps(host):
+    """A capacity beyond the buffer's own bytes is no memory that the call reads; the largest ones would wrap around."""
+    x, y = 1 << 46, 1 << 47
+    for size in (1 << 49, (1 << 64) - 1):
+        assert len(_maps(host, [(A, F32, 8, 2, x, None, size), (C_, F32, 8, 2, y, None, size)], compress=False)) == 1
+        assert _order(host, [(A, F32, 8, 2, x, None, size), (C_, F32, 8, 2, y, x + 256, size), (B_, F32, 8, 2, None, None, size)]) == [x, y, 5 << 38]
+
+
+def test_overlaps_of_random_ranges_are_those_of_every_pair(host):
+    import random
+    rng = random.Random(3)
+    seen = set()
+    for _ in range(400):
+        entries, outs, ins = [], [], []
+        for k in range(rng.randint(2, 6)):
+            shape, B = rng.choice([(A, 8), (B_, 8), (C_, 4)])
+            n = 4 * shape[0] * shape[1] * shape[2] * shape[3]
+            need = host.division_packed_bytes_3d(*_dims(shape), B, 2, F32)
+            o, p = (1 << 40) + 64 * rng.randint(0, 12000), (1 << 40) + 64 * rng.randint(0, 12000)
+            entries.append((shape, F32, B, 2, o, p))
+            outs.append((o, o + n, k))
+            ins.append((p, p + need, k))
+        if len({e[:4] for e in entries}) < 2:
+            continue
+        want = any(a[0] < b[1] and b[0] < a[1] for i, a in enumerate(outs) for b in outs[:i] + ins)
+        mixed = any(q.what == 2 for q in _maps(host, entries, compress=False))
+        assert mixed != want
+        seen.add(want)
+    assert seen == {True, False}
