@@ -674,9 +674,13 @@ __global__ void __launch_bounds__(kThreads) decompress_words_3d(DecArgs a) { dec
 // the next plane's codes, LFC and meta are loaded while the current one is rebuilt.
 // What bounds it on maps of a few planes per workgroup: the table.  Looked up per element and for all eight rounds, maps of 4 M bfloat16 elements
 // took (us, the call's 7 us of host included) 35 x 35 9.9, 55 x 55 10.2, 147 x 147 9.8; per unit and for the rounds there are 7.7, 7.9, 8.0.
+// WIDE: rows and blocks of at least three elements, which the look-up per unit asks for.  The others look up element by element and all
+// eight rounds, side by side and with no branch that would hold back the loads behind it, in a kernel of their own
+// (the one with a fourth argument): with both in one 3 x 3 x 13 x 24 x 22 under B = 2 took 5.9 us instead of 5.3, 40 x 16 x 35 x 35 in bfloat16 under
+// B = 18 5.4 instead of 5.2.
 constexpr int kUnitsLfc = 4;      // LFC values a lane stages per plane: planes of up to 4 * threads blocks
-template <typename T, int BITS, int NW>
-__global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) {
+template <typename T, int BITS, int NW, bool WIDE>
+__device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
     constexpr int NT = 64 * NW;
     constexpr int K = kUnitsK;
     constexpr int KL = kUnitsLfc;
@@ -702,9 +706,9 @@ __global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) {
     uint32_t lo[K][2];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        if (!round_live(k)) continue;
         uint32_t off[4];
-        if (a.W >= 3 && a.B >= 3) {
+        if constexpr (WIDE) {
+            if (!round_live(k)) continue;
             const uint32_t f = tid + NT * k, before = f ? 0u : shift;     // elements of the unit before the plane
             const uint32_t e0 = f ? 4u * f - shift : 0u;
             const uint32_t ra = fdiv(e0, a.d_W), c = e0 - ra * a.W;      // row, counted over all depth slices
@@ -827,6 +831,11 @@ __global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) {
         }
     }
 }
+
+template <typename T, int BITS, int NW>
+__global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) { decompress_units_body<T, BITS, NW, true>(a); }
+template <typename T, int BITS, int NW, int EACH>
+__global__ void __launch_bounds__(64 * NW) decompress_units(DecArgs a) { decompress_units_body<T, BITS, NW, false>(a); }
 
 // planes too large for the 32-bit index tricks above: one element per thread step
 template <typename T, int BITS, int ND>

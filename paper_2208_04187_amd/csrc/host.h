@@ -1180,6 +1180,9 @@ hipError_t do_compress(const CompLaunch& c, int b) {
     });
 }
 
+// the instances of decompress_units that look up per unit of four elements
+bool units_wide(const DecShape& a) { return a.W >= 3 && a.B >= 3; }
+
 template <typename T>
 hipError_t do_decompress(const DecLaunch& c, int b) {
     // every decompress kernel has an instance for 1-bit codes too
@@ -1195,9 +1198,14 @@ hipError_t do_decompress(const DecLaunch& c, int b) {
             return hipGetLastError();
         }
         if (kind == 6) {
-            kern = c.nw == 1 ? decompress_units<T, BITS, 1> : c.nw == 2 ? decompress_units<T, BITS, 2>
-                 : c.nw == 4 ? decompress_units<T, BITS, 4> : c.nw == 8 ? decompress_units<T, BITS, 8>
-                                                                        : decompress_units<T, BITS, 16>;
+            if (units_wide(c.a))
+                kern = c.nw == 1 ? decompress_units<T, BITS, 1> : c.nw == 2 ? decompress_units<T, BITS, 2>
+                     : c.nw == 4 ? decompress_units<T, BITS, 4> : c.nw == 8 ? decompress_units<T, BITS, 8>
+                                                                            : decompress_units<T, BITS, 16>;
+            else
+                kern = c.nw == 1 ? decompress_units<T, BITS, 1, 1> : c.nw == 2 ? decompress_units<T, BITS, 2, 1>
+                     : c.nw == 4 ? decompress_units<T, BITS, 4, 1> : c.nw == 8 ? decompress_units<T, BITS, 8, 1>
+                                                                                 : decompress_units<T, BITS, 16, 1>;
             hipLaunchKernelGGL(kern, dim3(c.gx, c.gy), dim3(64 * c.nw), c.lds, c.st, c.a);
             return hipGetLastError();
         }
@@ -1513,7 +1521,7 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
         DecArgs a{}; uint32_t grid = 0;
         const int kind = plan_decompress(L, D, H, W, B, es, data, &a, &grid);
         if (kind == 6)
-            n = snprintf(out, cap, "decompress_units<%s, %d, %d>", tn, b, (int)a.G);
+            n = snprintf(out, cap, "decompress_units<%s, %d, %d%s>", tn, b, (int)a.G, units_wide(a) ? "" : ", 1");
         else if (kind == 7)
             n = snprintf(out, cap, "decompress_stream%s<%s, %d>", sfx, tn, b);
         else if (kind == 8)

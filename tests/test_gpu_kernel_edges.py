@@ -307,3 +307,13 @@ def test_general_kernel_lanes_per_block(shape, B, b, mode):
 def test_items_of_even_widths(shape, B, mode, b):
     assert _names(shape, B, b, mode)[0].startswith("compress_seg<")
     _round_trip(shape, B, b, mode)
+
+
+# decompress_units: rows or blocks of one and two elements, which are looked up element by element, beside those that are not
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+@pytest.mark.parametrize("shape,B,b,each", [((3, 5, 35, 35), 2, 2, True), ((5, 3, 601, 2), 4, 1, True), ((2, 3, 1203, 1), 3, 8, True), ((3, 5, 36, 36), 1, 4, True), ((2, 3, 7, 13, 17), 2, 2, True),
+                                            ((300, 3, 27, 27), 2, 2, True), ((3, 5, 37, 37), 3, 2, False), ((5, 3, 401, 3), 3, 4, False), ((2, 3, 70, 71), 2, 2, True)])
+def test_decompress_units_of_narrow_rows_and_blocks(shape, B, b, each, mode):
+    name = _names(shape, B, b, mode)[1]
+    assert name.startswith("decompress_units<") and (name.count(",") == 3) == each, name
+    _round_trip(shape, B, b, mode)
