@@ -201,12 +201,13 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, 
     bool seg = false;
     if (D == 1 && H > 1 && (B == 4 || B == 8) && W % 2 == 0 && 4ull * L.HW + 16ull <= kWavePlaneMax) {
         // (4-byte elements, a plane for every CU: compress_seg where it takes them; 4 M elements of 57 x 70 under B = 4 36.2 -> 9.3 us,
-        // 19 x 46 under B = 8 14.3 -> 7.9, 42 x 18 11.1 -> 8.5, 63 x 32 9.8 -> 8.4, 116 x 12 level)
+        // 19 x 46 under B = 8 14.3 -> 7.9, 42 x 18 11.1 -> 8.5, 63 x 32 9.8 -> 8.4; not the narrow rows of whole vectors under B = 4, of which the wavefront kernel's lanes have a block
+        // row each: 308 x 16 x 134 x 12 13.5 -> 14.5, 116 x 8 level)
         SegArgs t{};
         uint32_t g = 0, nt = 0;
         size_t l = 0;
         int K = 0;
-        seg = b != 1 && L.P >= kUnitsManyPlanes && plan_seg(L, D, H, W, B, es, &t, &g, &l, &nt, &K);
+        seg = b != 1 && L.P >= kUnitsManyPlanes && !(B == 4 && W % 4 == 0 && W < 16) && plan_seg(L, D, H, W, B, es, &t, &g, &l, &nt, &K);
         if (!seg) return false;
     }
     const uint64_t q4 = (L.HW + 3) / 4;
