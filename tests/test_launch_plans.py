@@ -147,7 +147,7 @@ def test_calls_that_the_units_kernel_does_not_gain_keep_their_own(host):
     for shape, dt, B, b, want in (((1746, 1, 1, 2032), BF16, 4, 1, "compress_tile<"), ((1048, 1, 1, 7196), F32, 4, 8, "compress_tile<"), ((5340, 1, 1, 663), BF16, 64, 2, "compress_rows<"),
                                   ((5340, 1, 1, 663), BF16, 64, 1, "compress_units<"), ((5340, 1, 1, 663), F32, 64, 2, "compress_units<"), ((3760, 1, 131, 1), F32, 2, 4, "compress_rows<"),
                                   ((3760, 1, 131, 1), F32, 2, 1, "compress_units<"), ((2516, 1, 37, 5), BF16, 2, 4, "compress_rows<"), ((2516, 1, 37, 5), BF16, 12, 4, "compress_units<"),
-                                  ((308, 16, 134, 12), F32, 4, 4, "compress_wave<"), ((308, 16, 134, 12), F32, 8, 4, "compress_seg<"), ((308, 16, 134, 18), F32, 4, 4, "compress_seg<"),
+                                  ((308, 16, 134, 12), F32, 4, 4, "compress_wave<"), ((308, 16, 134, 12), F32, 8, 4, "compress_seg<"), ((308, 16, 42, 18), F32, 4, 4, "compress_seg<"),
                                   ((80, 16, 62, 20), F32, 4, 2, "compress_seg<")):
         assert host.division_kernel_name_3d(0, None, *_dims(shape), dt, B, b, pk, 128) == 0
         assert pk.value.decode().startswith(want), (shape, dt, B, b, pk.value)
