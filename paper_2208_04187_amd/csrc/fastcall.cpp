@@ -98,13 +98,14 @@ PyObject* tuple_of(std::initializer_list<at::Tensor> ts) {
     }
     return r;
 }
-// The library call without the interpreter's lock, as a call through ctypes makes it
+// The output tensors and the library call without the interpreter's lock, as torch.empty and a call through ctypes take them: an
+// allocation may wait for the device, other threads do not wait with it.  f touches no Python object.
 template <typename F> int without_lock(F&& f) {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f();
-    Py_END_ALLOW_THREADS
-    return rc;
+    struct Unlocked {
+        PyThreadState* state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }        // behind exceptions too
+    } unlocked;
+    return f();
 }
 
 #define PLAIN(n) if (nargs != (n) || !plain_state()) return none()
@@ -122,10 +123,14 @@ PyObject* py_compress(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     if (dt < 0 || x->dim() != nd || !dims_of(*x, &s) || !x->is_contiguous()) return none();
     const size_t need = packed_bytes(s.n, s.c, s.d, s.h, s.w, B, b, (division_dtype)dt);
     if (need == 0) return none();
-    at::Tensor packed = make({(int64_t)need}, at::kByte, x->device());
     const void* xp = x->data_ptr();
-    void *pk = packed.data_ptr(), *st = current_stream();
-    const int rc = without_lock([&] { return compress(xp, s.n, s.c, s.d, s.h, s.w, (division_dtype)dt, B, b, seed, pk, need, st); });
+    const c10::Device dev = x->device();
+    void* st = current_stream();
+    at::Tensor packed;
+    const int rc = without_lock([&] {
+        packed = make({(int64_t)need}, at::kByte, dev);
+        return compress(xp, s.n, s.c, s.d, s.h, s.w, (division_dtype)dt, B, b, seed, packed.data_ptr(), need, st);
+    });
     return rc ? PyLong_FromLong(rc) : wrap(std::move(packed));
     END_HANDLE_TH_ERRORS
 }
@@ -145,11 +150,15 @@ PyObject* py_decompress(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const int dt = type_of(t, a[5] == Py_True);
     // (sizes the library refuses: before a tensor of them is asked for)
     if (dt < 0 || packed_bytes(s.n, s.c, s.d, s.h, s.w, B, b, (division_dtype)dt) == 0) return none();
-    at::Tensor out = make(sizes, t, packed->device());
     const void* pk = packed->data_ptr();
-    void *y = out.data_ptr(), *st = current_stream();
     const size_t have = bytes(*packed);
-    const int rc = without_lock([&] { return decompress(pk, have, s.n, s.c, s.d, s.h, s.w, (division_dtype)dt, B, b, y, st); });
+    const c10::Device dev = packed->device();
+    void* st = current_stream();
+    at::Tensor out;
+    const int rc = without_lock([&] {
+        out = make(sizes, t, dev);
+        return decompress(pk, have, s.n, s.c, s.d, s.h, s.w, (division_dtype)dt, B, b, out.data_ptr(), st);
+    });
     return rc ? PyLong_FromLong(rc) : wrap(std::move(out));
     END_HANDLE_TH_ERRORS
 }
@@ -179,7 +188,7 @@ PyObject* py_compress_maps(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(a[0]);
     if (n == 0 || PySequence_Fast_GET_SIZE(a[3]) != n) return none();
     std::vector<division_map> maps((size_t)n);
-    std::vector<at::Tensor> made((size_t)n);
+    std::vector<at::Tensor> made((size_t)n), held((size_t)n);      // held: the maps, whose list another thread may change meanwhile
     for (Py_ssize_t i = 0; i < n; ++i) {
         division_map& m = maps[(size_t)i];
         const at::Tensor* x = device_tensor(PySequence_Fast_GET_ITEM(a[0], i));
@@ -194,14 +203,16 @@ PyObject* py_compress_maps(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
         if (m.packed_bytes == 0) return none();
         m.x = x->data_ptr();
         m.xhat = nullptr;
-    }
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        const at::Tensor& x = THPVariable_Unpack(PySequence_Fast_GET_ITEM(a[0], i));
-        made[(size_t)i] = make({(int64_t)maps[(size_t)i].packed_bytes}, at::kByte, x.device());
-        maps[(size_t)i].packed = made[(size_t)i].data_ptr();
+        held[(size_t)i] = *x;
     }
     void* st = current_stream();
-    const int rc = without_lock([&] { return compress_maps((int)n, maps.data(), st); });
+    const int rc = without_lock([&] {
+        for (size_t i = 0; i < maps.size(); ++i) {
+            made[i] = make({(int64_t)maps[i].packed_bytes}, at::kByte, held[i].device());
+            maps[i].packed = made[i].data_ptr();
+        }
+        return compress_maps((int)n, maps.data(), st);
+    });
     return rc ? PyLong_FromLong(rc) : list_of(made);
     END_HANDLE_TH_ERRORS
 }
@@ -214,7 +225,7 @@ PyObject* py_decompress_maps(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const Py_ssize_t n = PySequence_Fast_GET_SIZE(a[0]);
     if (n == 0 || PySequence_Fast_GET_SIZE(a[1]) != n) return none();
     std::vector<division_map> maps((size_t)n);
-    std::vector<at::Tensor> made((size_t)n);
+    std::vector<at::Tensor> made((size_t)n), held((size_t)n);
     std::vector<std::vector<int64_t>> sizes((size_t)n);
     std::vector<at::ScalarType> types((size_t)n);
     for (Py_ssize_t i = 0; i < n; ++i) {
@@ -235,14 +246,16 @@ PyObject* py_decompress_maps(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
         m.packed_bytes = bytes(*packed);
         m.x = nullptr;
         m.seed = 0;
-    }
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        const at::Tensor& packed = THPVariable_Unpack(PySequence_Fast_GET_ITEM(a[0], i));
-        made[(size_t)i] = make(sizes[(size_t)i], types[(size_t)i], packed.device());
-        maps[(size_t)i].xhat = made[(size_t)i].data_ptr();
+        held[(size_t)i] = *packed;
     }
     void* st = current_stream();
-    const int rc = without_lock([&] { return decompress_maps((int)n, maps.data(), st); });
+    const int rc = without_lock([&] {
+        for (size_t i = 0; i < maps.size(); ++i) {
+            made[i] = make(sizes[i], types[i], held[i].device());
+            maps[i].xhat = made[i].data_ptr();
+        }
+        return decompress_maps((int)n, maps.data(), st);
+    });
     return rc ? PyLong_FromLong(rc) : list_of(made);
     END_HANDLE_TH_ERRORS
 }
@@ -252,6 +265,9 @@ PyObject* py_decompress_maps(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
 // a contiguous device tensor of an element type the operators take (0, 1), else -1
 int flat_type(const at::Tensor* x) { return x && x->numel() > 0 && x->is_contiguous() ? type_of(x->scalar_type(), false) : -1; }
 at::Tensor new_mask(int64_t n, const at::Tensor& x) { return make({(int64_t)(mask_bytes(n) / 4)}, at::kInt, x.device()); }
+// y like x and a mask of x's elements
+struct Masked { at::Tensor y, mask; };
+Masked new_masked(const at::Tensor& x) { return {at::empty_like(x), new_mask(x.numel(), x)}; }
 
 // relu_forward(x)
 PyObject* py_relu_forward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
@@ -261,12 +277,14 @@ PyObject* py_relu_forward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const int dt = flat_type(x);
     if (dt < 0) return none();
     const int64_t n = x->numel();
-    at::Tensor y = at::empty_like(*x), mask = new_mask(n, *x);
     const void* xp = x->data_ptr();
-    void *yp = y.data_ptr(), *mp = mask.data_ptr(), *st = current_stream();
-    const size_t mb = bytes(mask);
-    const int rc = without_lock([&] { return relu_forward(xp, n, (division_dtype)dt, yp, mp, mb, st); });
-    return rc ? PyLong_FromLong(rc) : tuple_of({y, mask});
+    void* st = current_stream();
+    Masked o;
+    const int rc = without_lock([&] {
+        o = new_masked(*x);
+        return relu_forward(xp, n, (division_dtype)dt, o.y.data_ptr(), o.mask.data_ptr(), bytes(o.mask), st);
+    });
+    return rc ? PyLong_FromLong(rc) : tuple_of({o.y, o.mask});
     END_HANDLE_TH_ERRORS
 }
 
@@ -283,12 +301,16 @@ PyObject* py_relu_compress(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     if (dt < 0 || !dims_of(*x, &s)) return none();
     const size_t need = packed_bytes(s.n, s.c, 1, s.h, s.w, B, b, (division_dtype)dt);
     if (need == 0) return none();
-    at::Tensor y = at::empty_like(*x), mask = new_mask(x->numel(), *x), packed = make({(int64_t)need}, at::kByte, x->device());
     const void* xp = x->data_ptr();
-    void *yp = y.data_ptr(), *mp = mask.data_ptr(), *pk = packed.data_ptr(), *st = current_stream();
-    const size_t mb = bytes(mask);
-    const int rc = without_lock([&] { return relu_compress(xp, s.n, s.c, s.h, s.w, (division_dtype)dt, B, b, seed, yp, mp, mb, pk, need, st); });
-    return rc ? PyLong_FromLong(rc) : tuple_of({y, mask, packed});
+    void* st = current_stream();
+    Masked o;
+    at::Tensor packed;
+    const int rc = without_lock([&] {
+        o = new_masked(*x);
+        packed = make({(int64_t)need}, at::kByte, x->device());
+        return relu_compress(xp, s.n, s.c, s.h, s.w, (division_dtype)dt, B, b, seed, o.y.data_ptr(), o.mask.data_ptr(), bytes(o.mask), packed.data_ptr(), need, st);
+    });
+    return rc ? PyLong_FromLong(rc) : tuple_of({o.y, o.mask, packed});
     END_HANDLE_TH_ERRORS
 }
 
@@ -302,12 +324,14 @@ PyObject* py_dropout_forward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     if (dt < 0 || !PyFloat_CheckExact(a[1]) || !seed64(a[2], &seed)) return none();
     const float p = (float)PyFloat_AS_DOUBLE(a[1]);
     const int64_t n = x->numel();
-    at::Tensor y = at::empty_like(*x), mask = new_mask(n, *x);
     const void* xp = x->data_ptr();
-    void *yp = y.data_ptr(), *mp = mask.data_ptr(), *st = current_stream();
-    const size_t mb = bytes(mask);
-    const int rc = without_lock([&] { return dropout_forward(xp, n, (division_dtype)dt, p, seed, yp, mp, mb, st); });
-    return rc ? PyLong_FromLong(rc) : tuple_of({y, mask});
+    void* st = current_stream();
+    Masked o;
+    const int rc = without_lock([&] {
+        o = new_masked(*x);
+        return dropout_forward(xp, n, (division_dtype)dt, p, seed, o.y.data_ptr(), o.mask.data_ptr(), bytes(o.mask), st);
+    });
+    return rc ? PyLong_FromLong(rc) : tuple_of({o.y, o.mask});
     END_HANDLE_TH_ERRORS
 }
 
@@ -319,11 +343,14 @@ PyObject* py_mask_backward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     const int dt = flat_type(g);
     if (!mask || dt < 0) return none();
     const int64_t n = g->numel();
-    at::Tensor out = at::empty_like(*g);
     const void *mp = mask->data_ptr(), *gp = g->data_ptr();
-    void *op = out.data_ptr(), *st = current_stream();
     const size_t mb = bytes(*mask);
-    const int rc = without_lock([&] { return mask_backward(mp, mb, gp, n, (division_dtype)dt, op, st); });
+    void* st = current_stream();
+    at::Tensor out;
+    const int rc = without_lock([&] {
+        out = at::empty_like(*g);
+        return mask_backward(mp, mb, gp, n, (division_dtype)dt, out.data_ptr(), st);
+    });
     return rc ? PyLong_FromLong(rc) : wrap(std::move(out));
     END_HANDLE_TH_ERRORS
 }
@@ -337,11 +364,14 @@ PyObject* py_maxpool_forward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     int k;
     Dims s;
     if (dt < 0 || x->dim() != 4 || !whole32(a[1], &k) || k < 1 || !dims_of(*x, &s)) return none();
-    at::Tensor y = make({s.n, s.c, s.h / k, s.w / k}, x->scalar_type(), x->device()), mask = new_mask(x->numel(), *x);
     const void* xp = x->data_ptr();
-    void *yp = y.data_ptr(), *mp = mask.data_ptr(), *st = current_stream();
-    const size_t mb = bytes(mask);
-    const int rc = without_lock([&] { return maxpool_forward(xp, s.n, s.c, s.h, s.w, (division_dtype)dt, k, yp, mp, mb, st); });
+    void* st = current_stream();
+    at::Tensor y, mask;
+    const int rc = without_lock([&] {
+        y = make({s.n, s.c, s.h / k, s.w / k}, x->scalar_type(), x->device());
+        mask = new_mask(x->numel(), *x);
+        return maxpool_forward(xp, s.n, s.c, s.h, s.w, (division_dtype)dt, k, y.data_ptr(), mask.data_ptr(), bytes(mask), st);
+    });
     return rc ? PyLong_FromLong(rc) : tuple_of({y, mask});
     END_HANDLE_TH_ERRORS
 }
@@ -358,11 +388,14 @@ PyObject* py_maxpool_backward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     if (!mask || dt < 0 || !whole32(a[3], &k) || k < 1 || !dims_of(a[2], &s, &sizes) || sizes.size() != 4 || g->dim() != 4) return none();
     const auto gs = g->sizes();
     if (gs[0] != s.n || gs[1] != s.c || gs[2] != s.h / k || gs[3] != s.w / k) return none();
-    at::Tensor out = make(sizes, g->scalar_type(), g->device());
     const void *mp = mask->data_ptr(), *gp = g->data_ptr();
-    void *op = out.data_ptr(), *st = current_stream();
     const size_t mb = bytes(*mask);
-    const int rc = without_lock([&] { return maxpool_backward(mp, mb, gp, s.n, s.c, s.h, s.w, (division_dtype)dt, k, op, st); });
+    void* st = current_stream();
+    at::Tensor out;
+    const int rc = without_lock([&] {
+        out = make(sizes, g->scalar_type(), g->device());
+        return maxpool_backward(mp, mb, gp, s.n, s.c, s.h, s.w, (division_dtype)dt, k, out.data_ptr(), st);
+    });
     return rc ? PyLong_FromLong(rc) : wrap(std::move(out));
     END_HANDLE_TH_ERRORS
 }
