@@ -132,3 +132,38 @@ def test_other_threads_run_while_a_call_allocates():
         thread.join()
     torch.cuda.synchronize()
     assert min(native) < 5 * min(general) + 5e-5, (native, general)
+
+
+# every call's work is on the stream that is current for it: recorded into a graph with the others, replayed over other inputs
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_calls_run_on_the_current_stream(native):
+    import contextlib
+    gen = torch.Generator().manual_seed(11)
+    inputs = [torch.randn((3, 5, 14, 14), generator=gen).to("cuda:0") for _ in range(4)]
+    x = inputs[0].clone()
+
+    def calls():
+        y, mask = pkg.division_maxpool_forward(x, 3)
+        p = pkg.division_compress(x, 8, 2, 5)
+        ps = pkg.division_compress_maps([x, x[:2]], 8, [2, 4], [6, 7])
+        r = pkg.division_relu_forward(x)
+        return [y, mask, p, *ps, *r, *pkg.division_relu_compress(x, 8, 2, 3), *pkg.division_dropout_forward(x, 0.25, 9), pkg.division_decompress(p, x.shape, 8, 2),
+                *pkg.division_decompress_maps(ps, [x.shape, x[:2].shape], 8, [2, 4]), pkg.division_mask_backward(r[1], x), pkg.division_maxpool_backward(mask, y, x.shape, 3)]
+
+    with contextlib.nullcontext() if native else _General():
+        wanted = []
+        for v in inputs:
+            x.copy_(v)
+            wanted.append([t.clone() for t in calls()])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            outputs = calls()
+        for v, want in zip(inputs[::-1] + inputs, wanted[::-1] + wanted):
+            x.copy_(v)
+            graph.replay()
+            torch.cuda.synchronize()
+            for k, (got, ref) in enumerate(zip(outputs, want)):
+                assert torch.equal(got, ref), k
+            calls()
