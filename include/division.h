@@ -347,7 +347,8 @@ float division_block_mean_rule(double block_sum, uint32_t count, int *divided);
 float division_block_mean_rule_rcp(double block_sum, uint32_t count, double reciprocal, int *divided);
 double division_count_reciprocal(uint32_t count, double estimate);
 
-/* Version of this ABI (host-only). */
+/* Version of this ABI (host-only): DIVISION_ABI_VERSION of the header that the library was built with. */
+#define DIVISION_ABI_VERSION 1
 int division_abi_version(void);
 
 #ifdef __cplusplus

@@ -8,6 +8,8 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib
+import warnings
 from pathlib import Path
 
 import torch
@@ -103,17 +105,25 @@ class _NothingFast:
         return lambda *args: None
 
 
+_FAST_PATH = _LIB_PATH.with_name("_fastcall.so")
 _fast = None
 
 
 def _load_fast():
+    """The native side, bound to the library; built first only if no build exists.  Where it cannot be had (no compiler, another torch,
+    a build for another version of the library) every call takes the general way, with a warning once."""
     global _fast
     if _fast is None:
         L = lib()
         try:
-            from . import _fastcall as module
-            module.bind([ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _FAST_ENTRIES])
-        except ImportError:
+            if not _FAST_PATH.exists():
+                from . import _build
+                _build.build_fastcall()
+                importlib.invalidate_caches()
+            module = importlib.import_module("._fastcall", __package__)
+            module.bind([ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _FAST_ENTRIES], L.division_abi_version(), ctypes.sizeof(_MapDesc))
+        except (ImportError, ValueError, TypeError, RuntimeError, OSError) as err:
+            warnings.warn(f"the native side of the binding is not used, small calls take twice as long on the host: {err}", RuntimeWarning, stacklevel=3)
             module = _NothingFast()
         _fast = module
     return _fast

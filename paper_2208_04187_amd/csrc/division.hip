@@ -175,7 +175,7 @@ hipError_t division_bridge_relu_c16(const void* c, int b) { return do_relu<f32c1
 #if DIVISION_HOST
 extern "C" {
 
-int division_abi_version(void) { return 1; }
+int division_abi_version(void) { return DIVISION_ABI_VERSION; }
 
 size_t division_packed_bytes(int64_t N, int64_t C, int64_t H, int64_t W, int B, int b, division_dtype dt) {
     Layout L;

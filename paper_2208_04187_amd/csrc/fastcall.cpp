@@ -400,25 +400,32 @@ PyObject* py_maxpool_backward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses): the entries above in the order of the table
-PyObject* py_bind(PyObject*, PyObject* list) {
+// bind(addresses, version, map_bytes): the entries above in the order of the table, of a library of this ABI version whose descriptors
+// are so large.  A ValueError where this module was built for another library.
+PyObject* py_bind(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
     void** at[] = {(void**)&packed_bytes, (void**)&compress, (void**)&decompress, (void**)&compress_maps, (void**)&decompress_maps,
                    (void**)&relu_compress, (void**)&relu_forward, (void**)&dropout_forward, (void**)&mask_backward,
                    (void**)&maxpool_forward, (void**)&maxpool_backward, (void**)&mask_bytes};
     constexpr Py_ssize_t n = sizeof at / sizeof at[0];
-    if (!PyList_CheckExact(list) || PyList_GET_SIZE(list) != n) { PyErr_SetString(PyExc_ValueError, "a list of the library's entries"); return nullptr; }
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        void* p = PyLong_AsVoidPtr(PyList_GET_ITEM(list, i));
-        if (!p) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a null entry"); return nullptr; }
-        *at[i] = p;
+    int version = 0, map_bytes = 0;
+    if (nargs != 3 || !PyList_CheckExact(a[0]) || PyList_GET_SIZE(a[0]) != n || !whole32(a[1], &version) || !whole32(a[2], &map_bytes) ||
+        version != DIVISION_ABI_VERSION || map_bytes != (int)sizeof(division_map)) {
+        PyErr_Format(PyExc_ValueError, "built for ABI version %d with %d entries and descriptors of %d bytes", DIVISION_ABI_VERSION, (int)n, (int)sizeof(division_map));
+        return nullptr;
     }
+    void* found[n];
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        found[i] = PyLong_AsVoidPtr(PyList_GET_ITEM(a[0], i));
+        if (!found[i]) { if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a null entry"); return nullptr; }
+    }
+    for (Py_ssize_t i = 0; i < n; ++i) *at[i] = found[i];
     Py_RETURN_NONE;
 }
 
 #define FAST(name) {#name, (PyCFunction)(void*)py_##name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(compress), FAST(decompress), FAST(compress_maps), FAST(decompress_maps), FAST(relu_forward), FAST(relu_compress),
                          FAST(dropout_forward), FAST(mask_backward), FAST(maxpool_forward), FAST(maxpool_backward),
-                         {"bind", py_bind, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+                         FAST(bind), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -1,6 +1,8 @@
 """The native side of the binding serves plain calls with the results of the general one and leaves it all others."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -21,6 +23,41 @@ def test_native_side_is_built_and_leaves_host_tensors_alone():
             call()
     with pytest.raises(ValueError):
         fast.bind([1])
+
+
+def _loaded_anew(monkeypatch):
+    """binding._fast as a fresh process finds it"""
+    monkeypatch.setattr(binding, "_fast", None)
+    return binding._load_fast()
+
+
+def test_native_side_is_built_where_it_is_missing(monkeypatch, tmp_path):
+    from paper_2208_04187_amd import _build
+    built = []
+    monkeypatch.setattr(binding, "_FAST_PATH", tmp_path / "_fastcall.so")
+    monkeypatch.setattr(_build, "build_fastcall", lambda: built.append(True))
+    assert _loaded_anew(monkeypatch).__name__.endswith("_fastcall") and built == [True]
+
+    def no_compiler():
+        raise RuntimeError("g++ failed")
+    monkeypatch.setattr(_build, "build_fastcall", no_compiler)
+    with pytest.warns(RuntimeWarning, match="g\\+\\+ failed"):
+        assert isinstance(_loaded_anew(monkeypatch), binding._NothingFast)
+
+
+@pytest.mark.parametrize("entries,version,map_bytes", [(12, 2, None), (12, 1, 104), (11, 1, None), (12, None, None)])
+def test_native_side_of_another_library_is_not_used(monkeypatch, entries, version, map_bytes):
+    fast = binding._load_fast()
+    size = map_bytes or ctypes.sizeof(binding._MapDesc)
+    with pytest.raises(ValueError, match="ABI version 1 "):
+        fast.bind([1] * entries, version, size)
+    bind = fast.bind
+    monkeypatch.setattr(fast, "bind", lambda *args: bind([1] * entries, version, size))
+    with pytest.warns(RuntimeWarning, match="ABI version 1 "):
+        assert isinstance(_loaded_anew(monkeypatch), binding._NothingFast)
+    monkeypatch.undo()
+    x = torch.zeros(2, 2, 8, 8)
+    assert binding._load_fast() is fast and fast.compress(x, 8, 2, 1, False, 4) is None
 
 
 class _General:
