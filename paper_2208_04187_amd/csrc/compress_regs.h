@@ -62,7 +62,8 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     auto to_map = [&](uint32_t& map, uint32_t& plane) { while (plane >= a.P) { plane -= a.P; ++map; } };
     if constexpr (PIPE) to_map(ti, p);
     else p = xcd_run_index(p, a.P);
-    if constexpr (!PIPE) { if (blockIdx.x == 0) zero_pads(a.tab, a.rg, ti, tid); }
+    CompPtrs own{};                       // not PIPE: the workgroup's map
+    if constexpr (!PIPE) own = comp_ptrs(a.tab, a.rg, tid);
     // rounds of units a plane has (uniform); the one- and four-wavefront instances for B = 4 and 8
     // always run all K (their planes fill at least eight of them)
     auto round_live = [&](int k) -> bool { return FULL || (B != 0 && NW != 16 && ND == 2) || (uint32_t)(NT * k) < a.q4; };
@@ -91,7 +92,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     // zero).  Everything the workgroup has to set up (the block of each unit, the sentinel)
     // runs while the loads are in flight.
     {
-        const __amdgpu_buffer_rsrc_t rsrc = plane_buffer(a.tab.x[ti], p, true);
+        const __amdgpu_buffer_rsrc_t rsrc = plane_buffer(PIPE ? a.tab.x[ti] : own.x, p, true);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             x[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -99,7 +100,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
         }
     }
     for (bool first = true;; first = false) {
-        const CompPtrs pt = comp_ptrs_of(a.tab, a.rg, ti);
+        const CompPtrs pt = PIPE ? comp_ptrs_of(a.tab, a.rg, ti, static_cast<char*>(a.tab.pk[ti])) : own;
         if (first) {
             // which block each of the lane's units belongs to (nb = sentinel for units past the plane)
 #pragma unroll
@@ -327,7 +328,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
             const uint32_t padb = a.WPP * 4 - cbytes;
             if (tid < padb) cbase[cbytes + tid] = 0;
         }
-        if constexpr (PIPE) { if (p == 0) zero_pads(a.tab, a.rg, ti, tid); }
+        if constexpr (PIPE) { if (p == 0 && tid < 48) zero_pads(a.rg, static_cast<char*>(a.tab.pk[ti]), tid); }
         if (!there) break;
         ti = nti;
         p = np;

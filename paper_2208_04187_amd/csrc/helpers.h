@@ -180,10 +180,9 @@ struct DecTab { const void* pk[kMaxBatch]; void* xhat[kMaxBatch]; };
 // after them that must read as zero (each shorter than 16 bytes).
 struct Regions { size_t meta_off, lfc_off; size_t pad_off[3]; uint32_t pad_len[3]; };
 
-// the parts of map ti of the table
+// the parts of a packed buffer and what else belongs to its map
 struct CompPtrs { const void* x; uint32_t* codes; float* meta; void* lfc; uint32_t seed_a, seed_c; };
-__device__ __forceinline__ CompPtrs comp_ptrs_of(const CompTab& tab, const Regions& rg, uint32_t ti) {
-    char* pk = static_cast<char*>(tab.pk[ti]);
+__device__ __forceinline__ CompPtrs comp_ptrs_of(const CompTab& tab, const Regions& rg, uint32_t ti, char* pk) {
     CompPtrs pt;
     pt.x = tab.x[ti];
     pt.codes = reinterpret_cast<uint32_t*>(pk);
@@ -193,18 +192,17 @@ __device__ __forceinline__ CompPtrs comp_ptrs_of(const CompTab& tab, const Regio
     pt.seed_c = tab.seed_c[ti];
     return pt;
 }
-// the bytes between and behind the regions of map ti read as zero
-__device__ __forceinline__ void zero_pads(const CompTab& tab, const Regions& rg, uint32_t ti, uint32_t tid) {
-    if (tid < 48) {
-        const uint32_t k = tid >> 4, j = tid & 15u;
-        if (j < rg.pad_len[k]) static_cast<char*>(tab.pk[ti])[rg.pad_off[k] + j] = 0;
-    }
+// the bytes between and behind the regions read as zero
+__device__ __forceinline__ void zero_pads(const Regions& rg, char* pk, uint32_t tid) {
+    const uint32_t k = tid >> 4, j = tid & 15u;
+    if (j < rg.pad_len[k]) pk[rg.pad_off[k] + j] = 0;
 }
 // this workgroup's tensor
 __device__ __forceinline__ CompPtrs comp_ptrs(const CompTab& tab, const Regions& rg, uint32_t tid) {
     const uint32_t ti = blockIdx.y;
-    if (blockIdx.x == 0) zero_pads(tab, rg, ti, tid);
-    return comp_ptrs_of(tab, rg, ti);
+    char* pk = static_cast<char*>(tab.pk[ti]);
+    if (blockIdx.x == 0 && tid < 48) zero_pads(rg, pk, tid);
+    return comp_ptrs_of(tab, rg, ti, pk);
 }
 struct DecPtrs { const uint32_t* codes; const float* meta; const void* lfc; void* xhat; };
 __device__ __forceinline__ DecPtrs dec_ptrs(const DecTab& tab, const Regions& rg) {
