@@ -241,13 +241,16 @@ struct PoolArgs {
     uint32_t P, H, W, HW, OH, OW, k;
     uint32_t band;         // maxpool2_forward_fast: output rows a workgroup handles
     uint32_t chunk;        // maxpool_forward_kernel: elements a workgroup handles (a multiple of 32)
-    uint32_t quick;        // every quotient below is exact with the multiplier (fastdiv_ok)
-    uint32_t quick0;       // so are those of the place in the whole map
-    uint32_t lines;        // maxpool_backward_kernel: grad_in starts on a cache line
+    uint32_t quick;        // every quotient inside a workgroup's elements is exact with the multiplier (fastdiv_ok)
     uint64_t n;            // elements of the map
     uint64_t rows;         // maxpool2_forward_fast: output rows of all planes
-    double r_HW, r_wv, r_hv, r_OH;      // 1 / HW, 1 / pieces of a row, 1 / pieces of a plane, 1 / OH
-    FastDiv d_HW, d_W, d_OH, d_OW, d_k, d_wv, d_hv;
+    double r_HW, r_wv;     // 1 / HW, 1 / pieces of a row
+    FastDiv d_HW, d_W, d_OH, d_OW, d_k, d_wv;
+    // (behind what maxpool_forward_kernel reads)
+    uint32_t quick0;       // so are those of the place in the whole map
+    uint32_t lines;        // maxpool_backward_kernel: grad_in starts on a cache line
+    double r_hv, r_OH;     // 1 / pieces of a plane, 1 / OH
+    FastDiv d_hv;
 };
 
 // quotient by the multiplier where the host found it exact for all numerators of this launch, else by the division
