@@ -255,7 +255,8 @@ __device__ __forceinline__ uint32_t lfc_row2(const DecShape& a, uint32_t r) {
     }
 }
 // Vectors a lane rebuilds and elements of a chunk: the lookups of 2-byte elements go by pieces of four as well, so half as
-// many vectors keep the same number of loads in flight per lane (and of registers: 64, eight wavefronts per SIMD).
+// many vectors keep the same number of loads in flight per lane (and about as many registers: 64 and eight wavefronts per SIMD for 4-byte
+// elements; 65, one too many for the eighth wavefront, for 2-byte ones at b = 1, 2 and 4).
 template <typename T> constexpr int kAnyVecs = sizeof(T) == 4 ? kStreamK : kStreamK / 2;
 template <typename T> constexpr uint32_t kAnyChunk = 64u * kAnyVecs<T> * (16 / sizeof(T));
 template <typename T, int BITS, int ND>
@@ -415,8 +416,8 @@ __global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { decompr
 // The wavefront-per-chunk kernels over the maps of several shapes: a workgroup finds its shape and its map in tables of the
 // arguments (all uniform: scalar loads and compares) and runs the body that the shape would have a launch of its own for.
 // A launch of its own costs a shape the drain of the one before and its own filling, 2-4 us, and 2 us of the host.  The four
-// groups of a ResNet-18 / CIFAR step take 42 us in one launch, 48 in four; the seven odd-sized groups of an
-// AlexNet / Inception step 196 and 202; the eight groups of a Swin-T step 141 in eight, about 130 in one.  The look-up itself costs nothing
+// groups of a ResNet-18 / CIFAR step take 44 us in one launch, 48 in four; the seven odd-sized groups of an
+// AlexNet / Inception step 180 and 196; the eight groups of a Swin-T step 129 and 141; three small edge shapes 15 and 20.  The look-up itself costs nothing
 // that shows (64 x 256 x 56 x 56 on its own 31.9 us, beside a tiny map 32.2).
 // What a workgroup must know before anything else (the shape's first workgroup, chunks per map, kind and first map) sits at fixed
 // places, so that everything else it reads depends on one wait for scalar loads and not on three.

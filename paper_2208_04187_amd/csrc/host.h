@@ -187,8 +187,10 @@ constexpr uint64_t kUnitsSubMinAny = 20;  // under other block sizes and in thre
                                           // under B = 64 16.6 us there and 11.3 here, 2 x 7 x 7 under B = 12 17.8 and 15.1; level at 18 units (14 x 5)
 constexpr uint64_t kUnitsRowMin = 8;      // for maps of one row (maps of 4 M elements, against compress_wave: rows of 335 under B = 8 28.9 us
                                           // and 11.9 here, 1521 under B = 4 30.9 and 14.1)
-constexpr uint64_t kUnitsManyPlanes = 256;      // planes (a CU each) from which maps of one row, small planes and even widths leave the chunk
-                                          // kernels (wave, rows): below, a launch is its latency in either
+// planes of a map from which one row, small planes and even widths leave the chunk kernels (wave, rows, tile).  Maps of fewer would gain
+// as well (700 of them, medians: one row 13.9 us in compress_wave and 5.1 here, 8.4 and 5.7 in compress_rows, 23.4 and 8.6 in compress_tile, small
+// planes 6.2 and 5.1, volumes 8.4 and 5.1; 52 of the 700 slower): they keep the kernels they are known by
+constexpr uint64_t kUnitsManyPlanes = 256;
 bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, SegArgs* a, uint32_t* grid, size_t* lds,
               uint32_t* nt_out, int* K_out);
 // maps: of the launch.
