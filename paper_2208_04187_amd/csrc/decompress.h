@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { decompr
 // What a workgroup must know before anything else (the shape's first workgroup, chunks per map, kind and first map) sits at fixed
 // places, so that everything else it reads depends on one wait for scalar loads and not on three.
 constexpr int kMixShapes = 16, kMixMaps = 32;
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));      // (vectors: three wide scalar loads; from arrays the compiler makes a load and a branch per shape)
+// (vectors: three wide scalar loads; from arrays the compiler makes a load and a branch per shape)
 struct MixShape : DecShape { size_t meta_off, lfc_off; };
 struct MixArgs {
     u32x16 first;                         // first workgroup of each shape (beyond the last shape: 2^32 - 1)

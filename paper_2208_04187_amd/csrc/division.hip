@@ -43,6 +43,8 @@
 //   compress_plane   planes beyond LDS with vector rows and blocks (video volumes, image-sized maps):
 //                    a workgroup per plane, two vector passes over x
 //   compress_any     everything else (giant planes with odd extents, 1-bit codes of the shapes of compress_rows)
+//   compress_mixed   small maps of several shapes in one launch (division_compress_maps; spread_mixed of host.h): any width, units of four
+//                    consecutive elements in registers, lanes per plane by what the launch as a whole leaves idle
 //   decompress_mixed the wavefront-per-chunk kernels below over the maps of several shapes in one launch (division_decompress_maps)
 //   decompress_stream / decompress_stream_any / decompress_stream_one: one wavefront per 4 KB chunk of aligned vectors, no LDS:
 //                    rows of whole vectors inside one block (_stream), or any width where a vector may span two rows
@@ -144,6 +146,7 @@ constexpr int kLoadReuse = 0;
 #include "compress_rows.h"
 #include "compress_plane.h"
 #include "compress_any.h"
+#include "compress_mixed.h"
 #include "decompress.h"
 #include "host.h"
 
@@ -259,12 +262,12 @@ int division_relu_compress(const void* x, int64_t N, int64_t C, int64_t H, int64
     if (b != 1 && L.HW % 32 == 0 && (B == 4 || B == 8) && plan_regs(L, 1, H, W, B, es, both, &ra, &grid, &lds, &nw) && nw <= 4) {
         ra.tab.x[0] = x;
         ra.tab.pk[0] = packed;
-        ra.tab.seed_a[0] = mix32((uint32_t)(seed & 0xffffffffu) ^ 0x243F6A88u);
-        ra.tab.seed_c[0] = mix32((uint32_t)(seed >> 32) ^ 0x85A308D3u);
+        ra.tab.seed_a[0] = seed_key_a(seed);
+        ra.tab.seed_c[0] = seed_key_c(seed);
         ra.rg = make_regions(L);
         ra.y = y;
         ra.mask = static_cast<uint32_t*>(mask);
-        CompLaunch c{};
+        CompLaunch c;
         c.kind = REGS; c.B = B; c.nw = nw; c.gx = grid; c.gy = 1; c.lds = lds; c.st = st; c.ra = ra;
         const hipError_t err = bridge_relu(dt, c, b);
         return err == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
@@ -276,12 +279,12 @@ int division_relu_compress(const void* x, int64_t N, int64_t C, int64_t H, int64
     if (b != 1 && plan_relu_strip(L, H, W, Bc, es, both, &sa, &grid, &lds, &vec)) {
         sa.tab.x[0] = x;
         sa.tab.pk[0] = packed;
-        sa.tab.seed_a[0] = mix32((uint32_t)(seed & 0xffffffffu) ^ 0x243F6A88u);
-        sa.tab.seed_c[0] = mix32((uint32_t)(seed >> 32) ^ 0x85A308D3u);
+        sa.tab.seed_a[0] = seed_key_a(seed);
+        sa.tab.seed_c[0] = seed_key_c(seed);
         sa.rg = make_regions(L);
         sa.y = y;
         sa.mask = static_cast<uint32_t*>(mask);
-        CompLaunch c{};
+        CompLaunch c;
         c.kind = STRIP; c.B = Bc; c.vec = vec; c.gx = grid; c.gy = 1; c.lds = lds; c.st = st; c.sa = sa;
         const hipError_t err = bridge_relu(dt, c, b);
         return err == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
@@ -291,12 +294,12 @@ int division_relu_compress(const void* x, int64_t N, int64_t C, int64_t H, int64
     if (b != 1 && (Bc == 4 || Bc == 8) && plan_relu_items(L, H, W, Bc, es, both, &ia, &grid, &lds, &vec)) {
         ia.tab.x[0] = x;
         ia.tab.pk[0] = packed;
-        ia.tab.seed_a[0] = mix32((uint32_t)(seed & 0xffffffffu) ^ 0x243F6A88u);
-        ia.tab.seed_c[0] = mix32((uint32_t)(seed >> 32) ^ 0x85A308D3u);
+        ia.tab.seed_a[0] = seed_key_a(seed);
+        ia.tab.seed_c[0] = seed_key_c(seed);
         ia.rg = make_regions(L);
         ia.y = y;
         ia.mask = static_cast<uint32_t*>(mask);
-        CompLaunch c{};
+        CompLaunch c;
         c.kind = ITEMS; c.B = Bc; c.vec = vec; c.gx = grid; c.gy = 1; c.lds = lds; c.st = st; c.ia = ia;
         const hipError_t err = bridge_relu(dt, c, b);
         return err == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
@@ -341,12 +344,13 @@ static bool outputs_overlap(std::vector<Range>& ranges) {
 }
 
 // Both directions of the descriptor-array calls: validates every map, then serves the maps that
-// share a shape and parameters together, in order of first appearance.  Decompression puts the maps of several shapes into one
-// launch where their kernel can take part in one (decompress_mixed) and no output overlaps another map.
+// share a shape and parameters together, in order of first appearance.  The maps of several shapes go into one
+// launch where their kernel can take part in one (decompress_mixed) or they are small (compress_mixed) and no output overlaps another map.
 static int run_maps(int count, const division_map* maps, void* hip_stream, bool compress) {
     if (count < 0 || (count > 0 && !maps)) return DIVISION_EINVAL;
-    std::vector<Range> ranges;                                // of the maps of a decompress call
-    if (!compress) ranges.reserve(2 * (size_t)count);
+    std::vector<Range> ranges;
+    const bool several = count > 1;
+    if (several) ranges.reserve(2 * (size_t)count);
     for (int i = 0; i < count; ++i) {
         const division_map& m = maps[i];
         Layout L;
@@ -357,21 +361,20 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
         const size_t es = m.dt == DIVISION_BF16 ? 2 : 4;
         const void* data = compress ? m.x : m.xhat;
         if (((uintptr_t)data % es) != 0 || ((uintptr_t)m.packed % 16) != 0) return DIVISION_EALIGN;
-        if (!compress) {
-            const uintptr_t out = (uintptr_t)m.xhat, in = (uintptr_t)m.packed;
-            ranges.push_back({out, out + L.P * L.HW * es, true});
-            ranges.push_back({in, in + L.total, false});
-        }
+        if (!several) continue;
+        ranges.push_back({(uintptr_t)data, (uintptr_t)data + L.P * L.HW * es, !compress});
+        ranges.push_back({(uintptr_t)m.packed, (uintptr_t)m.packed + L.total, compress});
     }
     auto same = [](const division_map& p, const division_map& q) {
         return p.N == q.N && p.C == q.C && p.D == q.D && p.H == q.H && p.W == q.W && p.dt == q.dt && p.B == q.B && p.b == q.b;
     };
     // (a call of one shape, or of more maps than a few launches hold, has nothing to gain from mixing)
     bool mix = false;
-    for (int i = 1; i < count && !compress && count <= 256; ++i) mix = mix || !same(maps[0], maps[i]);
+    for (int i = 1; i < count && count <= 256; ++i) mix = mix || !same(maps[0], maps[i]);
     mix = mix && !outputs_overlap(ranges);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     Mixer mixer;
+    CompMixer comp;
     std::vector<char> done((size_t)count, 0);
     std::vector<const void*> in;
     std::vector<void*> out;
@@ -389,25 +392,42 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             if (maps[j].packed_bytes < cap) cap = maps[j].packed_bytes;
         }
         const division_map& m = maps[i];
-        if (mix && in.size() <= (size_t)kMixMaps) {
+        if (mix && in.size() <= (size_t)(compress ? kMixedMaps : kMixMaps)) {
             int64_t D = m.D, H = m.H, W = m.W;
             squeeze_dims(D, H, W);
             Layout L;
             make_layout(m.N, m.C, D, H, W, m.B, m.b, (int)m.dt, &L);
             const int B = covering_block(L, D, H, W, m.B);
-            uintptr_t all_out = 0;
-            for (void* o : out) all_out |= (uintptr_t)o;
-            DecShape sh{};
-            uint32_t chunks = 0;
-            const int kind = plan_mix(L, D, H, W, B, m.dt == DIVISION_BF16 ? 2 : 4, reinterpret_cast<const void*>(all_out), in.size(), &sh, &chunks);
-            const uint64_t workgroups = (uint64_t)chunks * in.size();
-            if (kind && launch_ok(workgroups, 64)) {
-                if (!mixer.fits(m, in.size(), workgroups)) {
-                    const int rc = mixer.flush(st);
-                    if (rc != DIVISION_OK) return rc;
+            const size_t es = m.dt == DIVISION_BF16 ? 2 : 4;
+            uintptr_t all = 0;
+            if (compress) {
+                for (const void* x : in) all |= (uintptr_t)x;
+                MixedShape sh{};
+                const void* x = reinterpret_cast<const void*>(all);
+                const bool can = plan_mixed(L, D, H, W, B, x, &sh);
+                const uint64_t lanes = (uint64_t)in.size() * L.P << sh.S_log2;
+                if (can && mixed_gains(L, D, H, W, B, m.b, es, x, in.size(), lanes)) {
+                    if (!comp.fits(m, in.size(), lanes)) {
+                        const int rc = comp.flush(st);
+                        if (rc != DIVISION_OK) return rc;
+                    }
+                    comp.add(m, sh, lanes, in.size(), cap, in.data(), out.data(), seeds.data());
+                    continue;
                 }
-                mixer.add(m, L, D == 1, kind, sh, chunks, in.size(), cap, in.data(), out.data());
-                continue;
+            } else {
+                for (void* o : out) all |= (uintptr_t)o;
+                DecShape sh{};
+                uint32_t chunks = 0;
+                const int kind = plan_mix(L, D, H, W, B, es, reinterpret_cast<const void*>(all), in.size(), &sh, &chunks);
+                const uint64_t workgroups = (uint64_t)chunks * in.size();
+                if (kind && launch_ok(workgroups, 64)) {
+                    if (!mixer.fits(m, in.size(), workgroups)) {
+                        const int rc = mixer.flush(st);
+                        if (rc != DIVISION_OK) return rc;
+                    }
+                    mixer.add(m, L, D == 1, kind, sh, chunks, in.size(), cap, in.data(), out.data());
+                    continue;
+                }
             }
         }
         const int rc = compress
@@ -415,7 +435,7 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             : decompress_impl((int)in.size(), in.data(), out.data(), cap, m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, hip_stream);
         if (rc != DIVISION_OK) return rc;
     }
-    return mixer.flush(st);
+    return compress ? comp.flush(st) : mixer.flush(st);
 }
 
 int division_compress_maps(int count, const division_map* maps, void* hip_stream) {

@@ -50,6 +50,10 @@ Regions make_regions(const Layout& L) {
     return rg;
 }
 
+// the two keys of a 64-bit seed
+uint32_t seed_key_a(uint64_t seed) { return mix32((uint32_t)(seed & 0xffffffffu) ^ 0x243F6A88u); }
+uint32_t seed_key_c(uint64_t seed) { return mix32((uint32_t)(seed >> 32) ^ 0x85A308D3u); }
+
 // Preferred LDS footprint of one wavefront's chunk in compress_wave (small chunks = many wavefronts
 // per CU; 8.7 KB measured best over the ResNet-50 set); a single plane of up to kWavePlaneMax bytes is
 // taken whatever the preference says.
@@ -135,6 +139,7 @@ bool plan_regs(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t e
     if (!fastdiv_ok(kRegUnits * nt, w4) || !fastdiv_ok(L.nb + nt, L.LW) || L.HW * es >= (1ull << 31)) return false;
     if (!fastdiv_ok((uint64_t)H, (uint64_t)B) || !fastdiv_ok(w4, (uint64_t)B / 4)) return false;
     if (!fastdiv_ok((uint64_t)D * (uint64_t)H, (uint64_t)H) || !fastdiv_ok(L.nb + nt, L.LH * L.LW)) return false;
+    *a = RegsArgs{};
     a->D = (uint32_t)D;
     a->d_H = make_fastdiv((uint32_t)H);
     a->d_slice = make_fastdiv((uint32_t)(L.LH * L.LW));
@@ -259,6 +264,7 @@ bool plan_units(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, 
         !fastdiv_ok(nitem + S, Br * Bz) || !fastdiv_ok(L.nb + S, L.LH * L.LW) ||
         !fastdiv_ok(4ull * kUnitsK * S + 4, (uint64_t)H))
         return false;
+    *a = UnitsArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
     a->D = (uint32_t)D; a->LH = (uint32_t)L.LH; a->Br = (uint32_t)Br; a->Bz = (uint32_t)Bz;
@@ -337,6 +343,7 @@ bool plan_seg(const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es
     // a workgroup per plane: maps of about 165 GB and more stay with compress_units, whose workgroups walk over the planes
     if (!launch_ok(L.P, best_nt)) return false;
     if (need > (48u << 10) || !fastdiv_ok(top, irows) || !fastdiv_ok(kSegThreads, CW) || !fastdiv_ok(L.nb + best_nt, L.LW) || !fastdiv_ok(L.nb + best_nt, L.LH * L.LW)) return false;
+    *a = SegArgs{};
     a->P = (uint32_t)L.P; a->D = (uint32_t)D; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
     a->CW = (uint32_t)CW; a->RS = (uint32_t)(best_nt / CW); a->irows = (uint32_t)irows; a->rows = (uint32_t)rows;
@@ -373,6 +380,7 @@ bool lane_shape(const Layout& L) { return L.nb == 1 && (L.HW & 1) == 1 && L.HW <
 // Fills the lane-per-plane compress plan; false when the shape is not covered.
 bool plan_lane(const Layout& L, size_t es, const void* x, LaneArgs* a, uint32_t* grid, size_t* lds) {
     if (!lane_shape(L)) return false;
+    *a = LaneArgs{};
     a->P = (uint32_t)L.P; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP;
     a->nrounds = (uint32_t)((L.P + 63) / 64);
     a->vec_load = ((uintptr_t)x % 16) == 0;
@@ -399,6 +407,7 @@ bool plan_items(const Layout& L, int64_t H, int64_t W, int B, size_t es, const v
     while (S < ipp) { S *= 2; ++lg; }
     const uint64_t ppr = 64 / S;
     if (ppr * L.WPP * 4 > 32u * 1024u || ppr * L.HW * es >= (1ull << 31)) return false;
+    *a = ItemsArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
     a->ipr = (uint32_t)ipr; a->ipp = (uint32_t)ipp; a->S = (uint32_t)S; a->S_log2 = (uint32_t)lg;
@@ -439,6 +448,7 @@ bool plan_strip(const Layout& L, int64_t H, int64_t W, int B, size_t es, const v
     const uint64_t nseg = ((uint64_t)W + B - 1) / B;
     const bool dpp = B == 4 || B == 8;
     if (L.LW != nseg || (!dpp && G * L.nb > 64)) return false;
+    *a = StripArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP; a->nb = (uint32_t)L.nb;
     a->nrounds = (uint32_t)((L.P + G - 1) / G);
     *grid = a->nrounds;
@@ -486,6 +496,7 @@ bool plan_rowstrip(const Layout& L, int64_t H, int64_t W, int B, size_t es, cons
     if ((B != 8 && B != 4) || H < 2 || (uint64_t)H > S) return false;
     const uint64_t G = 64 / S;
     if (L.LW != ((uint64_t)W + B - 1) / B) return false;
+    *a = StripArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP; a->nb = (uint32_t)L.nb;
     a->nrounds = (uint32_t)((L.P + G - 1) / G);
     *grid = a->nrounds;
@@ -616,6 +627,7 @@ bool plan_wave(const Layout& L, int64_t H, int64_t W, int B, int b, size_t es, c
     }
     if (G == 0) G = Gmax;          // Gmax == P < unit: a single chunk, aligned at its start
     if (!fastdiv_ok(ippp, ipr) || !fastdiv_ok(G * L.WPP + 64, L.WPP)) return false;
+    *a = WaveArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
     a->G = (uint32_t)G; a->ipr = (uint32_t)ipr; a->ipp = (uint32_t)ipp;
@@ -656,6 +668,7 @@ bool plan_one(const Layout& L, size_t es, const void* x, OneArgs* a, uint32_t* g
     // lanes per plane: a power of two from 4 up (a plane's lanes then read 64 contiguous bytes per round)
     uint32_t best_S = 0, best_log = 0, K = 0;
     if (!pick_lanes_and_rounds(qv, 2, &best_S, &best_log, &K)) return false;
+    *a = OneArgs{};
     a->P = (uint32_t)L.P; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP;
     a->qv = (uint32_t)qv;
     a->S = best_S; a->S_log2 = best_log;
@@ -690,6 +703,7 @@ bool plan_line(const Layout& L, int64_t D, int64_t H, int B, size_t es, const vo
     // plane's lanes then read 128 contiguous bytes per round)
     const uint32_t whole_log = upb_log > 3 ? upb_log : 3;
     uint32_t min_log = upb_log > 3 ? upb_log - 1 : 3;
+    *a = OneArgs{};
     for (;; min_log = whole_log) {
         uint32_t best_S = 0, best_log = 0, K = 0;
         if (!pick_lanes_and_rounds(qv, min_log, &best_S, &best_log, &K)) return false;
@@ -749,6 +763,7 @@ bool plan_rows(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, int b, 
     if (!fastdiv_ok(G * HLW + kThreads, HLW) || !fastdiv_ok(HLW, L.LW) || !fastdiv_ok(G * L.nb + kThreads, L.nb) ||
         !fastdiv_ok(L.nb, L.LW) || !fastdiv_ok(G * L.WPP + kThreads, L.WPP))
         return false;
+    *a = RowsArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)(L.LD * L.LH); a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
     a->D = (uint32_t)D; a->Hs = (uint32_t)Hs; a->LHs = (uint32_t)L.LH;
@@ -787,6 +802,7 @@ bool plan_plane(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t
     if (!fastdiv_ok(L.HW, (uint64_t)W) || !fastdiv_ok(H > (uint64_t)W ? H : (uint64_t)W, (uint64_t)B) ||
         !fastdiv_ok(H, (uint64_t)Hs) || !fastdiv_ok(nitem + kThreads, slice) || !fastdiv_ok(slice, L.LW))
         return false;
+    *a = PlaneArgs{};
     a->P = (uint32_t)L.P; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW; a->LW = (uint32_t)L.LW;
     a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
     a->D = (uint32_t)D; a->Hs = (uint32_t)Hs; a->LHs = (uint32_t)L.LH;
@@ -838,6 +854,7 @@ bool plan_tile(const Layout& L, int64_t H, int64_t W, int B, int b, size_t es, c
     const uint64_t nitems = G * ipp, nwords = G * L.WPP;
     if (!fastdiv_ok(nitems + 256, ipp) || !fastdiv_ok(ipp, ipr) || !fastdiv_ok(nwords + 256, L.WPP))
         return false;
+    *a = TileArgs{};
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
     a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP;
     a->G = (uint32_t)G; a->ipr = (uint32_t)ipr; a->ipp = (uint32_t)ipp;
@@ -1073,16 +1090,22 @@ int plan_mix(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es
     return kind;
 }
 
-enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, SEG, WAVE, TILE, ONE, ROWS, PLANE, ANY };
+enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, SEG, WAVE, TILE, ONE, ROWS, PLANE, ANY, MIXED };
 
-// everything a compress launch needs once the plan is made (the arguments of the kernel that was picked)
+// Everything a compress launch needs once the plan is made: the arguments of the kernel that was picked, which begin alike (head).  A
+// plan zeroes them before it fills them in.
+struct CompHead { CompTab tab; Regions rg; };
 struct CompLaunch {
     int kind, B, vec, nt, nw, flat;
     uint32_t gx, gy;
     size_t lds;
     hipStream_t st;
-    TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa;
-    SegArgs sg; uint32_t seg_nt; int seg_K;      // kind SEG: threads, items per lane
+    uint32_t seg_nt; int seg_K;                  // kind SEG: threads, items per lane
+    union {
+        CompHead head;
+        TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa; SegArgs sg;
+        const MixedArgs* mixed;                  // kind MIXED (nt threads)
+    };
 };
 struct MixLaunch { uint32_t grid; hipStream_t st; MixArgs a; };      // decompress_mixed
 struct DecLaunch {
@@ -1120,6 +1143,15 @@ hipError_t launch_line(const OneArgs& a, dim3 gd, size_t lds, hipStream_t st) {
     }
 }
 
+template <typename T, int BITS>
+hipError_t launch_mixed(const MixedArgs& a, dim3 gd, int nt, size_t lds, hipStream_t st) {
+    void (*kern)(MixedArgs) = compress_mixed<T, BITS>;
+    const hipError_t e = allow_large_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, gd, dim3(nt), lds, st, a);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t do_compress(const CompLaunch& c, int b) {
     const dim3 gd(c.gx, c.gy);
@@ -1139,6 +1171,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case ONE: return launch_one<T, 1>(c.oa, gd, st);
             case LINE: return launch_line<T, 1>(c.oa, gd, lds, st);
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
+            case MIXED: return launch_mixed<T, 1>(*c.mixed, gd, c.nt, lds, st);
             default: {
                 void (*kern)(AnyArgs) = flat ? compress_any<T, 1> : compress_any_3d<T, 1>;
                 hipLaunchKernelGGL(kern, gd, dim3(c.nt), 0, st, c.g);
@@ -1160,6 +1193,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case LANE: hipLaunchKernelGGL((compress_lane<T, BITS>), gd, dim3(64), lds, st, c.la); return hipGetLastError();
             case ONE: return launch_one<T, BITS>(c.oa, gd, st);
             case LINE: return launch_line<T, BITS>(c.oa, gd, lds, st);
+            case MIXED: return launch_mixed<T, BITS>(*c.mixed, gd, c.nt, lds, st);
             case ROWS: {
                 void (*kern)(RowsArgs) = flat ? compress_rows<T, BITS> : compress_rows_3d<T, BITS>;
                 const hipError_t e = allow_large_lds(kern, lds);
@@ -1300,6 +1334,50 @@ int packed_layout_impl(int64_t N, int64_t C, int64_t D, int64_t H, int64_t W, in
     return DIVISION_OK;
 }
 
+// The kernel of a map, or of `maps` maps of one shape in one launch: kind, grid, LDS and arguments, all but the maps themselves (head) and
+// what the caller adds (stream).  x: the OR of the maps' addresses (their common alignment).
+void plan_compress(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x, int maps, CompLaunch* c) {
+    size_t& lds = c->lds;
+    uint32_t& grid = c->gx;
+    const bool flat = D == 1;               // the register, item, wavefront and tile kernels take 2-D maps
+    // 1-bit codes (Q = 1) have no instance of the wave, rows and plane kernels, nor of the units kernel with
+    // sixteen wavefronts: the wave kernel's shapes go to the tile kernel, the others to the general kernel
+    const bool wide = b != 1;
+    lds = 0;
+    c->B = B; c->vec = 1; c->nt = 64; c->nw = 1; c->flat = flat;
+    if (line_first(L, es) && plan_line(L, D, H, B, es, x, &c->oa, &grid, &lds)) c->kind = LINE;
+    else if (plan_regs(L, D, H, W, B, es, x, &c->ra, &grid, &lds, &c->nw)) c->kind = REGS;
+    else if (plan_lane(L, es, x, &c->la, &grid, &lds)) c->kind = LANE;
+    else if (plan_line(L, D, H, B, es, x, &c->oa, &grid, &lds)) c->kind = LINE;
+    else if (flat && plan_strip(L, H, W, B, es, x, &c->sa, &grid, &lds, &c->vec)) c->kind = STRIP;
+    else if (flat && plan_rowstrip(L, H, W, B, es, x, &c->sa, &grid, &lds, &c->vec)) c->kind = ROWSTRIP;
+    else if (flat && plan_items(L, H, W, B, es, x, &c->ia, &grid, &lds, &c->vec)) c->kind = ITEMS;
+    else if (!one_shape(L, es, x) && plan_units(L, D, H, W, B, b, es, x, maps, &c->ua, &grid, &lds, &c->nw) && (wide || c->nw != 16)) c->kind = UNITS;
+    else if (wide && flat && plan_wave(L, H, W, B, b, es, x, &c->wa, &grid, &lds, &c->vec)) c->kind = WAVE;
+    else if (flat && plan_tile(L, H, W, B, b, es, x, &c->a, &grid, &lds, &c->vec, &c->nt)) c->kind = TILE;
+    else if (plan_one(L, es, x, &c->oa, &grid)) { c->kind = ONE; lds = 0; }
+    else if (wide && plan_rows(L, D, H, W, B, b, es, x, &c->wa2, &grid, &lds)) c->kind = ROWS;
+    else if (wide && plan_plane(L, D, H, W, B, es, x, &c->pa, &grid, &lds)) c->kind = PLANE;
+    else {
+        c->kind = ANY;
+        AnyArgs& g = c->g;
+        g = AnyArgs{};
+        g.P = (uint32_t)L.P; g.H = (uint32_t)H; g.W = (uint32_t)W; g.HW = (uint32_t)L.HW; g.D = (uint32_t)D;
+        g.LH = (uint32_t)L.LH; g.LW = (uint32_t)L.LW; g.nb = (uint32_t)L.nb; g.WPP = (uint32_t)L.WPP; g.B = (uint32_t)B;
+        grid = (uint32_t)L.P;
+        // a wavefront, four or sixteen per plane: one to sixteen rounds of four elements per lane; more lanes than 256 only
+        // where the launch still has fewer than 2^32
+        c->nt = L.HW <= 1024 ? 64 : L.HW <= 8192 || !launch_ok(L.P, 1024) ? kThreads : 1024;
+        // lanes per block: as many as there are, with a round of eight elements and more for each
+        const uint64_t elements = (uint64_t)std::min<int64_t>(B, W) * (uint64_t)std::min<int64_t>(B, H) * (uint64_t)std::min<int64_t>(B, D);
+        while (g.J_log2 < 6 && (L.nb << (g.J_log2 + 1)) <= (uint64_t)c->nt && (16ull << g.J_log2) <= elements) ++g.J_log2;
+    }
+    SegArgs sg;
+    if (c->kind == UNITS && plan_seg(L, D, H, W, B, es, &sg, &grid, &lds, &c->seg_nt, &c->seg_K)) { c->kind = SEG; c->sg = sg; }
+    c->gy = (uint32_t)maps;                 // of the grid: the maps, or one where the workgroups walk over all of them
+    if (c->kind == REGS && c->nw == 16 && regs_walk(L.P * (uint64_t)maps, L.HW / 4)) { c->ra.maps = c->gy; c->gy = 1; grid = (uint32_t)num_cus(); }
+}
+
 int compress_impl(int count, const void* const* x, void* const* packed, const uint64_t* seeds,
                   int64_t N, int64_t C, int64_t D, int64_t H, int64_t W, division_dtype dt,
                   int B, int b, size_t packed_capacity, void* hip_stream) {
@@ -1317,74 +1395,22 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         if (((uintptr_t)x[i] % es) != 0 || ((uintptr_t)packed[i] % 16) != 0) return DIVISION_EALIGN;
         all_x |= (uintptr_t)x[i];
     }
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const void* xa = reinterpret_cast<const void*>(all_x ? all_x : 16);
     const Regions rg = make_regions(L);
 
     for (int i0 = 0; i0 < count; i0 += kMaxBatch) {
         const int cnt = count - i0 < kMaxBatch ? count - i0 : kMaxBatch;
-        CompTab tab{};
+        CompLaunch c;
+        plan_compress(L, D, H, W, B, b, es, xa, cnt, &c);
+        c.st = static_cast<hipStream_t>(hip_stream);
+        c.head.rg = rg;
+        CompTab& tab = c.head.tab;
         for (int i = 0; i < cnt; ++i) {
             tab.x[i] = x[i0 + i];
             tab.pk[i] = packed[i0 + i];
-            tab.seed_a[i] = mix32((uint32_t)(seeds[i0 + i] & 0xffffffffu) ^ 0x243F6A88u);
-            tab.seed_c[i] = mix32((uint32_t)(seeds[i0 + i] >> 32) ^ 0x85A308D3u);
+            tab.seed_a[i] = seed_key_a(seeds[i0 + i]);
+            tab.seed_c[i] = seed_key_c(seeds[i0 + i]);
         }
-        TileArgs a{};
-        WaveArgs wa{};
-        RegsArgs ra{};
-        ItemsArgs ia{};
-        LaneArgs la{};
-        RowsArgs wa2{};
-        PlaneArgs pa{};
-        OneArgs oa{};
-        AnyArgs g{};
-        UnitsArgs ua{};
-        StripArgs sa{};
-        size_t lds = 0;
-        uint32_t grid = 0;
-        int vec = 1, nt = 64, nw = 1;
-        CompKind kind;
-        const bool flat = D == 1;               // the register, item, wavefront and tile kernels take 2-D maps
-        auto use_any = [&]() {
-            kind = ANY;
-            g.tab = tab; g.rg = rg;
-            g.P = (uint32_t)L.P; g.H = (uint32_t)H; g.W = (uint32_t)W; g.HW = (uint32_t)L.HW; g.D = (uint32_t)D;
-            g.LH = (uint32_t)L.LH; g.LW = (uint32_t)L.LW; g.nb = (uint32_t)L.nb; g.WPP = (uint32_t)L.WPP; g.B = (uint32_t)B;
-            grid = (uint32_t)L.P;
-            // a wavefront, four or sixteen per plane: one to sixteen rounds of four elements per lane; more lanes than 256 only
-            // where the launch still has fewer than 2^32
-            nt = L.HW <= 1024 ? 64 : L.HW <= 8192 || !launch_ok(L.P, 1024) ? kThreads : 1024;
-            // lanes per block: as many as there are, with a round of eight elements and more for each
-            const uint64_t elements = (uint64_t)std::min<int64_t>(B, W) * (uint64_t)std::min<int64_t>(B, H) * (uint64_t)std::min<int64_t>(B, D);
-            g.J_log2 = 0;
-            while (g.J_log2 < 6 && (L.nb << (g.J_log2 + 1)) <= (uint64_t)nt && (16ull << g.J_log2) <= elements) ++g.J_log2;
-        };
-        // 1-bit codes (Q = 1) have no instance of the wave, rows and plane kernels, nor of the units kernel with
-        // sixteen wavefronts: the wave kernel's shapes go to the tile kernel, the others to the general kernel
-        const bool wide = b != 1;
-        if (line_first(L, es) && plan_line(L, D, H, B, es, xa, &oa, &grid, &lds)) { kind = LINE; oa.tab = tab; oa.rg = rg; }
-        else if (plan_regs(L, D, H, W, B, es, xa, &ra, &grid, &lds, &nw)) { kind = REGS; ra.tab = tab; ra.rg = rg; }
-        else if (plan_lane(L, es, xa, &la, &grid, &lds)) { kind = LANE; la.tab = tab; la.rg = rg; }
-        else if (plan_line(L, D, H, B, es, xa, &oa, &grid, &lds)) { kind = LINE; oa.tab = tab; oa.rg = rg; }
-        else if (flat && plan_strip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = STRIP; sa.tab = tab; sa.rg = rg; }
-        else if (flat && plan_rowstrip(L, H, W, B, es, xa, &sa, &grid, &lds, &vec)) { kind = ROWSTRIP; sa.tab = tab; sa.rg = rg; }
-        else if (flat && plan_items(L, H, W, B, es, xa, &ia, &grid, &lds, &vec)) { kind = ITEMS; ia.tab = tab; ia.rg = rg; }
-        else if (!one_shape(L, es, xa) && plan_units(L, D, H, W, B, b, es, xa, cnt, &ua, &grid, &lds, &nw) && (wide || nw != 16)) { kind = UNITS; ua.tab = tab; ua.rg = rg; }
-        else if (wide && flat && plan_wave(L, H, W, B, b, es, xa, &wa, &grid, &lds, &vec)) {
-            kind = WAVE; wa.tab = tab; wa.rg = rg;
-        } else if (flat && plan_tile(L, H, W, B, b, es, xa, &a, &grid, &lds, &vec, &nt)) { kind = TILE; a.tab = tab; a.rg = rg; }
-        else if (plan_one(L, es, xa, &oa, &grid)) { kind = ONE; oa.tab = tab; oa.rg = rg; lds = 0; }
-        else if (wide && plan_rows(L, D, H, W, B, b, es, xa, &wa2, &grid, &lds)) { kind = ROWS; wa2.tab = tab; wa2.rg = rg; }
-        else if (wide && plan_plane(L, D, H, W, B, es, xa, &pa, &grid, &lds)) { kind = PLANE; pa.tab = tab; pa.rg = rg; }
-        else use_any();
-        CompLaunch c{};
-        if (kind == UNITS && plan_seg(L, D, H, W, B, es, &c.sg, &grid, &lds, &c.seg_nt, &c.seg_K)) { kind = SEG; c.sg.tab = tab; c.sg.rg = rg; }
-        uint32_t rows = (uint32_t)cnt;                            // of the grid: the maps, or one where the workgroups walk over all of them
-        if (kind == REGS && nw == 16 && regs_walk(L.P * (uint64_t)cnt, L.HW / 4)) { ra.maps = rows; rows = 1; grid = (uint32_t)num_cus(); }
-        c.kind = kind; c.B = B; c.vec = vec; c.nt = nt; c.nw = nw; c.flat = flat;
-        c.gx = grid; c.gy = rows; c.lds = lds; c.st = st;
-        c.sa = sa; c.a = a; c.wa = wa; c.ra = ra; c.ia = ia; c.la = la; c.wa2 = wa2; c.pa = pa; c.oa = oa; c.g = g; c.ua = ua;
         const hipError_t err = bridge_compress(dt, c, b);
         if (err != hipSuccess) return DIVISION_EHIP;
     }
@@ -1432,11 +1458,134 @@ int decompress_impl(int count, const void* const* packed, void* const* xhat, siz
     return DIVISION_OK;
 }
 
+// What follows from the lanes per plane; the LDS of a workgroup of `threads`
+size_t fit_mixed(MixedShape* a, uint32_t threads) {
+    const uint64_t S = 1ull << a->S_log2;
+    for (const uint32_t k : {1u, 2u, 3u, 4u, 6u, 8u}) { a->K = k; if (k * S >= a->q4) break; }
+    const uint64_t runs = (uint64_t)std::min(a->B, a->D) * a->Br * a->nch;      // of a block
+    a->J_log2 = 0;
+    while (((uint64_t)a->nb << (a->J_log2 + 1)) <= S && (2ull << a->J_log2) <= runs) ++a->J_log2;
+    a->reg_bytes = (uint32_t)((16 * a->K * S + 8 * (S / 16 + 1) + 4ull * (a->nb + 1) + 8 * (S / 64) + 15) & ~15ull);
+    a->G = std::min(threads >> a->S_log2, a->P);
+    while (a->G > 1 && (size_t)a->reg_bytes * a->G > kLdsMax / 2) a->G /= 2;
+    while (((uint64_t)a->G << a->S_log2) % 64 != 0) ++a->G;      // whole wavefronts
+    return (size_t)a->reg_bytes * a->G;
+}
+
+// Lanes, workgroups and LDS of a launch of several shapes.  Lanes per plane double where a lane has most units, while all of them
+// are on the machine at once (sixteen wavefronts per CU).
+void spread_mixed(MixedArgs& a, const uint32_t* maps, uint32_t shapes, uint32_t* grid, int* threads, size_t* lds) {
+    const uint64_t most = (uint64_t)num_cus() * 1024;
+    auto units = [&](const MixedShape& s) { return (s.q4 + (1u << s.S_log2) - 1) >> s.S_log2; };
+    uint64_t lanes = 0;
+    for (uint32_t s = 0; s < shapes; ++s) lanes += ((uint64_t)maps[s] * a.shape[s].P) << a.shape[s].S_log2;
+    for (;;) {
+        int at = -1;
+        uint32_t worst = 1;
+        for (uint32_t s = 0; s < shapes; ++s)
+            if (units(a.shape[s]) > worst && (1u << a.shape[s].S_log2) < (uint32_t)kMixedThreads) { worst = units(a.shape[s]); at = (int)s; }
+        if (at < 0) break;
+        const uint64_t more = ((uint64_t)maps[at] * a.shape[at].P) << a.shape[at].S_log2;
+        if (lanes + more > most) break;
+        lanes += more;
+        ++a.shape[at].S_log2;
+    }
+    uint32_t nt = 256;
+    for (uint32_t s = 0; s < shapes; ++s) nt = std::max(nt, 1u << a.shape[s].S_log2);
+    *grid = 0;
+    *lds = 0;
+    for (uint32_t s = 0; s < (uint32_t)kMixedShapes; ++s) a.first[s] = 0xffffffffu;
+    for (uint32_t s = 0; s < shapes; ++s) {
+        *lds = std::max(*lds, fit_mixed(&a.shape[s], nt));
+        a.chunks[s] = (a.shape[s].P + a.shape[s].G - 1) / a.shape[s].G;
+        a.first[s] = *grid;
+        *grid += a.chunks[s] * maps[s];
+    }
+    *threads = (int)nt;
+}
+
+// Fills what compress_mixed needs of a shape, with as few lanes per plane as take it; false when the shape is not covered.
+// x: the OR of its maps' addresses.
+bool plan_mixed(const Layout& L, int64_t D, int64_t H, int64_t W, int B, const void* x, MixedShape* a) {
+    const uint64_t q4 = (L.HW + 3) / 4, most = (uint64_t)kMixedUnits * kMixedThreads;
+    if (((uintptr_t)x % 4) != 0 || q4 > most || L.nb > 16383 || B > 32767) return false;      // H^L offsets are 16-bit byte offsets
+    const uint64_t Br = (uint64_t)std::min<int64_t>(B, H), nch = ((uint64_t)std::min<int64_t>(B, W) + 7) / 8, top = 4 * most + 4;
+    if (!fastdiv_ok(top, (uint64_t)W) || !fastdiv_ok(top, (uint64_t)B) || !fastdiv_ok(top, (uint64_t)H) || !fastdiv_ok(L.nb + kMixedThreads, L.LW) ||
+        !fastdiv_ok(L.nb + kMixedThreads, L.LH * L.LW) || !fastdiv_ok(top, nch) || !fastdiv_ok(top, Br))
+        return false;
+    a->P = (uint32_t)L.P; a->D = (uint32_t)D; a->H = (uint32_t)H; a->W = (uint32_t)W; a->HW = (uint32_t)L.HW;
+    a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
+    a->Br = (uint32_t)Br; a->nch = (uint32_t)nch;
+    a->q4 = (uint32_t)q4;
+    a->S_log2 = 3;
+    while (q4 > (uint64_t)kMixedUnits << a->S_log2) ++a->S_log2;
+    a->d_W = make_fastdiv((uint32_t)W); a->d_B = make_fastdiv((uint32_t)B); a->d_H = make_fastdiv((uint32_t)H);
+    a->d_LW = make_fastdiv((uint32_t)L.LW); a->d_slice = make_fastdiv((uint32_t)(L.LH * L.LW));
+    a->d_nch = make_fastdiv((uint32_t)nch); a->d_Br = make_fastdiv((uint32_t)Br);
+    a->rg = make_regions(L);
+    return fit_mixed(a, kMixedThreads) <= kLdsMax;
+}
+
+// Whether the maps of a shape are better off in a launch with other shapes than in one of their own.  lanes: what they take there, at
+// the fewest per plane, in parts of what the machine holds at once (sixteen wavefronts per CU).  Beside others a shape saves the 2-4 us that a launch waits for
+// the drain of the one before and then fills, and runs a kernel for any shape: about level with the kernels that stage planes in LDS (so: up to the
+// whole machine), up to twice as slow per element as those that hold them in registers (a quarter of it), three times as compress_line (an eighth).
+// 160 calls of two or three shapes of all sizes, sum of their times: 3281 us apart, 2630 so; with a half for the register kernels 2600, but maps of
+// 192 x 112 x 112 and 11554 x 16 x 13 in bfloat16 17.2 -> 19.7 with their decompression, and with a quarter for compress_line rows of 384 and 768 under B = 4 7.7 -> 9.8
+bool mixed_gains(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x, uint64_t maps, uint64_t lanes) {
+    const uint64_t machine = (uint64_t)num_cus() * 1024;
+    if (lanes > machine) return false;
+    CompLaunch own;
+    plan_compress(L, D, H, W, B, b, es, x, (int)std::min<uint64_t>(maps, kMaxBatch), &own);
+    switch (own.kind) {
+        case UNITS: case WAVE: case TILE: case ROWS: case PLANE: case ANY: return true;
+        case LINE: return lanes <= machine / 8;
+        default: return lanes <= machine / 4;
+    }
+}
+
+// Compression's launches of several shapes (one type and code width).  A shape that is left alone has a launch of its own, with its own kernel.
+struct CompMixer {
+    MixedArgs a;
+    uint32_t nshape = 0, nmap = 0;
+    uint32_t maps[kMixedShapes];
+    uint64_t seeds[kMixedMaps];
+    const division_map* first = nullptr;      // a descriptor of the first shape, and its smallest packed buffer
+    size_t first_bytes = 0;
+    uint64_t lanes = 0;                       // of all shapes, at the fewest per plane
+    bool fits(const division_map& m, size_t n, uint64_t more) const {
+        return nshape == 0 || (m.dt == first->dt && m.b == first->b && nshape < (uint32_t)kMixedShapes && nmap + n <= (size_t)kMixedMaps &&
+                               lanes + more <= (uint64_t)num_cus() * 1536);
+    }
+    void add(const division_map& m, const MixedShape& sh, uint64_t more, size_t n, size_t bytes, const void* const* x, void* const* packed, const uint64_t* seed) {
+        if (nshape == 0) { first = &m; first_bytes = bytes; nmap = 0; lanes = 0; }
+        lanes += more;
+        a.shape[nshape] = sh;
+        a.map0[nshape] = nmap;
+        maps[nshape++] = (uint32_t)n;
+        for (size_t i = 0; i < n; ++i, ++nmap) {
+            a.x[nmap] = x[i]; a.pk[nmap] = packed[i]; seeds[nmap] = seed[i];
+            a.seed_a[nmap] = seed_key_a(seed[i]); a.seed_c[nmap] = seed_key_c(seed[i]);
+        }
+    }
+    int flush(hipStream_t st) {
+        const uint32_t shapes = nshape;
+        nshape = 0;
+        if (shapes == 0) return DIVISION_OK;
+        if (shapes == 1)
+            return compress_impl((int)nmap, a.x, a.pk, seeds, first->N, first->C, first->D, first->H, first->W, first->dt, first->B, first->b, first_bytes, st);
+        CompLaunch c;
+        c.kind = MIXED; c.st = st; c.gy = 1; c.mixed = &a;
+        spread_mixed(a, maps, shapes, &c.gx, &c.nt, &c.lds);
+        return bridge_compress(first->dt, c, first->b) == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+};
+
 // Launches that hold the maps of several shapes (one type and code width): shapes are added while they fit, then flushed.  A shape that
 // is left alone has a launch of its own, with the kernel that serves it best (which shape a wavefront belongs to costs a launch of one
 // 0.4-0.8 us: 5 maps of 64 x 79 x 13 and the 4 of two other shapes in the other format 9.2 us in three launches, 10.0 in two mixed ones).
 struct Mixer {
-    MixLaunch c{};
+    MixLaunch c;
     uint32_t nshape = 0, nmap = 0;
     const division_map* first = nullptr;      // a descriptor of the first shape, and its smallest packed buffer
     size_t first_bytes = 0;
@@ -1485,41 +1634,24 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
     const char* tn = dt == DIVISION_BF16 ? "bf16_t" : dt == DIVISION_F32_C16 ? "f32c16_t" : "float";
     int n;
     if (direction == 0) {
-        const bool wide = b != 1;        // as in compress_impl
-        TileArgs a{}; WaveArgs wa{}; RegsArgs ra{}; ItemsArgs ia{}; LaneArgs la{}; RowsArgs wa2{}; PlaneArgs pa{}; OneArgs oa{}; UnitsArgs ua{}; StripArgs sa{}; size_t lds = 0; uint32_t grid = 0; int vec = 1, nt = 64, nw = 1;
-        if (line_first(L, es) && plan_line(L, D, H, B, es, data, &oa, &grid, &lds))
-            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u, %d>", tn, b, oa.K, oa.NG, line_lu(oa));
-        else if (plan_regs(L, D, H, W, B, es, data, &ra, &grid, &lds, &nw))
-            n = snprintf(out, cap, "compress_regs%s<%s, %d, %d, %d>", sfx, tn, b, (B == 4 || B == 8) ? B : 0, nw);
-        else if (plan_lane(L, es, data, &la, &grid, &lds))
-            n = snprintf(out, cap, "compress_lane<%s, %d>", tn, b);
-        else if (plan_line(L, D, H, B, es, data, &oa, &grid, &lds))
-            n = snprintf(out, cap, "compress_line<%s, %d, %u, %u, %d>", tn, b, oa.K, oa.NG, line_lu(oa));
-        else if (flat && plan_strip(L, H, W, B, es, data, &sa, &grid, &lds, &vec))
-            n = snprintf(out, cap, "compress_strip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
-        else if (flat && plan_rowstrip(L, H, W, B, es, data, &sa, &grid, &lds, &vec))
-            n = snprintf(out, cap, "compress_rowstrip<%s, %d, %d, %d>", tn, b, vec / 100, vec % 100);
-        else if (flat && plan_items(L, H, W, B, es, data, &ia, &grid, &lds, &vec))
-            n = snprintf(out, cap, "compress_items<%s, %d, %d, %d, %d>", tn, b, B, vec, H == 1 ? 1 : B);
-        else if (!one_shape(L, es, data) && plan_units(L, D, H, W, B, b, es, data, 1, &ua, &grid, &lds, &nw) && (wide || nw != 16)) {
-            SegArgs sg{}; uint32_t seg_nt = 0; int seg_K = 0;
-            if (plan_seg(L, D, H, W, B, es, &sg, &grid, &lds, &seg_nt, &seg_K))
-                n = snprintf(out, cap, "compress_seg<%s, %d, %d, %s, %d>", tn, b, B, W % 2 != 0 ? "true" : "false", seg_K);
-            else
-                n = snprintf(out, cap, "compress_units<%s, %d, %d>", tn, b, nw);
+        CompLaunch c;
+        plan_compress(L, D, H, W, B, b, es, data, 1, &c);
+        switch (c.kind) {
+            case LINE: n = snprintf(out, cap, "compress_line<%s, %d, %u, %u, %d>", tn, b, c.oa.K, c.oa.NG, line_lu(c.oa)); break;
+            case REGS: n = snprintf(out, cap, "compress_regs%s<%s, %d, %d, %d>", sfx, tn, b, (B == 4 || B == 8) ? B : 0, c.nw); break;
+            case LANE: n = snprintf(out, cap, "compress_lane<%s, %d>", tn, b); break;
+            case STRIP: n = snprintf(out, cap, "compress_strip<%s, %d, %d, %d>", tn, b, c.vec / 100, c.vec % 100); break;
+            case ROWSTRIP: n = snprintf(out, cap, "compress_rowstrip<%s, %d, %d, %d>", tn, b, c.vec / 100, c.vec % 100); break;
+            case ITEMS: n = snprintf(out, cap, "compress_items<%s, %d, %d, %d, %d>", tn, b, B, c.vec, H == 1 ? 1 : B); break;
+            case SEG: n = snprintf(out, cap, "compress_seg<%s, %d, %d, %s, %d>", tn, b, B, W % 2 != 0 ? "true" : "false", c.seg_K); break;
+            case UNITS: n = snprintf(out, cap, "compress_units<%s, %d, %d>", tn, b, c.nw); break;
+            case WAVE: n = snprintf(out, cap, "compress_wave<%s, %d, %d, %d>", tn, b, B, c.vec); break;
+            case TILE: n = snprintf(out, cap, "compress_tile<%s, %d, %d, %d, %d>", tn, b, B, c.vec, c.nt); break;
+            case ONE: n = snprintf(out, cap, "compress_one<%s, %d, %u>", tn, b, c.oa.K); break;
+            case ROWS: n = snprintf(out, cap, "compress_rows%s<%s, %d>", sfx, tn, b); break;
+            case PLANE: n = snprintf(out, cap, "compress_plane%s<%s, %d>", sfx, tn, b); break;
+            default: n = snprintf(out, cap, "compress_any%s<%s, %d>", sfx, tn, b);
         }
-        else if (wide && flat && plan_wave(L, H, W, B, b, es, data, &wa, &grid, &lds, &vec))
-            n = snprintf(out, cap, "compress_wave<%s, %d, %d, %d>", tn, b, B, vec);
-        else if (flat && plan_tile(L, H, W, B, b, es, data, &a, &grid, &lds, &vec, &nt))
-            n = snprintf(out, cap, "compress_tile<%s, %d, %d, %d, %d>", tn, b, B, vec, nt);
-        else if (plan_one(L, es, data, &oa, &grid))
-            n = snprintf(out, cap, "compress_one<%s, %d, %u>", tn, b, oa.K);
-        else if (wide && plan_rows(L, D, H, W, B, b, es, data, &wa2, &grid, &lds))
-            n = snprintf(out, cap, "compress_rows%s<%s, %d>", sfx, tn, b);
-        else if (wide && plan_plane(L, D, H, W, B, es, data, &pa, &grid, &lds))
-            n = snprintf(out, cap, "compress_plane%s<%s, %d>", sfx, tn, b);
-        else
-            n = snprintf(out, cap, "compress_any%s<%s, %d>", sfx, tn, b);
     } else {
         DecArgs a{}; uint32_t grid = 0;
         const int kind = plan_decompress(L, D, H, W, B, es, data, &a, &grid);

@@ -206,6 +206,61 @@ def test_decompress_of_several_shapes_in_one_call(mode, b):
         assert bool((v[x.numel():] == -7.0).all()), (shape, B)
 
 
+# maps of several shapes compressed in one launch: one to eight units per lane, planes of less than a unit, several planes per workgroup and
+# the last one short, blocks of one to many lanes, rows and blocks of one and two elements, planes that start in the middle of a dword
+SMALL = [((2, 3, 28, 28), 8), ((3, 5, 14, 14), 8), ((5, 7, 7, 7), 8), ((1, 3, 55, 55), 8), ((2, 3, 12, 20), 12), ((1, 1, 13, 13), 8), ((2, 3, 3, 9, 11), 4),
+         ((2, 2, 4, 8, 8), 4), ((3, 3, 9, 3), 4), ((2, 2, 8, 8), 2), ((1, 5, 17, 9), 64), ((1, 7, 1, 197), 8), ((2, 1, 1, 4100), 64), ((3, 1, 33, 65), 18),
+         ((1, 2, 3, 35, 35), 8), ((4, 3, 5, 2), 4), ((2, 5, 9, 1), 4), ((2, 67, 2, 2), 8), ((3, 3, 1, 1), 8), ((1, 1, 1, 3), 1), ((7, 3, 1, 5), 3),
+         ((1, 2, 147, 147), 8), ((1, 1, 180, 180), 64), ((1, 1, 16, 44, 45), 64), ((2, 1, 1, 3136), 4), ((1, 300, 4, 4), 4), ((2, 31, 6, 7), 1)]
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+def test_compress_of_several_shapes_in_one_call(mode, b):
+    dtype, c16, dt = FORMATS[mode]
+    gen = torch.Generator().manual_seed(b)
+    for first in range(0, len(SMALL), 9):
+        specs = [s for k, s in enumerate(SMALL[first:first + 9]) for _ in range(1 + (k * 5 + b) % 3)]
+        xs = [(torch.randn(s, generator=gen) * 1.5).relu_().to(dtype) if k % 2 else (torch.randn(s, generator=gen) - 0.5).to(dtype) for k, (s, _) in enumerate(specs)]
+        # every third map starts at an odd element of its memory
+        on = []
+        for k, x in enumerate(xs):
+            area = torch.zeros(x.numel() + 8, dtype=dtype, device="cuda:0")
+            at = 1 if k % 3 == 2 else 0
+            area[at:at + x.numel()] = x.reshape(-1).to("cuda:0")
+            on.append(area[at:at + x.numel()].view(x.shape))
+        ref = [oracle.compress(_host(x), B, b, (7 << 32) + k, dt, threads=16) for k, (x, (_, B)) in enumerate(zip(xs, specs))]
+        out = [torch.full((r.size + 16,), 0xA5, dtype=torch.uint8, device="cuda:0") for r in ref]
+        pkg.division_compress_maps(on, [B for _, B in specs], b, [(7 << 32) + k for k in range(len(specs))], packed=[p[:r.size] for p, r in zip(out, ref)], c16=c16)
+        torch.cuda.synchronize()
+        for (shape, B), r, p in zip(specs, ref, out):
+            got = p.cpu().numpy()
+            assert np.array_equal(got[:r.size], r), (shape, B)
+            assert bool((got[r.size:] == 0xA5).all()), (shape, B)
+
+
+# values at the edges of binary32 and planes of nothing but zeros of either sign, in a launch of several shapes
+@pytest.mark.parametrize("mode", ["f32", "bf16", "c16"])
+def test_compress_of_several_shapes_special_planes(mode):
+    dtype, c16, dt = FORMATS[mode]
+    shapes = [((1, 9, 14, 14), 8), ((1, 9, 9, 13), 4), ((1, 9, 3, 7, 7), 8), ((1, 9, 1, 96), 64), ((1, 9, 5, 5), 64)]
+    xs = []
+    for s, _ in shapes:
+        x = torch.randn(s, generator=torch.Generator().manual_seed(3))
+        f = x.view(9, -1)
+        f[0], f[1], f[2], f[3] = 0.0, -0.0, 2.5, torch.where(torch.arange(f.shape[1]) % 2 == 0, 0.0, -0.0)
+        f[4] *= 2.0 ** -140
+        f[5] *= 2.0 ** -91
+        f[6, 3] = 1e30
+        f[7] = -(2.0 ** -133 if mode == "bf16" else 2.0 ** -149) * (torch.arange(f.shape[1]) % 8 == 0)
+        xs.append(x.to(dtype))
+    ref = [oracle.compress(_host(x), B, 2, 5, dt) for x, (_, B) in zip(xs, shapes)]
+    packed = pkg.division_compress_maps([x.to("cuda:0") for x in xs], [B for _, B in shapes], 2, [5] * len(shapes), c16=c16)
+    torch.cuda.synchronize()
+    for s, r, p in zip(shapes, ref, packed):
+        assert np.array_equal(p.cpu().numpy(), r), s
+
+
 def test_decompress_of_maps_that_share_memory_keeps_their_order():
     # the second map is rebuilt over the first one
     gen = torch.Generator().manual_seed(1)

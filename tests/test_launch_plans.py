@@ -220,3 +220,31 @@ def test_overlaps_of_random_ranges_are_those_of_every_pair(host):
         assert mixed != want
         seen.add(want)
     assert seen == {True, False}
+
+
+MIXED = 14                     # the launch of several shapes
+
+
+def test_small_maps_of_several_shapes_compress_in_one_launch(host):
+    entries = [(A, F32, 8, 2), (B_, F32, 8, 2), (A, F32, 8, 2), (C_, F32, 64, 2), (C_, F32, 4, 2)]
+    assert [q.kind for q in _maps(host, entries)] == [MIXED]
+    # another type or code width, or a shape that is left alone: launches of their own
+    kinds = [q.kind for q in _maps(host, entries + [(A, BF16, 8, 2), (A, F32, 8, 4)])]
+    assert kinds[0] == MIXED and len(kinds) == 3 and MIXED not in kinds[1:]
+    # a large map beside them keeps its kernel, and so does what its own kernel serves far better
+    large = (64, 256, 56, 56)
+    assert sorted(q.kind == MIXED for q in _maps(host, [(large, F32, 8, 2)] + entries)) == [False, True]
+    assert all(q.kind != MIXED for q in _maps(host, [((22, 48, 1, 384), F32, 4, 8)] * 3 + [((2, 797, 1, 768), F32, 4, 8)]))
+    # ten shapes: eight in a launch; one shape: none
+    many = [q.kind for q in _maps(host, [((1, k + 1, 28, 28), F32, 8, 2) for k in range(10)])]
+    assert many == [MIXED, MIXED]
+    assert MIXED not in [q.kind for q in _maps(host, [(A, F32, 8, 2)] * 5)]
+
+
+def test_maps_that_share_memory_are_compressed_in_their_order(host):
+    """A packed buffer over another's input or output: a launch per shape, in the order of the descriptors."""
+    x, p = 1 << 46, 1 << 47
+    for out, packed in ((None, p + 64), (None, (1 << 38) + 256)):        # over the first map's packed buffer, over its input
+        found = _maps(host, [(A, F32, 8, 2, None, p), (B_, F32, 8, 2, out, packed), (C_, F32, 8, 2)])
+        assert len(found) == 3 and MIXED not in [q.kind for q in found]
+    assert len(_maps(host, [(A, F32, 8, 2, None, p), (B_, F32, 8, 2, None, x), (C_, F32, 8, 2)])) == 1
