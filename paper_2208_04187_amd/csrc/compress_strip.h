@@ -9,6 +9,9 @@ struct StripArgs {
     uint32_t nrounds;    // ceil(P / planes per round)
     void* y;             // relu_compress_strip: the activation's output map and its 1-bit mask (one map per launch);
     uint32_t* mask;      // a round's elements are a multiple of 32 then: its mask bits are whole words
+    // compress_rowstrip, rows of several planes side by side: where H^L and the extremes begin in LDS (0: slots)
+    uint32_t pack_off, LH;
+    FastDiv d_H, d_LH;
 };
 
 // Geometry of the strip kernel for planes of width W under block size B (both compile-time).

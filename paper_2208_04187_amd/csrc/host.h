@@ -501,6 +501,20 @@ bool plan_rowstrip(const Layout& L, int64_t H, int64_t W, int B, size_t es, cons
     a->nrounds = (uint32_t)((L.P + G - 1) / G);
     *grid = a->nrounds;
     *lds = 16ull * ((G * L.HW + 3) / 4) + 16;          // the round in whole 16-byte units
+    const int pack = W == 17 ? kRowPack<17> : W == 35 ? kRowPack<35> : 0;
+    if (pack && H <= W && L.P >= 2048 * G) {
+        // the rows of three planes side by side (planes of more rows keep their slots, and so do maps of less than eight wavefronts per CU, which wait for
+        // the longer chain through LDS: 72 planes of 35 x 35 4.4 us in slots, 4.8 so)
+        const uint64_t nseg = L.LW;
+        const size_t round = 16ull * ((kRowPackPlanes * L.HW + 3) / 4) + 16, shares = 8ull * nseg * 64 * pack;
+        a->pack_off = (uint32_t)((std::max(round, shares) + 15) & ~15ull);
+        a->LH = (uint32_t)L.LH;
+        a->d_H = make_fastdiv((uint32_t)H);
+        a->d_LH = make_fastdiv((uint32_t)L.LH);
+        a->nrounds = (uint32_t)((L.P + kRowPackPlanes - 1) / kRowPackPlanes);
+        *grid = a->nrounds;
+        *lds = a->pack_off + 4ull * kRowPackPlanes * L.nb + 8ull * kRowPackPlanes;
+    }
     *width = (int)(100 * W + B);
     return true;
 }
@@ -523,7 +537,8 @@ hipError_t launch_rowstrip(int width, const StripArgs& a, dim3 grid, size_t lds,
         case 5504: kern = compress_rowstrip<T, BITS, 55, 4>; break;
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(64), lds, st, a);
+    const int wavefronts = !a.pack_off ? 1 : width / 100 == 17 ? kRowPack<17> : kRowPack<35>;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * wavefronts), lds, st, a);
     return hipGetLastError();
 }
 

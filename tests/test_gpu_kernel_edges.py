@@ -372,3 +372,13 @@ def test_decompress_units_of_narrow_rows_and_blocks(shape, B, b, each, mode):
     name = _names(shape, B, b, mode)[1]
     assert name.startswith("decompress_units<") and (name.count(",") == 3) == each, name
     _round_trip(shape, B, b, mode)
+
+
+# rows of 17 and 35 elements, the rows of three planes side by side (maps of many planes): planes left over, fewer rows than columns, one row of
+# blocks, elements that start in the middle of a dword; and the same widths with more rows than columns, which keep their slots
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 1), ("bf16", 4), ("bf16", 8), ("c16", 2)])
+@pytest.mark.parametrize("shape,B", [((1, 4096, 17, 17), 8), ((1, 4097, 17, 17), 4), ((2, 2049, 3, 17), 8), ((1, 4099, 9, 17), 4), ((1, 4097, 21, 17), 8),
+                                     ((1, 2048, 35, 35), 8), ((1, 2050, 35, 35), 4), ((1, 2051, 2, 35), 8), ((1, 2049, 33, 35), 4), ((1, 2049, 37, 35), 8)])
+def test_rows_of_three_planes_side_by_side(shape, B, mode, b):
+    assert _names(shape, B, b, mode)[0].startswith("compress_rowstrip<")
+    _round_trip(shape, B, b, mode)
