@@ -40,9 +40,12 @@ constexpr int kRegUnits = 13;     // units per lane: planes of up to 13 * (threa
 // round puts each round into a basic block of its own that waits for every load; the instances that
 // must test because their planes may be short get a second copy of the body for planes that are not; the walk over
 // several planes has no tested copy: rounds past the plane load zeros and store nothing).
+// ROW: maps of one row, whose blocks are one row of units; the general way reads and adds B rows of them, those past the map as zeros (a body of its own: as
+// a branch of the block sums it took 56 x 56 from 4.5 to 4.7 us).  Rows of 3136 under B = 8: 98 planes 7.6 -> 5.1 us, 64 x 384 planes
+// 85 -> 64 (6.0 TB/s).
 // WALK: 0 a plane per workgroup, 1 the planes of one map, 2 of several (whose pointers are loaded anew for each plane: one volume map
 // of 32 x 64 x 16 x 56 x 56 96.4 us with them loaded so, 95.4 without, in bfloat16 74.1 and 72.0).
-template <typename T, int BITS, int B, int NW, bool RELU, int ND = 2, bool FULL = false, int WALK = 0>
+template <typename T, int BITS, int B, int NW, bool RELU, int ND = 2, bool FULL = false, int WALK = 0, bool ROW = false>
 __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
     constexpr int NT = 64 * NW;
     constexpr int K = kRegUnits;
@@ -239,6 +242,12 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
                 for (int z = 0; z < B; ++z) S += zsum[t * B + z];          // slices past the map hold 0
                 cnt = deps * rows * units * 4;
             } else if constexpr (B == 0) {
+            } else if constexpr (ROW) {
+                const uint32_t units = min((uint32_t)UPB, a.w4 - bj * UPB);
+                S = usum[bj * UPB];
+#pragma unroll
+                for (int u = 1; u < UPB; ++u) S += (uint32_t)u < units ? usum[bj * UPB + u] : 0.0;
+                cnt = units * 4;
             } else if (full_blocks) {
 #pragma unroll
                 for (int rr = 0; rr < B; ++rr)
@@ -350,6 +359,9 @@ __device__ __forceinline__ void compress_regs_rounds(const RegsArgs& a) {
 }
 template <typename T, int BITS, int B, int NW>
 __global__ void __launch_bounds__(64 * NW) compress_regs(RegsArgs a) {
+    if constexpr (B != 0 && NW == 1) {
+        if (a.H == 1) { compress_regs_body<T, BITS, B, NW, false, 2, false, 0, true>(a); return; }
+    }
     if constexpr (B == 0 || NW == 16) compress_regs_rounds<T, BITS, B, NW, 2>(a);
     else compress_regs_body<T, BITS, B, NW, false>(a);
 }

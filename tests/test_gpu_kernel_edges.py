@@ -382,3 +382,11 @@ def test_decompress_units_of_narrow_rows_and_blocks(shape, B, b, each, mode):
 def test_rows_of_three_planes_side_by_side(shape, B, mode, b):
     assert _names(shape, B, b, mode)[0].startswith("compress_rowstrip<")
     _round_trip(shape, B, b, mode)
+
+
+# rows long enough for the register kernel: a block is the units of one row, the last one may be short
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 8), ("c16", 4), ("f32", 1)])
+@pytest.mark.parametrize("shape,B", [((2, 3, 1, 3136), 8), ((2, 3, 1, 3136), 4), ((1, 3, 1, 2052), 8), ((1, 2, 1, 3324), 8), ((1, 2, 1, 8196), 8), ((1, 2, 1, 20000), 8)])
+def test_long_rows_in_registers(shape, B, mode, b):
+    assert _names(shape, B, b, mode)[0].startswith("compress_regs<")
+    _round_trip(shape, B, b, mode)
