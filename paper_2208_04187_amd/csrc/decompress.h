@@ -10,6 +10,7 @@ struct DecShape {        // the maps of one shape
     uint32_t Hs, LHs;    // 3-D maps: rows and block rows of one depth slice (H counts the rows of all slices)
     uint32_t whole8;     // decompress_stream, 2-byte elements: rows and blocks are whole vectors of eight elements
     uint32_t out_off;    // decompress_words: byte offset of the staged output in LDS
+    uint32_t rounds;     // decompress_units: rounds of units of a plane that a workgroup takes (all, or some where there are few planes)
     FastDiv d_q4, d_w4, d_B, d_W, d_HW, d_Hs, d_wpp;
     double r_q4, r_HW;   // 1 / q4, 1 / HW: a division per wavefront is 30 binary64 instructions
 };
@@ -679,6 +680,7 @@ __global__ void __launch_bounds__(kThreads) decompress_words_3d(DecArgs a) { dec
 // eight rounds, side by side and with no branch that would hold back the loads behind it, in a kernel of their own
 // (the one with a fourth argument): with both in one 3 x 3 x 13 x 24 x 22 under B = 2 took 5.9 us instead of 5.3, 40 x 16 x 35 x 35 in bfloat16 under
 // B = 18 5.4 instead of 5.2.
+// Few planes (host.h): the rounds of a plane are shared among workgroups, 8 x 147 x 147 7.4 -> 4.8 us, 9 x 147 x 111 6.3 -> 4.3.
 constexpr int kUnitsLfc = 4;      // LFC values a lane stages per plane: planes of up to 4 * threads blocks
 template <typename T, int BITS, int NW, bool WIDE>
 __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
@@ -692,7 +694,14 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
     const uint32_t nbp = (a.nb + 3u) & ~3u;
     const DecPtrs pt = dec_ptrs(a.tab, a.rg);
     const uint32_t tid = threadIdx.x;
-    auto round_live = [&](int k) -> bool { return (uint32_t)(NT * k) < a.q4; };
+    // where a plane's rounds of units are shared among workgroups, each has one plane and the units from `from` on
+    // (at most 8192 units: said to the compiler, which otherwise keeps an address per round: 97 -> 150 registers)
+    const uint32_t share = WIDE ? blockIdx.x / a.P : 0u, from = (share * a.rounds * NT) & 0x1fffu, tf = tid + from;
+    const uint32_t p0 = blockIdx.x - share * a.P;
+    const uint32_t units = min(a.q4 - from, a.rounds * NT);
+    auto round_live = [&](int k) -> bool { return (uint32_t)(NT * k) < units; };
+
+    auto unit0 = [&](int k) -> bool { return k == 0 && tf == 0u; };       // the plane's first unit
 
     // Planes whose element count is not a multiple of 4 start 1, 2 or 3 elements past a unit boundary of
     // the map.  Their units then start that many elements early: every store is a whole, aligned unit of
@@ -700,7 +709,7 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
     // with 16-byte stores at 4-byte-aligned addresses; 2-byte elements need it, a store in the middle of
     // a dword is not possible), the elements before the plane and those past it are left alone.  The
     // same for all planes of the workgroup: the grid is a multiple of 4, or every workgroup has one plane.
-    const uint32_t shift = (blockIdx.x * a.HW) & 3u;
+    const uint32_t shift = (p0 * a.HW) & 3u;
 
     // LDS byte offset of the LFC of each element's block (elements outside the plane: any block, never stored).  As in
     // compress_units: the blocks of the unit's first element and of the next row's start are looked up, the others follow.
@@ -710,8 +719,8 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
         uint32_t off[4];
         if constexpr (WIDE) {
             if (!round_live(k)) continue;
-            const uint32_t f = tid + NT * k, before = f ? 0u : shift;     // elements of the unit before the plane
-            const uint32_t e0 = f ? 4u * f - shift : 0u;
+            const uint32_t f = tf + NT * k, before = unit0(k) ? shift : 0u;     // elements of the unit before the plane
+            const uint32_t e0 = unit0(k) ? 0u : 4u * f - shift;
             const uint32_t ra = fdiv(e0, a.d_W), c = e0 - ra * a.W;      // row, counted over all depth slices
             uint32_t r = ra, rn = ra + 1u, zb = 0, zbn = 0;
             if (a.Hs != a.H) {
@@ -733,7 +742,7 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t e = 4u * (tid + NT * k) + j - shift;       // wraps for the element before the plane
+                const uint32_t e = 4u * (tf + NT * k) + j - shift;       // wraps for the element before the plane
                 const uint32_t ra = fdiv(e, a.d_W);
                 const uint32_t c = e - ra * a.W;
                 const uint32_t z = fdiv(ra, a.d_Hs);
@@ -758,18 +767,18 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (!round_live(k)) continue;
-                const uint32_t f = tid + NT * k;
-                const uint32_t bit = f ? (4u * f - shift) * BITS : 0u;
+                const uint32_t f = tf + NT * k;
+                const uint32_t bit = unit0(k) ? 0u : (4u * f - shift) * BITS;
                 wide[k] = __builtin_amdgcn_raw_buffer_load_b64(wrs, (bit >> 5) * 4u, 0, 0);
             }
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (!round_live(k) || shift) continue;
-            if constexpr (BITS == 1) wide[k].x = __builtin_amdgcn_raw_buffer_load_b8(crs, (tid + (uint32_t)(NT * k)) >> 1, 0, 0);   // two units per byte
-            else if constexpr (CB == 1) wide[k].x = __builtin_amdgcn_raw_buffer_load_b8(crs, tid, k * NT, 0);
-            else if constexpr (CB == 2) wide[k].x = __builtin_amdgcn_raw_buffer_load_b16(crs, tid * 2u, k * NT * 2, 0);
-            else wide[k].x = __builtin_amdgcn_raw_buffer_load_b32(crs, tid * 4u, k * NT * 4, 0);
+            if constexpr (BITS == 1) wide[k].x = __builtin_amdgcn_raw_buffer_load_b8(crs, (tf + (uint32_t)(NT * k)) >> 1, 0, 0);   // two units per byte
+            else if constexpr (CB == 1) wide[k].x = __builtin_amdgcn_raw_buffer_load_b8(crs, tf, k * NT, 0);
+            else if constexpr (CB == 2) wide[k].x = __builtin_amdgcn_raw_buffer_load_b16(crs, tf * 2u, k * NT * 2, 0);
+            else wide[k].x = __builtin_amdgcn_raw_buffer_load_b32(crs, tf * 4u, k * NT * 4, 0);
         }
 #pragma unroll
         for (int m = 0; m < KL; ++m) {
@@ -779,9 +788,9 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
         dd = meta_load(pt.meta, p, kC16<T>);
     };
 
-    if (blockIdx.x < a.P) issue_loads(blockIdx.x);
+    issue_loads(p0);
     uint32_t flip = 0;
-    for (uint32_t p = blockIdx.x; p < a.P; p += gridDim.x, flip ^= 1u) {
+    for (uint32_t p = p0; p < a.P; p += gridDim.x, flip ^= 1u) {
         float* lfcs = lbuf + flip * nbp;
 #pragma unroll
         for (int m = 0; m < KL; ++m) {
@@ -794,10 +803,10 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
             c4[k] = 0u;
             if (!round_live(k)) continue;
             if (shift) {
-                const uint32_t f = tid + NT * k;
-                const uint32_t bit = f ? (4u * f - shift) * BITS : 0u;
+                const uint32_t f = tf + NT * k;
+                const uint32_t bit = unit0(k) ? 0u : (4u * f - shift) * BITS;
                 const uint32_t c = __builtin_amdgcn_alignbit(wide[k].y, wide[k].x, bit & 31u);
-                c4[k] = f ? c : c << (shift * BITS);       // unit 0: the slots before the plane, then its first elements
+                c4[k] = unit0(k) ? c << (shift * BITS) : c;       // unit 0: the slots before the plane, then its first elements
                 continue;
             }
             c4[k] = BITS == 1 ? wide[k].x >> ((tid & 1u) * 4u) : wide[k].x;
@@ -811,14 +820,14 @@ __device__ __forceinline__ void decompress_units_body(const DecArgs& a) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (!round_live(k)) continue;
-            const uint32_t f = tid + NT * k;
+            const uint32_t f = tf + NT * k;
             float o[4];
             o[0] = dequant(c4[k] & Lq, sc.y, sc.x, *reinterpret_cast<const float*>(lb + (lo[k][0] & 0xffffu)));
             o[1] = dequant((c4[k] >> BITS) & Lq, sc.y, sc.x, *reinterpret_cast<const float*>(lb + (lo[k][0] >> 16)));
             o[2] = dequant((c4[k] >> (2 * BITS)) & Lq, sc.y, sc.x, *reinterpret_cast<const float*>(lb + (lo[k][1] & 0xffffu)));
             o[3] = dequant((c4[k] >> (3 * BITS)) & Lq, sc.y, sc.x, *reinterpret_cast<const float*>(lb + (lo[k][1] >> 16)));
             const uint32_t e0 = 4u * f - shift;                  // the unit's first element (wraps for unit 0 of a shifted plane)
-            if (e0 + 4u <= a.HW && (shift == 0u || f != 0u)) {
+            if (e0 + 4u <= a.HW && (shift == 0u || !unit0(k))) {
                 store4(out - shift, (size_t)f * 4, o[0], o[1], o[2], o[3]);
             } else {
                 // a unit that reaches outside the plane (the last one when H*W is not a multiple of 4,

@@ -390,3 +390,12 @@ def test_rows_of_three_planes_side_by_side(shape, B, mode, b):
 def test_long_rows_in_registers(shape, B, mode, b):
     assert _names(shape, B, b, mode)[0].startswith("compress_regs<")
     _round_trip(shape, B, b, mode)
+
+
+# decompress_units, the rounds of a plane shared among workgroups: two to eight shares, the last one short, planes that start anywhere in a unit
+@pytest.mark.parametrize("b", [1, 2, 4, 8])
+@pytest.mark.parametrize("shape,B", [((1, 1500, 27, 27), 8), ((1, 7, 27, 27), 4), ((1, 401, 73, 73), 8), ((1, 90, 73, 73), 18), ((1, 3, 147, 147), 8), ((1, 129, 147, 147), 8),
+                                     ((1, 5, 8, 14, 15), 8), ((1, 300, 55, 55), 18)])
+def test_decompress_units_of_few_planes(shape, B, b):
+    assert _names(shape, B, b, "bf16")[1].startswith("decompress_units<")
+    _round_trip(shape, B, b, "bf16")
