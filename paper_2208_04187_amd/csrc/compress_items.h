@@ -2,9 +2,7 @@
 
 // ------------------------------------------------------------------ compress, items straight from global memory
 
-struct ItemsArgs {
-    CompTab tab;
-    Regions rg;
+struct ItemsShape {
     uint32_t P, H, W, HW, LW, nb, WPP;
     uint32_t ipr;        // item slots per block row (padded to the items-per-block count)
     uint32_t ipp;        // item slots per plane = LH * ipr (<= 64)
@@ -17,6 +15,7 @@ struct ItemsArgs {
     void* y;             // relu_compress_items: the activation's output map and its 1-bit mask (one map per launch);
     uint32_t* mask;      // rpw * ppr * HW is a multiple of 32 then: a workgroup's mask bits are whole words
 };
+struct ItemsArgs : CompHead, ItemsShape {};
 
 // Small planes (at most 64 pooling items, e.g. 28x28 and 14x14 with B = 8): one
 // wavefront per round of 64/S whole planes, and x never goes through LDS.  A
@@ -32,8 +31,9 @@ struct ItemsArgs {
 // cache: y = x where x > 0 else +0 is written out row by row as it was loaded, and y is what gets
 // compressed.  The 1-bit mask (bit i of the whole map = x_i > 0) of the planes a workgroup handles
 // is OR-ed together in LDS and leaves as whole words when the workgroup is done.
+// wg: which run of rpw rounds the workgroup takes.
 template <typename T, int BITS, int B, int VEC, int R, bool RELU>
-__device__ __forceinline__ void compress_items_body(const ItemsArgs& a) {
+__device__ __forceinline__ void compress_items_body(const ItemsShape& a, const CompPtrs& pt, uint32_t wg) {
     constexpr int IPB = B / VEC;          // items per block (power of two)
     constexpr int CPW = 32 / BITS;        // codes per word
     constexpr float Lf = float((1 << BITS) - 1);
@@ -42,7 +42,6 @@ __device__ __forceinline__ void compress_items_body(const ItemsArgs& a) {
     uint32_t* mw = cw + ((a.ppr * a.WPP + 3u) & ~3u);         // RELU: [rpw * ppr * HW / 32] mask words of the workgroup
 
     const uint32_t lane = threadIdx.x;
-    const CompPtrs pt = comp_ptrs(a.tab, a.rg, lane);
 
     // the lane's item: the same in every round
     const uint32_t g = lane >> a.S_log2;                      // plane of the round
@@ -62,7 +61,6 @@ __device__ __forceinline__ void compress_items_body(const ItemsArgs& a) {
     const uint32_t rowW = (a.W / 2u) * kWeyl;                 // pair counter distance between rows
     const uint32_t rwords = a.ppr * a.WPP;
 
-    const uint32_t wg = xcd_run_index(blockIdx.x, gridDim.x);   // which run of rpw rounds this workgroup takes
     const uint32_t rend = min(a.nrounds, (wg + 1) * a.rpw);
     const uint32_t mbits = a.rpw * a.ppr * a.HW;               // RELU: mask bits of a workgroup (a multiple of 32)
     if constexpr (RELU) {
@@ -229,6 +227,6 @@ __device__ __forceinline__ void compress_items_body(const ItemsArgs& a) {
 }
 
 template <typename T, int BITS, int B, int VEC, int R>
-__global__ void __launch_bounds__(64) compress_items(ItemsArgs a) { compress_items_body<T, BITS, B, VEC, R, false>(a); }
+__global__ void __launch_bounds__(64) compress_items(ItemsArgs a) { compress_items_body<T, BITS, B, VEC, R, false>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, gridDim.x)); }
 template <typename T, int BITS, int B, int VEC>
-__global__ void __launch_bounds__(64) relu_compress_items(ItemsArgs a) { compress_items_body<T, BITS, B, VEC, B, true>(a); }
+__global__ void __launch_bounds__(64) relu_compress_items(ItemsArgs a) { compress_items_body<T, BITS, B, VEC, B, true>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, gridDim.x)); }

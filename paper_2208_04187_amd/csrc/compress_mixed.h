@@ -4,7 +4,6 @@
 
 constexpr uint32_t kMixedUnits = 8;       // units (four consecutive elements) per lane, at most
 constexpr int kMixedThreads = 1024;       // lanes per plane, and threads of a workgroup, at most
-constexpr int kMixedShapes = 8, kMixedMaps = 24;
 // (three runs of sixteen words: wide scalar loads)
 struct alignas(64) MixedShape {
     uint32_t P, D, H, W, HW, LH, LW, nb, WPP, B;      // D depth slices of H rows; LH block rows per slice
@@ -18,17 +17,7 @@ struct alignas(64) MixedShape {
     FastDiv d_W, d_B, d_H, d_LW, d_slice, d_nch, d_Br;      // d_slice divides by LH * LW
     Regions rg;
 };
-typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-struct MixedArgs {
-    u32x8 first;                          // first workgroup of each shape (beyond the last shape: 2^32 - 1)
-    u32x8 chunks;                         // workgroups per map
-    u32x8 map0;                           // its first map
-    MixedShape shape[kMixedShapes];
-    const void* x[kMixedMaps];
-    void* pk[kMixedMaps];
-    uint32_t seed_a[kMixedMaps], seed_c[kMixedMaps];
-};
+struct MixedArgs : SharedTab { MixedShape shape[kSharedShapes]; };
 
 // LDS byte offsets of the H^L of the four elements from e0 on (4 * nb = the sentinel for elements past the plane), two per word
 __device__ __forceinline__ void mixed_offsets(const MixedShape& a, uint32_t e0, uint32_t allrows, bool flat, uint32_t (&lo)[2]) {
@@ -262,38 +251,23 @@ template <typename T, int BITS>
 __global__ void __launch_bounds__(kMixedThreads, 4) compress_mixed(MixedArgs a) {
     extern __shared__ float4 smem4[];
     char* smem = reinterpret_cast<char*>(smem4);
-    const u32x8 first = a.first, chunks = a.chunks, map0 = a.map0;
-    uint32_t s = 0, wg = 0, n = chunks[0], m = map0[0];
-#pragma unroll
-    for (int i = 1; i < kMixedShapes; ++i) {
-        const bool later = blockIdx.x >= first[i];
-        s = later ? (uint32_t)i : s; wg = later ? first[i] : wg; n = later ? chunks[i] : n; m = later ? map0[i] : m;
-    }
-    wg = blockIdx.x - wg;
-    while (wg >= n) { wg -= n; ++m; }
+    const SharedPlace at = shared_place(a);
     MixedShape sh;
     {
-        const u32x16* from = reinterpret_cast<const u32x16*>(&a.shape[s]);
+        const u32x16* from = reinterpret_cast<const u32x16*>(&a.shape[at.shape]);
         const u32x16 w0 = from[0], w1 = from[1], w2 = from[2];
         __builtin_memcpy(reinterpret_cast<char*>(&sh), &w0, 64);
         __builtin_memcpy(reinterpret_cast<char*>(&sh) + 64, &w1, 64);
         __builtin_memcpy(reinterpret_cast<char*>(&sh) + 128, &w2, 64);
     }
-    char* pk = static_cast<char*>(a.pk[m]);
-    CompPtrs pt;
-    pt.x = a.x[m];
-    pt.codes = reinterpret_cast<uint32_t*>(pk);
-    pt.meta = reinterpret_cast<float*>(pk + sh.rg.meta_off);
-    pt.lfc = pk + sh.rg.lfc_off;
-    pt.seed_a = a.seed_a[m];
-    pt.seed_c = a.seed_c[m];
+    const CompPtrs pt = shared_ptrs(a, sh.rg, at.map);
     switch (sh.K) {
-        case 1: compress_mixed_body<T, BITS, 1>(sh, pt, wg, smem); break;
-        case 2: compress_mixed_body<T, BITS, 2>(sh, pt, wg, smem); break;
-        case 3: compress_mixed_body<T, BITS, 3>(sh, pt, wg, smem); break;
-        case 4: compress_mixed_body<T, BITS, 4>(sh, pt, wg, smem); break;
-        case 6: compress_mixed_body<T, BITS, 6>(sh, pt, wg, smem); break;
-        default: compress_mixed_body<T, BITS, 8>(sh, pt, wg, smem);
+        case 1: compress_mixed_body<T, BITS, 1>(sh, pt, at.wg, smem); break;
+        case 2: compress_mixed_body<T, BITS, 2>(sh, pt, at.wg, smem); break;
+        case 3: compress_mixed_body<T, BITS, 3>(sh, pt, at.wg, smem); break;
+        case 4: compress_mixed_body<T, BITS, 4>(sh, pt, at.wg, smem); break;
+        case 6: compress_mixed_body<T, BITS, 6>(sh, pt, at.wg, smem); break;
+        default: compress_mixed_body<T, BITS, 8>(sh, pt, at.wg, smem);
     }
-    if (wg == 0 && threadIdx.x < 48) zero_pads(a.shape[s].rg, pk, threadIdx.x);
+    if (at.wg == 0 && threadIdx.x < 48) zero_pads(a.shape[at.shape].rg, static_cast<char*>(a.pk[at.map]), threadIdx.x);
 }

@@ -2,9 +2,7 @@
 
 // ------------------------------------------------------------------ compress, planes that are one block
 
-struct OneArgs {
-    CompTab tab;
-    Regions rg;
+struct OneShape {
     uint32_t P, HW, WPP;
     uint32_t qv;         // 16-byte vectors per plane
     uint32_t S, S_log2;  // lanes per plane (power of two, at most 64)
@@ -14,6 +12,7 @@ struct OneArgs {
     uint32_t K;          // rounds of the instance to launch (3, 6, 12 or 13): not read by the kernels
     uint32_t NG;         // compress_line: groups of 64 / S planes per wavefront (1, or 12 / rounds per plane for tiny planes)
 };
+struct OneArgs : CompHead, OneShape {};
 
 constexpr int kOneUnits = 13;     // vectors per lane: planes of up to 13 * 64 vectors
 
@@ -181,7 +180,7 @@ constexpr int kLineUnits = 13;
 // 64 / S planes one after the other, all their loads issued first, so that it has K vectors per lane in
 // flight like the instances for larger planes (two or three would not cover the memory latency).
 template <typename T, int BITS, int K, int NG, int LU>
-__global__ void __launch_bounds__(64) compress_line(OneArgs a) {
+__device__ __forceinline__ void compress_line_body(const OneShape& a, const CompPtrs& pt, uint32_t wg) {
     constexpr int R = K / NG;
     static_assert(R * NG == K, "whole groups");
     constexpr bool LDS = LU < 0;
@@ -197,10 +196,9 @@ __global__ void __launch_bounds__(64) compress_line(OneArgs a) {
     constexpr uint32_t kDrop = 0x80000000u;              // an offset past every buffer here (and no wrap when a round's offset is added): the access is dropped
     constexpr uint32_t LB = (sizeof(T) == 2 || kC16<T>) ? 2u : 4u;          // bytes of a cached H^L value
     const uint32_t tid = threadIdx.x;
-    const CompPtrs pt = comp_ptrs(a.tab, a.rg, tid);
     const uint32_t S = a.S, sub = tid & (S - 1u), lp = tid >> a.S_log2;
     const uint32_t ppw = a.ppw * NG;                     // planes of the wavefront
-    const uint32_t p0 = xcd_run_index(blockIdx.x, gridDim.x) * ppw;
+    const uint32_t p0 = wg * ppw;
     const uint32_t Gc = min(ppw, a.P - p0);
 
     // Offset of round r's piece (`bytes` per vector) given that of round 0: in a whole round the step goes into the scalar
@@ -227,6 +225,7 @@ __global__ void __launch_bounds__(64) compress_line(OneArgs a) {
             }
         }
     }
+    __builtin_amdgcn_sched_barrier(0);                   // all loads ahead of the first wait (otherwise the masked rounds' may come behind it: 3.1 -> 3.4 us on small maps)
     const uint32_t cnt_full = a.upb * EPV, cnt_last = (a.qv - (a.nb - 1u) * a.upb) * EPV;
     const double rcp_last = LU == 0 ? 0.0 : 1.0 / (double)cnt_last;
     const double rcp_full = __longlong_as_double((long long)(1023u - (31u - (uint32_t)__builtin_clz(cnt_full))) << 52);     // a power of two
@@ -397,4 +396,23 @@ __global__ void __launch_bounds__(64) compress_line(OneArgs a) {
         }
     }
     }
+}
+
+template <typename T, int BITS, int K, int NG, int LU>
+__global__ void __launch_bounds__(64) compress_line(OneArgs a) {
+    compress_line_body<T, BITS, K, NG, LU>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, gridDim.x));
+}
+
+// The maps of several shapes that have the same instance, in one launch.  What it saves is the drain and the filling between the launches, 2-4 us
+// each: the compress side of a Swin-T step in eight launches 170 us, in four 162; two widths of a T5-base step 62 and 58.
+struct LinesArgs : SharedTab {
+    OneShape shape[kSharedShapes];
+    Regions rg[kSharedShapes];
+};
+template <typename T, int BITS, int K, int LU>
+__global__ void __launch_bounds__(64) compress_lines(LinesArgs a) {
+    const SharedPlace at = shared_place(a);
+    const Regions& rg = a.rg[at.shape];
+    if (at.wg == 0 && threadIdx.x < 48) zero_pads(rg, static_cast<char*>(a.pk[at.map]), threadIdx.x);
+    compress_line_body<T, BITS, K, 1, LU>(a.shape[at.shape], shared_ptrs(a, rg, at.map), xcd_run_index(at.wg, at.n));
 }

@@ -1,5 +1,35 @@
 // Part of division.hip (included inside its unnamed namespace, after compress_strip.h): compress_rowstrip.
 
+// ------------------------------------------------------------------ compress, strips and items of several shapes in one launch
+
+// The planes of compress_strip (B = 4, 8) and those of compress_items under B = 4, which have few registers in common (64 at most): the shapes of a call
+// that are these go out together.  A launch of its own costs a shape 2-4 us of draining and filling: the compress side of a ResNet-18 / CIFAR step in four launches
+// 65 us (4.4 TB/s), in one 50 (5.7).
+struct PlanesShape { uint32_t kind; union { StripShape strip; ItemsShape items; }; };      // kind: 100 W + B of the strips, 4 or 2 (elements per row of an item) of the items
+struct PlanesArgs : SharedTab {
+    PlanesShape shape[kSharedShapes];
+    Regions rg[kSharedShapes];
+};
+template <typename T, int BITS>
+__global__ void __launch_bounds__(64) compress_planes(PlanesArgs a) {
+    const SharedPlace at = shared_place(a);
+    const Regions& rg = a.rg[at.shape];
+    if (at.wg == 0 && threadIdx.x < 48) zero_pads(rg, static_cast<char*>(a.pk[at.map]), threadIdx.x);
+    const CompPtrs pt = shared_ptrs(a, rg, at.map);
+    const PlanesShape& s = a.shape[at.shape];
+    const uint32_t wg = xcd_run_index(at.wg, at.n);
+    switch (s.kind) {
+        case 3208: compress_strip_body<T, BITS, 32, 8, false>(s.strip, pt, wg); break;
+        case 2808: compress_strip_body<T, BITS, 28, 8, false>(s.strip, pt, wg); break;
+        case 1608: compress_strip_body<T, BITS, 16, 8, false>(s.strip, pt, wg); break;
+        case 1408: compress_strip_body<T, BITS, 14, 8, false>(s.strip, pt, wg); break;
+        case 3204: compress_strip_body<T, BITS, 32, 4, false>(s.strip, pt, wg); break;
+        case 1604: compress_strip_body<T, BITS, 16, 4, false>(s.strip, pt, wg); break;
+        case 4: compress_items_body<T, BITS, 4, 4, 4, false>(s.items, pt, wg); break;
+        default: compress_items_body<T, BITS, 4, 2, 4, false>(s.items, pt, wg);
+    }
+}
+
 // ------------------------------------------------------------------ compress, a row of an odd-width plane per lane
 
 // Geometry for planes of an odd width W (13, 15, 17, 27, 35, 55: maps of AlexNet and Inception-v3).

@@ -2,9 +2,7 @@
 
 // ------------------------------------------------------------------ compress, a strip of 28 or 32 elements per lane
 
-struct StripArgs {
-    CompTab tab;
-    Regions rg;
+struct StripShape {
     uint32_t P, H, HW, WPP, nb;
     uint32_t nrounds;    // ceil(P / planes per round)
     void* y;             // relu_compress_strip: the activation's output map and its 1-bit mask (one map per launch);
@@ -13,6 +11,7 @@ struct StripArgs {
     uint32_t pack_off, LH;
     FastDiv d_H, d_LH;
 };
+struct StripArgs : CompHead, StripShape {};
 
 // Geometry of the strip kernel for planes of width W under block size B (both compile-time).
 template <int W, int B>
@@ -51,7 +50,7 @@ struct StripGeom {
 // y leaves from the same registers (16-byte stores), the mask bits of a lane's unit are merged
 // over eight adjacent lanes (DPP OR) and leave as whole words; the codec then runs on y.
 template <typename T, int BITS, int W, int B, bool RELU>
-__device__ __forceinline__ void compress_strip_body(const StripArgs& a) {
+__device__ __forceinline__ void compress_strip_body(const StripShape& a, const CompPtrs& pt, uint32_t round) {
     using Geo = StripGeom<W, B>;
     constexpr int E = Geo::E, S = Geo::S, G = Geo::G, NSEG = Geo::NSEG, LBR = Geo::LBR, RPL = Geo::RPL;
     constexpr int UPL = E / 4;                  // units per lane
@@ -64,8 +63,6 @@ __device__ __forceinline__ void compress_strip_body(const StripArgs& a) {
     (void)part; (void)lfcs; (void)RPL;
 
     const uint32_t lane = threadIdx.x;
-    const CompPtrs pt = comp_ptrs(a.tab, a.rg, lane);
-    const uint32_t round = xcd_run_index(blockIdx.x, a.nrounds);
     const uint32_t p0 = round * G;
     const uint32_t Gc = min((uint32_t)G, a.P - p0);
 
@@ -261,6 +258,6 @@ __device__ __forceinline__ void compress_strip_body(const StripArgs& a) {
 }
 
 template <typename T, int BITS, int W, int B>
-__global__ void __launch_bounds__(64) compress_strip(StripArgs a) { compress_strip_body<T, BITS, W, B, false>(a); }
+__global__ void __launch_bounds__(64) compress_strip(StripArgs a) { compress_strip_body<T, BITS, W, B, false>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, a.nrounds)); }
 template <typename T, int BITS, int W, int B>
-__global__ void __launch_bounds__(64) relu_compress_strip(StripArgs a) { compress_strip_body<T, BITS, W, B, true>(a); }
+__global__ void __launch_bounds__(64) relu_compress_strip(StripArgs a) { compress_strip_body<T, BITS, W, B, true>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, a.nrounds)); }

@@ -375,6 +375,7 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     Mixer mixer;
     CompMixer comp;
+    SharedMixer shared;
     std::vector<char> done((size_t)count, 0);
     std::vector<const void*> in;
     std::vector<void*> out;
@@ -392,7 +393,7 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             if (maps[j].packed_bytes < cap) cap = maps[j].packed_bytes;
         }
         const division_map& m = maps[i];
-        if (mix && in.size() <= (size_t)(compress ? kMixedMaps : kMixMaps)) {
+        if (mix && in.size() <= (size_t)(compress ? kSharedMaps : kMixMaps)) {
             int64_t D = m.D, H = m.H, W = m.W;
             squeeze_dims(D, H, W);
             Layout L;
@@ -414,6 +415,7 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
                     comp.add(m, sh, lanes, in.size(), cap, in.data(), out.data(), seeds.data());
                     continue;
                 }
+                if (shared.add(m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
             } else {
                 for (void* o : out) all |= (uintptr_t)o;
                 DecShape sh{};
@@ -435,7 +437,9 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             : decompress_impl((int)in.size(), in.data(), out.data(), cap, m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, hip_stream);
         if (rc != DIVISION_OK) return rc;
     }
-    return compress ? comp.flush(st) : mixer.flush(st);
+    if (!compress) return mixer.flush(st);
+    const int rc = shared.flush(st);
+    return rc != DIVISION_OK ? rc : comp.flush(st);
 }
 
 int division_compress_maps(int count, const division_map* maps, void* hip_stream) {

@@ -8,6 +8,8 @@ struct bf16_t { uint16_t v; };
 // at run time
 struct f32c16_t { float v; };
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
@@ -196,6 +198,35 @@ __device__ __forceinline__ CompPtrs comp_ptrs_of(const CompTab& tab, const Regio
 __device__ __forceinline__ void zero_pads(const Regions& rg, char* pk, uint32_t tid) {
     const uint32_t k = tid >> 4, j = tid & 15u;
     if (j < rg.pad_len[k]) pk[rg.pad_off[k] + j] = 0;
+}
+// what the arguments of every compress kernel begin with
+struct CompHead { CompTab tab; Regions rg; };
+
+// Arguments of a compress launch that holds the maps of several shapes: a workgroup finds its shape by its first workgroup, its map by counting
+// down the workgroups of the maps before it.  (vectors: wide scalar loads)
+constexpr int kSharedShapes = 8, kSharedMaps = 24;
+struct SharedTab {
+    u32x8 first, chunks, map0;            // first workgroup of each shape (beyond the last shape: 2^32 - 1), workgroups per map, first map
+    const void* x[kSharedMaps];
+    void* pk[kSharedMaps];
+    uint32_t seed_a[kSharedMaps], seed_c[kSharedMaps];
+};
+struct SharedPlace { uint32_t shape, map, wg, n; };      // workgroup wg of the map's n
+__device__ __forceinline__ SharedPlace shared_place(const SharedTab& t) {
+    const u32x8 first = t.first, chunks = t.chunks, map0 = t.map0;
+    SharedPlace at{0, map0[0], 0, chunks[0]};
+#pragma unroll
+    for (int i = 1; i < kSharedShapes; ++i) {
+        const bool later = blockIdx.x >= first[i];
+        at.shape = later ? (uint32_t)i : at.shape; at.wg = later ? first[i] : at.wg; at.n = later ? chunks[i] : at.n; at.map = later ? map0[i] : at.map;
+    }
+    at.wg = blockIdx.x - at.wg;
+    while (at.wg >= at.n) { at.wg -= at.n; ++at.map; }
+    return at;
+}
+__device__ __forceinline__ CompPtrs shared_ptrs(const SharedTab& t, const Regions& rg, uint32_t map) {
+    char* pk = static_cast<char*>(t.pk[map]);
+    return CompPtrs{t.x[map], reinterpret_cast<uint32_t*>(pk), reinterpret_cast<float*>(pk + rg.meta_off), pk + rg.lfc_off, t.seed_a[map], t.seed_c[map]};
 }
 // this workgroup's tensor
 __device__ __forceinline__ CompPtrs comp_ptrs(const CompTab& tab, const Regions& rg, uint32_t tid) {

@@ -1122,11 +1122,10 @@ int plan_mix(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es
     return kind;
 }
 
-enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, SEG, WAVE, TILE, ONE, ROWS, PLANE, ANY, MIXED };
+enum CompKind { REGS, LANE, LINE, STRIP, ROWSTRIP, ITEMS, UNITS, SEG, WAVE, TILE, ONE, ROWS, PLANE, ANY, MIXED, LINES, PLANES };
 
 // Everything a compress launch needs once the plan is made: the arguments of the kernel that was picked, which begin alike (head).  A
 // plan zeroes them before it fills them in.
-struct CompHead { CompTab tab; Regions rg; };
 struct CompLaunch {
     int kind, B, vec, nt, nw, flat;
     uint32_t gx, gy;
@@ -1137,6 +1136,8 @@ struct CompLaunch {
         CompHead head;
         TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa; SegArgs sg;
         const MixedArgs* mixed;                  // kind MIXED (nt threads)
+        struct { const LinesArgs* a; uint32_t K; int lu; } lines;      // kind LINES: the instance its shapes share
+        const PlanesArgs* planes;                // kind PLANES
     };
 };
 struct MixLaunch { uint32_t grid; hipStream_t st; MixArgs a; };      // decompress_mixed
@@ -1176,6 +1177,26 @@ hipError_t launch_line(const OneArgs& a, dim3 gd, size_t lds, hipStream_t st) {
 }
 
 template <typename T, int BITS>
+hipError_t launch_lines(const LinesArgs& a, uint32_t K, int lu, dim3 gd, size_t lds, hipStream_t st) {
+    void (*kern)(LinesArgs);
+    switch (lu) {
+        case 0: kern = K == 4 ? compress_lines<T, BITS, 4, 0> : compress_lines<T, BITS, 6, 0>; break;
+        case 1: kern = K == 4 ? compress_lines<T, BITS, 4, 1> : compress_lines<T, BITS, 6, 1>; break;
+        case 2: kern = K == 4 ? compress_lines<T, BITS, 4, 2> : compress_lines<T, BITS, 6, 2>; break;
+        case -1: kern = K == 4 ? compress_lines<T, BITS, 4, -1> : compress_lines<T, BITS, 6, -1>; break;
+        default: kern = K == 4 ? compress_lines<T, BITS, 4, -2> : compress_lines<T, BITS, 6, -2>;
+    }
+    hipLaunchKernelGGL(kern, gd, dim3(64), lds, st, a);
+    return hipGetLastError();
+}
+
+template <typename T, int BITS>
+hipError_t launch_planes(const PlanesArgs& a, dim3 gd, size_t lds, hipStream_t st) {
+    hipLaunchKernelGGL((compress_planes<T, BITS>), gd, dim3(64), lds, st, a);
+    return hipGetLastError();
+}
+
+template <typename T, int BITS>
 hipError_t launch_mixed(const MixedArgs& a, dim3 gd, int nt, size_t lds, hipStream_t st) {
     void (*kern)(MixedArgs) = compress_mixed<T, BITS>;
     const hipError_t e = allow_large_lds(kern, lds);
@@ -1204,6 +1225,8 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case LINE: return launch_line<T, 1>(c.oa, gd, lds, st);
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
             case MIXED: return launch_mixed<T, 1>(*c.mixed, gd, c.nt, lds, st);
+            case LINES: return launch_lines<T, 1>(*c.lines.a, c.lines.K, c.lines.lu, gd, lds, st);
+            case PLANES: return launch_planes<T, 1>(*c.planes, gd, lds, st);
             default: {
                 void (*kern)(AnyArgs) = flat ? compress_any<T, 1> : compress_any_3d<T, 1>;
                 hipLaunchKernelGGL(kern, gd, dim3(c.nt), 0, st, c.g);
@@ -1226,6 +1249,8 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case ONE: return launch_one<T, BITS>(c.oa, gd, st);
             case LINE: return launch_line<T, BITS>(c.oa, gd, lds, st);
             case MIXED: return launch_mixed<T, BITS>(*c.mixed, gd, c.nt, lds, st);
+            case LINES: return launch_lines<T, BITS>(*c.lines.a, c.lines.K, c.lines.lu, gd, lds, st);
+            case PLANES: return launch_planes<T, BITS>(*c.planes, gd, lds, st);
             case ROWS: {
                 void (*kern)(RowsArgs) = flat ? compress_rows<T, BITS> : compress_rows_3d<T, BITS>;
                 const hipError_t e = allow_large_lds(kern, lds);
@@ -1524,7 +1549,7 @@ void spread_mixed(MixedArgs& a, const uint32_t* maps, uint32_t shapes, uint32_t*
     for (uint32_t s = 0; s < shapes; ++s) nt = std::max(nt, 1u << a.shape[s].S_log2);
     *grid = 0;
     *lds = 0;
-    for (uint32_t s = 0; s < (uint32_t)kMixedShapes; ++s) a.first[s] = 0xffffffffu;
+    for (uint32_t s = 0; s < (uint32_t)kSharedShapes; ++s) a.first[s] = 0xffffffffu;
     for (uint32_t s = 0; s < shapes; ++s) {
         *lds = std::max(*lds, fit_mixed(&a.shape[s], nt));
         a.chunks[s] = (a.shape[s].P + a.shape[s].G - 1) / a.shape[s].G;
@@ -1578,13 +1603,13 @@ bool mixed_gains(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b,
 struct CompMixer {
     MixedArgs a;
     uint32_t nshape = 0, nmap = 0;
-    uint32_t maps[kMixedShapes];
-    uint64_t seeds[kMixedMaps];
+    uint32_t maps[kSharedShapes];
+    uint64_t seeds[kSharedMaps];
     const division_map* first = nullptr;      // a descriptor of the first shape, and its smallest packed buffer
     size_t first_bytes = 0;
     uint64_t lanes = 0;                       // of all shapes, at the fewest per plane
     bool fits(const division_map& m, size_t n, uint64_t more) const {
-        return nshape == 0 || (m.dt == first->dt && m.b == first->b && nshape < (uint32_t)kMixedShapes && nmap + n <= (size_t)kMixedMaps &&
+        return nshape == 0 || (m.dt == first->dt && m.b == first->b && nshape < (uint32_t)kSharedShapes && nmap + n <= (size_t)kSharedMaps &&
                                lanes + more <= (uint64_t)num_cus() * 1536);
     }
     void add(const division_map& m, const MixedShape& sh, uint64_t more, size_t n, size_t bytes, const void* const* x, void* const* packed, const uint64_t* seed) {
@@ -1647,6 +1672,79 @@ struct Mixer {
             return decompress_impl((int)nmap, c.a.pk, c.a.xhat, first_bytes, first->N, first->C, first->D, first->H, first->W, first->dt, first->B, first->b, st);
         c.st = st;
         return bridge_decompress_mixed(first->dt, c, first->b) == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+};
+
+// Shapes of one type and code width that one kernel serves share a launch: those of one instance of compress_line, and those of compress_strip and
+// compress_items that compress_planes holds.  Kept until all shapes of a call are known; a shape that finds no other has a launch of its own.
+struct SharedMixer {
+    struct Shape {
+        const division_map* m;
+        size_t bytes;                             // the smallest of the packed buffers
+        CompLaunch c;
+        Regions rg;
+        int key;                                  // shapes of equal keys share a launch: the instance of compress_line, or 0
+        std::vector<const void*> x;
+        std::vector<void*> packed;
+        std::vector<uint64_t> seeds;
+    };
+    std::vector<Shape> shapes;
+    // takes the shape if its kernel can be shared
+    bool add(const division_map& m, const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, const void* all, size_t bytes,
+             const std::vector<const void*>& x, const std::vector<void*>& packed, const std::vector<uint64_t>& seeds) {
+        CompLaunch c;
+        plan_compress(L, D, H, W, B, m.b, es, all, (int)std::min<size_t>(x.size(), kMaxBatch), &c);
+        if (x.size() > (size_t)kSharedMaps || !launch_ok((uint64_t)c.gx * x.size(), 64)) return false;
+        int key = 0;
+        if (c.kind == LINE && c.oa.NG == 1 && (c.oa.K == 4 || c.oa.K == 6)) key = 100 * (int)c.oa.K + line_lu(c.oa);
+        else if (!(c.kind == STRIP && (B == 4 || B == 8)) && !(c.kind == ITEMS && B == 4 && H > 1)) return false;
+        shapes.push_back({&m, bytes, c, make_regions(L), key, x, packed, seeds});
+        return true;
+    }
+    static void put(LinesArgs& a, uint32_t n, const Shape& q) { a.shape[n] = q.c.oa; a.rg[n] = q.rg; }
+    static void put(PlanesArgs& a, uint32_t n, const Shape& q) {
+        a.shape[n].kind = (uint32_t)q.c.vec;
+        if (q.c.kind == STRIP) a.shape[n].strip = q.c.sa; else a.shape[n].items = q.c.ia;
+        a.rg[n] = q.rg;
+    }
+    // the launch of shapes[i] and of those behind it that share it
+    template <typename Args>
+    int launch(size_t i, std::vector<char>& done, hipStream_t st) {
+        const Shape& f = shapes[i];
+        Args a;
+        uint32_t n = 0, maps = 0, grid = 0;
+        CompLaunch c;
+        c.lds = 0;
+        for (int k = 0; k < kSharedShapes; ++k) a.first[k] = 0xffffffffu;
+        for (size_t j = i; j < shapes.size() && n < (uint32_t)kSharedShapes; ++j) {
+            const Shape& q = shapes[j];
+            if (done[j] || q.m->dt != f.m->dt || q.m->b != f.m->b || q.key != f.key || maps + q.x.size() > (size_t)kSharedMaps ||
+                !launch_ok(grid + (uint64_t)q.c.gx * q.x.size(), 64))
+                continue;
+            done[j] = 1;
+            a.first[n] = grid; a.chunks[n] = q.c.gx; a.map0[n] = maps;
+            put(a, n++, q);
+            for (size_t k = 0; k < q.x.size(); ++k, ++maps) {
+                a.x[maps] = q.x[k]; a.pk[maps] = q.packed[k]; a.seed_a[maps] = seed_key_a(q.seeds[k]); a.seed_c[maps] = seed_key_c(q.seeds[k]);
+            }
+            grid += q.c.gx * (uint32_t)q.x.size();
+            c.lds = std::max(c.lds, q.c.lds);
+        }
+        const division_map& m = *f.m;
+        if (n == 1) return compress_impl((int)f.x.size(), f.x.data(), f.packed.data(), f.seeds.data(), m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, f.bytes, st);
+        c.st = st; c.gx = grid; c.gy = 1;
+        if constexpr (std::is_same<Args, LinesArgs>::value) { c.kind = LINES; c.lines.a = &a; c.lines.K = f.c.oa.K; c.lines.lu = line_lu(f.c.oa); }
+        else { c.kind = PLANES; c.planes = &a; }
+        return bridge_compress(m.dt, c, m.b) == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+    int flush(hipStream_t st) {
+        std::vector<char> done(shapes.size(), 0);
+        for (size_t i = 0; i < shapes.size(); ++i) {
+            if (done[i]) continue;
+            const int rc = shapes[i].key ? launch<LinesArgs>(i, done, st) : launch<PlanesArgs>(i, done, st);
+            if (rc != DIVISION_OK) return rc;
+        }
+        return DIVISION_OK;
     }
 };
 

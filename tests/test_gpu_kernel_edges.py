@@ -399,3 +399,25 @@ def test_long_rows_in_registers(shape, B, mode, b):
 def test_decompress_units_of_few_planes(shape, B, b):
     assert _names(shape, B, b, "bf16")[1].startswith("decompress_units<")
     _round_trip(shape, B, b, "bf16")
+
+
+# shapes that one kernel serves, too large for the launch of small maps: rows of one instance of compress_line, and the planes of compress_strip and of
+# compress_items under B = 4; a shape that finds no other beside them, several maps of a shape, more maps than a launch holds
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 1), ("f32", 8), ("bf16", 4), ("bf16", 1), ("c16", 2)])
+@pytest.mark.parametrize("specs", [
+    [((1, 2101, 1, 384), 8), ((7, 301, 1, 768), 8), ((1, 2101, 1, 384), 8), ((2, 1100, 1, 776), 8), ((1, 1057, 1, 1000), 8)],
+    [((1, 2101, 1, 384), 64), ((7, 301, 1, 760), 64), ((1, 4201, 1, 192), 64)],
+    [((1, 2057, 32, 32), 4), ((3, 2741, 16, 16), 4), ((1, 8209, 8, 8), 4), ((1, 8209, 4, 4), 4), ((3, 2741, 16, 16), 4), ((1, 8203, 6, 14), 4), ((2, 4101, 20, 24), 4)],
+    [((1, 2059, 28, 28), 8), ((1, 8211, 14, 14), 8), ((3, 701, 21, 32), 8), ((1, 8205, 10, 16), 8), ((1, 8211, 4, 4), 64)],
+    [((1, 8209, 8, 8), 4)] * 13 + [((1, 8205, 4, 4), 4)] * 12,
+])
+def test_compress_of_shapes_that_share_a_kernel(specs, mode, b):
+    dtype, c16, dt = FORMATS[mode]
+    gen = torch.Generator().manual_seed(b)
+    xs = [torch.randn(s, generator=gen).to(dtype) for s, _ in specs]
+    ref = [oracle.compress(_host(x), B, b, (3 << 32) + k, dt, threads=16) for k, (x, (_, B)) in enumerate(zip(xs, specs))]
+    packed = [torch.full((r.size,), 0xA5, dtype=torch.uint8, device="cuda:0") for r in ref]
+    pkg.division_compress_maps([x.to("cuda:0") for x in xs], [B for _, B in specs], b, [(3 << 32) + k for k in range(len(specs))], packed=packed, c16=c16)
+    torch.cuda.synchronize()
+    for (shape, B), r, p in zip(specs, ref, packed):
+        assert np.array_equal(p.cpu().numpy(), r), (shape, B)

@@ -222,7 +222,7 @@ def test_overlaps_of_random_ranges_are_those_of_every_pair(host):
     assert seen == {True, False}
 
 
-MIXED = 14                     # the launch of several shapes
+MIXED, LINES, PLANES = 14, 15, 16                     # the launches of several shapes
 
 
 def test_small_maps_of_several_shapes_compress_in_one_launch(host):
@@ -248,3 +248,23 @@ def test_maps_that_share_memory_are_compressed_in_their_order(host):
         found = _maps(host, [(A, F32, 8, 2, None, p), (B_, F32, 8, 2, out, packed), (C_, F32, 8, 2)])
         assert len(found) == 3 and MIXED not in [q.kind for q in found]
     assert len(_maps(host, [(A, F32, 8, 2, None, p), (B_, F32, 8, 2, None, x), (C_, F32, 8, 2)])) == 1
+
+
+def test_shapes_of_one_kernel_share_a_launch(host):
+    rows = [((64, 3136, 1, 384), C16, 64, 2), ((64, 784, 1, 768), C16, 64, 2), ((64, 196, 1, 1536), C16, 64, 2)]
+    assert [q.kind for q in _maps(host, rows)] == [LINES]
+    # other instances (groups of planes per wavefront, another way to add a block) keep launches of their own
+    kinds = [q.kind for q in _maps(host, rows + [((64, 3136, 1, 96), C16, 64, 2), ((64, 784, 1, 192), C16, 64, 2)])]
+    assert sorted(k == LINES for k in kinds) == [False, False, True] and MIXED not in kinds
+    planes = [((128, 64, 32, 32), F32, 4, 2), ((128, 128, 16, 16), F32, 4, 2), ((128, 256, 8, 8), F32, 4, 2), ((128, 512, 4, 4), F32, 4, 2)]
+    (launch,) = _maps(host, [m for m in planes for _ in range(4)])
+    alone = [_maps(host, [m] * 4)[0] for m in planes]
+    assert launch.kind == PLANES and launch.gx == sum(q.gx * q.gy for q in alone) and launch.gy == 1
+    # types, code widths and the kernels of other shapes do not share it
+    kinds = [q.kind for q in _maps(host, [planes[0], planes[1], ((128, 64, 32, 32), BF16, 4, 2), ((128, 64, 32, 32), F32, 4, 4), ((64, 256, 56, 56), F32, 8, 2)])]
+    assert sorted(k == PLANES for k in kinds) == [False, False, False, True]
+    # 25 maps are two launches, and maps over one another's memory a launch for each shape
+    assert [q.kind for q in _maps(host, [planes[2]] * 13 + [planes[3]] * 12)].count(PLANES) == 0
+    assert [q.kind for q in _maps(host, [planes[2]] * 12 + [planes[3]] * 12 + [planes[1]])].count(PLANES) == 1
+    x = 1 << 46
+    assert PLANES not in [q.kind for q in _maps(host, [(*planes[2], None, x), (*planes[3], None, x + 256), planes[1]])]
