@@ -393,7 +393,7 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             if (maps[j].packed_bytes < cap) cap = maps[j].packed_bytes;
         }
         const division_map& m = maps[i];
-        if (mix && in.size() <= (size_t)(compress ? kSharedMaps : kMixMaps)) {
+        if ((mix || compress) && in.size() <= (size_t)(compress ? kSharedMaps : kMixMaps)) {
             int64_t D = m.D, H = m.H, W = m.W;
             squeeze_dims(D, H, W);
             Layout L;
@@ -407,15 +407,20 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
                 const void* x = reinterpret_cast<const void*>(all);
                 const bool can = plan_mixed(L, D, H, W, B, x, &sh);
                 const uint64_t lanes = (uint64_t)in.size() * L.P << sh.S_log2;
-                if (can && mixed_gains(L, D, H, W, B, m.b, es, x, in.size(), lanes)) {
+                const int gains = can ? mixed_gains(L, D, H, W, B, m.b, es, x, in.size(), lanes) : 0;
+                if (gains == 2 || (gains && mix)) {
                     if (!comp.fits(m, in.size(), lanes)) {
                         const int rc = comp.flush(st);
                         if (rc != DIVISION_OK) return rc;
                     }
-                    comp.add(m, sh, lanes, in.size(), cap, in.data(), out.data(), seeds.data());
+                    comp.add(m, sh, gains, lanes, in.size(), cap, in.data(), out.data(), seeds.data());
+                    if (!mix) {                               // maps that share memory: in their order
+                        const int rc = comp.flush(st);
+                        if (rc != DIVISION_OK) return rc;
+                    }
                     continue;
                 }
-                if (shared.add(m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
+                if (mix && shared.add(m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
             } else {
                 for (void* o : out) all |= (uintptr_t)o;
                 DecShape sh{};

@@ -1587,13 +1587,18 @@ bool plan_mixed(const Layout& L, int64_t D, int64_t H, int64_t W, int B, const v
 // whole machine), up to twice as slow per element as those that hold them in registers (a quarter of it), three times as compress_line (an eighth).
 // 160 calls of two or three shapes of all sizes, sum of their times: 3281 us apart, 2630 so; with a half for the register kernels 2600, but maps of
 // 192 x 112 x 112 and 11554 x 16 x 13 in bfloat16 17.2 -> 19.7 with their decompression, and with a quarter for compress_line rows of 384 and 768 under B = 4 7.7 -> 9.8
-bool mixed_gains(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x, uint64_t maps, uint64_t lanes) {
+// Two: also where no other shape shares the launch.  The chunk kernels on few planes are one long chain in a few workgroups: single shapes of 0.01 to 8 M
+// elements, in their own kernel and here, compress_tile / _plane / _any 18.4 and 10.1 us on average (60 shapes), compress_wave up to 0.3 M 8.6 and 4.5, above
+// level, compress_rows up to 0.1 M 6.1 and 4.6, above level.
+int mixed_gains(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x, uint64_t maps, uint64_t lanes) {
     const uint64_t machine = (uint64_t)num_cus() * 1024;
-    if (lanes > machine) return false;
+    if (lanes > machine) return 0;
     CompLaunch own;
     plan_compress(L, D, H, W, B, b, es, x, (int)std::min<uint64_t>(maps, kMaxBatch), &own);
     switch (own.kind) {
-        case UNITS: case WAVE: case TILE: case ROWS: case PLANE: case ANY: return true;
+        case TILE: case PLANE: case ANY: return 2;
+        case WAVE: case ROWS: return lanes <= machine / 16 ? 2 : 1;
+        case UNITS: return 1;
         case LINE: return lanes <= machine / 8;
         default: return lanes <= machine / 4;
     }
@@ -1608,12 +1613,13 @@ struct CompMixer {
     const division_map* first = nullptr;      // a descriptor of the first shape, and its smallest packed buffer
     size_t first_bytes = 0;
     uint64_t lanes = 0;                       // of all shapes, at the fewest per plane
+    bool alone = false;                       // the first shape gains by itself
     bool fits(const division_map& m, size_t n, uint64_t more) const {
         return nshape == 0 || (m.dt == first->dt && m.b == first->b && nshape < (uint32_t)kSharedShapes && nmap + n <= (size_t)kSharedMaps &&
                                lanes + more <= (uint64_t)num_cus() * 1536);
     }
-    void add(const division_map& m, const MixedShape& sh, uint64_t more, size_t n, size_t bytes, const void* const* x, void* const* packed, const uint64_t* seed) {
-        if (nshape == 0) { first = &m; first_bytes = bytes; nmap = 0; lanes = 0; }
+    void add(const division_map& m, const MixedShape& sh, int gains, uint64_t more, size_t n, size_t bytes, const void* const* x, void* const* packed, const uint64_t* seed) {
+        if (nshape == 0) { first = &m; first_bytes = bytes; nmap = 0; lanes = 0; alone = gains == 2; }
         lanes += more;
         a.shape[nshape] = sh;
         a.map0[nshape] = nmap;
@@ -1627,7 +1633,7 @@ struct CompMixer {
         const uint32_t shapes = nshape;
         nshape = 0;
         if (shapes == 0) return DIVISION_OK;
-        if (shapes == 1)
+        if (shapes == 1 && !alone)
             return compress_impl((int)nmap, a.x, a.pk, seeds, first->N, first->C, first->D, first->H, first->W, first->dt, first->B, first->b, first_bytes, st);
         CompLaunch c;
         c.kind = MIXED; c.st = st; c.gy = 1; c.mixed = &a;

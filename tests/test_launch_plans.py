@@ -268,3 +268,15 @@ def test_shapes_of_one_kernel_share_a_launch(host):
     assert [q.kind for q in _maps(host, [planes[2]] * 12 + [planes[3]] * 12 + [planes[1]])].count(PLANES) == 1
     x = 1 << 46
     assert PLANES not in [q.kind for q in _maps(host, [(*planes[2], None, x), (*planes[3], None, x + 256), planes[1]])]
+
+
+def test_chunk_kernels_of_few_planes_leave_their_launch(host):
+    """One shape by itself: planes that would be a few workgroups' chain in the chunk kernels."""
+    for shape, dt, B, b in (((2, 3, 64, 64), F32, 8, 1), ((1, 2, 8, 53, 53), F32, 64, 1), ((30, 1, 1, 3413), BF16, 8, 4), ((2, 20, 30, 30), F32, 4, 2), ((5, 33, 24, 24), F32, 18, 4)):
+        assert [q.kind for q in _maps(host, [(shape, dt, B, b)] * 2)] == [MIXED], shape
+    for shape, dt, B, b in (((64, 600, 30, 30), F32, 4, 2), ((4, 4, 147, 147), F32, 18, 2), ((2, 3, 56, 56), F32, 8, 2), ((1, 1, 300, 300), F32, 18, 2)):
+        assert MIXED not in [q.kind for q in _maps(host, [(shape, dt, B, b)] * 2)], shape
+    # over one another's memory: in their order, each by itself
+    x = 1 << 46
+    found = _maps(host, [((2, 3, 64, 64), F32, 8, 1, None, x), ((2, 20, 30, 30), F32, 4, 1, None, x + 64), ((2, 3, 56, 56), F32, 8, 1)])
+    assert [q.kind == MIXED for q in found] == [True, True, False]
