@@ -2,14 +2,13 @@
 
 // ------------------------------------------------------------------ one-block planes, a lane per plane
 
-struct LaneArgs {
-    CompTab tab;
-    Regions rg;
+struct LaneShape {
     uint32_t P, HW, WPP;
     uint32_t nrounds;    // ceil(P / 64): a round is 64 planes, one per lane
     uint32_t rpw;        // rounds a workgroup handles one after the other
     uint32_t vec_load;   // x is 16-byte aligned (a round starts on a 16-byte boundary)
 };
+struct LaneArgs : CompHead, LaneShape {};
 
 // Planes that are a single block (H <= B and W <= B, e.g. 7x7 with B = 8) with
 // an odd number of elements: one wavefront per round of 64 planes.  The round
@@ -18,8 +17,9 @@ struct LaneArgs {
 // stride of HW words (odd, so the 64 lanes hit 64 different banks), sums them in
 // binary64 in index order, takes min / max, and in a second pass quantises its
 // plane pair by pair into its WPP words.  No cross-lane step at all.
+// wg: which run of rpw rounds the workgroup takes.
 template <typename T, int BITS>
-__global__ void __launch_bounds__(64) compress_lane(LaneArgs a) {
+__device__ __forceinline__ void compress_lane_body(const LaneShape& a, const CompPtrs& pt, uint32_t wg) {
     constexpr int CPW = 32 / BITS;        // codes per word
     constexpr int PPW = CPW / 2;          // element pairs per word
     constexpr uint32_t EPV = 16 / sizeof(T);
@@ -28,11 +28,9 @@ __global__ void __launch_bounds__(64) compress_lane(LaneArgs a) {
     float* xs = reinterpret_cast<float*>(smem4);              // [64 * HW (+3)]
 
     const uint32_t lane = threadIdx.x;
-    const CompPtrs pt = comp_ptrs(a.tab, a.rg, lane);
     const uint32_t rscale = 1u << (16 - BITS);
     const float* mine = xs + lane * a.HW;
 
-    const uint32_t wg = xcd_run_index(blockIdx.x, gridDim.x);   // which run of rpw rounds this workgroup takes
     const uint32_t rend = min(a.nrounds, (wg + 1) * a.rpw);
     for (uint32_t round = wg * a.rpw; round < rend; ++round) {
         const uint32_t p0 = round * 64u;
@@ -123,4 +121,9 @@ __global__ void __launch_bounds__(64) compress_lane(LaneArgs a) {
         }
         wave_sync();      // LDS is reused by the next round
     }
+}
+
+template <typename T, int BITS>
+__global__ void __launch_bounds__(64) compress_lane(LaneArgs a) {
+    compress_lane_body<T, BITS>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, gridDim.x));
 }

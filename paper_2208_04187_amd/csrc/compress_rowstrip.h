@@ -1,35 +1,5 @@
 // Part of division.hip (included inside its unnamed namespace, after compress_strip.h): compress_rowstrip.
 
-// ------------------------------------------------------------------ compress, strips and items of several shapes in one launch
-
-// The planes of compress_strip (B = 4, 8) and those of compress_items under B = 4, which have few registers in common (64 at most): the shapes of a call
-// that are these go out together.  A launch of its own costs a shape 2-4 us of draining and filling: the compress side of a ResNet-18 / CIFAR step in four launches
-// 65 us (4.4 TB/s), in one 50 (5.7).
-struct PlanesShape { uint32_t kind; union { StripShape strip; ItemsShape items; }; };      // kind: 100 W + B of the strips, 4 or 2 (elements per row of an item) of the items
-struct PlanesArgs : SharedTab {
-    PlanesShape shape[kSharedShapes];
-    Regions rg[kSharedShapes];
-};
-template <typename T, int BITS>
-__global__ void __launch_bounds__(64) compress_planes(PlanesArgs a) {
-    const SharedPlace at = shared_place(a);
-    const Regions& rg = a.rg[at.shape];
-    if (at.wg == 0 && threadIdx.x < 48) zero_pads(rg, static_cast<char*>(a.pk[at.map]), threadIdx.x);
-    const CompPtrs pt = shared_ptrs(a, rg, at.map);
-    const PlanesShape& s = a.shape[at.shape];
-    const uint32_t wg = xcd_run_index(at.wg, at.n);
-    switch (s.kind) {
-        case 3208: compress_strip_body<T, BITS, 32, 8, false>(s.strip, pt, wg); break;
-        case 2808: compress_strip_body<T, BITS, 28, 8, false>(s.strip, pt, wg); break;
-        case 1608: compress_strip_body<T, BITS, 16, 8, false>(s.strip, pt, wg); break;
-        case 1408: compress_strip_body<T, BITS, 14, 8, false>(s.strip, pt, wg); break;
-        case 3204: compress_strip_body<T, BITS, 32, 4, false>(s.strip, pt, wg); break;
-        case 1604: compress_strip_body<T, BITS, 16, 4, false>(s.strip, pt, wg); break;
-        case 4: compress_items_body<T, BITS, 4, 4, 4, false>(s.items, pt, wg); break;
-        default: compress_items_body<T, BITS, 4, 2, 4, false>(s.items, pt, wg);
-    }
-}
-
 // ------------------------------------------------------------------ compress, a row of an odd-width plane per lane
 
 // Geometry for planes of an odd width W (13, 15, 17, 27, 35, 55: maps of AlexNet and Inception-v3).
@@ -116,7 +86,7 @@ __device__ __forceinline__ void rowstrip_codes(const float (&x)[W], float* xs, u
 }
 
 template <typename T, int BITS, int W, int B>
-__device__ __forceinline__ void compress_rowstrip_slots(const StripArgs& a) {
+__device__ __forceinline__ void compress_rowstrip_slots(const StripShape& a, const CompPtrs& pt, uint32_t round) {
     using Geo = RowStripGeom<W>;
     constexpr int S = Geo::S, G = Geo::G, LPL = Geo::LPL;
     constexpr int NSEG = (W + B - 1) / B;       // blocks per block row
@@ -126,8 +96,6 @@ __device__ __forceinline__ void compress_rowstrip_slots(const StripArgs& a) {
     float* xs = reinterpret_cast<float*>(smem4);                     // the round, later its code words
 
     const uint32_t lane = threadIdx.x;
-    const CompPtrs pt = comp_ptrs(a.tab, a.rg, lane);
-    const uint32_t round = xcd_run_index(blockIdx.x, a.nrounds);
     const uint32_t p0 = round * G;
     const uint32_t Gc = min((uint32_t)G, a.P - p0);
 
@@ -342,5 +310,5 @@ __global__ void __launch_bounds__(kRowPack<W> ? 64 * kRowPack<W> : 64) compress_
     if constexpr (kRowPack<W> != 0) {
         if (a.pack_off) { compress_rowstrip_packed<T, BITS, W, B>(a); return; }
     }
-    compress_rowstrip_slots<T, BITS, W, B>(a);
+    compress_rowstrip_slots<T, BITS, W, B>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, a.nrounds));
 }

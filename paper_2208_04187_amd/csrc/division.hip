@@ -146,6 +146,7 @@ constexpr int kLoadReuse = 0;
 #include "compress_rows.h"
 #include "compress_plane.h"
 #include "compress_any.h"
+#include "compress_planes.h"
 #include "compress_mixed.h"
 #include "decompress.h"
 #include "host.h"
@@ -408,7 +409,9 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
                 const bool can = plan_mixed(L, D, H, W, B, x, &sh);
                 const uint64_t lanes = (uint64_t)in.size() * L.P << sh.S_log2;
                 const int gains = can ? mixed_gains(L, D, H, W, B, m.b, es, x, in.size(), lanes) : 0;
-                if (gains == 2 || (gains && mix)) {
+                const bool small = gains == 2 || (gains && mix);
+                if (mix && gains < 2 && shared.add(sh, small ? lanes : 0, m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
+                if (small) {
                     if (!comp.fits(m, in.size(), lanes)) {
                         const int rc = comp.flush(st);
                         if (rc != DIVISION_OK) return rc;
@@ -420,7 +423,6 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
                     }
                     continue;
                 }
-                if (mix && shared.add(m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
             } else {
                 for (void* o : out) all |= (uintptr_t)o;
                 DecShape sh{};
@@ -443,7 +445,9 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
         if (rc != DIVISION_OK) return rc;
     }
     if (!compress) return mixer.flush(st);
-    const int rc = shared.flush(st);
+    int rc = shared.settle(comp, st);
+    if (rc != DIVISION_OK) return rc;
+    rc = shared.flush(st);
     return rc != DIVISION_OK ? rc : comp.flush(st);
 }
 

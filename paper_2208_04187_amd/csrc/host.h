@@ -1137,7 +1137,7 @@ struct CompLaunch {
         TileArgs a; WaveArgs wa; RegsArgs ra; ItemsArgs ia; LaneArgs la; RowsArgs wa2; PlaneArgs pa; OneArgs oa; AnyArgs g; UnitsArgs ua; StripArgs sa; SegArgs sg;
         const MixedArgs* mixed;                  // kind MIXED (nt threads)
         struct { const LinesArgs* a; uint32_t K; int lu; } lines;      // kind LINES: the instance its shapes share
-        const PlanesArgs* planes;                // kind PLANES
+        struct { const PlanesArgs* a; bool all; } planes;              // kind PLANES
     };
 };
 struct MixLaunch { uint32_t grid; hipStream_t st; MixArgs a; };      // decompress_mixed
@@ -1191,8 +1191,9 @@ hipError_t launch_lines(const LinesArgs& a, uint32_t K, int lu, dim3 gd, size_t 
 }
 
 template <typename T, int BITS>
-hipError_t launch_planes(const PlanesArgs& a, dim3 gd, size_t lds, hipStream_t st) {
-    hipLaunchKernelGGL((compress_planes<T, BITS>), gd, dim3(64), lds, st, a);
+hipError_t launch_planes(const PlanesArgs& a, bool all, dim3 gd, size_t lds, hipStream_t st) {
+    void (*kern)(PlanesArgs) = all ? compress_planes<T, BITS, true> : compress_planes<T, BITS, false>;
+    hipLaunchKernelGGL(kern, gd, dim3(64), lds, st, a);
     return hipGetLastError();
 }
 
@@ -1226,7 +1227,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case TILE: return launch_tile<T, 1>(c.B, c.vec, c.a, gd, lds, st);
             case MIXED: return launch_mixed<T, 1>(*c.mixed, gd, c.nt, lds, st);
             case LINES: return launch_lines<T, 1>(*c.lines.a, c.lines.K, c.lines.lu, gd, lds, st);
-            case PLANES: return launch_planes<T, 1>(*c.planes, gd, lds, st);
+            case PLANES: return launch_planes<T, 1>(*c.planes.a, c.planes.all, gd, lds, st);
             default: {
                 void (*kern)(AnyArgs) = flat ? compress_any<T, 1> : compress_any_3d<T, 1>;
                 hipLaunchKernelGGL(kern, gd, dim3(c.nt), 0, st, c.g);
@@ -1250,7 +1251,7 @@ hipError_t do_compress(const CompLaunch& c, int b) {
             case LINE: return launch_line<T, BITS>(c.oa, gd, lds, st);
             case MIXED: return launch_mixed<T, BITS>(*c.mixed, gd, c.nt, lds, st);
             case LINES: return launch_lines<T, BITS>(*c.lines.a, c.lines.K, c.lines.lu, gd, lds, st);
-            case PLANES: return launch_planes<T, BITS>(*c.planes, gd, lds, st);
+            case PLANES: return launch_planes<T, BITS>(*c.planes.a, c.planes.all, gd, lds, st);
             case ROWS: {
                 void (*kern)(RowsArgs) = flat ? compress_rows<T, BITS> : compress_rows_3d<T, BITS>;
                 const hipError_t e = allow_large_lds(kern, lds);
@@ -1681,36 +1682,46 @@ struct Mixer {
     }
 };
 
-// Shapes of one type and code width that one kernel serves share a launch: those of one instance of compress_line, and those of compress_strip and
-// compress_items that compress_planes holds.  Kept until all shapes of a call are known; a shape that finds no other has a launch of its own.
+// Workgroups per CU up to which the small planes of all kernels share a launch (compress_planes, ALL).  Multi-shape calls of 0.5-30 M elements that hold strips,
+// rows of odd width or lanes, 60 each, at limits of 0, 16, 32, 64 and 128: 897, 895, 887, 877, 877 us; 1119, 1100, 1074, 1057, 1058; 1152, 1116, 1106, 1098,
+// 1100.  Beyond, each kernel at its own registers.
+constexpr uint64_t kHeavyWorkgroups = 64;
+// Shapes of one type and code width that one kernel serves share a launch: those of one instance of compress_line, and those whose kernels
+// compress_planes holds.  Kept until all shapes of a call are known; a shape that finds no other has a launch of its own.
 struct SharedMixer {
     struct Shape {
         const division_map* m;
         size_t bytes;                             // the smallest of the packed buffers
         CompLaunch c;
         Regions rg;
-        int key;                                  // shapes of equal keys share a launch: the instance of compress_line, or 0
+        int key;                                  // shapes of equal keys share a launch: the instance of compress_line, LIGHT or HEAVY (compress_planes)
         std::vector<const void*> x;
         std::vector<void*> packed;
         std::vector<uint64_t> seeds;
+        MixedShape mixed;                         // mixed_lanes != 0: a small shape, which has its place in compress_mixed where none of these launches has one for it
+        uint64_t mixed_lanes;
     };
+    enum { LIGHT = 0, HEAVY = -1, OWN = -2, GONE = -3 };
     std::vector<Shape> shapes;
     // takes the shape if its kernel can be shared
-    bool add(const division_map& m, const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, const void* all, size_t bytes,
+    bool add(const MixedShape& mixed, uint64_t mixed_lanes, const division_map& m, const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, const void* all, size_t bytes,
              const std::vector<const void*>& x, const std::vector<void*>& packed, const std::vector<uint64_t>& seeds) {
         CompLaunch c;
         plan_compress(L, D, H, W, B, m.b, es, all, (int)std::min<size_t>(x.size(), kMaxBatch), &c);
         if (x.size() > (size_t)kSharedMaps || !launch_ok((uint64_t)c.gx * x.size(), 64)) return false;
-        int key = 0;
+        int key = LIGHT;
         if (c.kind == LINE && c.oa.NG == 1 && (c.oa.K == 4 || c.oa.K == 6)) key = 100 * (int)c.oa.K + line_lu(c.oa);
+        else if (c.kind == LANE || (c.kind == ITEMS && B == 8 && H > 1) || (c.kind == ROWSTRIP && !c.sa.pack_off)) key = HEAVY;
         else if (!(c.kind == STRIP && (B == 4 || B == 8)) && !(c.kind == ITEMS && B == 4 && H > 1)) return false;
-        shapes.push_back({&m, bytes, c, make_regions(L), key, x, packed, seeds});
+        shapes.push_back({&m, bytes, c, make_regions(L), key, x, packed, seeds, mixed, mixed_lanes});
         return true;
     }
     static void put(LinesArgs& a, uint32_t n, const Shape& q) { a.shape[n] = q.c.oa; a.rg[n] = q.rg; }
     static void put(PlanesArgs& a, uint32_t n, const Shape& q) {
-        a.shape[n].kind = (uint32_t)q.c.vec;
-        if (q.c.kind == STRIP) a.shape[n].strip = q.c.sa; else a.shape[n].items = q.c.ia;
+        a.shape[n].kind = q.c.kind == LANE ? 1u : q.c.kind == ITEMS ? 10u * (uint32_t)q.c.B + (uint32_t)q.c.vec : (uint32_t)q.c.vec;
+        if (q.c.kind == LANE) a.shape[n].lane = q.c.la;
+        else if (q.c.kind == ITEMS) a.shape[n].items = q.c.ia;
+        else a.shape[n].strip = q.c.sa;
         a.rg[n] = q.rg;
     }
     // the launch of shapes[i] and of those behind it that share it
@@ -1724,7 +1735,7 @@ struct SharedMixer {
         for (int k = 0; k < kSharedShapes; ++k) a.first[k] = 0xffffffffu;
         for (size_t j = i; j < shapes.size() && n < (uint32_t)kSharedShapes; ++j) {
             const Shape& q = shapes[j];
-            if (done[j] || q.m->dt != f.m->dt || q.m->b != f.m->b || q.key != f.key || maps + q.x.size() > (size_t)kSharedMaps ||
+            if (done[j] || (j > i && f.key == OWN) || q.m->dt != f.m->dt || q.m->b != f.m->b || q.key != f.key || maps + q.x.size() > (size_t)kSharedMaps ||
                 !launch_ok(grid + (uint64_t)q.c.gx * q.x.size(), 64))
                 continue;
             done[j] = 1;
@@ -1740,14 +1751,55 @@ struct SharedMixer {
         if (n == 1) return compress_impl((int)f.x.size(), f.x.data(), f.packed.data(), f.seeds.data(), m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, f.bytes, st);
         c.st = st; c.gx = grid; c.gy = 1;
         if constexpr (std::is_same<Args, LinesArgs>::value) { c.kind = LINES; c.lines.a = &a; c.lines.K = f.c.oa.K; c.lines.lu = line_lu(f.c.oa); }
-        else { c.kind = PLANES; c.planes = &a; }
+        else { c.kind = PLANES; c.planes.a = &a; c.planes.all = f.key == HEAVY; }
         return bridge_compress(m.dt, c, m.b) == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+    }
+    static bool planes(const Shape& p, const Shape& q) { return p.key <= LIGHT && q.key <= LIGHT && p.key > OWN && q.key > OWN && p.m->dt == q.m->dt && p.m->b == q.m->b; }
+    // The small shapes join a launch of their kernels that the call has in any case (the drawn calls above 877 -> 843, 1057 -> 1042 and 1098 -> 1069 us), or go where the small ones of
+    // all kernels are.
+    int settle(CompMixer& comp, hipStream_t st) {
+        for (size_t i = 0; i < shapes.size(); ++i) {
+            Shape& s = shapes[i];
+            if (s.mixed_lanes == 0) continue;
+            bool joins = false;
+            uint64_t workgroups = 0;
+            bool heavy = s.key == HEAVY;
+            for (const Shape& q : shapes) {
+                if (s.key <= LIGHT ? !planes(s, q) : !(q.key == s.key && q.m->dt == s.m->dt && q.m->b == s.m->b)) continue;
+                workgroups += (uint64_t)q.c.gx * q.x.size();
+                joins = joins || q.mixed_lanes == 0;
+                heavy = heavy || (q.key == HEAVY && q.mixed_lanes == 0);
+            }
+            if (joins && (!heavy || workgroups <= kHeavyWorkgroups * (uint64_t)num_cus())) continue;
+            if (!comp.fits(*s.m, s.x.size(), s.mixed_lanes)) {
+                const int rc = comp.flush(st);
+                if (rc != DIVISION_OK) return rc;
+            }
+            comp.add(*s.m, s.mixed, 1, s.mixed_lanes, s.x.size(), s.bytes, s.x.data(), s.packed.data(), s.seeds.data());
+            s.key = GONE;
+        }
+        return DIVISION_OK;
     }
     int flush(hipStream_t st) {
         std::vector<char> done(shapes.size(), 0);
         for (size_t i = 0; i < shapes.size(); ++i) {
+            done[i] = done[i] || shapes[i].key == GONE;
+            // all small planes of a type together, or those of few registers together and the others alone
+            if (shapes[i].key != HEAVY) continue;
+            uint64_t workgroups = 0;
+            for (const Shape& q : shapes)
+                if (planes(q, shapes[i])) workgroups += (uint64_t)q.c.gx * q.x.size();
+            const bool together = workgroups <= kHeavyWorkgroups * (uint64_t)num_cus();
+            for (size_t j = shapes.size(); j-- > 0;)
+                if (j != i && planes(shapes[j], shapes[i])) {
+                    if (together) shapes[j].key = HEAVY;
+                    else if (shapes[j].key == HEAVY) shapes[j].key = OWN;
+                }
+            if (!together) shapes[i].key = OWN;
+        }
+        for (size_t i = 0; i < shapes.size(); ++i) {
             if (done[i]) continue;
-            const int rc = shapes[i].key ? launch<LinesArgs>(i, done, st) : launch<PlanesArgs>(i, done, st);
+            const int rc = shapes[i].key > 0 ? launch<LinesArgs>(i, done, st) : launch<PlanesArgs>(i, done, st);
             if (rc != DIVISION_OK) return rc;
         }
         return DIVISION_OK;

@@ -401,8 +401,8 @@ def test_decompress_units_of_few_planes(shape, B, b):
     _round_trip(shape, B, b, "bf16")
 
 
-# shapes that one kernel serves, too large for the launch of small maps: rows of one instance of compress_line, and the planes of compress_strip and of
-# compress_items under B = 4; a shape that finds no other beside them, several maps of a shape, more maps than a launch holds
+# shapes that one kernel serves, too large for the launch of small maps: rows of one instance of compress_line, and the small planes that compress_planes
+# holds; a shape that finds no other beside them, several maps of a shape, more maps than a launch holds
 @pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 1), ("f32", 8), ("bf16", 4), ("bf16", 1), ("c16", 2)])
 @pytest.mark.parametrize("specs", [
     [((1, 2101, 1, 384), 8), ((7, 301, 1, 768), 8), ((1, 2101, 1, 384), 8), ((2, 1100, 1, 776), 8), ((1, 1057, 1, 1000), 8)],
@@ -410,6 +410,10 @@ def test_decompress_units_of_few_planes(shape, B, b):
     [((1, 2057, 32, 32), 4), ((3, 2741, 16, 16), 4), ((1, 8209, 8, 8), 4), ((1, 8209, 4, 4), 4), ((3, 2741, 16, 16), 4), ((1, 8203, 6, 14), 4), ((2, 4101, 20, 24), 4)],
     [((1, 2059, 28, 28), 8), ((1, 8211, 14, 14), 8), ((3, 701, 21, 32), 8), ((1, 8205, 10, 16), 8), ((1, 8211, 4, 4), 64)],
     [((1, 8209, 8, 8), 4)] * 13 + [((1, 8205, 4, 4), 4)] * 12,
+    # few enough workgroups that rows of odd width, items under B = 8 and lanes share it too
+    [((1, 8209, 13, 13), 8), ((3, 1801, 17, 17), 8), ((3, 1701, 20, 27), 8), ((1, 1031, 35, 35), 8), ((1, 771, 50, 55), 8), ((1, 8209, 9, 15), 8)],
+    [((1, 8209, 13, 13), 4), ((3, 1801, 17, 17), 4), ((3, 1701, 20, 27), 4), ((1, 1031, 35, 35), 4), ((1, 771, 55, 55), 4), ((1, 8209, 9, 15), 4)],
+    [((3, 2741, 10, 12), 8), ((3, 2741, 18, 22), 8), ((3, 5741, 7, 7), 8), ((1, 9209, 5, 7), 8), ((3, 3741, 11, 5), 16), ((1, 8211, 14, 14), 8), ((3, 2741, 8, 8), 4)],
 ])
 def test_compress_of_shapes_that_share_a_kernel(specs, mode, b):
     dtype, c16, dt = FORMATS[mode]

@@ -263,6 +263,14 @@ def test_shapes_of_one_kernel_share_a_launch(host):
     # types, code widths and the kernels of other shapes do not share it
     kinds = [q.kind for q in _maps(host, [planes[0], planes[1], ((128, 64, 32, 32), BF16, 4, 2), ((128, 64, 32, 32), F32, 4, 4), ((64, 256, 56, 56), F32, 8, 2)])]
     assert sorted(k == PLANES for k in kinds) == [False, False, False, True]
+    # rows of odd width, items under B = 8 and lanes share it up to 64 workgroups per CU; beyond, those have launches of their own
+    few = [((8, 64, 28, 28), F32, 8, 2), ((8, 256, 55, 55), F32, 8, 2), ((8, 512, 13, 13), F32, 8, 2), ((8, 960, 7, 7), F32, 8, 2), ((8, 512, 24, 24), F32, 8, 2)]
+    (launch,) = _maps(host, few)
+    assert launch.kind == PLANES and launch.gx == sum(q.gx * q.gy for q in (_maps(host, [m])[0] for m in few))
+    kinds = [q.kind for q in _maps(host, [((64, 256, 55, 55), F32, 8, 2), planes[0], planes[1]])]
+    assert len(kinds) == 2 and kinds.count(PLANES) == 1
+    kinds = [q.kind for q in _maps(host, [((256, 256, 55, 55), F32, 8, 2), ((256, 512, 13, 13), F32, 8, 2), planes[0]])]
+    assert len(kinds) == 3 and PLANES not in kinds
     # 25 maps are two launches, and maps over one another's memory a launch for each shape
     assert [q.kind for q in _maps(host, [planes[2]] * 13 + [planes[3]] * 12)].count(PLANES) == 0
     assert [q.kind for q in _maps(host, [planes[2]] * 12 + [planes[3]] * 12 + [planes[1]])].count(PLANES) == 1
