@@ -39,10 +39,14 @@ struct StripGeom {
 // LDS, a lane per block adds the shares of the block's rows in row order, and the lanes read the
 // H^L values back.  The plane's extremes are DPP reductions either way: no per-element lookup.
 //
-// Memory side: the round (all its planes are contiguous) is read with coalesced 16-byte loads that
-// are issued before anything else and land in LDS in the map's own order; each lane then takes its
-// strip out of LDS (a stride of 28 or 32 words).  The codes of a unit go back to LDS as one byte /
-// half-word / word and leave as whole coalesced words.
+// Memory side: the round (all its planes are contiguous) is read with coalesced loads of four elements that
+// are issued before anything else and land in LDS in the map's own order and type; each lane then takes its
+// strip out of LDS.  Strips of 32 elements lie on the same banks: their pieces are turned (see there), and
+// their codes, whole words, go straight to memory.  Of strips of 28 the codes of a unit go back to LDS as one
+// byte / half-word / word and leave as whole coalesced words.  Before, with pieces in order (an eightfold
+// bank conflict), all codes through LDS and 2-byte elements widened on their way into LDS, whose size bounds
+// the wavefronts per CU: 256 x 64 x 32 x 32 under B = 8, 8-bit codes 19.5 us, now 17.8 (2-bit codes 17.0 and
+// 16.6: HBM); bfloat16 15.6 and 12.3; 64 x 512 x 28 x 28 in bfloat16 20.4 and 19.3.
 // One round per workgroup of one wavefront.
 //
 // RELU: x is the input of a Relu operator (Appendix, Relu listing) whose output y is the map to
@@ -57,7 +61,9 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
     constexpr int CB = BITS / 2;                // code bytes per 4-element unit
     constexpr float Lf = float((1 << BITS) - 1);
     extern __shared__ float4 smem4[];
-    float* xs = reinterpret_cast<float*>(smem4);                     // [UPL * 64 units] the round, later its code words
+    constexpr bool kWords = E == 32;            // a strip's codes are whole words
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    T* xs = reinterpret_cast<T*>(smem4);                             // [UPL * 64 units] the round; strips of 28: later its code words
     double* part = reinterpret_cast<double*>(xs + UPL * 64 * 4);      // [64 * NSEG] a strip's share of each block of its block row
     float* lfcs = reinterpret_cast<float*>(part + 64 * NSEG);        // [G * nb <= 64] H^L of the round
     (void)part; (void)lfcs; (void)RPL;
@@ -67,7 +73,7 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
     const uint32_t Gc = min((uint32_t)G, a.P - p0);
 
     // ---- the round's loads first: coalesced, bounds-checked (units past the round read as zero)
-    u32x4 q[UPL];
+    u32x4 q[UPL];                               // 2-byte elements: the first two words
     {
         const T* src = static_cast<const T*>(pt.x) + (size_t)p0 * a.HW;
         const __amdgpu_buffer_rsrc_t rsrc =
@@ -77,9 +83,8 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
             if constexpr (sizeof(T) == 4) {
                 q[k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16u, k * 1024, kLoadAux);
             } else {
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                 const u32x2 h = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane * 8u, k * 512, kLoadAux);
-                q[k] = u32x4{h.x << 16, h.x & 0xffff0000u, h.y << 16, h.y & 0xffff0000u};
+                q[k].x = h.x; q[k].y = h.y;
             }
         }
     }
@@ -95,22 +100,24 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
 #pragma unroll
         for (int k = 0; k < UPL; ++k) {
             uint32_t nib = 0;
-            uint32_t v[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
+            uint32_t v[4];
+            if constexpr (sizeof(T) == 4) { v[0] = q[k].x; v[1] = q[k].y; v[2] = q[k].z; v[3] = q[k].w; }
+            else { v[0] = q[k].x << 16; v[1] = q[k].x & 0xffff0000u; v[2] = q[k].y << 16; v[3] = q[k].y & 0xffff0000u; }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const bool pos = __uint_as_float(v[e]) > 0.0f;
                 nib |= (pos ? 1u : 0u) << e;
                 v[e] = pos ? v[e] : 0u;
             }
-            q[k] = u32x4{v[0], v[1], v[2], v[3]};
             // stores past the round are dropped by the buffer bound
             if constexpr (sizeof(T) == 4) {
+                q[k] = u32x4{v[0], v[1], v[2], v[3]};
                 store_b128_checked(q[k], yrs, lane * 16u + (uint32_t)(k * 1024), 0);
             } else {
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                 u32x2 o;
                 o.x = (v[0] >> 16) | (v[1] & 0xffff0000u);
                 o.y = (v[2] >> 16) | (v[3] & 0xffff0000u);
+                q[k].x = o.x; q[k].y = o.y;
                 __builtin_amdgcn_raw_buffer_store_b64(o, yrs, lane * 8u, k * 512, 0);
             }
             uint32_t w = nib << (4u * (lane & 7u));
@@ -131,19 +138,43 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
     const uint32_t k2 = mix32(k1 + pt.seed_c);
     const uint32_t rscale = 1u << (16 - BITS);
     const uint32_t xv = G * a.HW / 4u;                                // units of a whole round
+    // Strips of 32 elements lie 32 or 16 words apart, a whole or half multiple of the 64 banks: the 16-byte pieces of strip t are put down in the order
+    // piece ^ (t / 2) (4-byte elements, eight pieces) or piece ^ (t / 4) (four), so that sixteen lanes find theirs in sixteen different places.
+    // (28 or 14 words apart they do as they are.)
+    constexpr uint32_t kSpread = sizeof(T) == 4 ? 1 : 2;               // strips that side by side fill the banks, log2
+    const uint32_t turn = !kWords ? 0u : sizeof(T) == 4 ? lane >> 4 : (lane >> 5) << 1;      // of unit lane + 64 k: with bit 2 flipped for odd k
 #pragma unroll
-    for (int k = 0; k < UPL; ++k)
-        if (lane + 64u * k < xv) reinterpret_cast<u32x4*>(xs)[lane + 64 * k] = q[k];
+    for (int k = 0; k < UPL; ++k) {
+        const uint32_t at = (lane ^ turn ^ (kWords ? 4u * (k & 1) : 0u)) + 64u * k;
+        if (lane + 64u * k < xv) {
+            if constexpr (sizeof(T) == 4) reinterpret_cast<u32x4*>(xs)[at] = q[k];
+            else reinterpret_cast<u32x2*>(xs)[at] = u32x2{q[k].x, q[k].y};
+        }
+    }
     wave_sync();
 
     // ---- the strip; lanes without one take strip 0 of the round and have their effects masked
+    const uint32_t first = valid ? g * (a.HW / 4u) + sl * UPL : 0u;    // its first unit in the round
     float x[E];
     {
-        const float4* sp = reinterpret_cast<const float4*>(xs + (valid ? g * a.HW + sl * E : 0u));
+        constexpr int PPS = kWords ? E * (int)sizeof(T) / 16 : UPL;    // pieces of a strip: of 16 bytes, or one unit
+        const uint32_t flip = kWords ? (first >> (3 + kSpread)) & (PPS - 1) : 0u;
+        const uint32_t piece = kWords && sizeof(T) == 2 ? first / 2u : first;
 #pragma unroll
-        for (int u = 0; u < UPL; ++u) {
-            const float4 v = sp[u];
-            x[4 * u] = v.x; x[4 * u + 1] = v.y; x[4 * u + 2] = v.z; x[4 * u + 3] = v.w;
+        for (int u = 0; u < PPS; ++u) {
+            if constexpr (sizeof(T) == 4) {
+                const float4 v = reinterpret_cast<const float4*>(xs)[piece + (u ^ flip)];
+                x[4 * u] = v.x; x[4 * u + 1] = v.y; x[4 * u + 2] = v.z; x[4 * u + 3] = v.w;
+            } else {
+                constexpr int N = kWords ? 4 : 2;                       // words of a piece
+                typedef uint32_t piece_t __attribute__((ext_vector_type(N)));
+                const piece_t h = reinterpret_cast<const piece_t*>(xs)[piece + (u ^ flip)];
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    x[2 * (N * u + i)] = __uint_as_float(h[i] << 16);
+                    x[2 * (N * u + i) + 1] = __uint_as_float(h[i] & 0xffff0000u);
+                }
+            }
         }
     }
 
@@ -175,8 +206,8 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
         // a lane per block of the round adds the shares of the block's strips in row order
         const uint32_t nbr = Gc * a.nb;                                   // at most 64 (the host checks G * nb)
         if (lane < nbr) {
-            const uint32_t bg = lane / a.nb, t = lane - bg * a.nb;       // plane of the round, block of the plane
-            const uint32_t tbi = t / NSEG, s = t - tbi * NSEG;
+            const uint32_t bg = lane / a.nb, blk = lane - bg * a.nb;     // plane of the round, block of the plane
+            const uint32_t tbi = blk / NSEG, s = blk - tbi * NSEG;
             const uint32_t brows = min((uint32_t)B, a.H - tbi * (uint32_t)B);    // >= 1: the block exists
             const uint32_t nstrips = (brows + RPL - 1) / RPL;
             const double* ps = part + (bg * S + tbi * LBR) * NSEG + s;
@@ -185,7 +216,7 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
             const uint32_t cols = min((uint32_t)B, (uint32_t)W - s * (uint32_t)B);
             const float m = lfc_round<T>(mean_of(Sb, brows * cols), kC16<T>);
             lfcs[lane] = m;
-            lfc_store<T>(pt.lfc, (size_t)(p0 + bg) * a.nb + t, m, kC16<T>);
+            lfc_store<T>(pt.lfc, (size_t)(p0 + bg) * a.nb + blk, m, kC16<T>);
         }
         wave_sync();
 #pragma unroll
@@ -210,7 +241,29 @@ __device__ __forceinline__ void compress_strip_body(const StripShape& a, const C
     const float invs = inv * (float)(1u << (32 - BITS));
     if (live && sl == 0) meta_store(pt.meta, p, delta, Delta, kC16<T>);
 
-    // ---- Quant + packing: a unit's four codes are one byte (b = 2), half-word or word of the plane's
+    // ---- Quant + packing
+    if constexpr (kWords) {
+        // a strip's codes are BITS whole words, and those of the round lie one after the other: straight to memory
+        constexpr int CPW = 32 / BITS;
+        const uint32_t xw0 = k1 + (sl * (uint32_t)(E / 2)) * kWeyl;
+        uint32_t c[BITS];
+#pragma unroll
+        for (int i = 0; i < BITS; ++i) {
+            c[i] = 0u;
+#pragma unroll
+            for (int e = (i + 1) * CPW - 2; e >= i * CPW; e -= 2) c[i] = push_pair<BITS>(c[i], x[e], x[e + 1], delta, invs, xw0 + (uint32_t)(e / 2) * kWeyl, k2, rscale);
+        }
+        if (valid) {
+            uint32_t* dst = pt.codes + (size_t)p0 * a.WPP + first / 8u * (uint32_t)BITS;
+            if constexpr (BITS == 1) dst[0] = c[0];
+            else if constexpr (BITS == 2) *reinterpret_cast<u32x2*>(dst) = u32x2{c[0], c[1]};
+            else
+#pragma unroll
+                for (int i = 0; i < BITS; i += 4) *reinterpret_cast<u32x4*>(dst + i) = u32x4{c[i], c[i + 1], c[i + 2], c[i + 3]};
+        }
+        return;
+    }
+    // strips of 28: a unit's four codes are one byte (b = 2), half-word or word of the plane's
     // code bytes; they are collected in LDS (over the round, which every lane has taken out by now)
     wave_sync();
     uint32_t* cw = reinterpret_cast<uint32_t*>(xs);

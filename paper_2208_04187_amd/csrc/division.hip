@@ -45,6 +45,8 @@
 //   compress_any     everything else (giant planes with odd extents, 1-bit codes of the shapes of compress_rows)
 //   compress_mixed   small maps of several shapes in one launch (division_compress_maps; spread_mixed of host.h): any width, units of four
 //                    consecutive elements in registers, lanes per plane by what the launch as a whole leaves idle
+//   compress_lines, compress_planes   the maps of several shapes that one instance of compress_line serves, or that the one-wavefront kernels of small planes
+//                    serve (strip, rowstrip, items, lane), in one launch (division_compress_maps; SharedMixer of host.h)
 //   decompress_mixed the wavefront-per-chunk kernels below over the maps of several shapes in one launch (division_decompress_maps)
 //   decompress_stream / decompress_stream_any / decompress_stream_one: one wavefront per 4 KB chunk of aligned vectors, no LDS:
 //                    rows of whole vectors inside one block (_stream), or any width where a vector may span two rows

@@ -453,7 +453,7 @@ bool plan_strip(const Layout& L, int64_t H, int64_t W, int B, size_t es, const v
     a->nrounds = (uint32_t)((L.P + G - 1) / G);
     *grid = a->nrounds;
     // the round; for the block sizes whose block rows are no DPP group also the strips' shares and the round's H^L
-    *lds = dpp ? 4ull * G * L.HW + 16 : upl * 1024 + 64 * nseg * 8 + 256 + 16;
+    *lds = dpp ? es * G * L.HW + 16 : upl * 256 * es + 64 * nseg * 8 + 256 + 16;
     *width = (int)(100 * W + B);
     return true;
 }
