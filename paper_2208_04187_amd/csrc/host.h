@@ -683,6 +683,10 @@ bool plan_one(const Layout& L, size_t es, const void* x, OneArgs* a, uint32_t* g
     // lanes per plane: a power of two from 4 up (a plane's lanes then read 64 contiguous bytes per round)
     uint32_t best_S = 0, best_log = 0, K = 0;
     if (!pick_lanes_and_rounds(qv, 2, &best_S, &best_log, &K)) return false;
+    // Planes of 49 to 52 vectors (14 x 14): four lanes of thirteen rounds leave the fewest slots empty, but each round reads half a line.  Sixteen lanes of
+    // four from a plane per CU on: 256 to 16384 planes of 14 x 14 4.1 -> 3.3 to 7.2 -> 6.0 us, 128 x 512 of them 19.0 -> 14.4; bfloat16 20 x 20 5.4 -> 3.6, 16384 of them
+    // 8.3 -> 8.1 (of 26 x 16, 52 vectors, 7.9 -> 8.1).
+    if (best_S == 4 && K == 13 && L.P >= (uint64_t)num_cus()) { best_S = 16; best_log = 4; K = 4; }
     *a = OneArgs{};
     a->P = (uint32_t)L.P; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP;
     a->qv = (uint32_t)qv;

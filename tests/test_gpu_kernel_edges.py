@@ -436,3 +436,13 @@ def test_compress_of_shapes_that_share_a_kernel(specs, mode, b):
 def test_strips_of_all_heights(shape, B, b, mode):
     assert _names(shape, B, b, mode)[0].startswith("compress_strip<")
     _round_trip(shape, B, b, mode)
+
+
+# single-block planes of 49 to 52 vectors: sixteen lanes of four rounds from a plane per CU on
+@pytest.mark.parametrize("b", [1, 2, 8])
+@pytest.mark.parametrize("shape,B,mode", [((4, 64, 14, 14), 64, "f32"), ((1, 257, 10, 20), 20, "f32"), ((3, 101, 16, 13), 16, "c16"), ((2, 133, 20, 20), 64, "bf16"), ((1, 301, 26, 16), 26, "bf16")])
+def test_single_block_planes_of_about_fifty_vectors(shape, B, b, mode):
+    name = _names(shape, B, b, mode)[0]
+    assert name.startswith("compress_one<") and name.endswith(", 4>")
+    assert _names((1, 8) + shape[2:], B, b, mode)[0].endswith(", 13>")
+    _round_trip(shape, B, b, mode)
