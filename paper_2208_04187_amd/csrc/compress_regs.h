@@ -244,7 +244,7 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
             } else if constexpr (B == 0) {
             } else if constexpr (ROW) {
                 const uint32_t units = min((uint32_t)UPB, a.w4 - bj * UPB);
-                S = usum[bj * UPB];
+                S += usum[bj * UPB];              // (to +0, like every sum here: a block of -0 has mean +0)
 #pragma unroll
                 for (int u = 1; u < UPB; ++u) S += (uint32_t)u < units ? usum[bj * UPB + u] : 0.0;
                 cnt = units * 4;

@@ -98,6 +98,7 @@ def test_rows_of_power_of_two_blocks(shape, B, lu4, lu2, b, mode):
     ((2, 3, 1, 200), 8), ((2, 3, 1, 72), 8), ((2, 3, 1, 24), 4), ((1, 2, 1, 1032), 16),      # the last round partly past the plane
     ((1, 3, 1, 96), 64), ((1, 2, 1, 160), 128),                             # block sums through LDS
     ((1, 2, 29, 29), 8), ((1, 2, 17, 17), 8), ((1, 2, 56, 56), 8),
+    ((2, 3, 1, 3136), 8), ((2, 3, 1, 3136), 4), ((1, 3, 1, 2052), 8),       # one row in the register kernel: a block's units are added from +0 too
 ])
 def test_tiny_negative_sum_has_mean_minus_zero(shape, B, mode):
     """A sum of one smallest negative number: its mean underflows to -0, which is kept; only a block of -0 has mean +0."""

@@ -1151,6 +1151,7 @@ SPECIAL_VALUE_SHAPES = [
     ((3, 4, 13, 13), 8), ((3, 4, 30, 30), 4), ((1, 12, 300, 300), 18), ((3, 4, 56, 56), 12), ((3, 4, 170, 170), 8),
     ((3, 4, 250, 250), 8), ((3, 4, 60, 60), 8), ((3, 4, 224, 224), 8), ((2, 6, 9, 6), 4), ((3, 4, 1, 3072), 4096),
     ((3, 4, 27, 27), 8), ((3, 4, 17, 17), 8), ((3, 4, 15, 15), 4),
+    ((3, 4, 1, 3136), 8), ((2, 6, 1, 2052), 4),
 ]
 
 
