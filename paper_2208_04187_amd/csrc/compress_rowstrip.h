@@ -12,12 +12,21 @@ struct RowStripGeom {
     static constexpr int NP = (W + 1) / 2;                       // element pairs a row touches
 };
 
+// What a round of `planes` planes from plane p0 on reads of a map that starts on a 4-byte boundary: whole aligned dwords, from the one that holds its first
+// element to the one that holds its last, so nothing beyond the map's own last dword (the bounds check of a buffer load is per dword).  Rounds of an odd number
+// of elements of two bytes start in the middle of a dword every other time: `before` is the element in front of the round then, which is read with it.
+struct RoundSpan { uint32_t before, bytes; };
+__host__ __device__ __forceinline__ RoundSpan round_span(uint32_t p0, uint32_t planes, uint32_t HW, uint32_t es) {
+    const uint32_t before = es == 2 ? (p0 * HW) & 1u : 0u;
+    return RoundSpan{before, ((planes * HW + before) * es + 3u) & ~3u};
+}
+
 // The strip kernel for planes whose rows are not whole 16-byte vectors: a lane owns one ROW of W
 // elements (W odd, compile-time) and keeps it in registers from the pooling to the codes; the lanes
 // of a plane sit side by side (16, 32 or 64 slots), B = 4 or 8 rows of a block row are an aligned DPP
 // group, so block sums and the plane's extremes are DPP reductions as in compress_strip.  The round
 // (its planes are contiguous) is read with coalesced 16-byte loads into LDS in the map's own order
-// (a round starts on a 4-byte boundary at least, which is all a buffer load needs); a lane takes
+// (from the 4-byte boundary at or before its first element, see round_span); a lane takes
 // its row out with scalar LDS reads (stride W words, odd: no bank conflicts inside a plane).
 //
 // Codes: the random word of Eq. (quantization)'s stochastic rounding belongs to a PAIR of elements
@@ -100,14 +109,12 @@ __device__ __forceinline__ void compress_rowstrip_slots(const StripShape& a, con
     const uint32_t Gc = min((uint32_t)G, a.P - p0);
 
     // ---- the round's loads first: coalesced, bounds-checked (units past the round read as zero)
+    static_assert(LPL * 256 > G * S * W, "with the element in front of the round");
+    const RoundSpan span = round_span(p0, Gc, a.HW, sizeof(T));
     u32x4 q[LPL];
     {
-        const T* src = static_cast<const T*>(pt.x) + (size_t)p0 * a.HW;
-        // the range ends with the dword that holds the round's last element (2-byte elements, an odd number of
-        // them: the bounds check is per dword, and the dword's other half is the next plane's first element or
-        // the two bytes behind the map, inside the same aligned dword)
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, (int)((Gc * a.HW * sizeof(T) + 3u) & ~3u), 0x00020000);
+        const T* src = static_cast<const T*>(pt.x) + ((size_t)p0 * a.HW - span.before);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, (int)span.bytes, 0x00020000);
 #pragma unroll
         for (int k = 0; k < LPL; ++k) {
             if constexpr (sizeof(T) == 4) {
@@ -128,7 +135,7 @@ __device__ __forceinline__ void compress_rowstrip_slots(const StripShape& a, con
     const uint32_t p = p0 + g;
     const uint32_t k1 = mix32(p ^ pt.seed_a);
     const uint32_t k2 = mix32(k1 + pt.seed_c);
-    const uint32_t xv = (G * a.HW + 3u) / 4u;                          // units of a whole round (the host sized LDS for them)
+    const uint32_t xv = (G * a.HW + span.before + 3u) / 4u;            // units of a whole round (the host sized LDS for them)
 #pragma unroll
     for (int k = 0; k < LPL; ++k)
         if (lane + 64u * k < xv) reinterpret_cast<u32x4*>(xs)[lane + 64 * k] = q[k];
@@ -137,7 +144,7 @@ __device__ __forceinline__ void compress_rowstrip_slots(const StripShape& a, con
     // ---- the row; lanes without one take row 0 of the round and have their effects masked
     float x[W];
     {
-        const float* sp = xs + (valid ? g * a.HW + sl * (uint32_t)W : 0u);
+        const float* sp = xs + span.before + (valid ? g * a.HW + sl * (uint32_t)W : 0u);
 #pragma unroll
         for (int e = 0; e < W; ++e) x[e] = sp[e];
     }
@@ -210,12 +217,13 @@ __device__ __forceinline__ void compress_rowstrip_packed(const StripArgs& a) {
     const uint32_t p0 = xcd_run_index(blockIdx.x, a.nrounds) * G;
     const uint32_t Gc = min((uint32_t)G, a.P - p0);
 
-    // ---- the round's loads first: coalesced, bounds-checked (units past the round read as zero; see above for its end)
+    // ---- the round's loads first: coalesced, bounds-checked (units past the round read as zero)
+    static_assert(LPL * 4 * NT > G * W * W, "with the element in front of the round");
+    const RoundSpan span = round_span(p0, Gc, a.HW, sizeof(T));
     u32x4 q[LPL];
     {
-        const T* src = static_cast<const T*>(pt.x) + (size_t)p0 * a.HW;
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, (int)((Gc * a.HW * sizeof(T) + 3u) & ~3u), 0x00020000);
+        const T* src = static_cast<const T*>(pt.x) + ((size_t)p0 * a.HW - span.before);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, (int)span.bytes, 0x00020000);
 #pragma unroll
         for (int k = 0; k < LPL; ++k) {
             if constexpr (sizeof(T) == 4) {
@@ -233,7 +241,7 @@ __device__ __forceinline__ void compress_rowstrip_packed(const StripArgs& a) {
     const uint32_t k1 = mix32(p ^ pt.seed_a);
     const uint32_t k2 = mix32(k1 + pt.seed_c);
     if (lane < 2 * G) ext[lane] = lane < G ? 0x7fffffff : (int)0x80000000;
-    const uint32_t xv = (G * a.HW + 3u) / 4u;                         // units of a whole round (the host sized LDS for them)
+    const uint32_t xv = (G * a.HW + span.before + 3u) / 4u;           // units of a whole round (the host sized LDS for them)
 #pragma unroll
     for (int k = 0; k < LPL; ++k)
         if (lane + (uint32_t)(NT * k) < xv) reinterpret_cast<u32x4*>(xs)[lane + NT * k] = q[k];
@@ -242,7 +250,7 @@ __device__ __forceinline__ void compress_rowstrip_packed(const StripArgs& a) {
     // ---- the row; lanes without one take row 0 of the round and have their effects masked
     float x[W];
     {
-        const float* sp = xs + (valid ? lane * (uint32_t)W : 0u);
+        const float* sp = xs + span.before + (valid ? lane * (uint32_t)W : 0u);
 #pragma unroll
         for (int e = 0; e < W; ++e) x[e] = sp[e];
     }

@@ -501,7 +501,7 @@ bool plan_rowstrip(const Layout& L, int64_t H, int64_t W, int B, size_t es, cons
     a->P = (uint32_t)L.P; a->H = (uint32_t)H; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP; a->nb = (uint32_t)L.nb;
     a->nrounds = (uint32_t)((L.P + G - 1) / G);
     *grid = a->nrounds;
-    *lds = 16ull * ((G * L.HW + 3) / 4) + 16;          // the round in whole 16-byte units
+    *lds = 16ull * ((G * L.HW + 3) / 4) + 16;          // the round in whole 16-byte units, and the element in front of it
     const int pack = W == 17 ? kRowPack<17> : W == 35 ? kRowPack<35> : 0;
     if (pack && H <= W && L.P >= 2048 * G) {
         // the rows of three planes side by side (planes of more rows keep their slots, and so do maps of less than eight wavefronts per CU, which wait for

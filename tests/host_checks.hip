@@ -55,4 +55,10 @@ int check_take_launches(check_launch* out, int cap) {
     return n;
 }
 int check_cus(void) { return num_cus(); }
+// what compress_rowstrip reads of a round: elements of the map in front of it, bytes from there on
+uint32_t check_round_span(uint32_t p0, uint32_t planes, uint32_t HW, uint32_t es, uint32_t* bytes) {
+    const RoundSpan span = round_span(p0, planes, HW, es);
+    *bytes = span.bytes;
+    return span.before;
+}
 }

@@ -1152,6 +1152,7 @@ SPECIAL_VALUE_SHAPES = [
     ((3, 4, 250, 250), 8), ((3, 4, 60, 60), 8), ((3, 4, 224, 224), 8), ((2, 6, 9, 6), 4), ((3, 4, 1, 3072), 4096),
     ((3, 4, 27, 27), 8), ((3, 4, 17, 17), 8), ((3, 4, 15, 15), 4),
     ((3, 4, 1, 3136), 8), ((2, 6, 1, 2052), 4),
+    ((1, 4099, 17, 17), 4), ((1, 2050, 35, 35), 8),       # the rows of three planes side by side
 ]
 
 

@@ -288,3 +288,20 @@ def test_chunk_kernels_of_few_planes_leave_their_launch(host):
     x = 1 << 46
     found = _maps(host, [((2, 3, 64, 64), F32, 8, 1, None, x), ((2, 20, 30, 30), F32, 4, 1, None, x + 64), ((2, 3, 56, 56), F32, 8, 1)])
     assert [q.kind == MIXED for q in found] == [True, True, False]
+
+
+@pytest.mark.parametrize("es", [2, 4])
+def test_rounds_of_odd_rows_read_no_dword_beyond_the_map(host, es):
+    """compress_rowstrip loads whole dwords: aligned ones, all that hold an element of the round, none behind the map's last (bfloat16 rounds that start in
+    the middle of a dword would otherwise end two bytes behind a map that ends with a page)."""
+    host.check_round_span.argtypes = [ctypes.c_uint32] * 4 + [ctypes.POINTER(ctypes.c_uint32)]
+    host.check_round_span.restype = ctypes.c_uint32
+    n = ctypes.c_uint32()
+    for G in (1, 2, 3, 4):
+        for HW in (2 * 13, 13 * 13, 17 * 17, 35 * 35, 36 * 55, 55 * 55):
+            for P in range(1, 26):
+                for p0 in range(0, P, G):
+                    planes = min(G, P - p0)
+                    begin = (p0 * HW - host.check_round_span(p0, planes, HW, es, ctypes.byref(n))) * es
+                    assert begin % 4 == 0 and n.value % 4 == 0
+                    assert begin <= p0 * HW * es < begin + 4 and (p0 + planes) * HW * es <= begin + n.value <= (P * HW * es + 3) // 4 * 4
