@@ -181,8 +181,11 @@ constexpr int kLineUnits = 13;
 // NG > 1: planes of at most R = K / NG rounds (a few hundred bytes each): a wavefront takes NG groups of
 // 64 / S planes one after the other, all their loads issued first, so that it has K vectors per lane in
 // flight like the instances for larger planes (two or three would not cover the memory latency).
-template <typename T, int BITS, int K, int NG, int LU>
-__device__ __forceinline__ void compress_line_body(const OneShape& a, const CompPtrs& pt, uint32_t wg) {
+// where(pt, wg): the wavefront's map and its place in it.  A callable, so that they are worked out in here: made by the caller and handed in, they have the
+// compiler put half of the loads behind the first wait, and a scheduling barrier against that costs registers (64 x 3136 x 1 x 96 under B = 4 23.0 us, 23.3 with
+// the barrier; 32 x 512 x 1 x 3072 in bfloat16 25.6 and 26.2, 26.6 without).
+template <typename T, int BITS, int K, int NG, int LU, typename Where>
+__device__ __forceinline__ void compress_line_body(const OneShape& a, Where where) {
     constexpr int R = K / NG;
     static_assert(R * NG == K, "whole groups");
     constexpr bool LDS = LU < 0;
@@ -198,6 +201,9 @@ __device__ __forceinline__ void compress_line_body(const OneShape& a, const Comp
     constexpr uint32_t kDrop = 0x80000000u;              // an offset past every buffer here (and no wrap when a round's offset is added): the access is dropped
     constexpr uint32_t LB = (sizeof(T) == 2 || kC16<T>) ? 2u : 4u;          // bytes of a cached H^L value
     const uint32_t tid = threadIdx.x;
+    CompPtrs pt;
+    uint32_t wg;
+    where(pt, wg);
     const uint32_t S = a.S, sub = tid & (S - 1u), lp = tid >> a.S_log2;
     const uint32_t ppw = a.ppw * NG;                     // planes of the wavefront
     const uint32_t p0 = wg * ppw;
@@ -227,7 +233,8 @@ __device__ __forceinline__ void compress_line_body(const OneShape& a, const Comp
             }
         }
     }
-    __builtin_amdgcn_sched_barrier(0);                   // all loads ahead of the first wait (otherwise the masked rounds' may come behind it: 3.1 -> 3.4 us on small maps)
+    // (the one case that gains from it: 64 x 3136 x 1 x 96 in bfloat16 under B = 64 21.3 -> 20.8 us)
+    if constexpr (sizeof(T) == 2 && NG > 1 && LDS) __builtin_amdgcn_sched_barrier(0);
     const uint32_t cnt_full = a.upb * EPV, cnt_last = (a.qv - (a.nb - 1u) * a.upb) * EPV;
     const double rcp_last = LU == 0 ? 0.0 : 1.0 / (double)cnt_last;
     const double rcp_full = __longlong_as_double((long long)(1023u - (31u - (uint32_t)__builtin_clz(cnt_full))) << 52);     // a power of two
@@ -402,7 +409,10 @@ __device__ __forceinline__ void compress_line_body(const OneShape& a, const Comp
 
 template <typename T, int BITS, int K, int NG, int LU>
 __global__ void __launch_bounds__(64) compress_line(OneArgs a) {
-    compress_line_body<T, BITS, K, NG, LU>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, gridDim.x));
+    compress_line_body<T, BITS, K, NG, LU>(a, [&](CompPtrs& pt, uint32_t& wg) {
+        pt = comp_ptrs(a.tab, a.rg, threadIdx.x);
+        wg = xcd_run_index(blockIdx.x, gridDim.x);
+    });
 }
 
 // The maps of several shapes that have the same instance, in one launch.  What it saves is the drain and the filling between the launches, 2-4 us
@@ -416,5 +426,8 @@ __global__ void __launch_bounds__(64) compress_lines(LinesArgs a) {
     const SharedPlace at = shared_place(a);
     const Regions& rg = a.rg[at.shape];
     if (at.wg == 0 && threadIdx.x < 48) zero_pads(rg, static_cast<char*>(a.pk[at.map]), threadIdx.x);
-    compress_line_body<T, BITS, K, 1, LU>(a.shape[at.shape], shared_ptrs(a, rg, at.map), xcd_run_index(at.wg, at.n));
+    compress_line_body<T, BITS, K, 1, LU>(a.shape[at.shape], [&](CompPtrs& pt, uint32_t& wg) {
+        pt = shared_ptrs(a, rg, at.map);
+        wg = xcd_run_index(at.wg, at.n);
+    });
 }
