@@ -411,7 +411,9 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
                 const bool can = plan_mixed(L, D, H, W, B, x, &sh);
                 const uint64_t lanes = (uint64_t)in.size() * L.P << sh.S_log2;
                 const int gains = can ? mixed_gains(L, D, H, W, B, m.b, es, x, in.size(), lanes) : 0;
-                const bool small = gains == 2 || (gains && mix);
+                bool small = gains == 2 || (gains && mix);
+                // more maps of a shape than their own kernel's launches hold, one over another's memory: those launches, in the order of the descriptors
+                if (small && !mix && in.size() > (size_t)kMaxBatch && outputs_overlap(ranges)) small = false;
                 if (mix && gains < 2 && shared.add(sh, small ? lanes : 0, m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
                 if (small) {
                     if (!comp.fits(m, in.size(), lanes)) {

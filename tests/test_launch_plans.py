@@ -290,6 +290,20 @@ def test_chunk_kernels_of_few_planes_leave_their_launch(host):
     assert [q.kind == MIXED for q in found] == [True, True, False]
 
 
+def test_chunk_kernels_of_one_shape_over_one_another_keep_launches_of_eight(host):
+    """Nine maps of a shape and more, two of them eight or more descriptors apart over the same memory: the later one is compressed last."""
+    shape, x, p = (2, 3, 64, 64), 1 << 46, 1 << 47
+    apart = [(shape, F32, 8, 1)] * 16
+    assert [(q.kind == MIXED, q.maps) for q in _maps(host, apart)] == [(True, 1)]
+    for first, last in (((None, p), (None, p)), ((None, p), (None, p + 64)), ((None, x), (None, (2 * 0 + 1) << 38))):
+        for others in ([], [(A, F32, 8, 2), (C_, F32, 64, 2)]):
+            entries = [(shape, F32, 8, 1, *first)] + [(shape, F32, 8, 1)] * 14 + [(shape, F32, 8, 1, *last)] + others
+            found = _maps(host, entries)
+            assert [(q.kind == MIXED, q.gy) for q in found[:2]] == [(False, 8), (False, 8)], (first, last, [(q.kind, q.gy) for q in found])
+    # eight of them never had an order among themselves
+    assert [q.kind == MIXED for q in _maps(host, [(shape, F32, 8, 1, None, p)] * 8)] == [True]
+
+
 @pytest.mark.parametrize("es", [2, 4])
 def test_rounds_of_odd_rows_read_no_dword_beyond_the_map(host, es):
     """compress_rowstrip loads whole dwords: aligned ones, all that hold an element of the round, none behind the map's last (bfloat16 rounds that start in
