@@ -994,8 +994,8 @@ bool units_wide(const DecShape& a) { return a.W >= 3 && a.B >= 3; }
 // Fills the decompress launch plan; returns 7 (row vectors, a wavefront per chunk), 0 (row vectors of 2-byte elements, staged), 3 (block table),
 // 8 (any width, a wavefront per chunk), 9 (the same for one-block planes), 6 (four consecutive elements
 // per lane step, any width), 5 (word by word through LDS), 1 (flat), 4 (lane per plane) or 2 (scalar).
-// Hs = rows of one depth slice, D = depth slices (1 for a 2-D map; the table kernel takes 2-D maps only).
-int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat,
+// Hs = rows of one depth slice, D = depth slices (1 for a 2-D map; the table kernel takes 2-D maps only).  maps: how many of them the launch holds.
+int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat, uint64_t maps,
                     DecArgs* a, uint32_t* grid) {
     const int64_t H = D * Hs;
     dec_shape(L, D, Hs, W, B, a);
@@ -1036,10 +1036,12 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
     if (D == 1 && L.HW % 4 == 0 && L.nb > 1 && L.nb <= 255 && small_idx && out_vec_aligned && fastdiv_ok(L.HW, (uint64_t)W)) {
         a->q4 = (uint32_t)(L.HW / 4);
         uint64_t G = dec_planes(L, es, 1);
-        // few planes: fewer of them per workgroup, down to a vector per lane, until every CU has a workgroup (1216 planes of 14 x 14 in bfloat16 are
-        // 16 workgroups of 32 KB: 5.7 us, 3.9 so; maps of up to 0.3 M elements 4.9 -> 3.7; until there are four for each CU, 14382 planes of 14 x 14
-        // 4.4 -> 4.8)
-        while (G > 1 && (L.P + G - 1) / G < (uint64_t)num_cus() && (G / 2) * a->q4 >= kThreads) G /= 2;
+        // few planes in the launch: fewer of them per workgroup, down to a vector per lane, until there are three workgroups for two CUs
+        // (1216 planes of 14 x 14 in bfloat16 are 16 workgroups of 32 KB: 5.7 us, 3.9 so; maps of up to 0.3 M elements 4.9 -> 3.7; until there are four for each
+        // CU, 14382 planes of 14 x 14 4.4 -> 4.8.  128 launches of one to eight 4-byte maps 659 us, 629 so, 639 where each map counted for itself, eight of
+        // 2432 x 14 x 14 4.9, 4.9 and 5.4; 64 of 2-byte maps 348, 276 and 279.  With one workgroup per CU 631 and 283, two 633 and 276)
+        const uint64_t enough = (uint64_t)num_cus() * 3 / 2;
+        while (G > 1 && (L.P + G - 1) / G * maps < enough && (G / 2) * a->q4 >= kThreads) G /= 2;
         while (G > 1 && !fastdiv_ok(G * a->q4 + kThreads, a->q4)) --G;
         if (fastdiv_ok(G * a->q4 + kThreads, a->q4) && dec_lds_bytes(L, es, G) + 4ull * a->q4 + 16 <= kDecLdsMax) {
             a->G = (uint32_t)G;
@@ -1066,10 +1068,12 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
             uint64_t g = (uint64_t)num_cus() * (16ull / nw);
             g = (g + 3) & ~3ull;        // the planes of a workgroup start alike within a unit of the map
             *grid = (uint32_t)(g < L.P ? g : L.P);
-            // few planes: the rounds of units of a plane shared among several workgroups, until there are a third of what the machine holds (maps of up
-            // to 0.3 M bfloat16 elements 5.5 -> 4.5 us; shared until it is full, 854 planes of 27 x 27 4.8 -> 5.1)
+            // few planes in the launch: the rounds of units of a plane shared among several workgroups, until there are half of what the machine holds, or as many as
+            // CUs where a workgroup has sixteen wavefronts (maps of up to 0.3 M bfloat16 elements 5.5 -> 4.5 us; shared until it is full, 854 planes of 27 x 27
+            // 4.8 -> 5.1.  120 launches of one to eight maps 787 us, 692 so; 710 with a half for sixteen wavefronts too, 737 with a third of it for each map by
+            // itself: eight of 300 x 27 x 27 6.3, 6.4, 6.4 and 8.5)
             const uint64_t rounds = (q4 + nt - 1) / nt;
-            uint64_t parts = units_wide(*a) ? g / (3 * L.P) : 1;
+            uint64_t parts = units_wide(*a) ? (nw == 16 ? g : g / 2) / (L.P * maps) : 1;
             if (parts > rounds) parts = rounds;
             a->rounds = (uint32_t)rounds;
             if (parts > 1) {
@@ -1126,7 +1130,7 @@ hipError_t with_bits(int b, F&& f) {
 // launch costs.
 int plan_mix(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, size_t es, const void* xhat, uint64_t maps, DecShape* a, uint32_t* grid) {
     DecArgs own{};
-    const int kind = plan_decompress(L, D, Hs, W, B, es, xhat, &own, grid);
+    const int kind = plan_decompress(L, D, Hs, W, B, es, xhat, maps, &own, grid);
     if (kind != 7 && kind != 8 && kind != 9) {
         if (kind == 0 || kind == 2 || maps * L.P * L.HW > (8u << 20) || !plan_any(L, D, Hs, W, B, es, xhat, grid)) return 0;
         *a = own;
@@ -1511,7 +1515,7 @@ int decompress_impl(int count, const void* const* packed, void* const* xhat, siz
         const int cnt = count - i0 < kMaxBatch ? count - i0 : kMaxBatch;
         DecArgs a{};
         uint32_t grid = 0;
-        const int kind = plan_decompress(L, D, H, W, B, es, reinterpret_cast<const void*>(all_out ? all_out : 16), &a, &grid);
+        const int kind = plan_decompress(L, D, H, W, B, es, reinterpret_cast<const void*>(all_out ? all_out : 16), (uint64_t)cnt, &a, &grid);
         for (int i = 0; i < cnt; ++i) { a.tab.pk[i] = packed[i0 + i]; a.tab.xhat[i] = xhat[i0 + i]; }
         a.rg = rg;
         // LDS of the streaming kernels: staged codes, meta and LFC of G planes (+ the block table)
@@ -1854,7 +1858,7 @@ int kernel_name_impl(int direction, const void* data, int64_t N, int64_t C, int6
         }
     } else {
         DecArgs a{}; uint32_t grid = 0;
-        const int kind = plan_decompress(L, D, H, W, B, es, data, &a, &grid);
+        const int kind = plan_decompress(L, D, H, W, B, es, data, 1, &a, &grid);
         if (kind == 6)
             n = snprintf(out, cap, "decompress_units<%s, %d, %d%s>", tn, b, (int)a.G, units_wide(a) ? "" : ", 1");
         else if (kind == 7)

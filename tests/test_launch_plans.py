@@ -304,6 +304,22 @@ def test_chunk_kernels_of_one_shape_over_one_another_keep_launches_of_eight(host
     assert [q.kind == MIXED for q in _maps(host, [(shape, F32, 8, 1, None, p)] * 8)] == [True]
 
 
+@pytest.mark.parametrize("shape,B,dt,kind,most", [((1, 300, 27, 27), 8, BF16, 6, 8), ((1, 50, 73, 73), 8, BF16, 6, 2), ((1, 30, 103, 103), 8, BF16, 6, 1), ((1, 40, 147, 147), 8, BF16, 6, 1),
+                                                  ((1, 1216, 14, 14), 8, F32, 3, 1), ((1, 600, 30, 30), 8, BF16, 3, 1), ((1, 2432, 14, 14), 8, C16, 3, 1)])
+def test_decompression_shares_planes_by_all_maps_of_the_launch(host, shape, B, dt, kind, most):
+    """decompress_units (6) and decompress_table (3): few planes are shared among more workgroups until a launch has `most` per CU, however many maps hold them."""
+    planes, found = shape[0] * shape[1], []
+    for maps in range(1, 9):
+        (launch,) = _maps(host, [(shape, dt, B, 2)] * maps, compress=False)
+        assert (launch.kind, launch.gy) == (kind, maps)
+        found.append(launch.gx)
+        assert kind != 6 or launch.gx == planes or launch.gx * maps <= most * host.check_cus()
+    assert found == sorted(found, reverse=True) and found[0] > found[-1]
+    if kind == 3:                                           # a workgroup per CU, or what each would be by itself in a launch of eight times the planes
+        big = (8 * shape[0],) + shape[1:]
+        assert found[-1] * 8 <= max(2 * host.check_cus() + 8, _maps(host, [(big, dt, B, 2)], compress=False)[0].gx + 8)
+
+
 @pytest.mark.parametrize("es", [2, 4])
 def test_rounds_of_odd_rows_read_no_dword_beyond_the_map(host, es):
     """compress_rowstrip loads whole dwords: aligned ones, all that hold an element of the round, none behind the map's last (bfloat16 rounds that start in
