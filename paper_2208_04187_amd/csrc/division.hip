@@ -73,6 +73,7 @@
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
+#include <utility>
 #include <vector>
 #include "../../include/division.h"
 
@@ -386,6 +387,7 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
     for (int i = 0; i < count; ++i) {
         if (done[(size_t)i]) continue;
         in.clear(); out.clear(); seeds.clear();
+        in.reserve((size_t)count); out.reserve((size_t)count); seeds.reserve((size_t)count);      // (once for all shapes, anew where they went along with one)
         size_t cap = ~(size_t)0;
         for (int j = i; j < count; ++j) {
             if (done[(size_t)j] || !same(maps[i], maps[j])) continue;
@@ -406,25 +408,32 @@ static int run_maps(int count, const division_map* maps, void* hip_stream, bool 
             uintptr_t all = 0;
             if (compress) {
                 for (const void* x : in) all |= (uintptr_t)x;
-                MixedShape sh{};
                 const void* x = reinterpret_cast<const void*>(all);
-                const bool can = plan_mixed(L, D, H, W, B, x, &sh);
-                const uint64_t lanes = (uint64_t)in.size() * L.P << sh.S_log2;
-                const int gains = can ? mixed_gains(L, D, H, W, B, m.b, es, x, in.size(), lanes) : 0;
+                CompLaunch own;
+                plan_compress(L, D, H, W, B, m.b, es, x, (int)std::min<size_t>(in.size(), kMaxBatch), &own);
+                const uint64_t lanes = (uint64_t)in.size() * L.P << mixed_lanes_log2(L.HW);
+                int gains = mixed_gains(own.kind, lanes);
+                MixedShape sh{};
+                if ((gains == 2 || (gains && mix)) && !plan_mixed(L, D, H, W, B, x, &sh)) gains = 0;
                 bool small = gains == 2 || (gains && mix);
                 // more maps of a shape than their own kernel's launches hold, one over another's memory: those launches, in the order of the descriptors
                 if (small && !mix && in.size() > (size_t)kMaxBatch && outputs_overlap(ranges)) small = false;
-                if (mix && gains < 2 && shared.add(sh, small ? lanes : 0, m, L, D, H, W, B, es, x, cap, in, out, seeds)) continue;
+                if (mix && gains < 2 && shared.add(own, sh, small ? lanes : 0, m, L, H, B, cap, in, out, seeds)) continue;
                 if (small) {
                     if (!comp.fits(m, in.size(), lanes)) {
                         const int rc = comp.flush(st);
                         if (rc != DIVISION_OK) return rc;
                     }
-                    comp.add(m, sh, gains, lanes, in.size(), cap, in.data(), out.data(), seeds.data());
+                    comp.add(m, own, sh, gains, lanes, in.size(), cap, in.data(), out.data(), seeds.data());
                     if (!mix) {                               // maps that share memory: in their order
                         const int rc = comp.flush(st);
                         if (rc != DIVISION_OK) return rc;
                     }
+                    continue;
+                }
+                if (in.size() <= (size_t)kMaxBatch) {
+                    const int rc = launch_compress(own, make_regions(L), (int)in.size(), in.data(), out.data(), seeds.data(), m.dt, m.b, st);
+                    if (rc != DIVISION_OK) return rc;
                     continue;
                 }
             } else {

@@ -1452,6 +1452,21 @@ void plan_compress(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int 
     if (c->kind == REGS && c->nw == 16 && regs_walk(L.P * (uint64_t)maps, L.HW / 4)) { c->ra.maps = c->gy; c->gy = 1; grid = (uint32_t)num_cus(); }
 }
 
+// Makes the launch that is planned for `count` maps (at most kMaxBatch) of a shape.
+int launch_compress(CompLaunch& c, const Regions& rg, int count, const void* const* x, void* const* packed, const uint64_t* seeds,
+                    division_dtype dt, int b, hipStream_t st) {
+    c.st = st;
+    c.head.rg = rg;
+    CompTab& tab = c.head.tab;
+    for (int i = 0; i < count; ++i) {
+        tab.x[i] = x[i];
+        tab.pk[i] = packed[i];
+        tab.seed_a[i] = seed_key_a(seeds[i]);
+        tab.seed_c[i] = seed_key_c(seeds[i]);
+    }
+    return bridge_compress(dt, c, b) == hipSuccess ? DIVISION_OK : DIVISION_EHIP;
+}
+
 int compress_impl(int count, const void* const* x, void* const* packed, const uint64_t* seeds,
                   int64_t N, int64_t C, int64_t D, int64_t H, int64_t W, division_dtype dt,
                   int B, int b, size_t packed_capacity, void* hip_stream) {
@@ -1476,17 +1491,8 @@ int compress_impl(int count, const void* const* x, void* const* packed, const ui
         const int cnt = count - i0 < kMaxBatch ? count - i0 : kMaxBatch;
         CompLaunch c;
         plan_compress(L, D, H, W, B, b, es, xa, cnt, &c);
-        c.st = static_cast<hipStream_t>(hip_stream);
-        c.head.rg = rg;
-        CompTab& tab = c.head.tab;
-        for (int i = 0; i < cnt; ++i) {
-            tab.x[i] = x[i0 + i];
-            tab.pk[i] = packed[i0 + i];
-            tab.seed_a[i] = seed_key_a(seeds[i0 + i]);
-            tab.seed_c[i] = seed_key_c(seeds[i0 + i]);
-        }
-        const hipError_t err = bridge_compress(dt, c, b);
-        if (err != hipSuccess) return DIVISION_EHIP;
+        const int err = launch_compress(c, rg, cnt, x + i0, packed + i0, seeds + i0, dt, b, static_cast<hipStream_t>(hip_stream));
+        if (err != DIVISION_OK) return err;
     }
     return DIVISION_OK;
 }
@@ -1578,6 +1584,13 @@ void spread_mixed(MixedArgs& a, const uint32_t* maps, uint32_t shapes, uint32_t*
     *threads = (int)nt;
 }
 
+// log2 of the fewest lanes per plane that compress_mixed takes a plane of HW elements with (at most kMixedUnits units of four per lane)
+uint32_t mixed_lanes_log2(uint64_t HW) {
+    uint32_t lg = 3;
+    while ((HW + 3) / 4 > (uint64_t)kMixedUnits << lg) ++lg;
+    return lg;
+}
+
 // Fills what compress_mixed needs of a shape, with as few lanes per plane as take it; false when the shape is not covered.
 // x: the OR of its maps' addresses.
 bool plan_mixed(const Layout& L, int64_t D, int64_t H, int64_t W, int B, const void* x, MixedShape* a) {
@@ -1591,8 +1604,7 @@ bool plan_mixed(const Layout& L, int64_t D, int64_t H, int64_t W, int B, const v
     a->LH = (uint32_t)L.LH; a->LW = (uint32_t)L.LW; a->nb = (uint32_t)L.nb; a->WPP = (uint32_t)L.WPP; a->B = (uint32_t)B;
     a->Br = (uint32_t)Br; a->nch = (uint32_t)nch;
     a->q4 = (uint32_t)q4;
-    a->S_log2 = 3;
-    while (q4 > (uint64_t)kMixedUnits << a->S_log2) ++a->S_log2;
+    a->S_log2 = mixed_lanes_log2(L.HW);
     a->d_W = make_fastdiv((uint32_t)W); a->d_B = make_fastdiv((uint32_t)B); a->d_H = make_fastdiv((uint32_t)H);
     a->d_LW = make_fastdiv((uint32_t)L.LW); a->d_slice = make_fastdiv((uint32_t)(L.LH * L.LW));
     a->d_nch = make_fastdiv((uint32_t)nch); a->d_Br = make_fastdiv((uint32_t)Br);
@@ -1600,7 +1612,7 @@ bool plan_mixed(const Layout& L, int64_t D, int64_t H, int64_t W, int B, const v
     return fit_mixed(a, kMixedThreads) <= kLdsMax;
 }
 
-// Whether the maps of a shape are better off in a launch with other shapes than in one of their own.  lanes: what they take there, at
+// Whether the maps of a shape are better off in a launch with other shapes than in one of their own (with the kernel `kind`).  lanes: what they take there, at
 // the fewest per plane, in parts of what the machine holds at once (sixteen wavefronts per CU).  Beside others a shape saves the 2-4 us that a launch waits for
 // the drain of the one before and then fills, and runs a kernel for any shape: about level with the kernels that stage planes in LDS (so: up to the
 // whole machine), up to twice as slow per element as those that hold them in registers (a quarter of it), three times as compress_line (an eighth).
@@ -1609,12 +1621,10 @@ bool plan_mixed(const Layout& L, int64_t D, int64_t H, int64_t W, int B, const v
 // Two: also where no other shape shares the launch.  The chunk kernels on few planes are one long chain in a few workgroups: single shapes of 0.01 to 8 M
 // elements, in their own kernel and here, compress_tile / _plane / _any 18.4 and 10.1 us on average (60 shapes), compress_wave up to 0.3 M 8.6 and 4.5, above
 // level, compress_rows up to 0.1 M 6.1 and 4.6, above level.
-int mixed_gains(const Layout& L, int64_t D, int64_t H, int64_t W, int B, int b, size_t es, const void* x, uint64_t maps, uint64_t lanes) {
+int mixed_gains(int kind, uint64_t lanes) {
     const uint64_t machine = (uint64_t)num_cus() * 1024;
     if (lanes > machine) return 0;
-    CompLaunch own;
-    plan_compress(L, D, H, W, B, b, es, x, (int)std::min<uint64_t>(maps, kMaxBatch), &own);
-    switch (own.kind) {
+    switch (kind) {
         case TILE: case PLANE: case ANY: return 2;
         case WAVE: case ROWS: return lanes <= machine / 16 ? 2 : 1;
         case UNITS: return 1;
@@ -1633,12 +1643,14 @@ struct CompMixer {
     size_t first_bytes = 0;
     uint64_t lanes = 0;                       // of all shapes, at the fewest per plane
     bool alone = false;                       // the first shape gains by itself
+    CompLaunch own;                           // the launch of the first shape by itself (its first kMaxBatch maps)
     bool fits(const division_map& m, size_t n, uint64_t more) const {
         return nshape == 0 || (m.dt == first->dt && m.b == first->b && nshape < (uint32_t)kSharedShapes && nmap + n <= (size_t)kSharedMaps &&
                                lanes + more <= (uint64_t)num_cus() * 1536);
     }
-    void add(const division_map& m, const MixedShape& sh, int gains, uint64_t more, size_t n, size_t bytes, const void* const* x, void* const* packed, const uint64_t* seed) {
-        if (nshape == 0) { first = &m; first_bytes = bytes; nmap = 0; lanes = 0; alone = gains == 2; }
+    void add(const division_map& m, const CompLaunch& c, const MixedShape& sh, int gains, uint64_t more, size_t n, size_t bytes, const void* const* x, void* const* packed,
+             const uint64_t* seed) {
+        if (nshape == 0) { first = &m; first_bytes = bytes; nmap = 0; lanes = 0; alone = gains == 2; own = c; }
         lanes += more;
         a.shape[nshape] = sh;
         a.map0[nshape] = nmap;
@@ -1652,6 +1664,7 @@ struct CompMixer {
         const uint32_t shapes = nshape;
         nshape = 0;
         if (shapes == 0) return DIVISION_OK;
+        if (shapes == 1 && !alone && nmap <= (uint32_t)kMaxBatch) return launch_compress(own, a.shape[0].rg, (int)nmap, a.x, a.pk, seeds, first->dt, first->b, st);
         if (shapes == 1 && !alone)
             return compress_impl((int)nmap, a.x, a.pk, seeds, first->N, first->C, first->D, first->H, first->W, first->dt, first->B, first->b, first_bytes, st);
         CompLaunch c;
@@ -1721,17 +1734,16 @@ struct SharedMixer {
     };
     enum { LIGHT = 0, HEAVY = -1, OWN = -2, GONE = -3 };
     std::vector<Shape> shapes;
-    // takes the shape if its kernel can be shared
-    bool add(const MixedShape& mixed, uint64_t mixed_lanes, const division_map& m, const Layout& L, int64_t D, int64_t H, int64_t W, int B, size_t es, const void* all, size_t bytes,
-             const std::vector<const void*>& x, const std::vector<void*>& packed, const std::vector<uint64_t>& seeds) {
-        CompLaunch c;
-        plan_compress(L, D, H, W, B, m.b, es, all, (int)std::min<size_t>(x.size(), kMaxBatch), &c);
+    // takes the shape, and its maps, if its kernel (c: the launch of its first kMaxBatch maps) can be shared
+    bool add(const CompLaunch& c, const MixedShape& mixed, uint64_t mixed_lanes, const division_map& m, const Layout& L, int64_t H, int B, size_t bytes,
+             std::vector<const void*>& x, std::vector<void*>& packed, std::vector<uint64_t>& seeds) {
         if (x.size() > (size_t)kSharedMaps || !launch_ok((uint64_t)c.gx * x.size(), 64)) return false;
         int key = LIGHT;
         if (c.kind == LINE && c.oa.NG == 1 && (c.oa.K == 4 || c.oa.K == 6)) key = 100 * (int)c.oa.K + line_lu(c.oa);
         else if (c.kind == LANE || (c.kind == ITEMS && B == 8 && H > 1) || (c.kind == ROWSTRIP && !c.sa.pack_off)) key = HEAVY;
         else if (!(c.kind == STRIP && (B == 4 || B == 8)) && !(c.kind == ITEMS && B == 4 && H > 1)) return false;
-        shapes.push_back({&m, bytes, c, make_regions(L), key, x, packed, seeds, mixed, mixed_lanes});
+        if (shapes.empty()) shapes.reserve(kSharedShapes);
+        shapes.push_back({&m, bytes, c, make_regions(L), key, std::move(x), std::move(packed), std::move(seeds), mixed, mixed_lanes});
         return true;
     }
     static void put(LinesArgs& a, uint32_t n, const Shape& q) { a.shape[n] = q.c.oa; a.rg[n] = q.rg; }
@@ -1766,6 +1778,10 @@ struct SharedMixer {
             c.lds = std::max(c.lds, q.c.lds);
         }
         const division_map& m = *f.m;
+        if (n == 1 && f.x.size() <= (size_t)kMaxBatch) {
+            c = f.c;
+            return launch_compress(c, f.rg, (int)f.x.size(), f.x.data(), f.packed.data(), f.seeds.data(), m.dt, m.b, st);
+        }
         if (n == 1) return compress_impl((int)f.x.size(), f.x.data(), f.packed.data(), f.seeds.data(), m.N, m.C, m.D, m.H, m.W, m.dt, m.B, m.b, f.bytes, st);
         c.st = st; c.gx = grid; c.gy = 1;
         if constexpr (std::is_same<Args, LinesArgs>::value) { c.kind = LINES; c.lines.a = &a; c.lines.K = f.c.oa.K; c.lines.lu = line_lu(f.c.oa); }
@@ -1793,7 +1809,7 @@ struct SharedMixer {
                 const int rc = comp.flush(st);
                 if (rc != DIVISION_OK) return rc;
             }
-            comp.add(*s.m, s.mixed, 1, s.mixed_lanes, s.x.size(), s.bytes, s.x.data(), s.packed.data(), s.seeds.data());
+            comp.add(*s.m, s.c, s.mixed, 1, s.mixed_lanes, s.x.size(), s.bytes, s.x.data(), s.packed.data(), s.seeds.data());
             s.key = GONE;
         }
         return DIVISION_OK;

@@ -320,6 +320,21 @@ def test_decompression_shares_planes_by_all_maps_of_the_launch(host, shape, B, d
         assert found[-1] * 8 <= max(2 * host.check_cus() + 8, _maps(host, [(big, dt, B, 2)], compress=False)[0].gx + 8)
 
 
+@pytest.mark.parametrize("maps", [1, 3, 8, 9, 25])
+def test_a_shape_by_itself_is_launched_as_a_batch_of_it(host, maps):
+    """division_compress_maps launches the plan that it has made to decide; division_compress_batch makes its own: the same launches, the same maps."""
+    host.division_compress_batch.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 3 + [ctypes.c_int64] * 4 + [ctypes.c_int] * 3 + [ctypes.c_size_t, ctypes.c_void_p]
+    for shape, dt, B, b in (((64, 256, 56, 56), F32, 8, 2), ((2, 3, 1, 3136), F32, 8, 2), ((2, 16, 28, 28), F32, 8, 2), ((3, 8, 33, 17), BF16, 8, 4), ((64, 768, 17, 17), F32, 8, 2),
+                            ((2, 2, 1, 768), BF16, 8, 4), ((64, 2048, 7, 7), C16, 8, 2), ((8, 512, 24, 24), F32, 8, 1), ((64, 600, 30, 30), F32, 4, 2), ((64, 64, 147, 147), F32, 8, 2),
+                            ((64, 256, 56, 56), BF16, 64, 2), ((1, 1, 300, 300), F32, 18, 2), ((64, 16, 224, 224), F32, 8, 2)):
+        mine = [(q.kind, q.dt, q.waves, q.gx, q.gy, q.walked) for q in _maps(host, [(shape, dt, B, b)] * maps)]
+        x = (ctypes.c_void_p * maps)(*[(2 * i + 1) << 38 for i in range(maps)])
+        packed = (ctypes.c_void_p * maps)(*[((2 * i + 1) << 38) + (1 << 37) for i in range(maps)])
+        seeds = (ctypes.c_uint64 * maps)()
+        assert host.division_compress_batch(maps, x, packed, seeds, *shape, dt, B, b, 1 << 40, None) == 0
+        assert mine == [(q.kind, q.dt, q.waves, q.gx, q.gy, q.walked) for q in _launches(host)], shape
+
+
 @pytest.mark.parametrize("es", [2, 4])
 def test_rounds_of_odd_rows_read_no_dword_beyond_the_map(host, es):
     """compress_rowstrip loads whole dwords: aligned ones, all that hold an element of the round, none behind the map's last (bfloat16 rounds that start in
