@@ -357,13 +357,14 @@ __device__ __forceinline__ void compress_regs_rounds(const RegsArgs& a) {
     if (full) compress_regs_body<T, BITS, B, NW, false, ND, true>(a);
     else compress_regs_body<T, BITS, B, NW, false, ND, false>(a);
 }
-// ROW: the instance for maps of one row (a branch to its body in the other instance cost 56 x 56 in bfloat16 0.5-2 %)
-template <typename T, int BITS, int B, int NW, bool ROW = false>
+template <typename T, int BITS, int B, int NW>
 __global__ void __launch_bounds__(64 * NW) compress_regs(RegsArgs a) {
-    if constexpr (ROW) compress_regs_body<T, BITS, B, NW, false, 2, false, 0, true>(a);
-    else if constexpr (B == 0 || NW == 16) compress_regs_rounds<T, BITS, B, NW, 2>(a);
+    if constexpr (B == 0 || NW == 16) compress_regs_rounds<T, BITS, B, NW, 2>(a);
     else compress_regs_body<T, BITS, B, NW, false>(a);
 }
+// maps of one row (a branch to their body in compress_regs cost 56 x 56 in bfloat16 0.5-2 %)
+template <typename T, int BITS, int B>
+__global__ void __launch_bounds__(64) compress_regs_row(RegsArgs a) { compress_regs_body<T, BITS, B, 1, false, 2, false, 0, true>(a); }
 template <typename T, int BITS, int B, int NW>
 __global__ void __launch_bounds__(64 * NW) relu_compress_regs(RegsArgs a) { compress_regs_body<T, BITS, B, NW, true>(a); }
 template <typename T, int BITS, int B, int NW>

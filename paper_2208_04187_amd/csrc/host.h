@@ -174,7 +174,7 @@ template <typename T, int BITS>
 hipError_t launch_regs(int B, int nw, const RegsArgs& a, dim3 grid, size_t lds, hipStream_t st) {
     void (*kern)(RegsArgs);
     if (a.D > 1) kern = nw == 1 ? compress_regs_3d<T, BITS, 8, 1> : nw == 4 ? compress_regs_3d<T, BITS, 8, 4> : compress_regs_3d<T, BITS, 8, 16>;
-    else if (nw == 1 && a.H == 1 && (B == 8 || B == 4)) kern = B == 8 ? compress_regs<T, BITS, 8, 1, true> : compress_regs<T, BITS, 4, 1, true>;
+    else if (nw == 1 && a.H == 1 && (B == 8 || B == 4)) kern = B == 8 ? compress_regs_row<T, BITS, 8> : compress_regs_row<T, BITS, 4>;
     else if (nw == 1) kern = B == 8 ? compress_regs<T, BITS, 8, 1> : B == 4 ? compress_regs<T, BITS, 4, 1> : compress_regs<T, BITS, 0, 1>;
     else if (nw == 4) kern = B == 8 ? compress_regs<T, BITS, 8, 4> : B == 4 ? compress_regs<T, BITS, 4, 4> : compress_regs<T, BITS, 0, 4>;
     else kern = B == 8 ? compress_regs<T, BITS, 8, 16> : compress_regs<T, BITS, 4, 16>;
