@@ -237,7 +237,8 @@ int division_maxpool_backward(const void *mask, size_t mask_bytes, const void *g
  * (direction 1, data = xhat) would launch for these arguments, as it appears
  * in a kernel trace, e.g. "compress_tile<float, 2, 8, 4>" (one-row maps that
  * "compress_regs<float, 2, 8, 1>" is named for appear there as
- * "compress_regs_row<float, 2, 8>").  The choice depends
+ * "compress_regs_row<float, 2, 8>", maps of many planes with rows of 17 and 35
+ * elements as "compress_rowstrip_packed<...>").  The choice depends
  * on the shape, the block size and the 16-byte alignment of `data` (which may
  * be null: treated as aligned).  out is a host buffer of cap bytes.
  * Returns DIVISION_OK, or DIVISION_ESIZE when cap is too small.

@@ -199,8 +199,9 @@ __device__ __forceinline__ void compress_rowstrip_slots(const StripShape& a, con
 // 35 x 35, two 53 -> 47; 6664 planes of 35 x 35 cached as bfloat16 under B = 4 14.9 -> 13.4.
 template <int W> constexpr int kRowPack = W == 17 ? 1 : W == 35 ? 2 : 0;      // wavefronts of a workgroup, 0: not packed
 constexpr int kRowPackPlanes = 3;
+// (A kernel of its own: as a branch of compress_rowstrip it took the slots' small calls from 3.2 to 3.3 us, 1500 x 35 x 35 from 5.6 to 5.75.)
 template <typename T, int BITS, int W, int B>
-__device__ __forceinline__ void compress_rowstrip_packed(const StripArgs& a) {
+__global__ void __launch_bounds__(64 * kRowPack<W>) compress_rowstrip_packed(StripArgs a) {
     constexpr int NT = 64 * kRowPack<W>, G = kRowPackPlanes;
     constexpr int LPL = (G * W * W + 4 * NT - 1) / (4 * NT);          // 16-byte units a lane loads (at most W rows)
     constexpr uint32_t NSEG = (W + B - 1) / B;                        // blocks per block row
@@ -314,9 +315,6 @@ __device__ __forceinline__ void compress_rowstrip_packed(const StripArgs& a) {
 }
 
 template <typename T, int BITS, int W, int B>
-__global__ void __launch_bounds__(kRowPack<W> ? 64 * kRowPack<W> : 64) compress_rowstrip(StripArgs a) {
-    if constexpr (kRowPack<W> != 0) {
-        if (a.pack_off) { compress_rowstrip_packed<T, BITS, W, B>(a); return; }
-    }
+__global__ void __launch_bounds__(64) compress_rowstrip(StripArgs a) {
     compress_rowstrip_slots<T, BITS, W, B>(a, comp_ptrs(a.tab, a.rg, threadIdx.x), xcd_run_index(blockIdx.x, a.nrounds));
 }

@@ -538,7 +538,12 @@ hipError_t launch_rowstrip(int width, const StripArgs& a, dim3 grid, size_t lds,
         case 5504: kern = compress_rowstrip<T, BITS, 55, 4>; break;
         default: return hipErrorInvalidValue;
     }
-    const int wavefronts = !a.pack_off ? 1 : width / 100 == 17 ? kRowPack<17> : kRowPack<35>;
+    int wavefronts = 1;
+    if (a.pack_off) {
+        kern = width == 1708 ? compress_rowstrip_packed<T, BITS, 17, 8> : width == 1704 ? compress_rowstrip_packed<T, BITS, 17, 4>
+             : width == 3508 ? compress_rowstrip_packed<T, BITS, 35, 8> : compress_rowstrip_packed<T, BITS, 35, 4>;
+        wavefronts = width / 100 == 17 ? kRowPack<17> : kRowPack<35>;
+    }
     hipLaunchKernelGGL(kern, grid, dim3(64 * wavefronts), lds, st, a);
     return hipGetLastError();
 }

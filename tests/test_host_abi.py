@@ -281,7 +281,7 @@ def test_kernel_names_are_those_of_the_library():
     """A name is a template instance that the library holds, as a kernel trace shows it."""
     from paper_2208_04187_amd import _build
     symbols = _build.LIB.read_bytes()
-    for name in {n for row in DISPATCH for n in row[3:]} | {"compress_regs_row<float, 2, 8>", "compress_regs_row<float, 1, 4>"}:
+    for name in {n for row in DISPATCH for n in row[3:]} | {"compress_regs_row<float, 2, 8>", "compress_regs_row<float, 1, 4>", "compress_rowstrip_packed<float, 2, 17, 8>"}:
         family, args = name[:-1].split("<")
         mangled = "".join({"float": "f", "true": "Lb1E", "false": "Lb0E"}.get(a) or "Li%sE" % a.replace("-", "n") for a in args.split(", "))
         assert ("%d%sI%sEEv" % (len(family), family, mangled)).encode() in symbols, name
