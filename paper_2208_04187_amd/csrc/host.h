@@ -691,16 +691,20 @@ bool plan_one(const Layout& L, size_t es, const void* x, OneArgs* a, uint32_t* g
     if (!pick_lanes_and_rounds(qv, 2, &best_S, &best_log, &K)) return false;
     // Planes of 49 to 52 vectors (14 x 14): four lanes of thirteen rounds leave the fewest slots empty, but each round reads half a line.  Sixteen lanes of
     // four from a plane per CU on: 256 to 16384 planes of 14 x 14 4.1 -> 3.3 to 7.2 -> 6.0 us, 128 x 512 of them 19.0 -> 14.4; bfloat16 20 x 20 5.4 -> 3.6, 16384 of them
-    // 8.3 -> 8.1 (of 26 x 16, 52 vectors, 7.9 -> 8.1).
-    if (best_S == 4 && K == 13 && L.P >= (uint64_t)num_cus()) { best_S = 16; best_log = 4; K = 4; }
+    // 8.3 -> 8.1.  Thirteen rounds leave no slot of 52 vectors empty: 2-byte ones (26 x 16) keep them from 128 planes per CU on, codes of four and eight bits up to
+    // 256 (at 2 bits 24576 planes 9.5 us with thirteen rounds and 9.0 with four, 32768 10.6 and 10.9, 65536 17.5 and 18.7; at 4 bits 65536 19.1 and 19.4, 98304 28.2 and
+    // 26.5; 4-byte ones gain at all sizes).
+    const uint64_t cus = (uint64_t)num_cus();
+    const bool fills = es == 2 && qv == 52 && L.P >= 128 * cus && (L.WPP * 32 <= 2 * L.HW || L.P < 256 * cus);
+    if (best_S == 4 && K == 13 && L.P >= cus && !fills) { best_S = 16; best_log = 4; K = 4; }
     // Thirteen rounds are a long chain where the machine is nearly empty: as few as lanes allow that are at most eight wavefronts per CU.  150 drawn maps in
     // float / bfloat16 705 / 818 us; at limits of 1, 2, 4, 8 wavefronts 670, 666, 664, 662 / 744, 737, 729, 720, none slower (without a limit maps of 4 M elements
     // 1.10; instances of six rounds as well: 12 of 150 slower).  1-bit codes: from a plane per CU on (which instance takes fewer is pinned by name).
-    if (K == 13 && (L.WPP * 32 >= 2 * L.HW || L.P >= (uint64_t)num_cus()))
+    if (K == 13 && (L.WPP * 32 >= 2 * L.HW || L.P >= cus))
         for (uint32_t lg = best_log + 1; lg <= 6; ++lg) {
             const uint64_t S = 1ull << lg, R = (qv + S - 1) / S;
             const uint32_t k = R <= 3 ? 3 : R <= 4 ? 4 : R <= 6 ? 6 : 13;
-            if (k < K && L.P * S <= 8ull * 64 * num_cus()) { best_S = (uint32_t)S; best_log = lg; K = k; }
+            if (k < K && L.P * S <= 8ull * 64 * cus) { best_S = (uint32_t)S; best_log = lg; K = k; }
         }
     *a = OneArgs{};
     a->P = (uint32_t)L.P; a->HW = (uint32_t)L.HW; a->WPP = (uint32_t)L.WPP;

@@ -287,6 +287,15 @@ def test_kernel_names_are_those_of_the_library():
         assert ("%d%sI%sEEv" % (len(family), family, mangled)).encode() in symbols, name
 
 
+def test_one_block_planes_of_fifty_two_vectors():
+    """Sixteen lanes of four rounds; 2-byte planes that fill thirteen rounds keep them in maps of very many planes (26 x 16: 52 vectors)."""
+    import torch
+    for planes, b, rounds in ((16384, 2, 4), (24576, 4, 4), (32768, 1, 13), (32768, 8, 13), (65535, 4, 13), (65536, 2, 13), (65536, 4, 4), (131072, 8, 4), (131072, 2, 13)):
+        assert pkg.division_kernel_name(0, (64, planes // 64, 26, 16) if planes % 64 == 0 else (1, planes, 26, 16), 64, b, torch.bfloat16) == "compress_one<bf16_t, %d, %d>" % (b, rounds)
+        assert pkg.division_kernel_name(0, (1, planes, 20, 20), 64, b, torch.bfloat16).endswith(", 4>")
+        assert pkg.division_kernel_name(0, (1, planes, 16, 13), 64, b).endswith(", 4>")
+
+
 def test_kernel_choice_for_3d_maps_and_2_byte_elements():
     import torch
     assert pkg.division_kernel_name_3d(0, (2, 4, 16, 56, 56), 8, 2) == "compress_regs_3d<float, 2, 8, 16>"
