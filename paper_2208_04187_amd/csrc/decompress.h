@@ -9,8 +9,10 @@ struct DecShape {        // the maps of one shape
     uint32_t w4;         // W / 4 (decompress_stream with whole8: W / 8)
     uint32_t Hs, LHs;    // 3-D maps: rows and block rows of one depth slice (H counts the rows of all slices)
     uint32_t whole8;     // decompress_stream, 2-byte elements: rows and blocks are whole vectors of eight elements
-    uint32_t out_off;    // decompress_words: byte offset of the staged output in LDS
-    uint32_t rounds;     // decompress_units: rounds of units of a plane that a workgroup takes (all, or some where there are few planes)
+    union {              // (one word for both: sixteen words up to here, so that scalar loads of the fields behind them are aligned)
+        uint32_t out_off;    // decompress_words: byte offset of the staged output in LDS
+        uint32_t rounds;     // decompress_units: rounds of units of a plane that a workgroup takes (all, or some where there are few planes)
+    };
     FastDiv d_q4, d_w4, d_B, d_W, d_HW, d_Hs, d_wpp;
     double r_q4, r_HW;   // 1 / q4, 1 / HW: a division per wavefront is 30 binary64 instructions
 };
