@@ -244,10 +244,13 @@ __device__ __forceinline__ void compress_regs_body(const RegsArgs& a) {
             } else if constexpr (B == 0) {
             } else if constexpr (ROW) {
                 const uint32_t units = min((uint32_t)UPB, a.w4 - bj * UPB);
-                S += usum[bj * UPB];              // (to +0, like every sum here: a block of -0 has mean +0)
+                S = usum[bj * UPB];
 #pragma unroll
                 for (int u = 1; u < UPB; ++u) S += (uint32_t)u < units ? usum[bj * UPB + u] : 0.0;
-                cnt = units * 4;
+                // four or eight elements: their mean is an exact scaling, which takes the zero that the sums of the other blocks begin with along (a block of -0 has
+                // mean +0, a negative sum that only binary32 rounds to zero keeps its sign; a sum from 0 took 4.56 us to 4.66)
+                S = __builtin_fma(S, units == (uint32_t)UPB ? 1.0 / B : 0.25, 0.0);
+                cnt = 1;
             } else if (full_blocks) {
 #pragma unroll
                 for (int rr = 0; rr < B; ++rr)
