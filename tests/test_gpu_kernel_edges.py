@@ -262,6 +262,39 @@ def test_compress_of_several_shapes_special_planes(mode):
         assert np.array_equal(p.cpu().numpy(), r), s
 
 
+# the launches of several shapes (small maps; rows of one instance of compress_line; planes of few registers; all small planes), on planes at the edges of
+# binary32 with planes of NaN and of infinities among them: those are unspecified, every other plane is what the oracle makes of it
+@pytest.mark.parametrize("mode,b", [("f32", 2), ("f32", 1), ("bf16", 4), ("c16", 2), ("c16", 8)])
+@pytest.mark.parametrize("specs", [
+    [((1, 40, 14, 14), 8), ((1, 41, 9, 13), 4), ((3, 14, 1, 96), 64), ((2, 21, 5, 5), 64), ((1, 39, 33, 17), 18), ((1, 15, 40, 44), 8)],
+    [((1, 2101, 1, 384), 8), ((7, 301, 1, 768), 8)], [((1, 2101, 1, 384), 64), ((1, 1201, 1, 768), 64)],
+    [((1, 2057, 32, 32), 4), ((1, 8209, 8, 8), 4)],
+    [((1, 8209, 13, 13), 8), ((1, 1031, 35, 35), 8), ((1, 8211, 14, 14), 8), ((3, 5741, 7, 7), 8), ((3, 2741, 10, 12), 8)],
+])
+def test_shared_launches_keep_planes_apart(specs, mode, b):
+    from tests.test_gpu_parity import _special_planes
+    dtype, c16, dt = FORMATS[mode]
+    xs, bad = [], []
+    for k, (s, _) in enumerate(specs):
+        x = _special_planes(s, 5 + k).to(dtype)
+        planes = s[0] * s[1]
+        hit = [1, planes // 2, planes - 1]
+        f = x.view(planes, -1)
+        sign = torch.where(torch.arange(f.shape[1]) % 3 == 0, 1.0, -1.0).to(dtype)
+        f[hit[0]], f[hit[1]], f[hit[2], ::5] = float("nan"), float("inf") * sign, float("nan")
+        xs.append(x)
+        bad.append(hit)
+    packed = pkg.division_compress_maps([x.to("cuda:0") for x in xs], [B for _, B in specs], b, [11] * len(specs), c16=c16)
+    torch.cuda.synchronize()
+    for (s, B), x, hit, p in zip(specs, xs, bad, packed):
+        planes = s[0] * s[1]
+        got, want = oracle.split_packed(p.cpu().numpy(), s, B, b, dt), oracle.split_packed(oracle.compress(_host(x), B, b, 11, dt, threads=16), s, B, b, dt)
+        good = np.setdiff1d(np.arange(planes), hit)
+        for part in ("codes", "meta", "lfc"):
+            g, w = np.ascontiguousarray(got[part]).reshape(planes, -1), np.ascontiguousarray(want[part]).reshape(planes, -1)
+            assert np.array_equal(g[good].view(np.uint8), w[good].view(np.uint8)), (s, B, part)
+
+
 def test_decompress_of_maps_that_share_memory_keeps_their_order():
     # the second map is rebuilt over the first one
     gen = torch.Generator().manual_seed(1)

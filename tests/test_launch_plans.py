@@ -278,6 +278,15 @@ def test_shapes_of_one_kernel_share_a_launch(host):
     assert PLANES not in [q.kind for q in _maps(host, [(*planes[2], None, x), (*planes[3], None, x + 256), planes[1]])]
 
 
+def test_the_launches_whose_planes_are_tested_for_not_a_number(host):
+    """What test_shared_launches_keep_planes_apart of the kernel tests sends where."""
+    for kinds, specs in (([MIXED], [((1, 40, 14, 14), 8), ((1, 41, 9, 13), 4), ((3, 14, 1, 96), 64), ((2, 21, 5, 5), 64), ((1, 39, 33, 17), 18), ((1, 15, 40, 44), 8)]),
+                         ([LINES], [((1, 2101, 1, 384), 8), ((7, 301, 1, 768), 8)]), ([LINES], [((1, 2101, 1, 384), 64), ((1, 1201, 1, 768), 64)]),
+                         ([PLANES], [((1, 2057, 32, 32), 4), ((1, 8209, 8, 8), 4)]),
+                         ([PLANES], [((1, 8209, 13, 13), 8), ((1, 1031, 35, 35), 8), ((1, 8211, 14, 14), 8), ((3, 5741, 7, 7), 8), ((3, 2741, 10, 12), 8)])):
+        assert [q.kind for q in _maps(host, [(s, F32, B, 2) for s, B in specs])] == kinds, specs
+
+
 def test_chunk_kernels_of_few_planes_leave_their_launch(host):
     """One shape by itself: planes that would be a few workgroups' chain in the chunk kernels."""
     for shape, dt, B, b in (((2, 3, 64, 64), F32, 8, 1), ((1, 2, 8, 53, 53), F32, 64, 1), ((30, 1, 1, 3413), BF16, 8, 4), ((2, 20, 30, 30), F32, 4, 2), ((5, 33, 24, 24), F32, 18, 4)):
