@@ -299,7 +299,10 @@ int division_relu_compress_fused(int64_t N, int64_t C, int64_t H, int64_t W, div
  * shapes, element types, block sizes and code widths (Algorithm 1 loops over the layers; this
  * call takes the loop's maps as an array of descriptors).  Map i gives exactly the bytes the
  * single-map call with its fields gives.  Maps that agree in (N, C, D, H, W, dt, B, b) are
- * served together, up to 8 per kernel launch, in the order of their first appearance.
+ * served together, and the maps of several such shapes may share a launch; where a map that is
+ * written overlaps another map of the call, the shapes are launched one after another in the order
+ * of their first appearance, and of a shape up to 8 maps at a time in the order of the array (two
+ * maps of one shape among the same 8 must not overlap).
  *
  *   maps   HOST array of `count` descriptors, read during the call only.
  *          x       device, the map (compress only; ignored by decompress)

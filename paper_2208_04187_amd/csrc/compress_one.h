@@ -9,7 +9,7 @@ struct OneShape {
     uint32_t ppw;        // planes per wavefront = 64 / S
     uint32_t upb, upb_log2;  // compress_line: vectors per block (power of two, at most S); nb = blocks per plane
     uint32_t nb;
-    uint32_t K;          // rounds of the instance to launch (3, 6, 12 or 13): not read by the kernels
+    uint32_t K;          // rounds of the instance to launch (3, 4, 6, 12 or 13): not read by the kernels
     uint32_t NG;         // compress_line: groups of 64 / S planes per wavefront (1, or 12 / rounds per plane for tiny planes)
 };
 struct OneArgs : CompHead, OneShape {};

@@ -5,7 +5,7 @@
 // The one-wavefront kernels of small planes over the maps of several shapes.  A launch of its own costs a shape 2-4 us of draining and filling: the
 // compress side of a ResNet-18 / CIFAR step in four launches 65 us (4.4 TB/s), in one 50 (5.7).
 // ALL = false: compress_strip (B = 4, 8) and compress_items under B = 4, which need 64 registers at most, as when they are alone.  ALL = true: also
-// compress_rowstrip, compress_items under B = 8 and compress_lane, all at the registers of the hungriest: for launches of a few generations of wavefronts, where
+// compress_rowstrip, compress_items under B = 8 and compress_lane, all at the registers of the hungriest (fp32 118 to 128, bfloat16 124 to 154): for launches of a few generations of wavefronts, where
 // how many are on the machine at once matters less than that no launch waits for the one before (five shapes of a small network, compress and decompress, 43.0 ->
 // 37.8 us; 60 drawn calls with compress_rowstrip in them 1119 -> 1057, with compress_lane 1152 -> 1098).
 struct PlanesShape { uint32_t kind; union { StripShape strip; ItemsShape items; LaneShape lane; }; };

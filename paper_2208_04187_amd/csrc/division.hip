@@ -349,7 +349,9 @@ static bool outputs_overlap(std::vector<Range>& ranges) {
 
 // Both directions of the descriptor-array calls: validates every map, then serves the maps that
 // share a shape and parameters together, in order of first appearance.  The maps of several shapes go into one
-// launch where their kernel can take part in one (decompress_mixed) or they are small (compress_mixed) and no output overlaps another map.
+// launch where no output overlaps another map and their kernel can take part in one (decompress_mixed; compress_lines, compress_planes) or they are
+// small (compress_mixed).  Where an output overlaps another map, the shapes' launches follow the order of the descriptors, and the maps of a shape are
+// in launches of at most kMaxBatch.
 static int run_maps(int count, const division_map* maps, void* hip_stream, bool compress) {
     if (count < 0 || (count > 0 && !maps)) return DIVISION_EINVAL;
     std::vector<Range> ranges;

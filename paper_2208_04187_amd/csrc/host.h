@@ -503,7 +503,7 @@ bool plan_rowstrip(const Layout& L, int64_t H, int64_t W, int B, size_t es, cons
     *grid = a->nrounds;
     *lds = 16ull * ((G * L.HW + 3) / 4) + 16;          // the round in whole 16-byte units, and the element in front of it
     const int pack = W == 17 ? kRowPack<17> : W == 35 ? kRowPack<35> : 0;
-    if (pack && H <= W && L.P >= 2048 * G) {
+    if (pack && H <= W && L.P >= 8ull * num_cus() * G) {
         // the rows of three planes side by side (planes of more rows keep their slots, and so do maps of less than eight wavefronts per CU, which wait for
         // the longer chain through LDS: 72 planes of 35 x 35 4.4 us in slots, 4.8 so)
         const uint64_t nseg = L.LW;
@@ -1724,7 +1724,9 @@ struct Mixer {
 
 // Workgroups per CU up to which the small planes of all kernels share a launch (compress_planes, ALL).  Multi-shape calls of 0.5-30 M elements that hold strips,
 // rows of odd width or lanes, 60 each, at limits of 0, 16, 32, 64 and 128: 897, 895, 887, 877, 877 us; 1119, 1100, 1074, 1057, 1058; 1152, 1116, 1106, 1098,
-// 1100.  Beyond, each kernel at its own registers.
+// 1100.  Beyond, each kernel at its own registers.  The same limit for all types and code widths, though ALL needs 138 and 154 registers for bfloat16 at two bits and
+// one (three wavefronts per SIMD instead of four): twelve calls each of 2 to 40 M elements in launches of their own / in one, bfloat16 at 1, 2, 4 and 8 bits 260 / 222, 268 / 221,
+// 307 / 263 and 248 / 196 us, fp32 245 / 201, 212 / 172, 292 / 233 and 243 / 206, none slower by more than 2 %.
 constexpr uint64_t kHeavyWorkgroups = 64;
 // Shapes of one type and code width that one kernel serves share a launch: those of one instance of compress_line, and those whose kernels
 // compress_planes holds.  Kept until all shapes of a call are known; a shape that finds no other has a launch of its own.
