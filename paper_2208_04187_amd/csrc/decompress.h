@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(64) decompress_stream_one(DecArgs a) { decompr
 // places, so that everything else it reads depends on one wait for scalar loads and not on three.
 constexpr int kMixShapes = 16, kMixMaps = 32;
 // (vectors: three wide scalar loads; from arrays the compiler makes a load and a branch per shape)
-struct MixShape : DecShape { size_t meta_off, lfc_off; };
+struct alignas(32) MixShape : DecShape { size_t meta_off, lfc_off; };      // (160 bytes, whole scalar loads; 152 apart small calls of several shapes take 1-2.5 % longer)
 struct MixArgs {
     u32x16 first;                         // first workgroup of each shape (beyond the last shape: 2^32 - 1)
     u32x16 chunks;                        // per map
