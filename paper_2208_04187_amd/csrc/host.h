@@ -1077,12 +1077,12 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
             uint64_t g = (uint64_t)num_cus() * (16ull / nw);
             g = (g + 3) & ~3ull;        // the planes of a workgroup start alike within a unit of the map
             *grid = (uint32_t)(g < L.P ? g : L.P);
-            // few planes in the launch: the rounds of units of a plane shared among several workgroups, until there are half of what the machine holds, or as many as
-            // CUs where a workgroup has sixteen wavefronts (maps of up to 0.3 M bfloat16 elements 5.5 -> 4.5 us; shared until it is full, 854 planes of 27 x 27
-            // 4.8 -> 5.1.  120 launches of one to eight maps 787 us, 692 so; 710 with a half for sixteen wavefronts too, 737 with a third of it for each map by
-            // itself: eight of 300 x 27 x 27 6.3, 6.4, 6.4 and 8.5)
+            // few planes in the launch: the rounds of units of a plane shared among several workgroups, until there are half of what the machine holds; a third of workgroups of
+            // one wavefront; as many as CUs of sixteen (maps of up to 0.3 M bfloat16 elements 5.5 -> 4.5 us; shared until it is full, 854 planes of 27 x 27
+            // 4.8 -> 5.1, until half 576 of them 3.9 -> 4.0.  120 launches of one to eight maps 787 us, 692 so; 710 with a half for sixteen wavefronts too, 737 with a third of it
+            // for each map by itself: eight of 300 x 27 x 27 6.3, 6.4, 6.4 and 8.5)
             const uint64_t rounds = (q4 + nt - 1) / nt;
-            uint64_t parts = units_wide(*a) ? (nw == 16 ? g : g / 2) / (L.P * maps) : 1;
+            uint64_t parts = units_wide(*a) ? (nw == 16 ? g : nw == 1 ? g / 3 : g / 2) / (L.P * maps) : 1;
             if (parts > rounds) parts = rounds;
             a->rounds = (uint32_t)rounds;
             if (parts > 1) {
