@@ -1045,14 +1045,15 @@ int plan_decompress(const Layout& L, int64_t D, int64_t Hs, int64_t W, int B, si
     if (D == 1 && L.HW % 4 == 0 && L.nb > 1 && L.nb <= 255 && small_idx && out_vec_aligned && fastdiv_ok(L.HW, (uint64_t)W)) {
         a->q4 = (uint32_t)(L.HW / 4);
         uint64_t G = dec_planes(L, es, 1);
-        // few planes in the launch: fewer of them per workgroup, down to a vector per lane: half as many up to three workgroups per CU, of 2-byte elements six, and again
-        // until there are three for two CUs (1216 planes of 14 x 14 in bfloat16 are 16 workgroups of 32 KB: 5.7 us, 3.9 so; maps of up to 0.3 M elements 4.9 -> 3.7; until there are
-        // four for each CU, 14382 planes of 14 x 14 4.4 -> 4.8.  128 launches of one to eight maps 676 us, 581 so; 588 without the first halving, 597 until a workgroup per CU
-        // where each map counted for itself: eight of 2432 x 14 x 14 4.9, 4.9, 4.9 and 5.4, four of 4000 x 24 x 24 under B = 18 in bfloat16 6.8, 6.1, 6.8 and 6.0)
+        // few planes in the launch: fewer of them per workgroup, down to a vector per lane, until every CU has a workgroup; where eight planes and more still share the
+        // table, half as many up to six workgroups per CU, and again until there are three for two CUs (1216 planes of 14 x 14 in bfloat16 are 16 workgroups of 32 KB: 5.7 us,
+        // 3.9 so; maps of up to 0.3 M elements 4.9 -> 3.7; until there are four for each CU, 14382 planes of 14 x 14 4.4 -> 4.8.  160 launches of one to eight maps 1047 us without,
+        // 948 so; 955 without the halving up to six, 961 until a workgroup per CU where each map counted for itself.
+        // Two of 1757 x 56 x 56 under B = 18, a few planes per workgroup, 6.9 and 7.3 when halved; one of 1040 x 1 x 3136 5.3 and 5.5)
         const uint64_t cus = (uint64_t)num_cus();
         auto halve = [&](uint64_t enough) { const bool few = G > 1 && (L.P + G - 1) / G * maps < enough && (G / 2) * a->q4 >= kThreads; if (few) G /= 2; return few; };
-        halve(cus * (es == 2 ? 6 : 3));
-        while (halve(cus * 3 / 2)) {}
+        if (G >= 16) halve(cus * 6);
+        while (halve(G >= 16 ? cus * 3 / 2 : cus)) {}
         while (G > 1 && !fastdiv_ok(G * a->q4 + kThreads, a->q4)) --G;
         if (fastdiv_ok(G * a->q4 + kThreads, a->q4) && dec_lds_bytes(L, es, G) + 4ull * a->q4 + 16 <= kDecLdsMax) {
             a->G = (uint32_t)G;
